@@ -218,22 +218,35 @@ __global__ void silu_mul_kernel(const float *__restrict__ partial, int splits, i
 
 // ---------------------------------------------------------------------------------------
 // Selection over the vocabulary.  Order: value descending, lower id first among equals.
-// One workgroup per selected row; pass p finds the best entry that comes strictly after
-// the previous winner in that order, so k passes give the sorted top-k and pass 0 alone
-// is the greedy argmax.  Reductions: per-lane scan (16-byte loads), wave shuffles, then the
-// workgroup's 16 waves via LDS.
+// One workgroup per selected row.  Every thread scans its share of the row once and keeps its best
+// entry; the workgroup's best is the first winner.  For the following ones (mask rows, k winners)
+// only the thread that owned the last winner looks through its share again, for its best entry
+// below it, and only its wave reduces again: a further winner costs one rescan by one wave, one
+// barrier and one pass over the 16 wave results instead of a scan of the whole row.
+// What bounds it: one row's 128 KB (32000 logits) through one CU, then the scan's vector
+// instructions; the k winners of a mask row were the tail of the launch.
 // (value, index) as one unsigned 64-bit key whose order is "larger value first, lower index on
 // equal values": the float's bits made monotone (sign flip for positives, complement for
 // negatives; -0 is first turned into +0) above the complemented index.  Logits are finite.
-__device__ __forceinline__ unsigned long long select_key(float v, int i) {
-    uint32_t u = __float_as_uint(v + 0.0f);
-    u ^= (u & 0x80000000u) ? 0xFFFFFFFFu : 0x80000000u;
-    return ((unsigned long long)u << 32) | (uint32_t)(0x7FFFFFFF - i);
+__device__ __forceinline__ uint32_t select_order(float v) {
+    const uint32_t u = __float_as_uint(v + 0.0f);
+    return max(u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u), 1u);     // (0 is kept for "no entry")
+}
+__device__ __forceinline__ unsigned long long select_key(uint32_t order, int i) {
+    return ((unsigned long long)order << 32) | (uint32_t)(0x7FFFFFFF - i);
 }
 __device__ __forceinline__ float select_key_value(unsigned long long k) {
     uint32_t u = (uint32_t)(k >> 32);
     u ^= (u & 0x80000000u) ? 0x80000000u : 0xFFFFFFFFu;
     return __uint_as_float(u);
+}
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long best) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long other = __shfl_xor(best, o, 64);
+        best = other > best ? other : best;
+    }
+    return best;
 }
 #define SELECT_THREADS 1024
 __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__restrict__ logits, TemplateDev t,
@@ -241,58 +254,49 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__r
                                                                 int32_t *__restrict__ topk_ids,
                                                                 float *__restrict__ topk_val) {
     constexpr int NW = SELECT_THREADS / 64;
-    __shared__ unsigned long long sk[NW];
-    const int b = blockIdx.y;
-    const int sel = blockIdx.x;                       // 0..T-1 tree rows, then G*n mask rows
+    __shared__ unsigned long long sk[2][NW];          // wave results, in turn: one barrier per winner
+    const int b = blockIdx.y, wave = threadIdx.x >> 6;
+    // mask rows (k winners) are dealt out first: theirs are the long workgroups
+    const int n_mask_sel = gridDim.x - t.n_tree;
+    const int sel = (int)blockIdx.x < n_mask_sel ? t.n_tree + blockIdx.x : blockIdx.x - n_mask_sel;   // 0..T-1 tree rows, then G*n mask rows
     const bool is_tree = sel < t.n_tree;
     const int r = is_tree ? sel : t.mask_rows[sel - t.n_tree];
     const int k = is_tree ? 1 : kmax;
     const float4 *row = reinterpret_cast<const float4 *>(logits + ((int64_t)b * t.rows + r) * vocab);   // vocab % 16 == 0
-    // A row of up to 32768 logits is fetched once (8 independent 16-byte loads per thread) and
-    // stays in registers for all k passes; longer rows are re-read from L2 pass by pass.
-    constexpr int CACHE = 8;
     const int n4 = vocab >> 2;
+    // this thread's best: its entries come in ascending index, so a strictly larger one replaces
+    uint32_t best_order = 0;
+    int best_i = 0x7FFFFFFF;                           // (key 0, below every real key: no entry yet)
+    auto scan = [&](const float4 &q, int i4) __attribute__((always_inline)) {
+        const float v[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const uint32_t o = select_order(v[e]);
+            if (o > best_order) { best_order = o; best_i = 4 * i4 + e; }
+        }
+    };
+    // A row of up to 32768 logits is fetched with 8 independent 16-byte loads per thread that stay
+    // in registers for the rescans; longer rows are fetched eight by eight and re-read from L2.
+    constexpr int CACHE = 8;
     const bool cached = n4 <= CACHE * SELECT_THREADS;
     float4 cq[CACHE];
-    if (cached) {
+    for (int base = 0; base < n4; base += CACHE * SELECT_THREADS) {
+#pragma unroll
+        for (int j = 0; j < CACHE; j++) cq[j] = row[min(base + (int)threadIdx.x + j * SELECT_THREADS, n4 - 1)];   // (slots past the row are skipped below)
 #pragma unroll
         for (int j = 0; j < CACHE; j++) {
-            const int i4 = threadIdx.x + j * SELECT_THREADS;
-            cq[j] = row[min(i4, n4 - 1)];                  // (slots past the row are skipped below)
+            const int i4 = base + threadIdx.x + j * SELECT_THREADS;
+            if (i4 < n4) scan(cq[j], i4);
         }
     }
-    unsigned long long prev = ~0ull;                      // pass p selects the largest key below pass p-1's
+    unsigned long long mine = select_key(best_order, best_i);
+    unsigned long long wave_best = wave_max_key(mine);
     for (int p = 0; p < k; p++) {
-        unsigned long long best = 0;                      // below every real key (indices are < 2^31 - 1)
-        auto scan = [&](const float4 &q, int i4) __attribute__((always_inline)) {
-            const float v[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const unsigned long long key = select_key(v[e], 4 * i4 + e);
-                best = (key < prev && key > best) ? key : best;
-            }
-        };
-        if (cached) {
-#pragma unroll
-            for (int j = 0; j < CACHE; j++) {
-                const int i4 = threadIdx.x + j * SELECT_THREADS;
-                if (i4 < n4) scan(cq[j], i4);
-            }
-        } else {
-            for (int i4 = threadIdx.x; i4 < n4; i4 += SELECT_THREADS) scan(row[i4], i4);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long other = __shfl_xor(best, o, 64);
-            best = other > best ? other : best;
-        }
-        if ((threadIdx.x & 63) == 0) sk[threadIdx.x >> 6] = best;
+        if ((threadIdx.x & 63) == 0) sk[p & 1][wave] = wave_best;
         __syncthreads();
-        best = sk[0];
+        unsigned long long best = sk[p & 1][0];
 #pragma unroll
-        for (int w = 1; w < NW; w++) best = sk[w] > best ? sk[w] : best;
-        __syncthreads();
-        prev = best;
+        for (int w = 1; w < NW; w++) best = sk[p & 1][w] > best ? sk[p & 1][w] : best;
         if (threadIdx.x == 0) {
             const int bi = 0x7FFFFFFF - (int)(uint32_t)(best & 0xFFFFFFFFu);
             if (is_tree) {
@@ -303,6 +307,28 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__r
                 if (topk_val) topk_val[o] = select_key_value(best);
             }
         }
+        if (p + 1 == k || wave_best != best) continue;           // wave-uniform: another wave's entry won
+        if (mine == best) {                                       // (keys are distinct: one thread)
+            mine = 0;
+            auto below = [&](const float4 &q, int i4) __attribute__((always_inline)) {
+                const float v[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const unsigned long long key = select_key(select_order(v[e]), 4 * i4 + e);
+                    mine = (key < best && key > mine) ? key : mine;
+                }
+            };
+            if (cached) {
+#pragma unroll
+                for (int j = 0; j < CACHE; j++) {
+                    const int i4 = threadIdx.x + j * SELECT_THREADS;
+                    if (i4 < n4) below(cq[j], i4);
+                }
+            } else {
+                for (int i4 = threadIdx.x; i4 < n4; i4 += SELECT_THREADS) below(row[i4], i4);
+            }
+        }
+        wave_best = wave_max_key(mine);
     }
 }
 
