@@ -220,11 +220,13 @@ __global__ void silu_mul_kernel(const float *__restrict__ partial, int splits, i
 // Selection over the vocabulary.  Order: value descending, lower id first among equals.
 // One workgroup per selected row.  Every thread scans its share of the row once and keeps its best
 // entry; the workgroup's best is the first winner.  For the following ones (mask rows, k winners)
-// only the thread that owned the last winner looks through its share again, for its best entry
-// below it, and only its wave reduces again: a further winner costs one rescan by one wave, one
-// barrier and one pass over the 16 wave results instead of a scan of the whole row.
-// What bounds it: one row's 128 KB (32000 logits) through one CU, then the scan's vector
-// instructions; the k winners of a mask row were the tail of the launch.
+// only the wave whose thread owned the last winner looks again: its 64 lanes fetch that thread's
+// share together, for the best entry below the winner, and the wave reduces again.  A further
+// winner costs 0.6 us (one round trip to L2, one barrier) instead of a scan of the whole row (3 us).
+// What bounds it: launch, one round trip for the row (128 KB at 32000 logits, through one CU) and
+// the scan's vector instructions for the tree rows, the winners' chain for the mask rows.
+// 68 rows x 32000 logits: 6.3 -> 4.4 us without mask rows, 15.3 -> 6.2 us with four winners per
+// mask row, 27.2 -> 8.8 us with eight.
 // (value, index) as one unsigned 64-bit key whose order is "larger value first, lower index on
 // equal values": the float's bits made monotone (sign flip for positives, complement for
 // negatives; -0 is first turned into +0) above the complemented index.  Logits are finite.
@@ -240,13 +242,19 @@ __device__ __forceinline__ float select_key_value(unsigned long long k) {
     u ^= (u & 0x80000000u) ? 0x80000000u : 0xFFFFFFFFu;
     return __uint_as_float(u);
 }
-__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long best) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long other = __shfl_xor(best, o, 64);
-        best = other > best ? other : best;
-    }
-    return best;
+// Largest key of a wave, the same in every lane: the order words first, then the index words of the
+// lanes that hold the largest.  Lane-to-lane moves inside the vector unit (row shifts, then the two
+// row broadcasts) instead of 12 dependent trips through LDS (12.6 -> 8.1 us at four winners of 32000).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+#define DPP_MAX(ctrl) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xF, 0xF, false))
+    DPP_MAX(0x111); DPP_MAX(0x112); DPP_MAX(0x114); DPP_MAX(0x118);      // row_shr 1, 2, 4, 8
+    DPP_MAX(0x142); DPP_MAX(0x143);                                      // row_bcast 15, 31
+#undef DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k) {
+    const uint32_t order = (uint32_t)(k >> 32), top = wave_max_u32(order);
+    return ((unsigned long long)top << 32) | wave_max_u32(order == top ? (uint32_t)k : 0u);
 }
 #define SELECT_THREADS 1024
 __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__restrict__ logits, TemplateDev t,
@@ -275,16 +283,13 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__r
             if (o > best_order) { best_order = o; best_i = 4 * i4 + e; }
         }
     };
-    // A row of up to 32768 logits is fetched with 8 independent 16-byte loads per thread that stay
-    // in registers for the rescans; longer rows are fetched eight by eight and re-read from L2.
-    constexpr int CACHE = 8;
-    const bool cached = n4 <= CACHE * SELECT_THREADS;
-    float4 cq[CACHE];
-    for (int base = 0; base < n4; base += CACHE * SELECT_THREADS) {
+    constexpr int BATCH = 8;                           // independent 16-byte loads per thread and round trip
+    for (int base = 0; base < n4; base += BATCH * SELECT_THREADS) {
+        float4 cq[BATCH];
 #pragma unroll
-        for (int j = 0; j < CACHE; j++) cq[j] = row[min(base + (int)threadIdx.x + j * SELECT_THREADS, n4 - 1)];   // (slots past the row are skipped below)
+        for (int j = 0; j < BATCH; j++) cq[j] = row[min(base + (int)threadIdx.x + j * SELECT_THREADS, n4 - 1)];   // (slots past the row are skipped below)
 #pragma unroll
-        for (int j = 0; j < CACHE; j++) {
+        for (int j = 0; j < BATCH; j++) {
             const int i4 = base + threadIdx.x + j * SELECT_THREADS;
             if (i4 < n4) scan(cq[j], i4);
         }
@@ -294,9 +299,7 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__r
     for (int p = 0; p < k; p++) {
         if ((threadIdx.x & 63) == 0) sk[p & 1][wave] = wave_best;
         __syncthreads();
-        unsigned long long best = sk[p & 1][0];
-#pragma unroll
-        for (int w = 1; w < NW; w++) best = sk[p & 1][w] > best ? sk[p & 1][w] : best;
+        const unsigned long long best = wave_max_key(sk[p & 1][threadIdx.x & (NW - 1)]);
         if (threadIdx.x == 0) {
             const int bi = 0x7FFFFFFF - (int)(uint32_t)(best & 0xFFFFFFFFu);
             if (is_tree) {
@@ -308,26 +311,20 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__r
             }
         }
         if (p + 1 == k || wave_best != best) continue;           // wave-uniform: another wave's entry won
-        if (mine == best) {                                       // (keys are distinct: one thread)
-            mine = 0;
-            auto below = [&](const float4 &q, int i4) __attribute__((always_inline)) {
-                const float v[4] = {q.x, q.y, q.z, q.w};
+        // the owner's share of the row, one 16-byte piece per lane of its wave (from L2: one round trip)
+        const int owner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(mine == best));     // (keys are distinct: one lane)
+        unsigned long long next = 0;
+        for (int i4 = (wave << 6) + owner + (threadIdx.x & 63) * SELECT_THREADS; i4 < n4; i4 += 64 * SELECT_THREADS) {
+            const float4 q = row[i4];
+            const float v[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const unsigned long long key = select_key(select_order(v[e]), 4 * i4 + e);
-                    mine = (key < best && key > mine) ? key : mine;
-                }
-            };
-            if (cached) {
-#pragma unroll
-                for (int j = 0; j < CACHE; j++) {
-                    const int i4 = threadIdx.x + j * SELECT_THREADS;
-                    if (i4 < n4) below(cq[j], i4);
-                }
-            } else {
-                for (int i4 = threadIdx.x; i4 < n4; i4 += SELECT_THREADS) below(row[i4], i4);
+            for (int e = 0; e < 4; e++) {
+                const unsigned long long key = select_key(select_order(v[e]), 4 * i4 + e);
+                next = (key < best && key > next) ? key : next;
             }
         }
+        next = wave_max_key(next);
+        if ((threadIdx.x & 63) == owner) mine = next;
         wave_best = wave_max_key(mine);
     }
 }
