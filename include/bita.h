@@ -215,7 +215,8 @@ int bita_compact_kv(const bita_model *m, const bita_kv *kv, const int32_t *d_pat
  * context in chunks of at most chunk_rows rows; a chunk is a verify pass whose
  * tree is a chain (row i hangs off row i-1), which is causal attention over
  * [cache, chunk], followed by committing every row of the chunk to the cache.
- * Same kernels and arithmetic as bita_verify_step / bita_compact_kv.
+ * Same kernels and arithmetic as bita_verify_step / bita_compact_kv; behind the last layer's K/V
+ * projection only the rows whose greedy token is asked for go on (one per sequence).
  *   d_tokens     [B][n_tokens]  context tokens, row b valid up to its length
  *   d_seq_len    [B] or NULL    per-sequence lengths (clamped to 0..n_tokens);
  *                               NULL = every sequence has n_tokens tokens

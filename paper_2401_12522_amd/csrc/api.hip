@@ -305,10 +305,10 @@ extern "C" size_t bita_workspace_bytes(const bita_model *m, int32_t batch, int32
     return ws_layout(m->cfg, batch, rows).total;
 }
 
-extern "C" int bita_verify_step(bita_model *m, const bita_kv *kv, const bita_tree_template *t,
-                                const int32_t *d_token, const int32_t *d_ctx_len, int32_t batch,
-                                void *d_workspace, size_t ws_bytes, int32_t kmax, int32_t *d_argmax,
-                                int32_t *d_topk_ids, float *d_topk_val, float *d_logits, void *stream) {
+int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, const int32_t *d_token,
+                const int32_t *d_ctx_len, int32_t batch, void *d_workspace, size_t ws_bytes, int32_t kmax,
+                int32_t *d_argmax, int32_t *d_topk_ids, float *d_topk_val, float *d_logits, void *stream,
+                const PassTail *tail) {
     if (!m || !kv || !t || !d_token || !d_ctx_len || !d_workspace || !d_argmax || batch <= 0)
         return bita_set_error(BITA_ERR_INVALID_ARG, "bita_verify_step: null argument or batch <= 0");
     const bita_config &c = m->cfg;
@@ -356,6 +356,39 @@ extern "C" int bita_verify_step(bita_model *m, const bita_kv *kv, const bita_tre
                                            : (size_t)batch * c.n_kv_heads * kv->smax * hd * 2;
     const size_t kv_layer_tree = (size_t)batch * c.n_kv_heads * td.rows * hd * 2;
 
+    // What follows attention in a layer, for Mr rows with their own buffers: x += attn_out Wo^T,
+    // x += FFN(norm(x)), the FFN's last partial sums left in `part` (their number is returned).
+    auto after_attention = [&](int l, int Mr, const void *attn, float *xr, unsigned char *hr, void *actr, float *part, float *ssqr,
+                               const GemmPlan &po, const GemmPlan &pgu, const GemmPlan &pdn) {
+        const RowScale rs = {ssqr, (d / 4 + 255) / 256, 1.0f / (float)d, c.rms_eps};
+        timed_gemm(attn, Mr, nq, m->wo[l], d, part, d, po, s);
+        launch_rmsnorm_prep(xr, part, po.splits, Mr, d, m->ffn_norm[l], hr, ssqr, s);
+        // with a single split the gate/up GEMM gates in its own epilogue and writes the slab itself
+        if (gemm_direct_output_possible(pgu, GEMM_OUT_SILU)) {
+            const GemmOutput gated = {GEMM_OUT_SILU, rs, (uint16_t *)actr, c.d_ffn};
+            timed_gemm(hr, Mr, d, m->w_gate_up[l], 2 * (int64_t)c.d_ffn, part, 2 * (int64_t)c.d_ffn, pgu, s, &gated);
+        } else {
+            timed_gemm(hr, Mr, d, m->w_gate_up[l], 2 * (int64_t)c.d_ffn, part, 2 * (int64_t)c.d_ffn, pgu, s);
+            launch_silu_mul(part, pgu.splits, Mr, c.d_ffn, actr, rs, s);
+        }
+        timed_gemm(actr, Mr, c.d_ffn, m->w_down[l], d, part, d, pdn, s);
+        return pdn.splits;
+    };
+    // Final norm, LM head and logits of Mr rows whose last FFN sums are still pending.
+    auto head = [&](int Mr, int n_pending, float *xr, unsigned char *hr, float *part, float *ssqr, float *lg, const GemmPlan &plm) {
+        const RowScale rs = {ssqr, (d / 4 + 255) / 256, 1.0f / (float)d, c.rms_eps};
+        launch_rmsnorm_prep(xr, part, n_pending, Mr, d, m->final_norm, hr, ssqr, s);
+        // the final norm's row factor: in the LM head's own epilogue when it runs as a single split,
+        // else in the reduction of its partial sums
+        if (gemm_direct_output_possible(plm, GEMM_OUT_SCALED)) {
+            const GemmOutput scaled = {GEMM_OUT_SCALED, rs, nullptr, 0};
+            timed_gemm(hr, Mr, d, m->lm_head, c.vocab, lg, c.vocab, plm, s, &scaled);
+        } else {
+            timed_gemm(hr, Mr, d, m->lm_head, c.vocab, part, c.vocab, plm, s);
+            launch_reduce_partials(part, plm.splits, Mr, c.vocab, c.vocab, lg, rs, s);
+        }
+    };
+
     launch_embed(d_token, td, batch, m->tok_emb, m->mask_emb, d, c.vocab, x, s);
     int pending = 0;                                    // split-K partials waiting to be added to x
     for (int l = 0; l < c.n_layers; l++) {
@@ -364,36 +397,46 @@ extern "C" int bita_verify_step(bita_model *m, const bita_kv *kv, const bita_tre
         void *kt = (unsigned char *)kv->k_tree + l * kv_layer_tree, *vt = (unsigned char *)kv->v_tree + l * kv_layer_tree;
         launch_qkv_rope(partial, p_qkv.splits, batch, td, c.n_heads, c.n_kv_heads, hd, d_ctx_len, m->rope_cos,
                         m->rope_sin, c.max_pos, q, q_lo, kt, vt, k_lo, v_lo, rs_norm, s);
+        const bool tail_layer = tail && l == c.n_layers - 1;
+        if (tail_layer && !tail->sel_row) break;         // nobody asks for anything but the rows' K/V
         launch_tree_attention(td, q, q_lo, (unsigned char *)kv->k_cache + l * kv_layer_cache,
                               (unsigned char *)kv->v_cache + l * kv_layer_cache, kt, vt, k_lo, v_lo, m->prompt_k[l],
                               m->prompt_v[l], d_ctx_len, d_token, batch, c.n_heads, c.n_kv_heads, hd, c.n_prompt, kv->smax,
-                              ap, part_o, part_ml, attn_out, nullptr, true, pm, s);
-        timed_gemm(attn_out, M, nq, m->wo[l], d, partial, d, p_o, s);
-        launch_rmsnorm_prep(x, partial, p_o.splits, M, d, m->ffn_norm[l], h, ssq, s);
-        // with a single split the gate/up GEMM gates in its own epilogue and writes the slab itself
-        if (gemm_direct_output_possible(p_gu, GEMM_OUT_SILU)) {
-            const GemmOutput gated = {GEMM_OUT_SILU, rs_norm, (uint16_t *)act, c.d_ffn};
-            timed_gemm(h, M, d, m->w_gate_up[l], 2 * (int64_t)c.d_ffn, partial, 2 * (int64_t)c.d_ffn, p_gu, s, &gated);
-        } else {
-            timed_gemm(h, M, d, m->w_gate_up[l], 2 * (int64_t)c.d_ffn, partial, 2 * (int64_t)c.d_ffn, p_gu, s);
-            launch_silu_mul(partial, p_gu.splits, M, c.d_ffn, act, rs_norm, s);
+                              ap, part_o, part_ml, attn_out, nullptr, true, pm, s, tail_layer ? tail->sel_row : nullptr);
+        if (tail_layer) {
+            // One row per sequence goes on: its attention output and residual are gathered, and the
+            // rest of the layer, the LM head and the selection run on `batch` rows.
+            const WsLayout T = ws_layout(c, batch, 1);
+            unsigned char *tw = (unsigned char *)tail->ws;
+            float *tx = (float *)(tw + T.x), *tpart = (float *)(tw + T.partial), *tssq = (float *)(tw + T.ssq), *tlog = (float *)(tw + T.logits);
+            launch_gather_rows(tail->sel_row, batch, td.rows, attn_out, (int)nq, x, d, tw + T.attn_out, tx, s);
+            const int n_pending = after_attention(l, batch, tw + T.attn_out, tx, tw + T.h, tw + T.act, tpart, tssq, gemm_plan(batch, d, nq),
+                                                  gemm_plan(batch, 2 * (int64_t)c.d_ffn, d), gemm_plan(batch, d, c.d_ffn));
+            head(batch, n_pending, tx, tw + T.h, tpart, tssq, tlog, gemm_plan(batch, c.vocab, d));
+            TemplateDev one = td;                        // one greedy row per sequence
+            one.rows = one.n_tree = 1;
+            one.n_groups = 0;
+            launch_select(tlog, batch, one, c.vocab, 1, d_argmax, nullptr, nullptr, s);
+            break;
         }
-        timed_gemm(act, M, c.d_ffn, m->w_down[l], d, partial, d, p_dn, s);
-        pending = p_dn.splits;
+        pending = after_attention(l, M, attn_out, x, h, act, partial, ssq, p_o, p_gu, p_dn);
     }
-    launch_rmsnorm_prep(x, partial, pending, M, d, m->final_norm, h, ssq, s);
-    // the final norm's row factor: in the LM head's own epilogue when it runs as a single split,
-    // else in the reduction of its partial sums
-    if (gemm_direct_output_possible(p_lm, GEMM_OUT_SCALED)) {
-        const GemmOutput scaled = {GEMM_OUT_SCALED, rs_norm, nullptr, 0};
-        timed_gemm(h, M, d, m->lm_head, c.vocab, logits, c.vocab, p_lm, s, &scaled);
-    } else {
-        timed_gemm(h, M, d, m->lm_head, c.vocab, partial, c.vocab, p_lm, s);
-        launch_reduce_partials(partial, p_lm.splits, M, c.vocab, c.vocab, logits, rs_norm, s);
+    if (tail) {
+        BITA_HIP_CHECK(hipGetLastError());
+        return BITA_OK;
     }
+    head(M, pending, x, h, partial, ssq, logits, p_lm);
     launch_select(logits, batch, td, c.vocab, kmax, d_argmax, n_sel_mask > 0 ? d_topk_ids : nullptr, d_topk_val, s);
     BITA_HIP_CHECK(hipGetLastError());
     return BITA_OK;
+}
+
+extern "C" int bita_verify_step(bita_model *m, const bita_kv *kv, const bita_tree_template *t,
+                                const int32_t *d_token, const int32_t *d_ctx_len, int32_t batch,
+                                void *d_workspace, size_t ws_bytes, int32_t kmax, int32_t *d_argmax,
+                                int32_t *d_topk_ids, float *d_topk_val, float *d_logits, void *stream) {
+    return verify_pass(m, kv, t, d_token, d_ctx_len, batch, d_workspace, ws_bytes, kmax, d_argmax, d_topk_ids, d_topk_val,
+                       d_logits, stream, nullptr);
 }
 
 int compact_kv_launch(const bita_config &cfg, const bita_kv *kv, const PageMap &pm, const int32_t *d_path,

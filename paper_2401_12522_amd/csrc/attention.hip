@@ -170,7 +170,8 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     const uint16_t *__restrict__ k_tree_lo, const uint16_t *__restrict__ v_tree_lo,
     const uint16_t *__restrict__ prompt_k, const uint16_t *__restrict__ prompt_v,
     const int32_t *__restrict__ token, float scale_log2, float *__restrict__ part_o, float *__restrict__ part_ml,
-    uint16_t *__restrict__ out, uint16_t *__restrict__ out_lo, int as_fragments, int m_tiles_out, PageMap pm) {
+    uint16_t *__restrict__ out, uint16_t *__restrict__ out_lo, int as_fragments, int m_tiles_out, PageMap pm,
+    const int32_t *__restrict__ only_row) {
     using C = AttCfg<HD, U>;
     constexpr int KSN = C::KSN, NTN = C::NTN, GPR = C::GPR, RPI = C::RPI, NVI = C::NVI;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -515,6 +516,9 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         for (int iv = 0; iv < NVI; iv++) emit(0, iv);
     }
     att_wait<0>();                                      // the first chunk and the prologue's loads have landed
+    // (looked at here, where the prologue's loads have landed anyway: ahead of them it cost 0.5 % of
+    // every launch; the whole workgroup leaves together)
+    if (only_row && (min(max(only_row[b], 0), R - 1) >> 4) != mt) return;
     // a tree row without a candidate (negative token) is absent from the pass: its output is zero
     int row_flags = (row_ok && mask_byte ? 1 : 0) | (row_ok && (mask_byte || tok_val >= 0) ? 2 : 0);
     asm volatile("" : "+v"(row_flags));                 // (looked at here, not inside the loop)
@@ -663,7 +667,7 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
                           const void *prompt_k, const void *prompt_v, const int32_t *ctx_len, const int32_t *token,
                           int batch, int Hq,
                           int Hkv, int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
-                          void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s) {
+                          void *out_lo, bool out_as_fragments, const PageMap &pm, const int32_t *only_row, hipStream_t s) {
     using C = AttCfg<HD, U>;
     static bool attr_set = false;
     if (!attr_set) {
@@ -683,7 +687,7 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
                        (const uint16_t *)k_tree, (const uint16_t *)v_tree, (const uint16_t *)k_tree_lo,
                        (const uint16_t *)v_tree_lo, (const uint16_t *)prompt_k, (const uint16_t *)prompt_v, token,
                        scale_log2, part_o, part_ml, (uint16_t *)out,
-                       (uint16_t *)out_lo, out_as_fragments ? 1 : 0, (batch * t.rows + 15) / 16, pm);
+                       (uint16_t *)out_lo, out_as_fragments ? 1 : 0, (batch * t.rows + 15) / 16, pm, only_row);
 }
 
 void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo, const void *k_cache, const void *v_cache,
@@ -691,11 +695,11 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            const void *prompt_k,
                            const void *prompt_v, const int32_t *ctx_len, const int32_t *token, int batch, int Hq, int Hkv, int hd,
                            int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
-                           void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s) {
+                           void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s, const int32_t *only_row) {
     // grouped-query models: two query heads of a K/V head per workgroup share its chunk loads
     const bool pair = (Hq / Hkv) % 2 == 0;
 #define ATT_LAUNCH_P(HD_, U_, PG_) launch_attn_t<HD_, U_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
-                                                   prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, s)
+                                                   prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, s)
 #define ATT_LAUNCH(HD_, U_) do { if (pm.table) ATT_LAUNCH_P(HD_, U_, true); else ATT_LAUNCH_P(HD_, U_, false); } while (0)
     if (hd == 128) {
         if (pair) ATT_LAUNCH(128, 2); else ATT_LAUNCH(128, 1);

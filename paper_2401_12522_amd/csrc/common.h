@@ -174,4 +174,20 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            const int32_t *token /* [B][R] or nullptr: rows with a negative token are absent */,
                            int batch, int n_heads, int n_kv_heads, int hd, int n_prompt, int smax,
                            const AttnPlan &p, float *part_o, float *part_ml, void *out, void *out_lo,
-                           bool out_as_fragments, const PageMap &pm, hipStream_t s);
+                           bool out_as_fragments, const PageMap &pm, hipStream_t s,
+                           const int32_t *only_row = nullptr /* [B]: only the row tile holding this row of each sequence */);
+
+// A prefill chunk needs from its pass the rows' K/V and, where a sequence may end in the chunk, the
+// greedy token after one row per sequence (sel_row [B], row inside the chunk): the last layer then
+// goes on with those rows alone behind the K/V projection.  sel_row == nullptr: K/V only.  ws: a
+// workspace of bita_workspace_bytes(m, batch, 1).
+struct PassTail { const int32_t *sel_row; void *ws; };
+// bita_verify_step, with an optional tail (argmax is then [B], one per sequence; no top-k, no logits)
+int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, const int32_t *d_token,
+                const int32_t *d_ctx_len, int32_t batch, void *d_workspace, size_t ws_bytes, int32_t kmax,
+                int32_t *d_argmax, int32_t *d_topk_ids, float *d_topk_val, float *d_logits, void *stream,
+                const PassTail *tail);
+// row sel_row[b] of each sequence of `rows`: its columns of a two-plane slab (fragment order) and of
+// the residual stream, into a slab and a stream of `batch` rows
+void launch_gather_rows(const int32_t *sel_row, int batch, int rows, const void *a_frag, int k, const float *x, int d,
+                        void *a_out, float *x_out, hipStream_t s);

@@ -330,6 +330,29 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__r
 }
 
 // ---------------------------------------------------------------------------------------
+// One row per sequence out of a pass' slab (both planes, 16-byte granules) and residual stream.
+// A few KB per row: nothing but launch and one round trip.
+__global__ void gather_rows_kernel(const int32_t *__restrict__ sel_row, int rows, const uint16_t *__restrict__ a_frag, int K,
+                                   const float *__restrict__ x, int d, uint16_t *__restrict__ a_out, float *__restrict__ x_out) {
+    const int b = blockIdx.x, batch = gridDim.x, i = blockIdx.y * blockDim.x + threadIdx.x;
+    const int row = b * rows + min(max(sel_row[b], 0), rows - 1), M = batch * rows;
+    if (i < (K >> 3)) {
+        const int ks = K >> 5, mt_in = (M + 15) >> 4, mt_out = (batch + 15) >> 4, off_in = frag_pack_offset(M), off_out = frag_pack_offset(batch);
+#pragma unroll
+        for (int plane = 0; plane < 2; plane++)
+            *reinterpret_cast<uint4 *>(a_out + frag_index(plane, b, 8 * i, ks, mt_out, off_out)) =
+                *reinterpret_cast<const uint4 *>(a_frag + frag_index(plane, row, 8 * i, ks, mt_in, off_in));
+    }
+    if (i < (d >> 2)) reinterpret_cast<float4 *>(x_out + (int64_t)b * d)[i] = reinterpret_cast<const float4 *>(x + (int64_t)row * d)[i];
+}
+
+// ---------------------------------------------------------------------------------------
+void launch_gather_rows(const int32_t *sel_row, int batch, int rows, const void *a_frag, int k, const float *x, int d,
+                        void *a_out, float *x_out, hipStream_t s) {
+    const int n = (k >> 3) > (d >> 2) ? (k >> 3) : (d >> 2);
+    hipLaunchKernelGGL(gather_rows_kernel, dim3(batch, (n + 255) / 256), dim3(256), 0, s, sel_row, rows, (const uint16_t *)a_frag, k,
+                       x, d, (uint16_t *)a_out, x_out);
+}
 void launch_embed(const int32_t *token, const TemplateDev &t, int batch, const void *tok_emb,
                   const void *mask_emb, int d, int vocab, float *x, hipStream_t s) {
     hipLaunchKernelGGL(embed_kernel, dim3(batch * t.rows), dim3(256), 0, s, token, t,

@@ -6,41 +6,47 @@
 #include <vector>
 
 // One launch per chunk: the chunk's token rows (gathered from the [B][n_tokens] input, -1 =
-// inactive row beyond a sequence's end), the identity path and the number of rows to commit.
+// inactive row beyond a sequence's end), the identity path, the number of rows to commit and the
+// row that holds the sequence's last token if it lies in this chunk (else some row of it).
 __global__ void prefill_chunk_kernel(const int32_t *__restrict__ tokens, int n_tokens,
                                      const int32_t *__restrict__ seq_len, int done, int m,
                                      int32_t *__restrict__ tok, int32_t *__restrict__ path,
-                                     int32_t *__restrict__ n_acc) {
+                                     int32_t *__restrict__ n_acc, int32_t *__restrict__ sel_row) {
     const int b = blockIdx.x;
     const int len = seq_len ? min(max(seq_len[b], 0), n_tokens) : n_tokens;
     for (int i = threadIdx.x; i < m; i += blockDim.x) {
         tok[b * m + i] = done + i < len ? tokens[(int64_t)b * n_tokens + done + i] : -1;
         path[b * m + i] = i;
     }
-    if (threadIdx.x == 0) n_acc[b] = min(max(len - done, 0), m);
+    if (threadIdx.x == 0) {
+        n_acc[b] = min(max(len - done, 0), m);
+        sel_row[b] = min(max(len - 1 - done, 0), m - 1);
+    }
 }
 
-// Greedy token after a sequence's last context token, once the chunk holding it has run.
+// Greedy token after a sequence's last context token (argmax [B]), once the chunk holding it has run.
 __global__ void prefill_pick_kernel(const int32_t *__restrict__ argmax, const int32_t *__restrict__ seq_len,
                                     int n_tokens, int done, int m, int batch, int32_t *__restrict__ next_token) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= batch) return;
     const int len = seq_len ? min(max(seq_len[b], 0), n_tokens) : n_tokens;
     const int last = len - 1 - done;
-    if (last >= 0 && last < m) next_token[b] = argmax[b * m + last];
+    if (last >= 0 && last < m) next_token[b] = argmax[b];
 }
 
 namespace {
-struct PrefillWs { size_t step, tok, argmax, path, n_acc, total; };
+struct PrefillWs { size_t step, tok, argmax, path, n_acc, sel_row, tail, total; };
 PrefillWs prefill_layout(const bita_model *m, int batch, int chunk_rows) {
     PrefillWs L;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
     L.step = take(bita_workspace_bytes(m, batch, chunk_rows));
     L.tok = take((size_t)batch * chunk_rows * 4);
-    L.argmax = take((size_t)batch * chunk_rows * 4);
+    L.argmax = take((size_t)batch * 4);
     L.path = take((size_t)batch * chunk_rows * 4);
     L.n_acc = take((size_t)batch * 4);
+    L.sel_row = take((size_t)batch * 4);
+    L.tail = take(bita_workspace_bytes(m, batch, 1));
     L.total = off;
     return L;
 }
@@ -106,7 +112,7 @@ extern "C" int bita_prefill(bita_model *m, const bita_kv *kv, const int32_t *d_t
     hipStream_t s = (hipStream_t)stream;
     unsigned char *ws = (unsigned char *)d_workspace;
     int32_t *tok = (int32_t *)(ws + L.tok), *argmax = (int32_t *)(ws + L.argmax);
-    int32_t *path = (int32_t *)(ws + L.path), *n_acc = (int32_t *)(ws + L.n_acc);
+    int32_t *path = (int32_t *)(ws + L.path), *n_acc = (int32_t *)(ws + L.n_acc), *sel_row = (int32_t *)(ws + L.sel_row);
 
     // at most two templates (full chunks and the ragged last one), kept in the model handle; a
     // capturing stream must find them there
@@ -123,13 +129,18 @@ extern "C" int bita_prefill(bita_model *m, const bita_kv *kv, const int32_t *d_t
         bita_kv chunk_kv = *kv;
         chunk_kv.rows = rows;                           // tree scratch laid out as [L][B][Hkv][rows][hd]
         chunk_kv.ctx_hint = kv->ctx_hint + done;
-        prefill_chunk_kernel<<<batch, 256, 0, s>>>(d_tokens, n_tokens, d_seq_len, done, rows, tok, path, n_acc);
-        rc = bita_verify_step(m, &chunk_kv, tmpl, tok, d_ctx_len, batch, ws + L.step, L.tok - L.step, 1,
-                              argmax, nullptr, nullptr, nullptr, stream);
+        prefill_chunk_kernel<<<batch, 256, 0, s>>>(d_tokens, n_tokens, d_seq_len, done, rows, tok, path, n_acc, sel_row);
+        // The logits of a context row are nobody's but the last one's: the rest of the last layer and
+        // the LM head run on one row per sequence, and only in chunks where a sequence may end (with
+        // lengths on the device any chunk may be, without them the last one is).
+        const bool may_end = d_next_token && (d_seq_len || done + rows >= n_tokens);
+        const PassTail tail = {may_end ? sel_row : nullptr, ws + L.tail};
+        rc = verify_pass(m, &chunk_kv, tmpl, tok, d_ctx_len, batch, ws + L.step, L.tok - L.step, 1,
+                         argmax, nullptr, nullptr, nullptr, stream, &tail);
         if (rc != BITA_OK) break;
         rc = bita_compact_kv(m, &chunk_kv, path, rows, n_acc, d_ctx_len, batch, stream);
         if (rc != BITA_OK) break;
-        if (d_next_token)
+        if (may_end)
             prefill_pick_kernel<<<(batch + 255) / 256, 256, 0, s>>>(argmax, d_seq_len, n_tokens, done, rows, batch,
                                                                     d_next_token);
     }
