@@ -117,8 +117,9 @@ __device__ __forceinline__ float row_scale_finish(const RowScale &rs, const RowS
     return 1.0f / sqrtf(tot * rs.inv_d + rs.eps);
 }
 __device__ __forceinline__ float row_scale(const RowScale &rs, int m) { return row_scale_finish(rs, row_scale_fetch(rs, m)); }
-// mt_pass: m-tiles per row pass of a tall launch (6..9), 0 = the variant's own row handling
-struct GemmPlan { int splits, ksteps_per_split, variant, mt_pass; };
+// mt_pass: m-tiles per row pass of a tall launch (6..9), 0 = the variant's own row handling;
+// tall_tiles: weight tiles per workgroup of a tall launch (16 or 12)
+struct GemmPlan { int splits, ksteps_per_split, variant, mt_pass, tall_tiles; };
 // What a GEMM launch with a single split (complete sums in its accumulators) may do instead of
 // storing fp32 partials: apply the deferred RMSNorm row factor and store the result, or apply it
 // and the SwiGLU gating to its tile-interleaved gate/up columns and store the next GEMM's

@@ -99,7 +99,11 @@ struct GemmCfg {
     // those beyond NFRAG land in one shared dump slot after the ring
     static constexpr int RING = KG * D * NFRAG * 1024;          // one ring per k group
     static constexpr int MERGE = KG > 1 ? WN * MT * NW * 1024 : 0;   // accumulators of one k group
-    static constexpr int STAGE = NW % 2 == 0 ? 2 * (WN * NW * 8 / 16) * MT * 512 : 0;    // gated output slab of the workgroup
+    // outputs on their way out: the gated slab of the workgroup, or (three tiles per wave) each wave's
+    // sums as rows of 48 floats, 4 floats apart from the next (rows 4g of the four lane groups then
+    // start 16 banks apart)
+    static constexpr int ROW3 = 52;
+    static constexpr int STAGE = NW % 2 == 0 ? 2 * (WN * NW * 8 / 16) * MT * 512 : NW == 3 ? WN * MT * 16 * ROW3 * 4 : 0;
     static constexpr int SMEM = (RING > MERGE ? (RING > STAGE ? RING : STAGE) : (MERGE > STAGE ? MERGE : STAGE)) + 1024;
     static_assert((D - 2) * LOADS < 64, "vmcnt counter range");
 };
@@ -367,7 +371,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
                     }
             }
         }
-        if (kg != 0) return;
+        // (three tiles per wave: gate and up of a feature sit in different waves, the gating below is done
+        // by all waves from LDS)
+        if (kg != 0 && !(NW == 3 && DIRECT && direct.kind == GEMM_OUT_SILU)) return;
     }
     if constexpr (PACK) {
         // the packed tile's low-plane products sit pack_off rows (pack_off / 4 lane groups)
@@ -379,13 +385,35 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     }
     // D layout: lane (g = lane/16, c = lane%16) holds rows 4g..4g+3, column c of each tile.
     const int g = lane >> 4, cc = lane & 15;
+    // Three tiles per wave: the wave's sums as rows in LDS (its own region behind the merge; the same
+    // wave wrote and reads, or a barrier follows).  A wave's region starts where its merge region
+    // does not: the other waves of k group 0 are past theirs first.
+    auto stage_rows3 = [&](float *stage, auto &&value) __attribute__((always_inline)) {
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int i = 0; i < MT; i++)
+#pragma unroll
+                for (int j = 0; j < NW; j++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) stage[(i * 16 + 4 * g + r) * C::ROW3 + j * 16 + cc] = value(i, j, r);
+        }
+    };
     // Stores of the wave's MT x NW tiles (k group 0 after the merge).  With k groups they go
     // through the wave's own LDS region (the one its partners wrote into, private since the
     // merge) and leave as 16 bytes per lane: whole NW*64-byte row segments instead of 64-byte
     // pieces.  Rows of 4-row group g sit in the half of the row given by g's parity (two-way
     // instead of four-way bank conflicts).
     auto store_tiles = [&](float *o, auto &&value) __attribute__((always_inline)) {
-        if constexpr (KG > 1) {
+        if constexpr (NW == 3) {
+            float *stage = reinterpret_cast<float *>(smem_u4) + wn * (MT * 16 * C::ROW3);
+            stage_rows3(stage, value);
+            for (int idx = lane; idx < MT * 16 * 12; idx += 64) {
+                const int row = idx / 12, chunk = idx % 12, m = m_base + row, t = t0 + (chunk >> 2);
+                const float4 v = *reinterpret_cast<const float4 *>(stage + row * C::ROW3 + chunk * 4);
+                if (m < M && t < NT) *reinterpret_cast<float4 *>(o + (int64_t)m * ldo + t0 * 16 + chunk * 4) = v;
+            }
+        } else if constexpr (KG > 1) {
             constexpr int CPR = NW * 4, RPI = 64 / CPR;       // 16-byte chunks per row, rows per store instruction
             float *stage = reinterpret_cast<float *>(smem_u4) + wn * (MT * NW * 256);
 #pragma unroll
@@ -437,6 +465,50 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         if (direct.kind == GEMM_OUT_SCALED) {
             // (the row factors sit in the dump slot behind the ring, outside the staging regions)
             store_tiles(out, [&](int i, int j, int r) { return acc[i][j][r] * sc[i][r]; });
+        } else if constexpr (NW == 3) {
+            // Gate and up tiles of the workgroup's 12 (WN * 3) alternate across the waves' regions; an
+            // item is 8 features of one row: two pieces of gate, two of up, one 16-byte store per plane
+            // (16 rows next to each other: 256 contiguous bytes of a fragment).
+            constexpr int TILES = WN * 3, OCTS = TILES;               // 8 features per octet, 8 * TILES features
+            static_assert(TILES % 4 == 0, "whole k-steps of the next slab");
+            float *stage = reinterpret_cast<float *>(smem_u4);
+            stage_rows3(stage + wn * (MT * 16 * C::ROW3), [&](int i, int j, int r) { return acc[i][j][r]; });
+            __syncthreads();
+            const int F = direct.d_ffn, n_ksteps = (F + 31) >> 5, mt_all = (M + 15) >> 4;
+            auto piece = [&](int tile, int row, int c4) __attribute__((always_inline)) {
+                return *reinterpret_cast<const float4 *>(stage + (tile / 3) * (MT * 16 * C::ROW3) + row * C::ROW3 + (tile % 3) * 16 + c4);
+            };
+            for (int idx = tid; idx < MT * 16 * OCTS; idx += WAVES * 64) {
+                const int row = idx % (MT * 16), oct = idx / (MT * 16);                  // octet inside the workgroup
+                const int f = bx * (TILES * 8) + oct * 8, gate = 2 * (oct >> 1), c4 = (oct & 1) * 8;
+                if ((f >> 5) >= n_ksteps || bz * MT + (row >> 4) >= mt_all) continue;
+                const float sc = scale_lds[row];
+                uint32_t hi[4], lo[4];
+#pragma unroll
+                for (int q = 0; q < 2; q++) {
+                    const float4 gv = piece(gate, row, c4 + 4 * q), uv = piece(gate + 1, row, c4 + 4 * q);
+                    const float gs[4] = {gv.x * sc, gv.y * sc, gv.z * sc, gv.w * sc}, us[4] = {uv.x * sc, uv.y * sc, uv.z * sc, uv.w * sc};
+                    uint16_t h[4], l[4];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) split_bf16(f < F ? gs[e] / (1.0f + expf(-gs[e])) * us[e] : 0.f, h[e], l[e]);
+                    hi[2 * q] = h[0] | ((uint32_t)h[1] << 16); hi[2 * q + 1] = h[2] | ((uint32_t)h[3] << 16);
+                    lo[2 * q] = l[0] | ((uint32_t)l[1] << 16); lo[2 * q + 1] = l[2] | ((uint32_t)l[3] << 16);
+                }
+                uint16_t *dst = direct.act_frag + frag_index(0, m_base + row, f, n_ksteps, mt_all, 0);
+                *reinterpret_cast<uint4 *>(dst) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+                *reinterpret_cast<uint4 *>(dst + (int64_t)n_ksteps * mt_all * 512) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            }
+            // (an odd number of 16-feature halves: the octets at or beyond F of the last k-step are
+            // stored as zeros by the workgroup whose columns run over it; where the grid's columns end
+            // at F, the last workgroup clears the half, as below)
+            if (((F >> 4) & 1) && bx * (TILES * 8) + TILES * 8 == F)
+                for (int idx = tid; idx < MT * 16 * 2; idx += WAVES * 64) {
+                    const int row = idx % (MT * 16), f = F + 8 * (idx / (MT * 16));
+                    if (bz * MT + (row >> 4) >= mt_all) continue;
+                    uint16_t *dst = direct.act_frag + frag_index(0, m_base + row, f, n_ksteps, mt_all, 0);
+                    *reinterpret_cast<uint4 *>(dst) = make_uint4(0, 0, 0, 0);
+                    *reinterpret_cast<uint4 *>(dst + (int64_t)n_ksteps * mt_all * 512) = make_uint4(0, 0, 0, 0);
+                }
         } else if constexpr (NW % 2 == 0) {
             // Tiles alternate gate, up: accumulators (j, j+1) hold gate and up of the same 16
             // features for the same rows and lanes.  The workgroup's WN*NW*8 features are whole
@@ -559,7 +631,7 @@ struct GemmVariant { int nw, waves, depth, kgroups; };
 static const GemmVariant g_variants[] = {
     {1, 4, 4, 1}, {2, 4, 4, 1}, {4, 4, 4, 1}, {2, 8, 6, 1}, {4, 8, 6, 1},
     {2, 8, 4, 2}, {4, 8, 4, 2}, {1, 8, 4, 2}, {2, 8, 3, 2}, {2, 16, 3, 2}, {2, 6, 3, 2}, {2, 14, 3, 2},
-    {4, 8, 3, 2},     // 12: tall passes (6 to 9 m-tiles per pass), 16 tiles per k group
+    {4, 8, 3, 2},     // 12: tall passes (6 to 9 m-tiles per pass), 16 tiles per k group (or 12: GemmPlan::tall_tiles)
 };
 #define GEMM_N_VARIANTS ((int)(sizeof(g_variants) / sizeof(g_variants[0])))
 static int g_force_variant = -1, g_force_splits = -1;
@@ -600,6 +672,7 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
     int passes = m_tiles > 7 ? (m_tiles + 4) / 5 : 1;
     if (passes >= 2) p.variant = (NT >= 1024 && NT < 3000) ? 11 : 9;
     p.mt_pass = 0;
+    p.tall_tiles = 16;
     // Tall passes (6 to 9 m-tiles per pass, variant 12): fewer passes over the weights and 16
     // weight tiles per activation fragment, against fewer, fatter workgroups.  What decides is the
     // traffic through one CU's vector L1 (weights + activation slab of the workgroup's k range) times
@@ -629,17 +702,25 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
         const GemmVariant &vn = g_variants[m_tiles <= 7 ? 8 : p.variant];
         const double t_now = estimate(m_tiles <= 7 ? m_tiles : 5, passes, vn.nw * vn.waves / vn.kgroups, &sp_now);
         double t_best = 0.8 * t_now;
+        // 16 or 12 weight tiles per workgroup: a single-split launch whose 16-tile workgroups leave CUs
+        // idle (172 of 256 at 272 rows of the 7B gate/up, 9 m-tiles) or take a nearly empty last round is
+        // cut finer where the estimate falls by a twentieth (gate/up, K = 4096: 170 rows 77.5 -> 72.1 us,
+        // 272 rows 102.4 -> 95.7, 512 rows 198 -> 167 in passes of 8 instead of 5; K = 512, 265 rows:
+        // 26.0 -> 23.9; 7B QKV at 512 rows 99.8 -> 91.5).  Narrower ones were not built: at 12 tiles the
+        // activation reads already take five sixths of the LDS cycles that the multiplies last.
         for (int cap = 9; cap >= 6; cap--) {
             const int n_pass = (m_tiles + cap - 1) / cap, mt = (m_tiles + n_pass - 1) / n_pass;
             if (mt < 6) continue;
-            int sp = 1;
-            const double t = estimate(mt, n_pass, 16, &sp);
-            if (t < t_best) { t_best = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; }
+            for (int tiles : {16, 12}) {
+                int sp = 1;
+                const double t = estimate(mt, n_pass, tiles, &sp);
+                if (t < (tiles == 12 && p.mt_pass ? 0.95 : 1.0) * t_best) { t_best = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; p.tall_tiles = tiles; }
+            }
         }
     }
     if (g_force_variant >= 0 && g_force_variant < GEMM_N_VARIANTS) p.variant = g_force_variant;
     const GemmVariant &v = g_variants[p.variant];
-    const int tiles_wg = v.nw * v.waves / v.kgroups;
+    const int tiles_wg = p.mt_pass ? p.tall_tiles : v.nw * v.waves / v.kgroups;
     const int64_t wgs_n = (NT + tiles_wg - 1) / tiles_wg;
     int64_t splits = (v.waves > 4 ? 256 : 512) / (wgs_n * passes);
     const int64_t max_splits = KS / 8;                          // at least 8 stages per split
@@ -728,7 +809,10 @@ void launch_gemm(const void *a_frag, bool two_planes, int M, int64_t K, const vo
     if (p.mt_pass >= 6 && two_planes) {
         const bool d = direct.kind != GEMM_OUT_PARTIAL;
 #define TALL(MT_) case MT_: \
-            if (d) launch_gemm_t<MT_, 4, true, 8, 3, 2, true>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
+            if (p.tall_tiles == 12) { \
+                if (d) launch_gemm_t<MT_, 3, true, 8, 3, 2, true>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
+                else launch_gemm_t<MT_, 3, true, 8, 3, 2, false>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
+            } else if (d) launch_gemm_t<MT_, 4, true, 8, 3, 2, true>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
             else launch_gemm_t<MT_, 4, true, 8, 3, 2, false>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
             return;
         switch (p.mt_pass) { TALL(6) TALL(7) TALL(8) TALL(9) }

@@ -1,0 +1,63 @@
+"""Tall row passes with 12 weight tiles per workgroup (GPU): the launch heuristic takes them, alone and
+inside a step, at shapes with a ragged last m-tile, a last pass shorter than the others, a ragged
+last column group and gated outputs that end inside a k-step of the next product."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from oracle.model import silu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K", [(170, 22016, 512), (272, 22016, 256), (265, 22000, 288), (488, 12288, 256), (300, 12288, 256),
+                                   (250, 22016, 96)])
+def test_gemm_rows_of_twelve_tiles(M, N, K):
+    import paper_2401_12522_amd as bita
+    g = torch.Generator().manual_seed(N + K + M)
+    a32 = torch.randn(M, K, generator=g)
+    hi = a32.to(torch.bfloat16)
+    lo = (a32 - hi.float()).to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=g) * 0.05).to(torch.bfloat16)
+    out = bita.gemm(hi.cuda(), bita.pack_weight(w.cuda()), N, a_lo=lo.cuda()).cpu().double()
+    ref = (hi.double() + lo.double()) @ w.double().T
+    scale = float(ref.abs().max())
+    assert torch.isfinite(out).all()
+    assert float((out - ref).abs().max()) <= 2e-5 * scale + 1e-6         # fp32 accumulation, as everywhere
+
+
+@pytest.mark.parametrize("d_ffn,batch", [(11008, 4), (10976, 3), (11024, 4), (6160, 8)])
+def test_gated_output_of_twelve_tile_workgroups(d_ffn, batch):
+    """One layer with a wide FFN on 34-row (x batch) passes; the pass with the widths' own launch shapes
+    against the same pass in the older forms (passes of 5 m-tiles), whose parity the step tests hold."""
+    import paper_2401_12522_amd as bita
+    from paper_2401_12522_amd import binding as B
+    cfg = synth.get_config("tiny", d_ffn=d_ffn, n_layers=1)
+    w = synth.SynthWeights(cfg, seed=2, device="cuda", norm_std=0.3)
+    model = bita.Model(cfg, w, max_pos=256)
+    tin = synth.attach_mask_groups(synth.full_branching_tree([4, 3, 2, 1], 64), [0], cfg.n_mask)
+    tmpl = bita.TreeTemplate(tin.parent, tin.is_mask, tin.n_tree, cfg.n_mask)
+    kv = bita.KVState(cfg, 1, batch, 128, tmpl.rows)
+    kv.k_cache.normal_()
+    kv.v_cache.normal_()
+    kv.ctx_len.fill_(50)
+    buf = bita.StepBuffers(model, tmpl, batch, 4, want_logits=True)
+    rng = np.random.default_rng(d_ffn)
+    buf.token.copy_(torch.tensor(rng.integers(0, cfg.vocab, size=tuple(buf.token.shape)), dtype=torch.int32))
+    buf.token[:, tin.n_tree:] = torch.arange(4, dtype=torch.int32, device="cuda")
+
+    def logits():
+        buf.workspace.fill_(0x7F)                       # stale NaNs wherever a kernel does not write
+        bita.verify_step(model, kv, 50, tmpl, buf, batch)
+        torch.cuda.synchronize()
+        return buf.logits.double().cpu()
+    got = logits()
+    B.lib().bita_tune_gemm(-2, -1)
+    try:
+        ref = logits()
+    finally:
+        B.lib().bita_tune_gemm(-1, -1)
+    assert torch.isfinite(got).all()
+    assert float((got - ref).abs().max()) <= 1e-4       # the small shape's regression bound of the step tests
