@@ -108,7 +108,12 @@ struct GemmCfg {
     static_assert((D - 2) * LOADS < 64, "vmcnt counter range");
 };
 
-template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool DIRECT, bool PACK>
+// THROUGH: fp32 outputs are written through the L2 (store_through).  It pays where the launch leaves
+// megabytes behind that would be written back between this kernel and the next: split-K partial sums
+// from 8 MB on and the logits (7B widths, 68 rows: 17 + 9 + 9 MB of partial sums a layer, 9 MB of
+// logits: 3 us of the 340 of two layers and the head); below, and for a single split's sums, the write-back is short and the
+// stores' way to memory costs the workgroups' tails more (68 rows x 22016, 6 MB: 45.2 us plain, 45.5).
+template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool DIRECT, bool PACK, bool THROUGH>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // The first 14 dwords of the argument block arrive in scalar registers with the wave
     // (kernel-argument preload); everything the first loads depend on is among them, the grid's
@@ -405,13 +410,19 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // pieces.  Rows of 4-row group g sit in the half of the row given by g's parity (two-way
     // instead of four-way bank conflicts).
     auto store_tiles = [&](float *o, auto &&value) __attribute__((always_inline)) {
+        // THROUGH: a store's 32-bit offset counts from the instruction's first row (8 rows at most)
+        auto put = [&](int row0, int row, int chunk, const float4 &v) __attribute__((always_inline)) {
+            if constexpr (!THROUGH) *reinterpret_cast<float4 *>(o + (int64_t)(m_base + row) * ldo + t0 * 16 + chunk * 4) = v;
+            else store_through(through_rsrc(o + (int64_t)(m_base + row0) * ldo, 0xFFFFFFFCu),
+                          ((uint32_t)(row - row0) * (uint32_t)ldo + (uint32_t)(t0 * 16 + chunk * 4)) * 4u, v);
+        };
         if constexpr (NW == 3) {
             float *stage = reinterpret_cast<float *>(smem_u4) + wn * (MT * 16 * C::ROW3);
             stage_rows3(stage, value);
-            for (int idx = lane; idx < MT * 16 * 12; idx += 64) {
-                const int row = idx / 12, chunk = idx % 12, m = m_base + row, t = t0 + (chunk >> 2);
+            for (int i0 = 0; i0 < MT * 16 * 12; i0 += 64) {       // (a multiple of 64)
+                const int idx = i0 + lane, row = idx / 12, chunk = idx % 12, m = m_base + row, t = t0 + (chunk >> 2);
                 const float4 v = *reinterpret_cast<const float4 *>(stage + row * C::ROW3 + chunk * 4);
-                if (m < M && t < NT) *reinterpret_cast<float4 *>(o + (int64_t)m * ldo + t0 * 16 + chunk * 4) = v;
+                if (m < M && t < NT) put(i0 / 12, row, chunk, v);
             }
         } else if constexpr (KG > 1) {
             constexpr int CPR = NW * 4, RPI = 64 / CPR;       // 16-byte chunks per row, rows per store instruction
@@ -432,7 +443,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
                 const int phys = chunk ^ ((CPR / 2) * ((row >> 2) & 1));
                 const float4 v = *reinterpret_cast<const float4 *>(stage + row * (NW * 16) + phys * 4);
                 const int m = m_base + row, t = t0 + (chunk >> 2);
-                if (m < M && t < NT) *reinterpret_cast<float4 *>(o + (int64_t)m * ldo + t0 * 16 + chunk * 4) = v;
+                if (m < M && t < NT) put(k * RPI, row, chunk, v);
             }
         } else {
 #pragma unroll
@@ -735,20 +746,26 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
     return p;
 }
 
-template <int MT, int NW, bool SPLIT, int WAVES, int D, int KG, bool DIRECT, bool PACK = false>
+template <int MT, int NW, bool SPLIT, int WAVES, int D, int KG, bool DIRECT, bool PACK = false, bool THROUGH = DIRECT>
 static void launch_gemm_t(const void *a_frag, int M, int64_t K, const void *w, int64_t N, float *out, int64_t ldo,
                           const GemmPlan &p, hipStream_t s, const GemmOutput &direct) {
+    if constexpr (MT > 1 && SPLIT && KG > 1 && !THROUGH) {
+        if (p.splits > 1 && (int64_t)p.splits * M * ldo * 4 >= (8 << 20)) {
+            launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, true>(a_frag, M, K, w, N, out, ldo, p, s, direct);
+            return;
+        }
+    }
     constexpr int KC = 1;
     using C = GemmCfg<MT, NW, SPLIT, KC, D, WAVES, KG, PACK>;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK>,
+        (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
         attr_set = true;
     }
     const int NT = (int)(N / 16), KS = (int)((K + 31) / 32), m_tiles = (M + 15) / 16;
     dim3 grid((NT + C::WN * NW - 1) / (C::WN * NW), p.splits, (m_tiles + MT - 1) / MT);
-    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK>), grid, dim3(WAVES * 64), C::SMEM, s,
+    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH>), grid, dim3(WAVES * 64), C::SMEM, s,
                        (const uint4 *)a_frag, (const uint4 *)w, KS * m_tiles, M, m_tiles, NT, KS, p.ksteps_per_split,
                        (int)grid.x, (int)grid.y, (int)grid.z, out, ldo, direct);
 }
