@@ -262,12 +262,13 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         }
 
     f32x4 o_acc[U][NTN];
-    float m_run[U], l_run[U];
+    float m_run[U], neg_m[U], l_run[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
 #pragma unroll
         for (int nt = 0; nt < NTN; nt++) o_acc[u][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
         m_run[u] = -INFINITY;
+        neg_m[u] = 0.f;
         l_run[u] = 0.f;
     }
 
@@ -279,19 +280,13 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     // plus 16 rows: an immediate offset of the read)
     static_assert(att_swizzle_k<HD>(16) == 0 && att_swizzle<HD>(16) == 0, "row bit 4 outside the swizzles");
     constexpr int ROWS16 = 16 * HD * 2;
-    uint32_t k_addr[KSN];
-#pragma unroll
-    for (int ks = 0; ks < KSN; ks++)
-        k_addr[ks] = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)v_ring) +
-                     c * (HD * 2) + (((4 * ks + g) ^ att_swizzle_k<HD>(c)) * 16);
-    uint32_t v_addr[NTN];
-#pragma unroll
-    for (int nt = 0; nt < NTN; nt++) {
-        const int rho = 4 * g + (c >> 2);
-        const int gran = (2 * nt + ((c & 3) >> 1)) ^ att_swizzle<HD>(rho);
-        v_addr[nt] = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)v_ring) +
-                     C::KV_BYTES + rho * (HD * 2) + gran * 16 + (c & 1) * 8;
-    }
+    // The k-step and the head-dim tile sit in address bits that neither the row nor the ring slot
+    // touches: one register each, the others an exclusive-or away (11 registers less, which two heads
+    // per workgroup spilled before).
+    const uint32_t k_addr = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)v_ring) +
+                            c * (HD * 2) + ((g ^ att_swizzle_k<HD>(c)) * 16);
+    const uint32_t v_addr = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)v_ring) + C::KV_BYTES +
+                            (4 * g + (c >> 2)) * (HD * 2) + ((((c & 3) >> 1)) ^ att_swizzle<HD>(4 * g + (c >> 2))) * 16 + (c & 1) * 8;
 
     // Per-lane byte offsets of the fast path (a chunk that lies wholly inside the cache).  Both
     // operands are copied row-major, 1 KiB (RPI rows) per global->LDS instruction: instruction
@@ -304,13 +299,6 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     const int v_lane_row = lane / GPR;                                  // row inside one instruction
     const int lane_slot = att_slot_of_row(v_lane_row);
     const int lane_tree_row = 4 * (lane_slot >> 3) + (lane_slot & 3);
-    uint32_t k_gran[4], v_gran[2];                                      // source granule (bytes) at this lane's position
-#pragma unroll
-    for (int par = 0; par < 4; par++) {
-        const int rho = par * RPI + v_lane_row;
-        k_gran[par] = ((lane % GPR) ^ att_swizzle_k<HD>(rho)) * 16;
-        if (par < 2) v_gran[par] = ((lane % GPR) ^ att_swizzle<HD>(rho)) * 16;
-    }
 
     // The two global->LDS loads (one K, one V instruction) number iv < NVI of this wave's stage i,
     // the mask word riding with the last.  A chunk wholly inside the cache takes one uniform base
@@ -320,13 +308,15 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     auto emit = [&](int i, int iv) __attribute__((always_inline)) {
         const int chunk = chunk_begin + wave + ATT_WAVES * i;
         const int base = chunk * ATT_CHUNK;
+        const uint32_t k_gran_iv = ((lane % GPR) ^ att_swizzle_k<HD>((iv & 3) * RPI + v_lane_row)) * 16;
+        const uint32_t v_gran_iv = ((lane % GPR) ^ att_swizzle<HD>((iv & 1) * RPI + v_lane_row)) * 16;
         const unsigned char *zero_b = reinterpret_cast<const unsigned char *>(zero);
         const int slot0 = att_slot_of_row(iv * RPI);                    // slot of the instruction's first row
         gptr k_src, v_src, a_src = (gptr)(zero_b + (lane & 1) * 8);
         if (base >= P && base + ATT_CHUNK <= n_ctx_keys && one_page(base - P)) {
             const int64_t row_bytes = (slot_off(base - P) + (int64_t)(slot0 + lane_slot) * HD) * 2;
-            k_src = (gptr)(reinterpret_cast<const unsigned char *>(ck) + row_bytes + k_gran[iv & 3]);
-            v_src = (gptr)(reinterpret_cast<const unsigned char *>(cv) + row_bytes + v_gran[iv & 1]);
+            k_src = (gptr)(reinterpret_cast<const unsigned char *>(ck) + row_bytes + k_gran_iv);
+            v_src = (gptr)(reinterpret_cast<const unsigned char *>(cv) + row_bytes + v_gran_iv);
         } else if (chunk >= n_cc) {
             // over the pass rows: one plane and 4-row group per instruction, rows beyond R are zero
             const int j_first = (chunk - n_cc) * 16;
@@ -334,8 +324,8 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
             const int j = j_first + 4 * (slot0 >> 3) + lane_tree_row;
             const uint16_t *kp = (slot0 & 4) ? tk_lo : tk, *vp = (slot0 & 4) ? tv_lo : tv;   // uniform
             const bool k_ok = j < R && kp, v_ok = j < R && vp;
-            k_src = (gptr)(reinterpret_cast<const unsigned char *>(k_ok ? kp + (int64_t)j * HD : zero) + k_gran[iv & 3]);
-            v_src = (gptr)(reinterpret_cast<const unsigned char *>(v_ok ? vp + (int64_t)j * HD : zero) + v_gran[iv & 1]);
+            k_src = (gptr)(reinterpret_cast<const unsigned char *>(k_ok ? kp + (int64_t)j * HD : zero) + k_gran_iv);
+            v_src = (gptr)(reinterpret_cast<const unsigned char *>(v_ok ? vp + (int64_t)j * HD : zero) + v_gran_iv);
         } else {
             // a chunk with prefix rows or the ragged end of the cache
             const int kidx = base + slot0 + lane_slot;
@@ -343,8 +333,8 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
             const int64_t off = in_cache ? slot_off(kidx - P) : 0;
             const uint16_t *krow = in_prefix ? pk + (int64_t)kidx * HD : (in_cache ? ck + off : zero);
             const uint16_t *vrow = in_prefix ? pv + (int64_t)kidx * HD : (in_cache ? cv + off : zero);
-            k_src = (gptr)(reinterpret_cast<const unsigned char *>(krow) + k_gran[iv & 3]);
-            v_src = (gptr)(reinterpret_cast<const unsigned char *>(vrow) + v_gran[iv & 1]);
+            k_src = (gptr)(reinterpret_cast<const unsigned char *>(krow) + k_gran_iv);
+            v_src = (gptr)(reinterpret_cast<const unsigned char *>(vrow) + v_gran_iv);
         }
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)k_src,
                                          (__attribute__((address_space(3))) void *)(v_ring + iv * 1024), 16, 0, 0);
@@ -353,15 +343,22 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         if (iv == NVI - 1) anc_next = *(const __attribute__((address_space(1))) uint64_t *)a_src;
     };
 
-    // The same two loads for a chunk known to lie wholly inside the cache (all but a handful):
-    // one uniform base per operand, the lane's constant offset, the instruction's constant row.
-    const uint32_t lane_row_bytes = (uint32_t)lane_slot * (HD * 2);
-    auto emit_cache = [&](const unsigned char *kb, const unsigned char *vb, int iv) __attribute__((always_inline)) {
-        const uint32_t row0_bytes = (uint32_t)att_slot_of_row(iv * RPI) * (HD * 2);      // compile-time per iv
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr)(kb + (lane_row_bytes + k_gran[iv & 3] + row0_bytes)),
-                                         (__attribute__((address_space(3))) void *)(v_ring + iv * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr)(vb + (lane_row_bytes + v_gran[iv & 1] + row0_bytes)),
-                                         (__attribute__((address_space(3))) void *)(v_ring + C::KV_BYTES + iv * 1024), 16, 0, 0);
+    // The same two loads for a chunk known to lie wholly inside the cache (all but a handful), as
+    // buffer loads: a uniform descriptor per operand, the lane's constant offset in a register, the
+    // chunk's and the instruction's first row in the scalar offset: no vector instruction per load
+    // and no 64-bit lane addresses, so that two heads per workgroup have the registers for it too.
+    // (Descriptors span the sequence's cached slots, or a page's; the offsets stay inside.)
+    uint32_t k_off[4], v_off[2];
+#pragma unroll
+    for (int par = 0; par < 4; par++) {
+        const int rho = par * RPI + v_lane_row;                         // (source granule, in bytes, at this lane's position)
+        k_off[par] = (uint32_t)lane_slot * (HD * 2) + ((lane % GPR) ^ att_swizzle_k<HD>(rho)) * 16;
+        if (par < 2) v_off[par] = (uint32_t)lane_slot * (HD * 2) + ((lane % GPR) ^ att_swizzle<HD>(rho)) * 16;
+    }
+    auto emit_cache = [&](__amdgpu_buffer_rsrc_t kr, __amdgpu_buffer_rsrc_t vr, uint32_t chunk_bytes, int iv) __attribute__((always_inline)) {
+        const uint32_t at = chunk_bytes + (uint32_t)att_slot_of_row(iv * RPI) * (HD * 2);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void *)(v_ring + iv * 1024), 16, k_off[iv & 3], at, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void *)(v_ring + C::KV_BYTES + iv * 1024), 16, v_off[iv & 1], at, 0, 0);
     };
 
     // One chunk.  Its K and V fragments are all pulled into registers first, which frees the
@@ -373,16 +370,18 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         const bool tree_chunk = chunk >= n_cc;
         const int base = chunk * ATT_CHUNK;
         u32x4 kf[2][KSN];
+        uint32_t ka = k_addr, va = v_addr;
+        if constexpr (U > 1) asm volatile("" : "+v"(ka), "+v"(va));   // (the derived addresses are not kept across chunks)
 #pragma unroll
-        for (int tt = 0; tt < 2; tt++)
-#pragma unroll
-            for (int ks = 0; ks < KSN; ks++)
-                kf[tt][ks] = tt ? lds_read_b128<ROWS16>(k_addr[ks]) : lds_read_b128<0>(k_addr[ks]);
+        for (int ks = 0; ks < KSN; ks++) {
+            kf[0][ks] = lds_read_b128<0>(ka ^ (64 * ks));
+            kf[1][ks] = lds_read_b128<ROWS16>(ka ^ (64 * ks));
+        }
         s16x4 vh[NTN][2];
 #pragma unroll
         for (int nt = 0; nt < NTN; nt++) {
-            vh[nt][0] = lds_read_tr16<0>(v_addr[nt]);
-            vh[nt][1] = lds_read_tr16<ROWS16>(v_addr[nt]);
+            vh[nt][0] = lds_read_tr16<0>(va ^ (32 * nt));
+            vh[nt][1] = lds_read_tr16<ROWS16>(va ^ (32 * nt));
         }
         lds_wait_all(kf, vh);
         f32x4 s_acc[U][2];
@@ -399,20 +398,24 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
             }
         };
         const int base_n = base + ATT_WAVES * ATT_CHUNK;                 // the wave's next chunk
-        // (with two heads per workgroup the second code path costs registers the kernel does not have)
-        if (U == 1 && more && base_n >= P && base_n + ATT_CHUNK <= n_ctx_keys && one_page(base_n - P)) {   // wave-uniform
-            const int64_t off_n = slot_off(base_n - P) * 2;
-            const unsigned char *kb = reinterpret_cast<const unsigned char *>(ck) + off_n;
-            const unsigned char *vb = reinterpret_cast<const unsigned char *>(cv) + off_n;
+        // (a sequence of more than 2^23 slots leaves the descriptors' 32-bit offsets: general path)
+        if (more && base_n >= P && base_n + ATT_CHUNK <= n_ctx_keys && one_page(base_n - P) && Lc <= (1 << 23)) {   // wave-uniform
+            // contiguous: one descriptor for the sequence's slots; paged: one for the chunk's page
+            const int64_t first = PAGED ? (int64_t)__builtin_amdgcn_readfirstlane(tbl[(base_n - P) >> page_lg]) * page_stride : 0;
+            const uint32_t slot = PAGED ? (base_n - P) & page_mask : base_n - P;
+            const uint32_t span = (uint32_t)(PAGED ? 1 << page_lg : Lc) * (HD * 2);
+            const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)(ck + first), 0, span, 0x00027000);
+            const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)(cv + first), 0, span, 0x00027000);
+            const uint32_t chunk_bytes = slot * (HD * 2);
 #pragma unroll
             for (int iv = 0; iv < NVI; iv++) {
-                emit_cache(kb, vb, iv);
+                emit_cache(kr, vr, chunk_bytes, iv);
                 __builtin_amdgcn_sched_barrier(0);
                 qk(iv);
                 __builtin_amdgcn_sched_barrier(0);
             }
             anc_next = 0;
-        } else {
+        } else if constexpr (U == 1) {
 #pragma unroll
             for (int iv = 0; iv < NVI; iv++) {
                 if (more) emit(i + 1, iv);
@@ -420,6 +423,17 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
                 qk(iv);
                 __builtin_amdgcn_sched_barrier(0);
             }
+        } else {
+            // one copy of the general loads ahead of the matrix instructions: unrolled between them they
+            // cost the two-head form its registers (a reload per chunk) and most of its instructions
+            if (more) {
+#pragma unroll 1
+                for (int iv = 0; iv < NVI; iv++) emit(i + 1, iv);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int iv = 0; iv < NVI; iv++) qk(iv);
+            __builtin_amdgcn_sched_barrier(0);
         }
         // the visibility of a key depends on the row and the key only: one mask word for all heads
         const bool need_mask = tree_chunk || (base < P) || (base + ATT_CHUNK > n_ctx_keys);
@@ -453,11 +467,11 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
                            vh[nt][1][0], vh[nt][1][1], vh[nt][1][2], vh[nt][1][3]};
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            float sv[8];
+            float sv[8];                     // q.k, unscaled: the scale rides in the exponent's multiply-add
 #pragma unroll
             for (int tt = 0; tt < 2; tt++)
 #pragma unroll
-                for (int r = 0; r < 4; r++) sv[tt * 4 + r] = s_acc[u][tt][r] * scale_log2;
+                for (int r = 0; r < 4; r++) sv[tt * 4 + r] = s_acc[u][tt][r];
             if (tree_chunk) {                // score = q.k_hi + q.k_lo; partner slots leave the softmax
 #pragma unroll
                 for (int e = 0; e < 4; e++) sv[e] += sv[e + 4];
@@ -469,18 +483,26 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
             float mx = sv[0];
 #pragma unroll
             for (int e = 1; e < 8; e++) mx = fmaxf(mx, sv[e]);
-            mx = max_over_lane_groups(mx);
-            const float m_new = fmaxf(m_run[u], mx);
-            const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-            const float alpha = fast_exp2(m_run[u] - m_use);
-            m_run[u] = m_new;
+            // The running maximum rarely moves after the first chunks: the lane groups are reduced and
+            // the sums rescaled only where some lane's scores exceed it.  neg_m = -(maximum x scale), the
+            // number every exponent is taken against (0 while a row has seen no key).
+            if (__builtin_amdgcn_ballot_w64(mx > m_run[u]) != 0) {
+                const float m_new = fmaxf(m_run[u], max_over_lane_groups(mx));
+                const float neg_new = m_new == -INFINITY ? 0.f : -m_new * scale_log2;
+                const float alpha = m_run[u] == -INFINITY ? 0.f : fast_exp2(neg_new - neg_m[u]);
+                m_run[u] = m_new;
+                neg_m[u] = neg_new;
+                l_run[u] *= alpha;
+#pragma unroll
+                for (int nt = 0; nt < NTN; nt++) o_acc[u][nt] *= alpha;
+            }
             // probabilities as two bf16 planes (value and rounding residual), like every other
             // MFMA input of the pass
             float ps = 0.f;
             uint32_t pk2[4], pl2[4];
 #pragma unroll
             for (int e = 0; e < 8; e += 2) {
-                const float p0 = fast_exp2(sv[e] - m_use), p1 = fast_exp2(sv[e + 1] - m_use);
+                const float p0 = fast_exp2(fmaf(sv[e], scale_log2, neg_m[u])), p1 = fast_exp2(fmaf(sv[e + 1], scale_log2, neg_m[u]));
                 ps += p0 + p1;
                 const uint32_t hi = cvt_pk_bf16(p0, p1);
                 pk2[e >> 1] = hi;
@@ -492,13 +514,8 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
                 pl2[2] = pl2[0];
                 pl2[3] = pl2[1];
             }
-            l_run[u] = l_run[u] * alpha + ps;
-            // O^T[hd][q] = alpha * O^T + V^T[hd][slots 8g..8g+7] * P^T; the running maximum rarely
-            // moves after the first chunks, and then alpha is exactly 1 in every lane
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-                for (int nt = 0; nt < NTN; nt++) o_acc[u][nt] *= alpha;
-            }
+            l_run[u] += ps;
+            // O^T[hd][q] += V^T[hd][slots 8g..8g+7] * P^T
             const bf16x8 pf = __builtin_bit_cast(bf16x8, make_uint4(pk2[0], pk2[1], pk2[2], pk2[3]));
             const bf16x8 pf_lo = __builtin_bit_cast(bf16x8, make_uint4(pl2[0], pl2[1], pl2[2], pl2[3]));
 #pragma unroll
@@ -512,8 +529,13 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
 
     // ---- per-wave loop: one chunk in flight behind the one being multiplied -------------------
     if (n_my > 0) {
+        if constexpr (U == 1) {
 #pragma unroll
-        for (int iv = 0; iv < NVI; iv++) emit(0, iv);
+            for (int iv = 0; iv < NVI; iv++) emit(0, iv);
+        } else {
+#pragma unroll 1
+            for (int iv = 0; iv < NVI; iv++) emit(0, iv);
+        }
     }
     att_wait<0>();                                      // the first chunk and the prologue's loads have landed
     // (looked at here, where the prologue's loads have landed anyway: ahead of them it cost 0.5 % of
@@ -539,8 +561,9 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         const int h = h0 + u;
         __syncthreads();                     // the chunk buffers (first head) or the previous head's sums are done with
         const float l = sum_over_lane_groups(l_run[u]);
+        const float m_log2 = m_run[u] == -INFINITY ? -INFINITY : -neg_m[u];     // the maximum in powers of two
         if (g == 0) {
-            sm[wave * 16 + c] = m_run[u];
+            sm[wave * 16 + c] = m_log2;
             sl[wave * 16 + c] = l;
         }
         __syncthreads();
@@ -551,7 +574,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         float l_tot = 0.f;
 #pragma unroll
         for (int w = 0; w < ATT_WAVES; w++) l_tot += sl[w * 16 + c] * fast_exp2(sm[w * 16 + c] - m_use);
-        const float f = fast_exp2(m_run[u] - m_use);
+        const float f = fast_exp2(m_log2 - m_use);
 #pragma unroll
         for (int nt = 0; nt < NTN; nt++)
             region[(wave * NTN + nt) * 64 + lane] =
