@@ -734,8 +734,10 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
         for (int cap = 9; cap >= 6; cap--) {
             const int n_pass = (m_tiles + cap - 1) / cap, mt = (m_tiles + n_pass - 1) / n_pass;
             if (mt < 6) continue;
+            int sp = 1;
             for (int tiles : {16, 12}) {
-                int sp = 1;
+                // (small matrices, fewer than half the CUs at 16 tiles, are latency: the shorter epilogue wins)
+                if (tiles == 12 && (NT + 15) / 16 * n_pass * sp < 128) continue;
                 const double t = estimate(mt, n_pass, tiles, &sp);
                 if (t < (tiles == 12 && p.mt_pass ? 0.95 : 1.0) * t_best) { t_best = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; p.tall_tiles = tiles; }
             }
