@@ -371,7 +371,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         const int base = chunk * ATT_CHUNK;
         u32x4 kf[2][KSN];
         uint32_t ka = k_addr, va = v_addr;
-        if constexpr (U > 1) asm volatile("" : "+v"(ka), "+v"(va));   // (the derived addresses are not kept across chunks)
+        if constexpr (U > 1 && HD == 128) asm volatile("" : "+v"(ka), "+v"(va));   // (the derived addresses are not kept across chunks)
 #pragma unroll
         for (int ks = 0; ks < KSN; ks++) {
             kf[0][ks] = lds_read_b128<0>(ka ^ (64 * ks));
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
                 __builtin_amdgcn_sched_barrier(0);
             }
             anc_next = 0;
-        } else if constexpr (U == 1) {
+        } else if constexpr (U == 1 || HD == 64) {
 #pragma unroll
             for (int iv = 0; iv < NVI; iv++) {
                 if (more) emit(i + 1, iv);
@@ -424,8 +424,8 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
-            // one copy of the general loads ahead of the matrix instructions: unrolled between them they
-            // cost the two-head form its registers (a reload per chunk) and most of its instructions
+            // (two heads of 128) one copy of the general loads ahead of the matrix instructions: unrolled
+            // between them they cost the registers (a reload per chunk) and most of the instructions
             if (more) {
 #pragma unroll 1
                 for (int iv = 0; iv < NVI; iv++) emit(i + 1, iv);
@@ -529,13 +529,8 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
 
     // ---- per-wave loop: one chunk in flight behind the one being multiplied -------------------
     if (n_my > 0) {
-        if constexpr (U == 1) {
 #pragma unroll
-            for (int iv = 0; iv < NVI; iv++) emit(0, iv);
-        } else {
-#pragma unroll 1
-            for (int iv = 0; iv < NVI; iv++) emit(0, iv);
-        }
+        for (int iv = 0; iv < NVI; iv++) emit(0, iv);
     }
     att_wait<0>();                                      // the first chunk and the prologue's loads have landed
     // (looked at here, where the prologue's loads have landed anyway: ahead of them it cost 0.5 % of
