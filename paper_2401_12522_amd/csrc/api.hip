@@ -389,10 +389,10 @@ int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, c
         }
     };
 
-    launch_embed(d_token, td, batch, m->tok_emb, m->mask_emb, d, c.vocab, x, s);
     int pending = 0;                                    // split-K partials waiting to be added to x
     for (int l = 0; l < c.n_layers; l++) {
-        launch_rmsnorm_prep(x, partial, pending, M, d, m->attn_norm[l], h, ssq, s);
+        if (l == 0) launch_embed_prep(d_token, td, batch, m->tok_emb, m->mask_emb, d, c.vocab, m->attn_norm[0], x, h, ssq, s);
+        else launch_rmsnorm_prep(x, partial, pending, M, d, m->attn_norm[l], h, ssq, s);
         timed_gemm(h, M, d, m->wqkv[l], nqkv, partial, nqkv, p_qkv, s);
         void *kt = (unsigned char *)kv->k_tree + l * kv_layer_tree, *vt = (unsigned char *)kv->v_tree + l * kv_layer_tree;
         launch_qkv_rope(partial, p_qkv.splits, batch, td, c.n_heads, c.n_kv_heads, hd, d_ctx_len, m->rope_cos,

@@ -156,8 +156,11 @@ void launch_reduce_partials(const float *partial, int splits, int m_rows, int64_
 void launch_pack(const void *src, int64_t n_rows, int64_t k, void *dst, int64_t tile0,
                  int64_t tile_stride, int64_t total_tiles, hipStream_t s);
 
-void launch_embed(const int32_t *token, const TemplateDev &t, int batch, const void *tok_emb,
-                  const void *mask_emb, int d, int vocab, float *x, hipStream_t s);
+// Where the first layer's norm takes its rows from (see rmsnorm_prep_kernel).
+struct EmbedSource { const int32_t *token; const uint8_t *is_mask; const int32_t *mask_index; const uint16_t *tok_emb, *mask_emb; int rows, vocab; };
+// x = embeddings of the pass' rows, and the first norm's slab and sums of squares
+void launch_embed_prep(const int32_t *token, const TemplateDev &t, int batch, const void *tok_emb, const void *mask_emb, int d,
+                       int vocab, const void *gain, float *x, void *h_frag, float *ssq, hipStream_t s);
 // x += sum of partials (optional), then h = rmsnorm(x) * gain as bf16 with row stride ldh
 // RMSNorm is split: the prep kernel writes x*gain (two planes, fragment order) and per-chunk
 // sums of squares ssq[m_rows][RMS_MAX_CHUNKS]; the row factor rsqrt(sum(ssq)/d + eps) commutes
