@@ -347,7 +347,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     // buffer loads: a uniform descriptor per operand, the lane's constant offset in a register, the
     // chunk's and the instruction's first row in the scalar offset: no vector instruction per load
     // and no 64-bit lane addresses, so that two heads per workgroup have the registers for it too.
-    // (Descriptors span the sequence's cached slots, or a page's; the offsets stay inside.)
+    // (Descriptors span the sequence's cached slots, or those of them a page can hold; the offsets stay inside.)
     uint32_t k_off[4], v_off[2];
 #pragma unroll
     for (int par = 0; par < 4; par++) {
@@ -403,7 +403,9 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
             // contiguous: one descriptor for the sequence's slots; paged: one for the chunk's page
             const int64_t first = PAGED ? (int64_t)__builtin_amdgcn_readfirstlane(tbl[(base_n - P) >> page_lg]) * page_stride : 0;
             const uint32_t slot = PAGED ? (base_n - P) & page_mask : base_n - P;
-            const uint32_t span = (uint32_t)(PAGED ? 1 << page_lg : Lc) * (HD * 2);
+            // (both in slots of at most 2^23: a page may be larger than a descriptor can span, what of it
+            // lies inside the sequence is not, and a chunk wholly inside the cache ends there)
+            const uint32_t span = (uint32_t)(PAGED ? min(1 << page_lg, Lc) : Lc) * (HD * 2);
             const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)(ck + first), 0, span, 0x00027000);
             const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)(cv + first), 0, span, 0x00027000);
             const uint32_t chunk_bytes = slot * (HD * 2);

@@ -89,6 +89,34 @@ def test_paged_steps_are_bit_identical_to_contiguous(bita, cfg_name, n_layers, p
     assert spare and not paged.k_cache[:, spare].any() and not paged.v_cache[:, spare].any()
 
 
+@pytest.mark.parametrize("hd,heads,page_lg", [(128, 1, 23), (128, 1, 24), (128, 2, 24), (128, 1, 25), (64, 2, 24), (64, 1, 25)])
+def test_pages_whose_bytes_leave_32_bits(bita, hd, heads, page_lg):
+    """One page larger than the sequence, of 2, 4 or 8 GiB per K/V head (4 GiB and its multiples are zero
+    in 32 bits): the step still equals the contiguous one bit for bit, over a context of several
+    chunks per wave."""
+    cfg = synth.get_config("tiny", n_layers=1, d_model=128, n_heads=heads, n_kv_heads=1, head_dim=hd, d_ffn=256)
+    n = 900
+    tin = synth.attach_mask_groups(synth.random_tree(12, 4, 1), [0], cfg.n_mask)
+    model = bita.Model(cfg, synth.SynthWeights(cfg, seed=4, device="cuda"), max_pos=n + 128)
+    tmpl = bita.TreeTemplate(tin.parent, tin.is_mask, tin.n_tree, cfg.n_mask)
+    flat = bita.KVState(cfg, 1, 1, n + 64, tmpl.rows)
+    paged = bita.PagedKVState(cfg, 1, 1, n + 64, tmpl.rows, 1 << page_lg)
+    _random_cache(flat, [n], 5)
+    paged.load_contiguous(0, flat.k_cache[:, 0], flat.v_cache[:, 0], n)
+    bufs = [bita.StepBuffers(model, tmpl, 1, tmpl.kmax, want_logits=True) for _ in range(2)]
+    rng = np.random.default_rng(13)
+    root, cand = dev_i32(rng.integers(0, cfg.vocab, 1)), dev_i32(rng.integers(0, cfg.vocab, (1, cfg.n_mask, tmpl.kmax)))
+    for kv, buf in ((flat, bufs[0]), (paged, bufs[1])):
+        bita.decode_step(model, kv, n, tmpl, buf, 1, root, cand)
+    torch.cuda.synchronize()
+    assert torch.isfinite(bufs[0].logits).all()
+    assert torch.equal(bufs[0].logits, bufs[1].logits), (bufs[0].logits - bufs[1].logits).abs().max().item()
+    grown = int(flat.ctx_len[0])
+    assert grown == int(paged.ctx_len[0]) > n
+    assert torch.equal(paged.k_cache[0, 0, :, :grown], flat.k_cache[0, 0, :, :grown])
+    assert torch.equal(paged.v_cache[0, 0, :, :grown], flat.v_cache[0, 0, :, :grown])
+
+
 def test_paged_prefill_and_decode_against_oracle(bita):
     """Prompt -> pages -> tokens: the pages hold the oracle's causal-pass K/V and the stream is
     the oracle's greedy stream where its margins are decisive."""
