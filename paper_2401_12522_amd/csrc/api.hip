@@ -551,7 +551,6 @@ extern "C" int bita_gemm(const void *d_a, const void *d_a_lo, int32_t m_rows, in
 // forbid hipMalloc): the split-K partial sums and the re-laid activation fragments, which
 // bita_gemm takes from the caller's workspace, live in a static device array instead.  Every GPU
 // holds its own copy of the array at its own address; the address is looked up once per device.
-#define BITA_NOALLOC_SCRATCH_BYTES (32u << 20)
 #define BITA_NOALLOC_MAX_DEVICES 64
 static __device__ __align__(256) unsigned char scratch[BITA_NOALLOC_SCRATCH_BYTES];
 static void *g_scratch_ptr[BITA_NOALLOC_MAX_DEVICES] = {};

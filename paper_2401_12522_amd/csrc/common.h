@@ -143,6 +143,9 @@ enum { GEMM_OUT_PARTIAL = 0, GEMM_OUT_SCALED = 1, GEMM_OUT_SILU = 2 };
 struct GemmOutput { int kind; RowScale rs; uint16_t *act_frag; int d_ffn; };
 bool gemm_direct_output_possible(const GemmPlan &p, int kind);
 void gemm_force_plan(int variant, int splits);   // tuning aid: < 0 restores the heuristic
+// Device bytes of the static scratch behind bita_gemm_noalloc.  The planner knows it because a shape's
+// plan, and with it the result's last bits, is the same for every caller.
+#define BITA_NOALLOC_SCRATCH_BYTES (32u << 20)
 GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k);
 size_t frag_bytes(int m_rows, int64_t k);        // bytes of a two-plane activation slab
 // a_frag: activations in fragment order (see frag_index); out_partial: [splits][m_rows][ldo] fp32

@@ -725,12 +725,20 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
         const GemmVariant &vn = g_variants[m_tiles <= 7 ? 8 : p.variant];
         const double t_now = estimate(m_tiles <= 7 ? m_tiles : 5, passes, vn.nw * vn.waves / vn.kgroups, &sp_now);
         double t_best = 0.8 * t_now;
-        // 16 or 12 weight tiles per workgroup: a single-split launch whose 16-tile workgroups leave CUs
-        // idle (172 of 256 at 272 rows of the 7B gate/up, 9 m-tiles) or take a nearly empty last round is
-        // cut finer where the estimate falls by a twentieth (gate/up, K = 4096: 170 rows 77.5 -> 72.1 us,
+        // 16 or 12 weight tiles per workgroup: a launch whose 16-tile workgroups leave CUs idle (172 of
+        // 256 at 272 rows of the 7B gate/up, 9 m-tiles) or take a nearly empty last round is cut finer
+        // where the estimate falls by a twentieth (gate/up, K = 4096: 170 rows 77.5 -> 72.1 us,
         // 272 rows 102.4 -> 95.7, 512 rows 198 -> 167 in passes of 8 instead of 5; K = 512, 265 rows:
-        // 26.0 -> 23.9; 7B QKV at 512 rows 99.8 -> 91.5).  Narrower ones were not built: at 12 tiles the
-        // activation reads already take five sixths of the LDS cycles that the multiplies last.
+        // 26.0 -> 23.9; 7B QKV at 512 rows 99.8 -> 91.5).  Between 81 and 144 rows that can mean two or
+        // four k splits where passes of 5 or 7 m-tiles had one or two, and for gate/up the gating in a
+        // kernel of its own, which the estimate leaves out; it pays all the same (one 7B layer and the
+        // LM head, all reducers included, 12 tiles at one split only -> this rule: 84 rows 228 -> 223 us,
+        // 96 243 -> 233, 105 260 -> 253, 112 261 -> 254, 120 267 -> 259, 128 271 -> 265, 134 300 -> 292,
+        // 144 300 -> 294, four sequences of 68 454 -> 440).  Narrower workgroups were not built: at 12
+        // tiles the activation reads already take five sixths of the LDS cycles that the multiplies last.
+        // More splits need more scratch: where they would not fit the static one of bita_gemm_noalloc the
+        // form is left out, so that it takes no shape away from that call (none of the 7B, 13B and 70B
+        // matrices up to 544 rows comes near).
         for (int cap = 9; cap >= 6; cap--) {
             const int n_pass = (m_tiles + cap - 1) / cap, mt = (m_tiles + n_pass - 1) / n_pass;
             if (mt < 6) continue;
@@ -739,6 +747,9 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
                 // (small matrices, fewer than half the CUs at 16 tiles, are latency: the shorter epilogue wins)
                 if (tiles == 12 && (NT + 15) / 16 * n_pass * sp < 128) continue;
                 const double t = estimate(mt, n_pass, tiles, &sp);
+                if (tiles == 12 && sp > 1 &&
+                    (((size_t)sp * m_rows * n_rows * 4 + 255) & ~(size_t)255) + frag_bytes(m_rows, k) > BITA_NOALLOC_SCRATCH_BYTES)
+                    continue;
                 if (t < (tiles == 12 && p.mt_pass ? 0.95 : 1.0) * t_best) { t_best = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; p.tall_tiles = tiles; }
             }
         }
