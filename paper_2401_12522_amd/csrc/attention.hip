@@ -347,7 +347,14 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     // buffer loads: a uniform descriptor per operand, the lane's constant offset in a register, the
     // chunk's and the instruction's first row in the scalar offset: no vector instruction per load
     // and no 64-bit lane addresses, so that two heads per workgroup have the registers for it too.
-    // (Descriptors span the sequence's cached slots, or those of them a page can hold; the offsets stay inside.)
+    // (Descriptors span the sequence's cached slots, or those of them a page can hold; the offsets stay
+    // inside.  Slots from 2^23 on would leave their 32 bits and take the general path, by the one bound
+    // below, kept in a scalar register.  Lc <= 2^23 as a condition of its own in the loop cost the
+    // single-head forms up to 5 %: 32/32 heads of 128, 16 sequences of 512 with 25 rows 41.8 against
+    // 39.8 us, 170 rows on 1024 25.9 against 25.0; two heads: 64/8, 8 sequences of 4096 204.8 against 203.0.)
+    const int desc_slots = min(Lc, 1 << 23);
+    int desc_end = P + desc_slots;
+    asm("" : "+s"(desc_end));
     uint32_t k_off[4], v_off[2];
 #pragma unroll
     for (int par = 0; par < 4; par++) {
@@ -398,14 +405,13 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
             }
         };
         const int base_n = base + ATT_WAVES * ATT_CHUNK;                 // the wave's next chunk
-        // (a sequence of more than 2^23 slots leaves the descriptors' 32-bit offsets: general path)
-        if (more && base_n >= P && base_n + ATT_CHUNK <= n_ctx_keys && one_page(base_n - P) && Lc <= (1 << 23)) {   // wave-uniform
+        if (more && base_n >= P && base_n + ATT_CHUNK <= desc_end && one_page(base_n - P)) {   // wave-uniform
             // contiguous: one descriptor for the sequence's slots; paged: one for the chunk's page
             const int64_t first = PAGED ? (int64_t)__builtin_amdgcn_readfirstlane(tbl[(base_n - P) >> page_lg]) * page_stride : 0;
             const uint32_t slot = PAGED ? (base_n - P) & page_mask : base_n - P;
-            // (both in slots of at most 2^23: a page may be larger than a descriptor can span, what of it
-            // lies inside the sequence is not, and a chunk wholly inside the cache ends there)
-            const uint32_t span = (uint32_t)(PAGED ? min(1 << page_lg, Lc) : Lc) * (HD * 2);
+            // (a page may be larger than a descriptor can span; what of it the sequence's first 2^23 slots
+            // can lie in is not)
+            const uint32_t span = (uint32_t)(PAGED ? min(1 << page_lg, desc_slots) : desc_slots) * (HD * 2);
             const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)(ck + first), 0, span, 0x00027000);
             const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)(cv + first), 0, span, 0x00027000);
             const uint32_t chunk_bytes = slot * (HD * 2);
