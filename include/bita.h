@@ -292,7 +292,7 @@ int bita_gemm(const void *d_a, const void *d_a_lo, int32_t m_rows, int64_t k, in
  * allocates nothing (no hipMalloc / hipFree, no allocating library routine), only enqueues on
  * `stream`, and returns BITA_ERR_CAPACITY, with the sizes in bita_last_error(), when the shape
  * needs more than that (bita_gemm_noalloc_scratch_bytes(m_rows, n_rows, k) says how much a
- * shape needs).  d_a, d_a_lo, d_w_packed, d_out are device pointers owned by the caller.
+ * shape needs, the larger of its needs with one and with two activation planes).  d_a, d_a_lo, d_w_packed, d_out are device pointers owned by the caller.
  * All calls on one GPU share that GPU's array, which keeps the last call's contents (nothing in
  * it needs to start at zero): calls that overlap in time on one GPU, on different streams or
  * from different threads, race and must be ordered by the caller. */
@@ -324,6 +324,10 @@ void bita_tune_gemm(int32_t variant, int32_t splits);
  * reports): out4 (HOST) = {k splits, workgroup shape index, m-tiles per row pass of a tall
  * launch (0 = the shape's own row handling: one pass, or passes of 5 m-tiles), k-steps per split}. */
 int bita_gemm_plan_info(int32_t m_rows, int64_t n_rows, int64_t k, int32_t *out4);
+/* The same for activations of `planes` bf16 planes (1: bita_gemm / bita_gemm_noalloc without d_a_lo; 2: the
+ * step's launches, and what bita_gemm_plan_info answers for): out5 (HOST) = the four values above and the
+ * weight tiles (16 columns each) per workgroup of a tall launch, 16 or 12, 0 where the launch is not tall. */
+int bita_gemm_plan_detail(int32_t m_rows, int64_t n_rows, int64_t k, int32_t planes, int32_t *out5);
 
 const char *bita_last_error(void);
 

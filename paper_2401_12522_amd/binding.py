@@ -17,7 +17,7 @@ EXPORTS = [
     "bita_tree_template_info", "bita_build_tree", "bita_verify_step", "bita_accept",
     "bita_compact_kv", "bita_prefill_workspace_bytes", "bita_prefill_prepare", "bita_prefill", "bita_attention_workspace_bytes", "bita_tree_attention",
     "bita_gemm_workspace_bytes", "bita_gemm", "bita_gemm_noalloc_max_scratch_bytes", "bita_gemm_noalloc_scratch_bytes",
-    "bita_gemm_noalloc", "bita_select", "bita_tune_gemm", "bita_gemm_plan_info", "bita_profile_enable",
+    "bita_gemm_noalloc", "bita_select", "bita_tune_gemm", "bita_gemm_plan_info", "bita_gemm_plan_detail", "bita_profile_enable",
     "bita_profile_disable", "bita_profile_read", "bita_last_error",
 ]
 
@@ -90,6 +90,7 @@ def lib():
     L.bita_select.restype, L.bita_select.argtypes = C.c_int, [vp, vp, i32, i32, i32, vp, vp, vp, vp]
     L.bita_tune_gemm.restype, L.bita_tune_gemm.argtypes = None, [i32, i32]
     L.bita_gemm_plan_info.restype, L.bita_gemm_plan_info.argtypes = C.c_int, [i32, i64, i64, vp]
+    L.bita_gemm_plan_detail.restype, L.bita_gemm_plan_detail.argtypes = C.c_int, [i32, i64, i64, i32, vp]
     L.bita_profile_enable.restype, L.bita_profile_enable.argtypes = C.c_int, [i32]
     L.bita_profile_disable.restype, L.bita_profile_disable.argtypes = None, []
     L.bita_profile_read.restype, L.bita_profile_read.argtypes = C.c_int, [i32, vp, vp, vp]
@@ -424,11 +425,12 @@ def gemm_noalloc(a, w_packed, n_rows, out, k=None, a_lo=None):
     return out
 
 
-def gemm_plan_info(m_rows, n_rows, k):
-    """{splits, variant, mt_pass, ksteps_per_split} the launch heuristic picks for this GEMM shape."""
-    out = (C.c_int32 * 4)()
-    _check(lib().bita_gemm_plan_info(int(m_rows), int(n_rows), int(k), out))
-    return dict(splits=out[0], variant=out[1], mt_pass=out[2], ksteps_per_split=out[3])
+def gemm_plan_info(m_rows, n_rows, k, planes=2):
+    """{splits, variant, mt_pass, ksteps_per_split, tall_tiles} the launch heuristic picks for this GEMM shape
+    with `planes` activation planes."""
+    out = (C.c_int32 * 5)()
+    _check(lib().bita_gemm_plan_detail(int(m_rows), int(n_rows), int(k), int(planes), out))
+    return dict(splits=out[0], variant=out[1], mt_pass=out[2], ksteps_per_split=out[3], tall_tiles=out[4])
 
 
 def select(tmpl, logits, kmax):

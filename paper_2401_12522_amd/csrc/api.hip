@@ -516,6 +516,15 @@ extern "C" int bita_gemm_plan_info(int32_t m_rows, int64_t n_rows, int64_t k, in
     return BITA_OK;
 }
 
+extern "C" int bita_gemm_plan_detail(int32_t m_rows, int64_t n_rows, int64_t k, int32_t planes, int32_t *out5) {
+    if (!out5 || m_rows <= 0 || n_rows <= 0 || k <= 0 || planes < 1 || planes > 2)
+        return bita_set_error(BITA_ERR_INVALID_ARG, "bita_gemm_plan_detail: bad argument");
+    const GemmPlan p = gemm_plan(m_rows, n_rows, k, planes);
+    out5[0] = p.splits; out5[1] = p.variant; out5[2] = p.mt_pass; out5[3] = p.ksteps_per_split;
+    out5[4] = p.mt_pass ? p.tall_tiles : 0;
+    return BITA_OK;
+}
+
 extern "C" size_t bita_gemm_workspace_bytes(int32_t m_rows, int64_t n_rows, int64_t k) {
     if (m_rows <= 0 || n_rows <= 0 || k <= 0) return 0;
     // split-K partials (never more than 32 splits) + the activations re-laid in fragment order
@@ -529,7 +538,7 @@ extern "C" int bita_gemm(const void *d_a, const void *d_a_lo, int32_t m_rows, in
         return bita_set_error(BITA_ERR_INVALID_ARG, "bita_gemm: bad argument");
     if (n_rows % 16 || k % 8 || lda % 8)
         return bita_set_error(BITA_ERR_UNSUPPORTED, "bita_gemm: n_rows must be a multiple of 16, k and lda of 8");
-    const GemmPlan p = gemm_plan(m_rows, n_rows, k);
+    const GemmPlan p = gemm_plan(m_rows, n_rows, k, d_a_lo ? 2 : 1);
     const size_t part_bytes = align_up((size_t)p.splits * m_rows * n_rows * 4, 256);
     if (ws_bytes < part_bytes + frag_bytes(m_rows, k))
         return bita_set_error(BITA_ERR_CAPACITY, "bita_gemm: workspace too small");
@@ -578,8 +587,10 @@ extern "C" size_t bita_gemm_noalloc_max_scratch_bytes(void) { return BITA_NOALLO
 
 extern "C" size_t bita_gemm_noalloc_scratch_bytes(int32_t m_rows, int64_t n_rows, int64_t k) {
     if (m_rows <= 0 || n_rows <= 0 || k <= 0) return 0;
-    const GemmPlan p = gemm_plan(m_rows, n_rows, k);
-    const size_t part = p.splits > 1 ? align_up((size_t)p.splits * m_rows * n_rows * 4, 256) : 0;
+    // one activation plane and two may be split differently: what either needs
+    const int two = gemm_plan(m_rows, n_rows, k, 2).splits, one = gemm_plan(m_rows, n_rows, k, 1).splits;
+    const int splits = two > one ? two : one;
+    const size_t part = splits > 1 ? align_up((size_t)splits * m_rows * n_rows * 4, 256) : 0;
     return part + frag_bytes(m_rows, k);
 }
 
@@ -589,7 +600,7 @@ extern "C" int bita_gemm_noalloc(const void *d_a, const void *d_a_lo, int32_t m_
         return bita_set_error(BITA_ERR_INVALID_ARG, "bita_gemm_noalloc: bad argument");
     if (n_rows % 16 || k % 8 || lda % 8)
         return bita_set_error(BITA_ERR_UNSUPPORTED, "bita_gemm_noalloc: n_rows must be a multiple of 16, k and lda of 8");
-    const GemmPlan p = gemm_plan(m_rows, n_rows, k);
+    const GemmPlan p = gemm_plan(m_rows, n_rows, k, d_a_lo ? 2 : 1);
     const size_t part_bytes = p.splits > 1 ? align_up((size_t)p.splits * m_rows * n_rows * 4, 256) : 0;
     const size_t need = part_bytes + frag_bytes(m_rows, k);
     if (need > BITA_NOALLOC_SCRATCH_BYTES)

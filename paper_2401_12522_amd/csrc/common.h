@@ -146,7 +146,8 @@ void gemm_force_plan(int variant, int splits);   // tuning aid: < 0 restores the
 // Device bytes of the static scratch behind bita_gemm_noalloc.  The planner knows it because a shape's
 // plan, and with it the result's last bits, is the same for every caller.
 #define BITA_NOALLOC_SCRATCH_BYTES (32u << 20)
-GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k);
+// planes: of the activations (every launch of a step has two); a plan holds for that number only
+GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes = 2);
 size_t frag_bytes(int m_rows, int64_t k);        // bytes of a two-plane activation slab
 // a_frag: activations in fragment order (see frag_index); out_partial: [splits][m_rows][ldo] fp32
 void launch_gemm(const void *a_frag, bool two_planes, int m_rows, int64_t k, const void *w_packed,

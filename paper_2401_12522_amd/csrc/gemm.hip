@@ -665,7 +665,7 @@ static int g_force_variant = -1, g_force_splits = -1;
 // variant: >= 0 forces that workgroup shape, -1 the heuristic, -2 the heuristic without tall passes
 void gemm_force_plan(int variant, int splits) { g_force_variant = variant < -2 ? -1 : variant; g_force_splits = splits; }
 
-GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
+GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
     GemmPlan p;
     const int64_t NT = n_rows / 16, KS = (k + 31) / 32;
     // Shapes measured on MI355X at 68 rows (7B- and 70B-like widths): 2 k groups of 4 waves
@@ -696,7 +696,13 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
     // workgroups.  The passes fill the CUs, so fewer k splits are needed, and the widest
     // workgroups (16 waves, or 14 on the gate/up-like widths) share each activation fragment
     // among the most weight tiles.
-    int passes = m_tiles > 7 ? (m_tiles + 4) / 5 : 1;
+    // A single-plane slab has no forms of 6 to 9 m-tiles, neither the one-pass nor the tall ones.  It was
+    // given their plans and ran them in passes of 5; planned as what it is (whole calls, one plane,
+    // splits and workgroups for two planes -> its own): 96 x 22016 x 4096 65.9 -> 56.0 us, 128 rows
+    // 70.4 -> 58.8, 272 rows 108.6 -> 99.6; 272 x 12288 x 4096 66.4 -> 54.1; 170 x 4096 x 11008 51.9 -> 42.1.
+    // The passes begin at 6 m-tiles, but below 256 weight tiles at 8: a 16-tile workgroup is most of such
+    // a matrix (96 x 256 x 688 10.5 us in the 8-tile form, 12.9; 96 x 1024 x 4096 13.5 and 14.8).
+    int passes = m_tiles > (planes == 1 && NT >= 256 ? 5 : 7) ? (m_tiles + 4) / 5 : 1;
     if (passes >= 2) p.variant = (NT >= 1024 && NT < 3000) ? 11 : 9;
     p.mt_pass = 0;
     p.tall_tiles = 16;
@@ -707,7 +713,7 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k) {
     // same estimate for both forms, the tall one taken where it predicts at least a fifth less
     // (measured on the 7B-shaped matrices at 105 to 512 rows: the estimate ranks the forms right
     // beyond that margin and the choice is then 12 to 36 % faster; inside it they are within 5 %).
-    if (m_tiles >= 6 && g_force_variant == -1) {
+    if (planes == 2 && m_tiles >= 6 && g_force_variant == -1) {
         auto estimate = [&](int mt, int n_pass, int tiles_wg, int *splits_out) {
             const int64_t wgs_n = (NT + tiles_wg - 1) / tiles_wg;
             int64_t sp = 256 / (wgs_n * n_pass);
@@ -882,7 +888,7 @@ void launch_gemm(const void *a_frag, bool two_planes, int M, int64_t K, const vo
         return;
     }
     GemmPlan q = p;
-    if (q.variant == 12) q.variant = 9;     // (a single-plane slab has no tall form: passes of 5 m-tiles, same splits)
+    if (q.variant == 12) q.variant = 9;     // (12 exists as tall passes alone, which a forced variant does not plan)
     if (two_planes) launch_gemm_v<5, true>(a_frag, M, K, w, N, out, ldo, q, s, direct);
     else launch_gemm_v<5, false>(a_frag, M, K, w, N, out, ldo, q, s, direct);
 }

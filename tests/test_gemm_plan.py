@@ -16,3 +16,23 @@ def test_a_finer_cut_takes_no_shape_away_from_the_static_scratch(m, n, k):
     the 12-tile form would need 8 and does not fit."""
     L = _lib()
     assert L.bita_gemm_noalloc_scratch_bytes(m, n, k) <= L.bita_gemm_noalloc_max_scratch_bytes()
+
+
+@pytest.mark.parametrize("m,n,k,splits", [(128, 22016, 4096, 1), (144, 22016, 4096, 1), (272, 12288, 4096, 1), (512, 22016, 4096, 1),
+                                          (96, 22016, 4096, 1), (170, 4096, 11008, 5), (112, 1024, 4096, 8)])
+def test_one_plane_is_planned_for_the_passes_it_runs(m, n, k, splits):
+    """A single-plane launch has no tall form: its splits are those of passes of 5 m-tiles (or, for a small
+    matrix up to 7 m-tiles, of the 8-tile form), not of a form that only two planes have."""
+    import ctypes
+    from paper_2401_12522_amd import binding as B
+    L = _lib()
+    one, two = B.gemm_plan_info(m, n, k, planes=1), B.gemm_plan_info(m, n, k)
+    assert one["mt_pass"] == one["tall_tiles"] == 0 and one["splits"] == splits, one
+    out4 = (ctypes.c_int32 * 4)()
+    assert L.bita_gemm_plan_info(m, n, k, out4) == 0
+    assert list(out4) == [two[f] for f in ("splits", "variant", "mt_pass", "ksteps_per_split")]
+    frag = 2 * ((k + 31) // 32) * ((m + 15) // 16) * 1024
+    for plan in (one, two):
+        part = (plan["splits"] * m * n * 4 + 255) // 256 * 256 if plan["splits"] > 1 else 0
+        assert L.bita_gemm_noalloc_scratch_bytes(m, n, k) >= part + frag
+    assert L.bita_gemm_plan_detail(m, n, k, 3, out4) == -1
