@@ -1,6 +1,7 @@
-"""Tall row passes with 12 weight tiles per workgroup (GPU): the launch heuristic takes them, alone and
-inside a step, at shapes with a ragged last m-tile, a last pass shorter than the others, a ragged
-last column group and gated outputs that end inside a k-step of the next product."""
+"""Tall row passes with 12 and with 16 weight tiles per workgroup (GPU): the launch heuristic takes the form
+that a case names (0: passes of 5 m-tiles), alone and inside a step, at shapes with a ragged last m-tile, a last pass shorter than
+the others, a ragged last column group, one and several k splits, and gated outputs that end inside a
+k-step of the next product."""
 import numpy as np
 import pytest
 import torch
@@ -12,10 +13,15 @@ from oracle.model import silu
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K", [(170, 22016, 512), (272, 22016, 256), (265, 22000, 288), (488, 12288, 256), (300, 12288, 256),
-                                   (250, 22016, 96)])
-def test_gemm_rows_of_twelve_tiles(M, N, K):
+@pytest.mark.parametrize("M,N,K,tiles,mt_pass,splits", [
+    (170, 22016, 512, 12, 6, 1), (272, 22016, 256, 12, 9, 1), (265, 22000, 288, 12, 9, 1), (488, 12288, 256, 12, 8, 1),
+    (300, 12288, 256, 0, 0, 1), (300, 32000, 256, 12, 7, 1), (250, 22016, 96, 12, 8, 1), (105, 22016, 4096, 12, 7, 2), (265, 12288, 4096, 12, 9, 2),
+    (81, 57344, 256, 16, 6, 1), (165, 27648, 256, 16, 6, 1), (257, 27648, 256, 16, 9, 1), (162, 15360, 2048, 16, 6, 2),
+    (257, 10240, 4096, 16, 9, 3)])
+def test_gemm_rows_of_twelve_tiles(M, N, K, tiles, mt_pass, splits):
     import paper_2401_12522_amd as bita
+    plan = bita.binding.gemm_plan_info(M, N, K)
+    assert (plan["tall_tiles"], plan["mt_pass"], plan["splits"]) == (tiles, mt_pass, splits), plan
     g = torch.Generator().manual_seed(N + K + M)
     a32 = torch.randn(M, K, generator=g)
     hi = a32.to(torch.bfloat16)
@@ -28,9 +34,9 @@ def test_gemm_rows_of_twelve_tiles(M, N, K):
     assert float((out - ref).abs().max()) <= 2e-5 * scale + 1e-6         # fp32 accumulation, as everywhere
 
 
-@pytest.mark.parametrize("d_ffn,batch", [(11008, 4), (10976, 3), (11024, 4), (6160, 8)])
-def test_gated_output_of_twelve_tile_workgroups(d_ffn, batch):
-    """One layer with a wide FFN on 34-row (x batch) passes; the pass with the widths' own launch shapes
+@pytest.mark.parametrize("d_ffn,batch,tiles", [(11008, 4, 12), (10976, 3, 12), (11024, 4, 12), (6160, 8, 16), (6128, 8, 12), (11520, 5, 12)])
+def test_gated_output_of_twelve_tile_workgroups(d_ffn, batch, tiles):
+    """One layer with a wide FFN on passes of 68 rows x batch; the pass with the widths' own launch shapes
     against the same pass in the older forms (passes of 5 m-tiles), whose parity the step tests hold."""
     import paper_2401_12522_amd as bita
     from paper_2401_12522_amd import binding as B
@@ -39,6 +45,8 @@ def test_gated_output_of_twelve_tile_workgroups(d_ffn, batch):
     model = bita.Model(cfg, w, max_pos=256)
     tin = synth.attach_mask_groups(synth.full_branching_tree([4, 3, 2, 1], 64), [0], cfg.n_mask)
     tmpl = bita.TreeTemplate(tin.parent, tin.is_mask, tin.n_tree, cfg.n_mask)
+    plan = B.gemm_plan_info(batch * tmpl.rows, 2 * d_ffn, cfg.d_model)
+    assert (plan["tall_tiles"], plan["splits"]) == (tiles, 1), plan     # complete sums: the workgroup gates its own output
     kv = bita.KVState(cfg, 1, batch, 128, tmpl.rows)
     kv.k_cache.normal_()
     kv.v_cache.normal_()

@@ -63,8 +63,8 @@ def test_gemm_two_plane_activation(bita, M, N, K):
 @pytest.mark.parametrize("M,N,K,mt_pass", [(170, 12288, 4096, 6), (105, 57344, 1024, 7), (512, 4096, 11008, 8),
                                             (265, 22016, 512, 9)])
 def test_gemm_tall_row_passes(bita, M, N, K, mt_pass):
-    """Many-row shapes for which the launch heuristic takes tall row passes (6 to 9 m-tiles per pass
-    and 16 weight tiles per workgroup and k group) instead of passes of 5: with and without a
+    """Many-row shapes for which the launch heuristic takes tall row passes (6 to 9 m-tiles per pass,
+    12 or 16 weight tiles per workgroup and k group) instead of passes of 5: with and without a
     k split, a ragged last m-tile, a last pass shorter than the others."""
     from paper_2401_12522_amd import binding as BB
     plan = BB.gemm_plan_info(M, N, K)
