@@ -410,7 +410,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // pieces.  Rows of 4-row group g sit in the half of the row given by g's parity (two-way
     // instead of four-way bank conflicts).
     auto store_tiles = [&](float *o, auto &&value) __attribute__((always_inline)) {
-        // THROUGH: a store's 32-bit offset counts from the instruction's first row (8 rows at most)
+        // THROUGH: a store's 32-bit offset counts from the instruction's first row (16 rows at most)
         auto put = [&](int row0, int row, int chunk, const float4 &v) __attribute__((always_inline)) {
             if constexpr (!THROUGH) *reinterpret_cast<float4 *>(o + (int64_t)(m_base + row) * ldo + t0 * 16 + chunk * 4) = v;
             else store_through(through_rsrc(o + (int64_t)(m_base + row0) * ldo, 0xFFFFFFFCu),
@@ -481,6 +481,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
             // item is 8 features of one row: two pieces of gate, two of up, one 16-byte store per plane
             // (16 rows next to each other: 256 contiguous bytes of a fragment).
             constexpr int TILES = WN * 3, OCTS = TILES;               // 8 features per octet, 8 * TILES features
+            // (8 * TILES features are whole k-steps: a d_ffn that ends inside one leaves its other half to the
+            // workgroup that holds it, which stores zeros there)
             static_assert(TILES % 4 == 0, "whole k-steps of the next slab");
             float *stage = reinterpret_cast<float *>(smem_u4);
             stage_rows3(stage + wn * (MT * 16 * C::ROW3), [&](int i, int j, int r) { return acc[i][j][r]; });
@@ -509,17 +511,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
                 *reinterpret_cast<uint4 *>(dst) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
                 *reinterpret_cast<uint4 *>(dst + (int64_t)n_ksteps * mt_all * 512) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
             }
-            // (an odd number of 16-feature halves: the octets at or beyond F of the last k-step are
-            // stored as zeros by the workgroup whose columns run over it; where the grid's columns end
-            // at F, the last workgroup clears the half, as below)
-            if (((F >> 4) & 1) && bx * (TILES * 8) + TILES * 8 == F)
-                for (int idx = tid; idx < MT * 16 * 2; idx += WAVES * 64) {
-                    const int row = idx % (MT * 16), f = F + 8 * (idx / (MT * 16));
-                    if (bz * MT + (row >> 4) >= mt_all) continue;
-                    uint16_t *dst = direct.act_frag + frag_index(0, m_base + row, f, n_ksteps, mt_all, 0);
-                    *reinterpret_cast<uint4 *>(dst) = make_uint4(0, 0, 0, 0);
-                    *reinterpret_cast<uint4 *>(dst + (int64_t)n_ksteps * mt_all * 512) = make_uint4(0, 0, 0, 0);
-                }
         } else if constexpr (NW % 2 == 0) {
             // Tiles alternate gate, up: accumulators (j, j+1) hold gate and up of the same 16
             // features for the same rows and lanes.  The workgroup's WN*NW*8 features are whole
@@ -855,7 +846,7 @@ void launch_gemm(const void *a_frag, bool two_planes, int M, int64_t K, const vo
                  float *out, int64_t ldo, const GemmPlan &p, hipStream_t s, const GemmOutput *directp) {
     GemmOutput direct;
     memset(&direct, 0, sizeof(direct));
-    // direct outputs need complete sums and, for the gating, gate/up tile pairs inside one wave
+    // direct outputs need complete sums and, for the gating, gate/up tile pairs inside one workgroup
     if (directp && gemm_direct_output_possible(p, directp->kind)) direct = *directp;
     const int m_tiles = (M + 15) / 16;
     if (p.mt_pass >= 6 && two_planes) {
@@ -894,7 +885,9 @@ void launch_gemm(const void *a_frag, bool two_planes, int M, int64_t K, const vo
 }
 bool gemm_direct_output_possible(const GemmPlan &p, int kind) {
     (void)kind;
-    return p.splits == 1 && (p.variant == 5 || p.variant == 6 || p.variant >= 8);   // (12: four tiles per wave)   // even tiles per wave, see launch_gemm_v
+    // the k-group shapes with whole gate/up tile pairs per wave, or (12, tall) per workgroup: its waves
+    // hold four tiles, or three that are gated from LDS
+    return p.splits == 1 && (p.variant == 5 || p.variant == 6 || p.variant >= 8);
 }
 
 size_t frag_bytes(int m_rows, int64_t k) {                     // two planes
