@@ -378,9 +378,9 @@ int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, c
     auto head = [&](int Mr, int n_pending, float *xr, unsigned char *hr, float *part, float *ssqr, float *lg, const GemmPlan &plm) {
         const RowScale rs = {ssqr, (d / 4 + 255) / 256, 1.0f / (float)d, c.rms_eps};
         launch_rmsnorm_prep(xr, part, n_pending, Mr, d, m->final_norm, hr, ssqr, s);
-        // the final norm's row factor: in the LM head's own epilogue when it runs as a single split,
-        // else in the reduction of its partial sums
-        if (gemm_direct_output_possible(plm, GEMM_OUT_SCALED)) {
+        // the final norm's row factor: in the LM head's own epilogue when it runs as a single split (and its
+        // rows are within the reach of that epilogue's stores), else in the reduction of its partial sums
+        if (c.vocab <= GEMM_THROUGH_MAX_LD && gemm_direct_output_possible(plm, GEMM_OUT_SCALED)) {
             const GemmOutput scaled = {GEMM_OUT_SCALED, rs, nullptr, 0};
             timed_gemm(hr, Mr, d, m->lm_head, c.vocab, lg, c.vocab, plm, s, &scaled);
         } else {

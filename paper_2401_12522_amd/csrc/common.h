@@ -55,10 +55,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 // 16-byte store that is written through the XCD's L2 instead of staying there dirty until the end of
 // the kernel: what a kernel leaves dirty is written back between it and the next one, when nothing
-// else runs (256 workgroups that store 9 / 17 MB and end: 3.1 -> 2.5 / 4.6 -> 3.6 us).  For whole cache
-// lines only: a part of a line costs memory a transaction of its own.
+// else runs (256 workgroups that store 9 / 17 MB and end: 3.1 -> 2.5 / 4.6 -> 3.6 us).  For row pieces of
+// 128 bytes and more; the 192-byte ones of three-tile waves, one and a half cache lines, still gain (whole
+// calls, plain / through: 272 x 12288 x 4096 66.7 / 65.8 us, 140 x 6144 x 16384 77.4 / 76.6, 170 x 12288 x 4096 51.1 / 50.2).
 // (A buffer store with the scope bit, so that the compiler knows the instruction: as inline assembly
 // it does not keep the store's data registers untouched for the wait state a 16-byte store needs.)
+// Its offset has 32 bits: the 16 rows that one instruction may span have at most this many floats each.
+#define GEMM_THROUGH_MAX_LD (1 << 26)
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t through_rsrc(void *base, uint32_t bytes) {      // base: wave-uniform
     return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000);

@@ -108,11 +108,13 @@ struct GemmCfg {
     static_assert((D - 2) * LOADS < 64, "vmcnt counter range");
 };
 
-// THROUGH: fp32 outputs are written through the L2 (store_through).  It pays where the launch leaves
-// megabytes behind that would be written back between this kernel and the next: split-K partial sums
-// from 8 MB on and the logits (7B widths, 68 rows: 17 + 9 + 9 MB of partial sums a layer, 9 MB of
-// logits: 3 us of the 340 of two layers and the head); below, and for a single split's sums, the write-back is short and the
-// stores' way to memory costs the workgroups' tails more (68 rows x 22016, 6 MB: 45.2 us plain, 45.5).
+// THROUGH: split-K partial sums are written through the L2 (store_through) from 8 MB on, where the launch
+// leaves megabytes behind that would be written back between this kernel and the next (7B widths, 68 rows:
+// 17 + 9 + 9 MB a layer: 3 us of the 340 of two layers and the head).  Below, and for a single split's
+// plain sums, the write-back is short and the stores' way to memory costs the workgroups' tails more
+// (68 rows x 22016, 6 MB: 45.2 us plain, 45.5).  The logits of a direct launch go through at every size,
+// though it hardly matters there (one layer and the head, through / plain: 7B, 1 row 149.1 / 149.1 us,
+// 48 rows 196.5 / 197.0, 68 rows 204.8 / 204.0, four sequences of 68 431.4 / 430.2; 13B, 25 rows 213.8 / 214.8).
 template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool DIRECT, bool PACK, bool THROUGH>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // The first 14 dwords of the argument block arrive in scalar registers with the wave
@@ -776,7 +778,7 @@ template <int MT, int NW, bool SPLIT, int WAVES, int D, int KG, bool DIRECT, boo
 static void launch_gemm_t(const void *a_frag, int M, int64_t K, const void *w, int64_t N, float *out, int64_t ldo,
                           const GemmPlan &p, hipStream_t s, const GemmOutput &direct) {
     if constexpr (MT > 1 && SPLIT && KG > 1 && !THROUGH) {
-        if (p.splits > 1 && (int64_t)p.splits * M * ldo * 4 >= (8 << 20)) {
+        if (p.splits > 1 && (int64_t)p.splits * M * ldo * 4 >= (8 << 20) && ldo <= GEMM_THROUGH_MAX_LD) {
             launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, true>(a_frag, M, K, w, N, out, ldo, p, s, direct);
             return;
         }
