@@ -624,11 +624,13 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
 
 // out[b][r][h*HD + 4i .. +4] = sum_s w_s O_s / sum_s w_s l_s,  w_s = 2^(m_s - max m).
 // One thread per 4 head-dim elements; blockDim = (HD/4) * heads_per_block.
+// only_row: one row per sequence (the others' partials were not written either), grid x 1.
 __global__ void attn_merge_kernel(const float *__restrict__ part_o, const float *__restrict__ part_ml,
                                   int R, int Hq, int HD, int n_splits, uint16_t *__restrict__ out,
-                                  uint16_t *__restrict__ out_lo, int as_fragments, int m_tiles) {
+                                  uint16_t *__restrict__ out_lo, int as_fragments, int m_tiles,
+                                  const int32_t *__restrict__ only_row) {
     const int per_head = HD >> 2;
-    const int r = blockIdx.x, b = blockIdx.z;
+    const int b = blockIdx.z, r = only_row ? min(max(only_row[b], 0), R - 1) : (int)blockIdx.x;
     const int h = blockIdx.y * (blockDim.x / per_head) + threadIdx.x / per_head, i4 = threadIdx.x % per_head;
     if (h >= Hq) return;
     const int64_t pbase = ((int64_t)b * Hq + h) * n_splits;
@@ -736,8 +738,9 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
 #undef ATT_LAUNCH
     if (p.splits > 1) {
         const int heads_per_block = (256 / (hd / 4)) < Hq ? (256 / (hd / 4)) : Hq;
-        hipLaunchKernelGGL(attn_merge_kernel, dim3(t.rows, (Hq + heads_per_block - 1) / heads_per_block, batch),
+        hipLaunchKernelGGL(attn_merge_kernel, dim3(only_row ? 1 : t.rows, (Hq + heads_per_block - 1) / heads_per_block, batch),
                            dim3(heads_per_block * (hd / 4)), 0, s, part_o, part_ml, t.rows,
-                           Hq, hd, p.splits, (uint16_t *)out, (uint16_t *)out_lo, out_as_fragments ? 1 : 0, (batch * t.rows + 15) / 16);
+                           Hq, hd, p.splits, (uint16_t *)out, (uint16_t *)out_lo, out_as_fragments ? 1 : 0, (batch * t.rows + 15) / 16,
+                           only_row);
     }
 }

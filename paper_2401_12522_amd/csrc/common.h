@@ -201,7 +201,7 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            int batch, int n_heads, int n_kv_heads, int hd, int n_prompt, int smax,
                            const AttnPlan &p, float *part_o, float *part_ml, void *out, void *out_lo,
                            bool out_as_fragments, const PageMap &pm, hipStream_t s,
-                           const int32_t *only_row = nullptr /* [B]: only the row tile holding this row of each sequence */);
+                           const int32_t *only_row = nullptr /* [B]: only this row of each sequence is asked for (its row tile is computed) */);
 
 // A prefill chunk needs from its pass the rows' K/V and, where a sequence may end in the chunk, the
 // greedy token after one row per sequence (sel_row [B], row inside the chunk): the last layer then

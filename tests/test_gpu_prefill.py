@@ -290,3 +290,54 @@ def test_next_token_comes_from_the_last_rows_alone(bita, batch, chunk):
         last = buf.logits[0, len_b - 1].cpu().numpy()
         # both sides are within 1e-4 of exact logits (chunks after the first see a bf16 cache: 3e-2)
         assert nxt[b] == argmax_low(last) or _margin(last) < (2e-4 if len_b <= chunk else MARGIN), (b, len_b)
+
+
+@pytest.mark.parametrize("cfg_name,batch,n", [("tiny", 1, 16), ("tiny_gqa", 1, 21), ("tiny_gqa", 2, 35)])
+def test_next_token_behind_a_split_key_axis(bita, cfg_name, batch, n):
+    """Chunks of 16 rows on a context long enough that attention splits its keys: the partial sums of the one
+    row that goes on are merged, from a workspace that held NaN; token and cache equal those of passes
+    that finish every row."""
+    from paper_2401_12522_amd import binding as B
+    cfg = synth.get_config(cfg_name)
+    ctx, chunk = 2300, 16
+    P, hd = cfg.n_prompt, cfg.head_dim
+    ws_of = lambda rows, at: B.lib().bita_attention_workspace_bytes(batch, rows, cfg.n_heads, hd, at, P)     # noqa: E731
+    for at in range(0, n, chunk):
+        rows = min(chunk, n - at)                        # more than one split's partial sums (hd + 2 floats a row)
+        assert ws_of(rows, ctx + at) >= 2 * batch * cfg.n_heads * rows * (hd + 2) * 4
+    model = bita.Model(cfg, synth.SynthWeights(cfg, seed=9), max_pos=ctx + 128)
+    lens = [n - 5 * b for b in range(batch)]
+    rng = np.random.default_rng(n)
+    toks = dev_i32(rng.integers(0, cfg.vocab, size=(batch, n)))
+    kv = [bita.KVState(cfg, cfg.n_layers, batch, ctx + 64, chunk) for _ in range(2)]
+    g = torch.Generator(device="cuda").manual_seed(1)
+    for name in ("k_cache", "v_cache"):
+        fill = torch.randn(kv[0].k_cache[:, :, :, :ctx].shape, generator=g, device="cuda").to(torch.bfloat16)
+        for s in kv:
+            getattr(s, name)[:, :, :, :ctx] = fill
+    for s in kv:
+        s.ctx_len.fill_(ctx)
+    ws = bita.prefill_workspace(model, batch, chunk)
+    ws.fill_(0xFF)
+    nxt = bita.prefill(model, kv[0], ctx, toks, chunk, seq_len=dev_i32(lens), workspace=ws).cpu().tolist()
+    last = [None] * batch
+    for at in range(0, n, chunk):
+        rows = min(chunk, n - at)
+        kv[1].resize_rows(cfg.n_layers, cfg, rows)
+        chain = bita.TreeTemplate(synth.chain_tree(rows), np.zeros(rows, np.uint8), rows, 0)
+        buf = bita.StepBuffers(model, chain, batch, 1, want_logits=True)
+        inside = torch.arange(rows, device="cuda")[None] + at < dev_i32(lens)[:, None]
+        buf.token.copy_(torch.where(inside, toks[:, at:at + rows], -1))
+        bita.verify_step(model, kv[1], ctx + at, chain, buf, batch)
+        n_acc = inside.sum(1).to(torch.int32)
+        path = torch.arange(rows, dtype=torch.int32, device="cuda").expand(batch, rows).contiguous()
+        bita.compact_kv(model, kv[1], ctx + at, buf, batch, path=path, n_acc=n_acc)
+        for b in range(batch):
+            if at < lens[b] <= at + rows:
+                last[b] = buf.logits[b, lens[b] - 1 - at].cpu().numpy()
+    torch.cuda.synchronize()
+    for b in range(batch):
+        assert torch.equal(kv[0].k_cache[:, b, :, :ctx + lens[b]], kv[1].k_cache[:, b, :, :ctx + lens[b]])
+        assert torch.equal(kv[0].v_cache[:, b, :, :ctx + lens[b]], kv[1].v_cache[:, b, :, :ctx + lens[b]])
+        assert np.isfinite(last[b]).all()
+        assert nxt[b] == argmax_low(last[b]) or _margin(last[b]) < 2e-4, b     # (both sides within 1e-4 of exact logits)
