@@ -111,7 +111,8 @@ def _ptr(t):
 def _stream():
     # the current stream's handle without building a Stream object around it (3.2 -> 0.4 us, and a step
     # asks four times); a null handle is the default stream
-    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # not a public name: a torch may come without it
+    return C.c_void_p(raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream)
 
 
 def packed_bytes(n_rows, k):

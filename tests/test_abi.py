@@ -66,3 +66,17 @@ def test_resource_remarks_are_parsed():
     assert build._kernel_resources(remarks) == {"_Zk1": {"vgprs": 20, "scratch": 8, "occupancy": 4}, "_Zk2": {"agprs": 3}}
     lines = ["x.hip:3:1: warning: something", remarks[0], "    1 | code", "      | ^", "real error"]
     assert build._without_remarks(lines) == ["x.hip:3:1: warning: something", "real error"]
+
+
+def test_current_stream_with_and_without_torchs_raw_handle(monkeypatch):
+    """The binding asks torch for the stream's raw handle where there is such a function, else for the
+    stream object; either way it gets the current stream of the current device."""
+    import torch
+    from types import SimpleNamespace
+    from paper_2401_12522_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: SimpleNamespace(cuda_stream=0x1230))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x4560 + device, raising=False)
+    assert binding._stream().value == 0x4563
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert binding._stream().value == 0x1230
