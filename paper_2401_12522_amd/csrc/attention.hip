@@ -262,13 +262,13 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         }
 
     f32x4 o_acc[U][NTN];
-    float m_run[U], neg_m[U], l_run[U];
+    float m_run[U], base_m[U], l_run[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
 #pragma unroll
         for (int nt = 0; nt < NTN; nt++) o_acc[u][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
         m_run[u] = -INFINITY;
-        neg_m[u] = 0.f;
+        base_m[u] = 0.f;
         l_run[u] = 0.f;
     }
 
@@ -475,11 +475,15 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
                            vh[nt][1][0], vh[nt][1][1], vh[nt][1][2], vh[nt][1][3]};
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            float sv[8];                     // q.k, unscaled: the scale rides in the exponent's multiply-add
+            // Scores in powers of two, scaled before anything else: the exponent of the largest is then exactly
+            // zero.  With the scale in the exponent's multiply-add it was off by the product's rounding (1.5e-5
+            // of a value at scores of 5e4) for 1 % of the two-head forms' time (64/8 heads, 8 sequences of
+            // 4096: 207.4 against 209.6 us) and none of the others'.
+            float sv[8];
 #pragma unroll
             for (int tt = 0; tt < 2; tt++)
 #pragma unroll
-                for (int r = 0; r < 4; r++) sv[tt * 4 + r] = s_acc[u][tt][r];
+                for (int r = 0; r < 4; r++) sv[tt * 4 + r] = s_acc[u][tt][r] * scale_log2;
             if (tree_chunk) {                // score = q.k_hi + q.k_lo; partner slots leave the softmax
 #pragma unroll
                 for (int e = 0; e < 4; e++) sv[e] += sv[e + 4];
@@ -492,15 +496,14 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
             for (int e = 1; e < 8; e++) mx = fmaxf(mx, sv[e]);
             // The running maximum rarely moves after the first chunks: the lane groups are reduced and
-            // the sums rescaled only where some lane's scores exceed it.  neg_m = -(maximum x scale), the
-            // number every exponent is taken against (0 while a row has seen no key).
+            // the sums rescaled only where some lane's scores exceed it.  base_m is the number every
+            // exponent is taken against (0 while a row has seen no key).
+            float alpha = 1.f;
             if (__builtin_amdgcn_ballot_w64(mx > m_run[u]) != 0) {
                 const float m_new = fmaxf(m_run[u], max_over_lane_groups(mx));
-                const float neg_new = m_new == -INFINITY ? 0.f : -m_new * scale_log2;
-                const float alpha = m_run[u] == -INFINITY ? 0.f : fast_exp2(neg_new - neg_m[u]);
+                base_m[u] = m_new == -INFINITY ? 0.f : m_new;
+                alpha = fast_exp2(m_run[u] - base_m[u]);
                 m_run[u] = m_new;
-                neg_m[u] = neg_new;
-                l_run[u] *= alpha;
 #pragma unroll
                 for (int nt = 0; nt < NTN; nt++) o_acc[u][nt] *= alpha;
             }
@@ -510,7 +513,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
             uint32_t pk2[4], pl2[4];
 #pragma unroll
             for (int e = 0; e < 8; e += 2) {
-                const float p0 = fast_exp2(fmaf(sv[e], scale_log2, neg_m[u])), p1 = fast_exp2(fmaf(sv[e + 1], scale_log2, neg_m[u]));
+                const float p0 = fast_exp2(sv[e] - base_m[u]), p1 = fast_exp2(sv[e + 1] - base_m[u]);
                 ps += p0 + p1;
                 const uint32_t hi = cvt_pk_bf16(p0, p1);
                 pk2[e >> 1] = hi;
@@ -522,7 +525,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
                 pl2[2] = pl2[0];
                 pl2[3] = pl2[1];
             }
-            l_run[u] += ps;
+            l_run[u] = l_run[u] * alpha + ps;
             // O^T[hd][q] += V^T[hd][slots 8g..8g+7] * P^T
             const bf16x8 pf = __builtin_bit_cast(bf16x8, make_uint4(pk2[0], pk2[1], pk2[2], pk2[3]));
             const bf16x8 pf_lo = __builtin_bit_cast(bf16x8, make_uint4(pl2[0], pl2[1], pl2[2], pl2[3]));
@@ -564,9 +567,8 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         const int h = h0 + u;
         __syncthreads();                     // the chunk buffers (first head) or the previous head's sums are done with
         const float l = sum_over_lane_groups(l_run[u]);
-        const float m_log2 = m_run[u] == -INFINITY ? -INFINITY : -neg_m[u];     // the maximum in powers of two
         if (g == 0) {
-            sm[wave * 16 + c] = m_log2;
+            sm[wave * 16 + c] = m_run[u];
             sl[wave * 16 + c] = l;
         }
         __syncthreads();
@@ -577,7 +579,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         float l_tot = 0.f;
 #pragma unroll
         for (int w = 0; w < ATT_WAVES; w++) l_tot += sl[w * 16 + c] * fast_exp2(sm[w * 16 + c] - m_use);
-        const float f = fast_exp2(m_log2 - m_use);
+        const float f = fast_exp2(m_run[u] - m_use);
 #pragma unroll
         for (int nt = 0; nt < NTN; nt++)
             region[(wave * NTN + nt) * 64 + lane] =
