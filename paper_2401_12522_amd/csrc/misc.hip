@@ -94,72 +94,85 @@ __global__ __launch_bounds__(256) void rmsnorm_prep_kernel(float *__restrict__ x
 // ctx_len + depth(row) in the half-split pairing, write q [B][R][Hq][hd] and the rows'
 // k/v into the per-pass tree scratch [B][Hkv][R][hd].  q, k and v are all written as hi and lo
 // bf16 planes; only the hi planes of accepted rows are ever committed to the cache.
-#define ROPE_HEADS_PER_WG 4      // one wave per head: fewer, larger workgroups to dispatch
-__global__ __launch_bounds__(64 * ROPE_HEADS_PER_WG) void qkv_rope_kernel(
+// A thread takes four neighbouring rotation pairs of a head: 16-byte loads, 8-byte stores.  What bounds it
+// is the sums and planes it moves (512 rows of 96 heads: 50 MB); with one pair a thread, 4-byte loads and 2-byte
+// stores, they moved at 2.3 TB/s, now at 4.6 (rocprofv3, 7B widths: 512 rows 21.8 -> 11.0 us, 272 rows in two
+// k splits 14.3 -> 8.8, 170 rows 10.4 -> 6.7; 68 rows, where the launch and two round trips are most of it, 5.6 -> 5.8).
+#define ROPE_THREADS 128
+template <int HD>
+__global__ __launch_bounds__(ROPE_THREADS) void qkv_rope_kernel(
     // (what the first loads depend on sits in the first 14 dwords, which arrive in registers)
     const float *__restrict__ partial, const int32_t *__restrict__ ctx_len, const int32_t *__restrict__ depth,
-    const float *__restrict__ rs_ssq, int splits, int M, int R, int Hq, int Hkv, int hd, int max_pos,
+    const float *__restrict__ rs_ssq, int splits, int M, int R, int Hq, int Hkv, int max_pos,
     const float *__restrict__ rope_cos, const float *__restrict__ rope_sin, uint16_t *__restrict__ q,
     uint16_t *__restrict__ q_lo, uint16_t *__restrict__ k_tree, uint16_t *__restrict__ v_tree,
     uint16_t *__restrict__ k_tree_lo, uint16_t *__restrict__ v_tree_lo, int rs_chunks, float rs_inv_d, float rs_eps) {
-    const int row = blockIdx.x, head = blockIdx.y * ROPE_HEADS_PER_WG + (threadIdx.x >> 6);   // head over Hq + 2*Hkv
+    constexpr int half = HD / 2, LANES = half / 4;           // threads per head
+    const int row = blockIdx.x, head = blockIdx.y * (ROPE_THREADS / LANES) + threadIdx.x / LANES;   // head over Hq + 2*Hkv
     if (head >= Hq + 2 * Hkv) return;
     const int b = row / R, r = row % R;
-    const int half = hd >> 1, i = threadIdx.x & 63;
-    if (i >= half) return;
+    const int i = (threadIdx.x % LANES) * 4;
     // Two memory round trips: the row's position and the sums behind its norm factor, then the
-    // rotary table entry together with the partial sums (the table is read for value heads too,
+    // rotary table entries together with the partial sums (the table is read for value heads too,
     // and ignored).
     const int row_ctx = ctx_len[b], row_depth = depth[r];
     const RowScale rs{rs_ssq, rs_chunks, rs_inv_d, rs_eps};
     const float sc = row_scale(rs, row);          // RMSNorm's row factor, deferred past the GEMM
     int pos = row_ctx + row_depth;
     pos = pos < max_pos ? pos : max_pos - 1;          // host checks capacity; stay in bounds
-    const float tab_c = rope_cos[(int64_t)pos * half + i], tab_s = rope_sin[(int64_t)pos * half + i];
-    const int64_t ncols = (int64_t)(Hq + 2 * Hkv) * hd;
-    const int64_t col = (int64_t)head * hd + i;
-    float lo = 0.f, hi = 0.f;
+    const float4 tab_c = *reinterpret_cast<const float4 *>(rope_cos + (int64_t)pos * half + i);
+    const float4 tab_s = *reinterpret_cast<const float4 *>(rope_sin + (int64_t)pos * half + i);
+    const int64_t ncols = (int64_t)(Hq + 2 * Hkv) * HD;
+    const int64_t col = (int64_t)head * HD + i;
+    float lo[4] = {0.f, 0.f, 0.f, 0.f}, hi[4] = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < splits; s0 += 8) {     // eight splits per round trip, summed in split order
-        float pl[8], ph[8];
+        float4 pl[8], ph[8];
 #pragma unroll
         for (int u = 0; u < 8; u++) {
             const float *p = partial + ((int64_t)min(s0 + u, splits - 1) * M + row) * ncols + col;
-            pl[u] = p[0];
-            ph[u] = p[half];
+            pl[u] = *reinterpret_cast<const float4 *>(p);
+            ph[u] = *reinterpret_cast<const float4 *>(p + half);
         }
 #pragma unroll
         for (int u = 0; u < 8; u++)
-            if (s0 + u < splits) { lo += pl[u]; hi += ph[u]; }
+            if (s0 + u < splits) {
+                lo[0] += pl[u].x; lo[1] += pl[u].y; lo[2] += pl[u].z; lo[3] += pl[u].w;
+                hi[0] += ph[u].x; hi[1] += ph[u].y; hi[2] += ph[u].z; hi[3] += ph[u].w;
+            }
     }
-    lo *= sc;
-    hi *= sc;
-    uint16_t *dst, *dst_lo = nullptr;
+    uint16_t *dst, *dst_lo;
     if (head < Hq) {
-        dst = q + ((int64_t)row * Hq + head) * hd;
-        dst_lo = q_lo + ((int64_t)row * Hq + head) * hd;
+        dst = q + ((int64_t)row * Hq + head) * HD;
+        dst_lo = q_lo + ((int64_t)row * Hq + head) * HD;
     } else if (head < Hq + Hkv) {
-        const int64_t o = (((int64_t)b * Hkv + (head - Hq)) * R + r) * hd;
+        const int64_t o = (((int64_t)b * Hkv + (head - Hq)) * R + r) * HD;
         dst = k_tree + o;
         dst_lo = k_tree_lo + o;      // the pass keeps the rounding residual of its own K/V rows
     } else {
-        const int64_t o = (((int64_t)b * Hkv + (head - Hq - Hkv)) * R + r) * hd;
+        const int64_t o = (((int64_t)b * Hkv + (head - Hq - Hkv)) * R + r) * HD;
         dst = v_tree + o;
         dst_lo = v_tree_lo + o;
     }
-    if (head < Hq + Hkv) {
-        const float nlo = lo * tab_c - hi * tab_s, nhi = hi * tab_c + lo * tab_s;
-        lo = nlo;
-        hi = nhi;
+    const float c[4] = {tab_c.x, tab_c.y, tab_c.z, tab_c.w}, sn[4] = {tab_s.x, tab_s.y, tab_s.z, tab_s.w};
+    uint16_t a_hi[4], a_lo[4], b_hi[4], b_lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        float x = lo[e] * sc, y = hi[e] * sc;
+        if (head < Hq + Hkv) {
+            const float nx = x * c[e] - y * sn[e], ny = y * c[e] + x * sn[e];
+            x = nx;
+            y = ny;
+        }
+        split_bf16(x, a_hi[e], a_lo[e]);
+        split_bf16(y, b_hi[e], b_lo[e]);
     }
-    uint16_t a_hi, a_lo, b_hi, b_lo;
-    split_bf16(lo, a_hi, a_lo);
-    split_bf16(hi, b_hi, b_lo);
-    dst[i] = a_hi;
-    dst[i + half] = b_hi;
-    if (dst_lo) {
-        dst_lo[i] = a_lo;
-        dst_lo[i + half] = b_lo;
-    }
+    auto put = [](uint16_t *p, const uint16_t (&v)[4]) __attribute__((always_inline)) {
+        *reinterpret_cast<uint2 *>(p) = make_uint2(v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16));
+    };
+    put(dst + i, a_hi);
+    put(dst + i + half, b_hi);
+    put(dst_lo + i, a_lo);
+    put(dst_lo + i + half, b_lo);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -361,9 +374,10 @@ void launch_qkv_rope(const float *partial, int splits, int batch, const Template
                      int Hkv, int hd, const int32_t *ctx_len, const float *rope_cos,
                      const float *rope_sin, int max_pos, void *q, void *q_lo, void *k_tree, void *v_tree,
                      void *k_tree_lo, void *v_tree_lo, const RowScale &rs, hipStream_t s) {
-    hipLaunchKernelGGL(qkv_rope_kernel, dim3(batch * t.rows, (Hq + 2 * Hkv + ROPE_HEADS_PER_WG - 1) / ROPE_HEADS_PER_WG),
-                       dim3(64 * ROPE_HEADS_PER_WG), 0, s, partial, ctx_len, t.depth,
-                       rs.ssq, splits, batch * t.rows, t.rows, Hq, Hkv, hd, max_pos, rope_cos, rope_sin,
+    const int per_wg = ROPE_THREADS / (hd / 8);
+    hipLaunchKernelGGL(hd == 128 ? qkv_rope_kernel<128> : qkv_rope_kernel<64>, dim3(batch * t.rows, (Hq + 2 * Hkv + per_wg - 1) / per_wg),
+                       dim3(ROPE_THREADS), 0, s, partial, ctx_len, t.depth,
+                       rs.ssq, splits, batch * t.rows, t.rows, Hq, Hkv, max_pos, rope_cos, rope_sin,
                        (uint16_t *)q, (uint16_t *)q_lo, (uint16_t *)k_tree, (uint16_t *)v_tree,
                        (uint16_t *)k_tree_lo, (uint16_t *)v_tree_lo, rs.chunks, rs.inv_d, rs.eps);
 }
