@@ -4,8 +4,8 @@
 //
 // Flash-style, one workgroup per (sequence, query head, 16 query rows, key split):
 //  * A workgroup owns one m-tile of 16 query rows and walks the key axis
-//    [prefix | cache | pass rows] in chunks of 32 key slots.  Its 8 wavefronts (two per SIMD,
-//    so that one wave's softmax arithmetic overlaps the other's matrix instructions) take
+//    [prefix | cache | pass rows] in chunks of 32 key slots.  Its 8 wavefronts, or 4 of two workgroups
+//    per CU (two per SIMD, so that one wave's softmax arithmetic overlaps the other's matrix instructions) take
 //    chunks round-robin and never synchronise inside the loop: each keeps its own
 //    online-softmax state, merged through LDS once at the end (fixed order, deterministic).  With 16 rows
 //    per workgroup no split over the keys is needed to fill the chip at the verify shapes,
@@ -32,7 +32,6 @@
 #include "common.h"
 #include <type_traits>
 
-#define ATT_WAVES 8
 #define ATT_CHUNK 32            // key slots per chunk
 
 // one all-zero K/V row (head dim <= 128): padding slots read it like any other row
@@ -128,19 +127,21 @@ __device__ __forceinline__ void lds_wait_all(u32x4 (&k)[2][N], s16x4 (&v)[M][2])
     }
 }
 
-template <int HD, int U>
+// U query heads and W waves per workgroup
+template <int HD, int U, int W>
 struct AttCfg {
     static constexpr int KSN = HD / 32;                       // k-steps of the QK^T contraction
     static constexpr int NTN = HD / 16;                       // 16-wide tiles of the head dimension
     static constexpr int GPR = HD / 8;                        // 16-byte granules per K/V row
     static constexpr int RPI = 64 / GPR;                      // V rows per global->LDS instruction
     static constexpr int NVI = ATT_CHUNK / RPI;               // such instructions per chunk
-    static constexpr int LOADS = 2 * NVI + 1;                 // vector-memory loads per wave per chunk (K, V, mask word)
     static constexpr int KV_BYTES = ATT_CHUNK * HD * 2;       // the K (or V) rows of one chunk
     static constexpr int CHUNK_BYTES = 2 * KV_BYTES;          // one ring slot: [K rows | V rows]
-    static constexpr int RING_BYTES = ATT_WAVES * CHUNK_BYTES;       // one buffer per wave
-    static constexpr int MERGE_BYTES = 2 * ATT_WAVES * 16 * 4 + ATT_WAVES * NTN * 64 * 16;
-    static constexpr int SMEM = RING_BYTES > MERGE_BYTES ? RING_BYTES : MERGE_BYTES;
+    static constexpr int RING_BYTES = W * CHUNK_BYTES;       // one buffer per wave
+    // the merge: every wave's tiles over the chunk buffers, and behind them its rows' maxima and sums
+    static constexpr int MERGE_BYTES = U * W * NTN * 64 * 16, ML_BYTES = 2 * U * W * 16 * 4;
+    static constexpr int ML = RING_BYTES > MERGE_BYTES ? RING_BYTES : MERGE_BYTES;
+    static constexpr int SMEM = ML + ML_BYTES;
 };
 
 // LDS row of key slot s inside a V chunk: the two 4-slot halves of each lane group's 8 slots
@@ -159,11 +160,11 @@ __device__ __forceinline__ constexpr int att_swizzle_k(int rho) { return HD == 1
 // PAGED: the cache operands are page pools [n_pages][Hkv][page][HD] and key slot s of sequence b
 // lives in page table[b][s >> page_lg] at row s & (page - 1); the sequence's table entries are
 // copied to LDS (behind the chunk buffers) once per workgroup.
-template <int HD, int U, bool PAGED>
-__global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(ATT_WAVES / 4, ATT_WAVES / 4))) void tree_attn_kernel(
+template <int HD, int U, int W, bool PAGED>
+__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void tree_attn_kernel(
     // the first 14 dwords arrive in scalar registers with the wave (kernel-argument preload):
     // what the workgroup needs to find its work and to issue its first loads comes first
-    const int32_t *__restrict__ ctx_len, int batch, int Hq, int Hkv, int n_mt, int n_splits, int P, int R, int smax,
+    const int32_t *__restrict__ ctx_len, int batch, int qpk /* query heads per K/V head */, int Hkv, int n_mt, int n_splits, int P, int R, int smax,
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ q_lo,
     TemplateDev t, const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
     const uint16_t *__restrict__ k_tree, const uint16_t *__restrict__ v_tree,
@@ -172,24 +173,24 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     const int32_t *__restrict__ token, float scale_log2, float *__restrict__ part_o, float *__restrict__ part_ml,
     uint16_t *__restrict__ out, uint16_t *__restrict__ out_lo, int as_fragments, int m_tiles_out, PageMap pm,
     const int32_t *__restrict__ only_row) {
-    using C = AttCfg<HD, U>;
+    using C = AttCfg<HD, U, W>;
     constexpr int KSN = C::KSN, NTN = C::NTN, GPR = C::GPR, RPI = C::RPI, NVI = C::NVI;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
+    const int Hq = qpk * Hkv;
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, and known to be
     // ---- workgroup id -> (kv group, query head of the group, m-tile, split), kv groups dealt
-    //      round-robin to the XCDs
-    const int qpk = Hq / Hkv;                                // query heads per K/V head
-    const int per_group = (qpk / U) * n_mt * n_splits;       // U query heads of the group per workgroup
-    const int xcd = blockIdx.x & 7, slot_in_xcd = blockIdx.x >> 3;
-    const int group = xcd + 8 * (slot_in_xcd / per_group);  // (sequence, kv head)
+    //      round-robin to the XCDs (grid x runs over the XCDs first)
+    const int group = (blockIdx.x & 7) + 8 * blockIdx.y;     // (sequence, kv head)
     if (group >= batch * Hkv) return;
-    int w_in = slot_in_xcd % per_group;
-    const int split = w_in % n_splits; w_in /= n_splits;
-    const int mt = n_mt - 1 - (w_in % n_mt);                 // long m-tiles first
-    const int qh = w_in / n_mt;
-    const int b = group / Hkv, kvh = group % Hkv, h0 = kvh * qpk + qh * U;   // heads h0 .. h0+U-1
+    int w_in = blockIdx.x >> 3, split = 0;
+    if (n_splits > 1) {                                      // (each integer division is 25 scalar instructions)
+        split = w_in % n_splits;
+        w_in /= n_splits;
+    }
+    const int qh = w_in / n_mt, mt = n_mt - 1 - (w_in - qh * n_mt);          // long m-tiles first
+    const int b = group / Hkv, kvh = group - b * Hkv, h0 = kvh * qpk + qh * U;   // heads h0 .. h0+U-1
 
     int Lc = ctx_len[b];
     const int32_t *tbl = reinterpret_cast<const int32_t *>(smem + C::SMEM);
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         Lc = min(Lc, pm.tbl_cap << page_lg);
         int32_t *dst = reinterpret_cast<int32_t *>(smem + C::SMEM);
         const int n_used = (Lc + page_mask) >> page_lg;
-        for (int i = tid; i < n_used; i += ATT_WAVES * 64)
+        for (int i = tid; i < n_used; i += W * 64)
             dst[i] = min(max(pm.table[(int64_t)b * pm.max_pages + i], 0), pm.n_pages - 1);
         __syncthreads();
     }
@@ -212,8 +213,8 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     const int per_split = (n_chunks + n_splits - 1) / n_splits;
     const int chunk_begin = split * per_split;
     const int chunk_end = min(n_chunks, chunk_begin + per_split);
-    // this wave's chunks: chunk_begin + wave + ATT_WAVES * i, i < n_my
-    const int n_my = max(0, (chunk_end - chunk_begin - wave + ATT_WAVES - 1) / ATT_WAVES);
+    // this wave's chunks: chunk_begin + wave + W * i, i < n_my
+    const int n_my = max(0, (chunk_end - chunk_begin - wave + W - 1) / W);
 
     const uint16_t *pk = prompt_k + (int64_t)kvh * P * HD, *pv = prompt_v + (int64_t)kvh * P * HD;
     const int64_t page_stride = (int64_t)Hkv * HD << page_lg;           // elements per page (all kv heads)
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     typedef const __attribute__((address_space(1))) unsigned char *gptr;   // keeps the loads global, not flat
     uint64_t anc_next = 0;                                              // ancestor bits for the stage in flight
     auto emit = [&](int i, int iv) __attribute__((always_inline)) {
-        const int chunk = chunk_begin + wave + ATT_WAVES * i;
+        const int chunk = chunk_begin + wave + W * i;
         const int base = chunk * ATT_CHUNK;
         const uint32_t k_gran_iv = ((lane % GPR) ^ att_swizzle_k<HD>((iv & 3) * RPI + v_lane_row)) * 16;
         const uint32_t v_gran_iv = ((lane % GPR) ^ att_swizzle<HD>((iv & 1) * RPI + v_lane_row)) * 16;
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     // with the QK^T matrix instructions, and have the rest of the step to land.
     auto compute = [&](int i, bool more) __attribute__((always_inline)) {
         const uint64_t anc_cur = anc_next;
-        const int chunk = chunk_begin + wave + ATT_WAVES * i;
+        const int chunk = chunk_begin + wave + W * i;
         const bool tree_chunk = chunk >= n_cc;
         const int base = chunk * ATT_CHUNK;
         u32x4 kf[2][KSN];
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
                 s_acc[u][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qf[u][1][ks], s_acc[u][tt], 0, 0, 0);
             }
         };
-        const int base_n = base + ATT_WAVES * ATT_CHUNK;                 // the wave's next chunk
+        const int base_n = base + W * ATT_CHUNK;                 // the wave's next chunk
         if (more && base_n >= P && base_n + ATT_CHUNK <= desc_end && one_page(base_n - P)) {   // wave-uniform
             // contiguous: one descriptor for the sequence's slots; paged: one for the chunk's page
             const int64_t first = PAGED ? (int64_t)__builtin_amdgcn_readfirstlane(tbl[(base_n - P) >> page_lg]) * page_stride : 0;
@@ -557,69 +558,78 @@ __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         att_wait<0>();                                  // the next chunk has landed
     }
 
-    // ---- merge the wavefronts (disjoint key subsets), head by head: every wave leaves its rescaled
-    //      tiles in LDS, wave nt then sums tile nt of the head dimension over the waves in wave order
-    //      (fixed order, deterministic) and finishes and stores those 16 columns -----------------------
-    float *sm = reinterpret_cast<float *>(smem), *sl = sm + ATT_WAVES * 16;
-    float4 *region = reinterpret_cast<float4 *>(smem + 2 * ATT_WAVES * 16 * 4);   // [WAVES][NTN][64]
+    // ---- merge the wavefronts (disjoint key subsets): every wave leaves its maxima and sums, then its
+    //      rescaled tiles in LDS, wave nt then sums tile nt of the head dimension over the waves in wave
+    //      order (fixed order, deterministic) and finishes and stores those 16 columns.  All heads at a
+    //      time: two barriers for the workgroup instead of three per head --------------------------------
+    float *sm = reinterpret_cast<float *>(smem + C::ML), *sl = sm + U * W * 16;   // [U][W][16]
+    float4 *region = reinterpret_cast<float4 *>(smem);                            // [U][W][NTN][64]
 #pragma unroll
     for (int u = 0; u < U; u++) {
-        const int h = h0 + u;
-        __syncthreads();                     // the chunk buffers (first head) or the previous head's sums are done with
         const float l = sum_over_lane_groups(l_run[u]);
         if (g == 0) {
-            sm[wave * 16 + c] = m_run[u];
-            sl[wave * 16 + c] = l;
+            sm[(u * W + wave) * 16 + c] = m_run[u];
+            sl[(u * W + wave) * 16 + c] = l;
         }
-        __syncthreads();
-        float m_tot = -INFINITY;
+    }
+    __syncthreads();                         // (every wave is past its chunk buffer, too)
+    float m_tot[U], l_tot[U];
 #pragma unroll
-        for (int w = 0; w < ATT_WAVES; w++) m_tot = fmaxf(m_tot, sm[w * 16 + c]);
-        const float m_use = (m_tot == -INFINITY) ? 0.f : m_tot;
-        float l_tot = 0.f;
+    for (int u = 0; u < U; u++) {
+        m_tot[u] = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < ATT_WAVES; w++) l_tot += sl[w * 16 + c] * fast_exp2(sm[w * 16 + c] - m_use);
+        for (int w = 0; w < W; w++) m_tot[u] = fmaxf(m_tot[u], sm[(u * W + w) * 16 + c]);
+        const float m_use = (m_tot[u] == -INFINITY) ? 0.f : m_tot[u];
+        l_tot[u] = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; w++) l_tot[u] += sl[(u * W + w) * 16 + c] * fast_exp2(sm[(u * W + w) * 16 + c] - m_use);
         const float f = fast_exp2(m_run[u] - m_use);
 #pragma unroll
         for (int nt = 0; nt < NTN; nt++)
-            region[(wave * NTN + nt) * 64 + lane] =
+            region[((u * W + wave) * NTN + nt) * 64 + lane] =
                 make_float4(o_acc[u][nt][0] * f, o_acc[u][nt][1] * f, o_acc[u][nt][2] * f, o_acc[u][nt][3] * f);
-        __syncthreads();
-        if (wave >= NTN || !row_ok) continue;
-        const int nt = wave;                 // this wave's 16 columns of the head
-        float4 o = region[nt * 64 + lane];
+    }
+    __syncthreads();
+    if (!row_ok) return;
 #pragma unroll
-        for (int w = 1; w < ATT_WAVES; w++) {
-            const float4 v = region[(w * NTN + nt) * 64 + lane];
-            o.x += v.x; o.y += v.y; o.z += v.z; o.w += v.w;
-        }
-        // ---- lane (g, c) holds O[row rq][hd 16nt + 4g .. +4] -----------------------------------
-        if (n_splits > 1) {                  // unnormalised partial for attn_merge_kernel
-            const int64_t prow = (((int64_t)b * Hq + h) * n_splits + split) * R + rq;
-            *reinterpret_cast<float4 *>(part_o + prow * HD + nt * 16 + 4 * g) = o;
-            if (nt == 0 && g == 0) {
-                part_ml[prow * 2] = m_tot;
-                part_ml[prow * 2 + 1] = row_present ? l_tot : 0.f;      // (a zero sum makes the merge write zeros)
+    for (int u = 0; u < U; u++) {
+        const int h = h0 + u;
+#pragma unroll
+        for (int nt = wave; nt < NTN; nt += W) {     // this wave's columns of the head, 16 at a time
+            float4 o = region[(u * W * NTN + nt) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < W; w++) {
+                const float4 v = region[((u * W + w) * NTN + nt) * 64 + lane];
+                o.x += v.x; o.y += v.y; o.z += v.z; o.w += v.w;
             }
-            continue;
-        }
-        const float inv = (l_tot > 0.f && row_present) ? 1.0f / l_tot : 0.f;
-        const int mrow = b * R + rq, n_ksteps = (Hq * HD) >> 5;
-        const float ov[4] = {o.x * inv, o.y * inv, o.z * inv, o.w * inv};
-        uint16_t hi[4], lo[4];
+            // ---- lane (g, c) holds O[row rq][hd 16nt + 4g .. +4] -----------------------------------
+            if (n_splits > 1) {                  // unnormalised partial for attn_merge_kernel
+                const int64_t prow = (((int64_t)b * Hq + h) * n_splits + split) * R + rq;
+                *reinterpret_cast<float4 *>(part_o + prow * HD + nt * 16 + 4 * g) = o;
+                if (nt == 0 && g == 0) {
+                    part_ml[prow * 2] = m_tot[u];
+                    part_ml[prow * 2 + 1] = row_present ? l_tot[u] : 0.f;      // (a zero sum makes the merge write zeros)
+                }
+                continue;
+            }
+            const float inv = (l_tot[u] > 0.f && row_present) ? 1.0f / l_tot[u] : 0.f;
+            const int mrow = b * R + rq, n_ksteps = (Hq * HD) >> 5;
+            const float ov[4] = {o.x * inv, o.y * inv, o.z * inv, o.w * inv};
+            uint16_t hi[4], lo[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) split_bf16(ov[e], hi[e], lo[e]);
-        uint2 ph, pl;
-        ph.x = hi[0] | ((uint32_t)hi[1] << 16); ph.y = hi[2] | ((uint32_t)hi[3] << 16);
-        pl.x = lo[0] | ((uint32_t)lo[1] << 16); pl.y = lo[2] | ((uint32_t)lo[3] << 16);
-        const int k = h * HD + nt * 16 + 4 * g;
-        if (as_fragments) {                  // two planes, the O-projection's activation slab
-            const int pack_off = frag_pack_offset(batch * R);
-            *reinterpret_cast<uint2 *>(out + frag_index(0, mrow, k, n_ksteps, m_tiles_out, pack_off)) = ph;
-            *reinterpret_cast<uint2 *>(out + frag_index(1, mrow, k, n_ksteps, m_tiles_out, pack_off)) = pl;
-        } else {
-            *reinterpret_cast<uint2 *>(out + (int64_t)mrow * Hq * HD + k) = ph;
-            if (out_lo) *reinterpret_cast<uint2 *>(out_lo + (int64_t)mrow * Hq * HD + k) = pl;
+            for (int e = 0; e < 4; e++) split_bf16(ov[e], hi[e], lo[e]);
+            uint2 ph, pl;
+            ph.x = hi[0] | ((uint32_t)hi[1] << 16); ph.y = hi[2] | ((uint32_t)hi[3] << 16);
+            pl.x = lo[0] | ((uint32_t)lo[1] << 16); pl.y = lo[2] | ((uint32_t)lo[3] << 16);
+            const int k = h * HD + nt * 16 + 4 * g;
+            if (as_fragments) {                  // two planes, the O-projection's activation slab
+                const int pack_off = frag_pack_offset(batch * R);
+                *reinterpret_cast<uint2 *>(out + frag_index(0, mrow, k, n_ksteps, m_tiles_out, pack_off)) = ph;
+                *reinterpret_cast<uint2 *>(out + frag_index(1, mrow, k, n_ksteps, m_tiles_out, pack_off)) = pl;
+            } else {
+                *reinterpret_cast<uint2 *>(out + (int64_t)mrow * Hq * HD + k) = ph;
+                if (out_lo) *reinterpret_cast<uint2 *>(out_lo + (int64_t)mrow * Hq * HD + k) = pl;
+            }
         }
     }
 }
@@ -691,17 +701,17 @@ AttnPlan attn_plan(int batch, int rows, int n_heads, int hd, int ctx_hint, int n
     return p;
 }
 
-template <int HD, int U, bool PAGED>
+template <int HD, int U, int W, bool PAGED>
 static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo, const void *k_cache, const void *v_cache,
                           const void *k_tree, const void *v_tree, const void *k_tree_lo, const void *v_tree_lo,
                           const void *prompt_k, const void *prompt_v, const int32_t *ctx_len, const int32_t *token,
                           int batch, int Hq,
                           int Hkv, int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
                           void *out_lo, bool out_as_fragments, const PageMap &pm, const int32_t *only_row, hipStream_t s) {
-    using C = AttCfg<HD, U>;
+    using C = AttCfg<HD, U, W>;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)tree_attn_kernel<HD, U, PAGED>,
+        (void)hipFuncSetAttribute((const void *)tree_attn_kernel<HD, U, W, PAGED>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   C::SMEM + (PAGED ? ATT_PAGE_TABLE_MAX * 4 : 0));
         attr_set = true;
@@ -710,9 +720,9 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
     const int n_mt = (t.rows + 15) / 16;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     const int groups = batch * Hkv, per_group = (Hq / Hkv / U) * n_mt * p.splits;
-    const int grid = 8 * ((groups + 7) / 8) * per_group;
-    hipLaunchKernelGGL((tree_attn_kernel<HD, U, PAGED>), dim3(grid), dim3(ATT_WAVES * 64), smem_bytes, s,
-                       ctx_len, batch, Hq, Hkv, n_mt, p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
+    const dim3 grid(8 * per_group, (groups + 7) / 8);
+    hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, PAGED>), grid, dim3(W * 64), smem_bytes, s,
+                       ctx_len, batch, Hq / Hkv, Hkv, n_mt, p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
                        (const uint16_t *)k_cache, (const uint16_t *)v_cache,
                        (const uint16_t *)k_tree, (const uint16_t *)v_tree, (const uint16_t *)k_tree_lo,
                        (const uint16_t *)v_tree_lo, (const uint16_t *)prompt_k, (const uint16_t *)prompt_v, token,
@@ -728,9 +738,19 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s, const int32_t *only_row) {
     // grouped-query models: two query heads of a K/V head per workgroup share its chunk loads
     const bool pair = (Hq / Hkv) % 2 == 0;
-#define ATT_LAUNCH_P(HD_, U_, PG_) launch_attn_t<HD_, U_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
+    // Eight waves walk one workgroup's keys, or four: with four a CU holds two workgroups, one in its loop while the
+    // other is in its prologue or merge (6 us of a workgroup's time together), and the merge is half as wide.
+    // Four where the workgroups are more than the CUs, eight where each has a CU to itself and fewer waves would
+    // only make its walk longer (eight / four, 68 rows unless stated: 64/8 heads, 8 sequences of 1024 to 4096 keys
+    // 167.5 / 152.0 us, 3 of 300 28.8 / 21.1; 32 heads, 2 of 800 23.0 / 18.4, 4 of 1400 42.4 / 38.8, 8 of 2000
+    // 98.8 / 90.7, 170 rows on 1024 27.4 / 24.2, 512 rows on 512 57.8 / 50.6; but one sequence, 160 workgroups:
+    // 64/8 heads 30.1 / 35.4, 32 heads 14.5 / 16.9).
+    const bool four = (int64_t)batch * (Hq / (pair ? 2 : 1)) * ((t.rows + 15) / 16) * p.splits > 256;
+#define ATT_LAUNCH_P(HD_, U_, W_, PG_) launch_attn_t<HD_, U_, W_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
                                                    prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, s)
-#define ATT_LAUNCH(HD_, U_) do { if (pm.table) ATT_LAUNCH_P(HD_, U_, true); else ATT_LAUNCH_P(HD_, U_, false); } while (0)
+#define ATT_LAUNCH(HD_, U_) do { \
+        if (four) { if (pm.table) ATT_LAUNCH_P(HD_, U_, 4, true); else ATT_LAUNCH_P(HD_, U_, 4, false); } \
+        else { if (pm.table) ATT_LAUNCH_P(HD_, U_, 8, true); else ATT_LAUNCH_P(HD_, U_, 8, false); } } while (0)
     if (hd == 128) {
         if (pair) ATT_LAUNCH(128, 2); else ATT_LAUNCH(128, 1);
     } else {
