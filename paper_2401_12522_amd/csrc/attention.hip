@@ -2,8 +2,9 @@
 // the pass attends to all cached tokens and to its ancestors-or-self among the rows of the
 // pass; mask-token rows additionally attend to the per-layer prompt prefix.
 //
-// Flash-style, one workgroup per (sequence, query head, 16 query rows, key split):
-//  * A workgroup owns one m-tile of 16 query rows and walks the key axis
+// Flash-style, one workgroup per (sequence, query head, 16 query rows, key split), or, where query heads share
+// a K/V head, per 32 queries of several heads and correspondingly fewer rows:
+//  * A workgroup owns one tile of 16 queries, or two, and walks the key axis
 //    [prefix | cache | pass rows] in chunks of 32 key slots.  Its 8 wavefronts, or 4 of two workgroups
 //    per CU (two per SIMD, so that one wave's softmax arithmetic overlaps the other's matrix instructions) take
 //    chunks round-robin and never synchronise inside the loop: each keeps its own
@@ -28,7 +29,7 @@
 //    copied to the partner before P.V, all lane-locally.
 //  * The tree mask is derived from per-row ancestor bitsets and only evaluated in chunks that
 //    touch the prefix, the ragged end of the cache or the pass rows.  A parent always has a
-//    smaller row index than its child, so m-tile mt skips pass-row chunks beyond its own.
+//    smaller row index than its child, so a workgroup skips pass-row chunks beyond its rows.
 #include "common.h"
 #include <type_traits>
 
@@ -127,7 +128,7 @@ __device__ __forceinline__ void lds_wait_all(u32x4 (&k)[2][N], s16x4 (&v)[M][2])
     }
 }
 
-// U query heads and W waves per workgroup
+// U tiles of 16 queries and W waves per workgroup
 template <int HD, int U, int W>
 struct AttCfg {
     static constexpr int KSN = HD / 32;                       // k-steps of the QK^T contraction
@@ -164,7 +165,7 @@ template <int HD, int U, int W, bool PAGED>
 __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void tree_attn_kernel(
     // the first 14 dwords arrive in scalar registers with the wave (kernel-argument preload):
     // what the workgroup needs to find its work and to issue its first loads comes first
-    const int32_t *__restrict__ ctx_len, int batch, int qpk /* query heads per K/V head */, int Hkv, int n_mt, int n_splits, int P, int R, int smax,
+    const int32_t *__restrict__ ctx_len, int batch, int qpk /* query heads per K/V head */, int Hkv, int n_mt_lg, int n_splits, int P, int R, int smax,
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ q_lo,
     TemplateDev t, const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
     const uint16_t *__restrict__ k_tree, const uint16_t *__restrict__ v_tree,
@@ -189,8 +190,12 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         split = w_in % n_splits;
         w_in /= n_splits;
     }
+    // A tile's 16 query lanes are 2^lg_rows rows of 2^lg_ht heads (one head per workgroup: 16 rows of it); the
+    // workgroup's second tile has the same rows of the next heads.
+    const int n_mt = n_mt_lg & 0xFFFF, lg_ht = U > 1 ? n_mt_lg >> 16 : 0, lg_rows = 4 - lg_ht;
     const int qh = w_in / n_mt, mt = n_mt - 1 - (w_in - qh * n_mt);          // long m-tiles first
-    const int b = group / Hkv, kvh = group - b * Hkv, h0 = kvh * qpk + qh * U;   // heads h0 .. h0+U-1
+    const int b = group / Hkv, kvh = group - b * Hkv;
+    const int h0 = kvh * qpk + (U > 1 ? qh << (1 + lg_ht) : qh);                // the workgroup's first head
 
     int Lc = ctx_len[b];
     const int32_t *tbl = reinterpret_cast<const int32_t *>(smem + C::SMEM);
@@ -205,10 +210,10 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             dst[i] = min(max(pm.table[(int64_t)b * pm.max_pages + i], 0), pm.n_pages - 1);
         __syncthreads();
     }
-    const int row0 = mt * 16;
+    const int row0 = mt << lg_rows;
     const int n_ctx_keys = P + Lc;
     const int n_cc = (n_ctx_keys + ATT_CHUNK - 1) / ATT_CHUNK;           // chunks over [prefix | cache]
-    const int n_tc = min((R + 15) >> 4, mt + 1);                         // chunks over the pass rows
+    const int n_tc = min((R + 15) >> 4, ((row0 + (1 << lg_rows) - 1) >> 4) + 1);   // chunks over the pass rows
     const int n_chunks = n_cc + n_tc;
     const int per_split = (n_chunks + n_splits - 1) / n_splits;
     const int chunk_begin = split * per_split;
@@ -240,7 +245,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     //      All loads of this prologue (mask byte, token, query fragments) are unconditional, from
     //      a clamped row, and their values are first looked at behind the wait for the first chunk:
     //      one memory round trip instead of one per dependent condition.
-    const int rq = row0 + c;
+    const int rq = row0 + (c & ((1 << lg_rows) - 1)), hq = h0 + (c >> lg_rows);   // tile u: head hq + (u << lg_ht)
     const bool row_ok = rq < R;
     const int rqc = min(rq, R - 1);
     const uint32_t mask_byte = t.is_mask[rqc];
@@ -256,7 +261,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             const bool live = row_ok && (pl == 0 || q_lo);
 #pragma unroll
             for (int ks = 0; ks < KSN; ks++) {
-                uint4 v = *reinterpret_cast<const uint4 *>(src + (((int64_t)b * R + rqc) * Hq + h0 + u) * HD + ks * 32 + g * 8);
+                uint4 v = *reinterpret_cast<const uint4 *>(src + (((int64_t)b * R + rqc) * Hq + hq + (u << lg_ht)) * HD + ks * 32 + g * 8);
                 if (!live) v = make_uint4(0, 0, 0, 0);
                 qf[u][pl][ks] = __builtin_bit_cast(bf16x8, v);
             }
@@ -547,7 +552,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     att_wait<0>();                                      // the first chunk and the prologue's loads have landed
     // (looked at here, where the prologue's loads have landed anyway: ahead of them it cost 0.5 % of
     // every launch; the whole workgroup leaves together)
-    if (only_row && (min(max(only_row[b], 0), R - 1) >> 4) != mt) return;
+    if (only_row && (min(max(only_row[b], 0), R - 1) >> lg_rows) != mt) return;
     // a tree row without a candidate (negative token) is absent from the pass: its output is zero
     int row_flags = (row_ok && mask_byte ? 1 : 0) | (row_ok && (mask_byte || tok_val >= 0) ? 2 : 0);
     asm volatile("" : "+v"(row_flags));                 // (looked at here, not inside the loop)
@@ -562,14 +567,17 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     //      rescaled tiles in LDS, wave nt then sums tile nt of the head dimension over the waves in wave
     //      order (fixed order, deterministic) and finishes and stores those 16 columns.  All heads at a
     //      time: two barriers for the workgroup instead of three per head --------------------------------
+    // (the lane's place is asked for again: kept through the loop it cost two heads per workgroup a spill)
+    const int lane_m = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), g_m = lane_m >> 4, c_m = lane_m & 15;
+    const int rq_m = row0 + (c_m & ((1 << lg_rows) - 1)), hq_m = h0 + (c_m >> lg_rows);
     float *sm = reinterpret_cast<float *>(smem + C::ML), *sl = sm + U * W * 16;   // [U][W][16]
     float4 *region = reinterpret_cast<float4 *>(smem);                            // [U][W][NTN][64]
 #pragma unroll
     for (int u = 0; u < U; u++) {
         const float l = sum_over_lane_groups(l_run[u]);
-        if (g == 0) {
-            sm[(u * W + wave) * 16 + c] = m_run[u];
-            sl[(u * W + wave) * 16 + c] = l;
+        if (g_m == 0) {
+            sm[(u * W + wave) * 16 + c_m] = m_run[u];
+            sl[(u * W + wave) * 16 + c_m] = l;
         }
     }
     __syncthreads();                         // (every wave is past its chunk buffer, too)
@@ -578,42 +586,42 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     for (int u = 0; u < U; u++) {
         m_tot[u] = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < W; w++) m_tot[u] = fmaxf(m_tot[u], sm[(u * W + w) * 16 + c]);
+        for (int w = 0; w < W; w++) m_tot[u] = fmaxf(m_tot[u], sm[(u * W + w) * 16 + c_m]);
         const float m_use = (m_tot[u] == -INFINITY) ? 0.f : m_tot[u];
         l_tot[u] = 0.f;
 #pragma unroll
-        for (int w = 0; w < W; w++) l_tot[u] += sl[(u * W + w) * 16 + c] * fast_exp2(sm[(u * W + w) * 16 + c] - m_use);
+        for (int w = 0; w < W; w++) l_tot[u] += sl[(u * W + w) * 16 + c_m] * fast_exp2(sm[(u * W + w) * 16 + c_m] - m_use);
         const float f = fast_exp2(m_run[u] - m_use);
 #pragma unroll
         for (int nt = 0; nt < NTN; nt++)
-            region[((u * W + wave) * NTN + nt) * 64 + lane] =
+            region[((u * W + wave) * NTN + nt) * 64 + lane_m] =
                 make_float4(o_acc[u][nt][0] * f, o_acc[u][nt][1] * f, o_acc[u][nt][2] * f, o_acc[u][nt][3] * f);
     }
     __syncthreads();
-    if (!row_ok) return;
+    if (rq_m >= R) return;
 #pragma unroll
     for (int u = 0; u < U; u++) {
-        const int h = h0 + u;
+        const int h = hq_m + (u << lg_ht);
 #pragma unroll
         for (int nt = wave; nt < NTN; nt += W) {     // this wave's columns of the head, 16 at a time
-            float4 o = region[(u * W * NTN + nt) * 64 + lane];
+            float4 o = region[(u * W * NTN + nt) * 64 + lane_m];
 #pragma unroll
             for (int w = 1; w < W; w++) {
-                const float4 v = region[((u * W + w) * NTN + nt) * 64 + lane];
+                const float4 v = region[((u * W + w) * NTN + nt) * 64 + lane_m];
                 o.x += v.x; o.y += v.y; o.z += v.z; o.w += v.w;
             }
             // ---- lane (g, c) holds O[row rq][hd 16nt + 4g .. +4] -----------------------------------
             if (n_splits > 1) {                  // unnormalised partial for attn_merge_kernel
-                const int64_t prow = (((int64_t)b * Hq + h) * n_splits + split) * R + rq;
-                *reinterpret_cast<float4 *>(part_o + prow * HD + nt * 16 + 4 * g) = o;
-                if (nt == 0 && g == 0) {
+                const int64_t prow = (((int64_t)b * Hq + h) * n_splits + split) * R + rq_m;
+                *reinterpret_cast<float4 *>(part_o + prow * HD + nt * 16 + 4 * g_m) = o;
+                if (nt == 0 && g_m == 0) {
                     part_ml[prow * 2] = m_tot[u];
                     part_ml[prow * 2 + 1] = row_present ? l_tot[u] : 0.f;      // (a zero sum makes the merge write zeros)
                 }
                 continue;
             }
             const float inv = (l_tot[u] > 0.f && row_present) ? 1.0f / l_tot[u] : 0.f;
-            const int mrow = b * R + rq, n_ksteps = (Hq * HD) >> 5;
+            const int mrow = b * R + rq_m, n_ksteps = (Hq * HD) >> 5;
             const float ov[4] = {o.x * inv, o.y * inv, o.z * inv, o.w * inv};
             uint16_t hi[4], lo[4];
 #pragma unroll
@@ -621,7 +629,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             uint2 ph, pl;
             ph.x = hi[0] | ((uint32_t)hi[1] << 16); ph.y = hi[2] | ((uint32_t)hi[3] << 16);
             pl.x = lo[0] | ((uint32_t)lo[1] << 16); pl.y = lo[2] | ((uint32_t)lo[3] << 16);
-            const int k = h * HD + nt * 16 + 4 * g;
+            const int k = h * HD + nt * 16 + 4 * g_m;
             if (as_fragments) {                  // two planes, the O-projection's activation slab
                 const int pack_off = frag_pack_offset(batch * R);
                 *reinterpret_cast<uint2 *>(out + frag_index(0, mrow, k, n_ksteps, m_tiles_out, pack_off)) = ph;
@@ -701,13 +709,14 @@ AttnPlan attn_plan(int batch, int rows, int n_heads, int hd, int ctx_hint, int n
     return p;
 }
 
+// lg_ht: log2 of the heads that share a tile (two heads per workgroup and more)
 template <int HD, int U, int W, bool PAGED>
 static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo, const void *k_cache, const void *v_cache,
                           const void *k_tree, const void *v_tree, const void *k_tree_lo, const void *v_tree_lo,
                           const void *prompt_k, const void *prompt_v, const int32_t *ctx_len, const int32_t *token,
                           int batch, int Hq,
                           int Hkv, int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
-                          void *out_lo, bool out_as_fragments, const PageMap &pm, const int32_t *only_row, hipStream_t s) {
+                          void *out_lo, bool out_as_fragments, const PageMap &pm, const int32_t *only_row, int lg_ht, hipStream_t s) {
     using C = AttCfg<HD, U, W>;
     static bool attr_set = false;
     if (!attr_set) {
@@ -717,12 +726,12 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
         attr_set = true;
     }
     const size_t smem_bytes = C::SMEM + (PAGED ? (size_t)((pm.tbl_cap + 3) / 4) * 16 : 0);
-    const int n_mt = (t.rows + 15) / 16;
+    const int per_wg = 16 >> lg_ht, n_mt = (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
-    const int groups = batch * Hkv, per_group = (Hq / Hkv / U) * n_mt * p.splits;
+    const int groups = batch * Hkv, per_group = (Hq / Hkv / U >> lg_ht) * n_mt * p.splits;
     const dim3 grid(8 * per_group, (groups + 7) / 8);
     hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, PAGED>), grid, dim3(W * 64), smem_bytes, s,
-                       ctx_len, batch, Hq / Hkv, Hkv, n_mt, p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
+                       ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16, p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
                        (const uint16_t *)k_cache, (const uint16_t *)v_cache,
                        (const uint16_t *)k_tree, (const uint16_t *)v_tree, (const uint16_t *)k_tree_lo,
                        (const uint16_t *)v_tree_lo, (const uint16_t *)prompt_k, (const uint16_t *)prompt_v, token,
@@ -736,18 +745,29 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            const void *prompt_v, const int32_t *ctx_len, const int32_t *token, int batch, int Hq, int Hkv, int hd,
                            int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
                            void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s, const int32_t *only_row) {
-    // grouped-query models: two query heads of a K/V head per workgroup share its chunk loads
-    const bool pair = (Hq / Hkv) % 2 == 0;
+    // Grouped-query models: a workgroup's two tiles of 16 queries share its chunk loads.  The tiles take as many heads
+    // of the K/V head's group as a power of two divides evenly, and so fewer rows: eight heads of 4 rows for 64/8 heads,
+    // 17 workgroups per K/V head for the 68 rows of a 64-node tree where pairs of heads with 16 rows each took 20
+    // (three of their four tiles over the last 16 rows held 4), a finer grain for the CUs, and fewer keys masked away at
+    // a row tile's end.  Pairs of heads / this, us: 68 rows, 8 sequences of 1024 to 4096 keys 157.0 / 136.3, 2 of 1000
+    // 28.4 / 27.1, one of 2048 29.6 / 28.3; 170 rows on 1024 34.1 / 29.6, 512 rows on 512 74.3 / 63.7, 25 rows, 4 of
+    // 2000 28.9 / 26.6, one row 14.2 / 14.0: never slower.
+    const int qpk = Hq / Hkv;
+    const bool pair = qpk % 2 == 0;
+    int lg_ht = 0;
+    while (pair && lg_ht < 3 && qpk % (4 << lg_ht) == 0) lg_ht++;
     // Eight waves walk one workgroup's keys, or four: with four a CU holds two workgroups, one in its loop while the
     // other is in its prologue or merge (6 us of a workgroup's time together), and the merge is half as wide.
     // Four where the workgroups are more than the CUs, eight where each has a CU to itself and fewer waves would
     // only make its walk longer (eight / four, 68 rows unless stated: 64/8 heads, 8 sequences of 1024 to 4096 keys
-    // 167.5 / 152.0 us, 3 of 300 28.8 / 21.1; 32 heads, 2 of 800 23.0 / 18.4, 4 of 1400 42.4 / 38.8, 8 of 2000
-    // 98.8 / 90.7, 170 rows on 1024 27.4 / 24.2, 512 rows on 512 57.8 / 50.6; but one sequence, 160 workgroups:
-    // 64/8 heads 30.1 / 35.4, 32 heads 14.5 / 16.9).
-    const bool four = (int64_t)batch * (Hq / (pair ? 2 : 1)) * ((t.rows + 15) / 16) * p.splits > 256;
+    // 159.5 / 136.3 us, 3 of 300 26.3 / 19.8; 32 heads, 2 of 800 22.5 / 17.9, 4 of 700 to 1400 35.4 / 30.6, 8 of 2000
+    // 111 / 94.5, 170 rows on 1024 25.1 / 21.8, 488 rows on 512 50.8 / 43.8; but one sequence, 136 and 160 workgroups:
+    // 64/8 heads 28.3 / 33.2, 32 heads 13.0 / 15.5).  Where one row per sequence is asked for, one row tile of each
+    // has work, the others leave.
+    const int rows_wg = 16 >> lg_ht, n_mt = only_row ? 1 : (t.rows + rows_wg - 1) / rows_wg;
+    const bool four = (int64_t)batch * (pair ? Hq >> (1 + lg_ht) : Hq) * n_mt * p.splits > 256;
 #define ATT_LAUNCH_P(HD_, U_, W_, PG_) launch_attn_t<HD_, U_, W_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
-                                                   prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, s)
+                                                   prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, lg_ht, s)
 #define ATT_LAUNCH(HD_, U_) do { \
         if (four) { if (pm.table) ATT_LAUNCH_P(HD_, U_, 4, true); else ATT_LAUNCH_P(HD_, U_, 4, false); } \
         else { if (pm.table) ATT_LAUNCH_P(HD_, U_, 8, true); else ATT_LAUNCH_P(HD_, U_, 8, false); } } while (0)
