@@ -10,7 +10,22 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-// RMSNorm, first half.  Grid (row, 1024-column chunk): x += sum_s partial[s] (fixed order), then
+// Which (row, column chunk) a workgroup of the kernels that write an activation slab takes.  A 128-byte line
+// of the slab holds 16 bytes of each of eight rows, and consecutive workgroup ids go round-robin over the XCDs: with
+// the row as the id eight L2s held an eighth of every line each and wrote it to memory piece by piece.  The 16 rows of
+// a slab tile go to one XCD here, 8 ids apart (tile t of the (chunk, row tile) grid on XCD t % 8), so that their lines leave
+// whole.  Norm kernel, row as the id / this (rocprofv3): 512 rows of 4096 12.6 -> 10.4 us, first layer 10.0 -> 7.9; 272 rows
+// 9.2 -> 8.7, first layer 7.5 -> 6.8; 170 rows 7.8 -> 7.1; 68 rows of 8192 8.0 -> 6.8, of 4096 6.1 -> 5.6; fewer rows the same.
+// Workgroups beyond the last row or chunk have nothing to do (false).
+__device__ __forceinline__ bool slab_block(int M, int chunks, int &row, int &chunk) {
+    const int mt_n = (M + 15) >> 4, q = blockIdx.x >> 3, t = (q >> 4) * 8 + (blockIdx.x & 7);
+    chunk = t / mt_n;
+    row = (t - chunk * mt_n) * 16 + (q & 15);
+    return row < M && chunk < chunks;
+}
+static dim3 slab_grid(int M, int chunks) { return dim3((unsigned)(((M + 15) / 16 * chunks + 7) / 8 * 128)); }
+
+// RMSNorm, first half.  Per (row, 1024-column chunk): x += sum_s partial[s] (fixed order), then
 // the *unnormalised* x * gain is written as two bf16 planes (hi, lo) in the GEMM's fragment
 // order, and the chunk's sum of squares goes to ssq[row][chunk].  The row factor
 // rsqrt(mean(x^2) + eps) is a scalar per row and commutes with the matrix product, so the GEMM
@@ -27,8 +42,9 @@ __global__ __launch_bounds__(256) void rmsnorm_prep_kernel(float *__restrict__ x
                                                            uint16_t *__restrict__ h_frag, float *__restrict__ ssq,
                                                            EmbedSource e) {
     __shared__ float red[4];
-    const int row = blockIdx.x, chunk = blockIdx.y, tid = threadIdx.x;
-    const int n_ksteps = (d + 31) >> 5, m_tiles = (M + 15) >> 4;
+    int row, chunk;
+    if (!slab_block(M, (d + 1023) >> 10, row, chunk)) return;
+    const int tid = threadIdx.x, n_ksteps = (d + 31) >> 5, m_tiles = (M + 15) >> 4;
     const int c = chunk * 256 + tid;                         // float4 column
     float ss = 0.f;
     if (c < (d >> 2)) {
@@ -182,9 +198,10 @@ __global__ __launch_bounds__(ROPE_THREADS) void qkv_rope_kernel(
 // (fragment order; features beyond d_ffn inside the last k-step are written as zeros).
 __global__ void silu_mul_kernel(const float *__restrict__ partial, int splits, int M, int F,
                                 uint16_t *__restrict__ act_frag, RowScale rs) {
-    const int f8 = blockIdx.x * blockDim.x + threadIdx.x;
-    const int row = blockIdx.y;
     const int n_ksteps = (F + 31) >> 5, m_tiles = (M + 15) >> 4;
+    int row, chunk;
+    if (!slab_block(M, (n_ksteps * 4 + blockDim.x - 1) / blockDim.x, row, chunk)) return;
+    const int f8 = chunk * blockDim.x + threadIdx.x;
     const int f = f8 * 8;
     if (f >= n_ksteps * 32) return;
     float o[8];
@@ -361,13 +378,12 @@ void launch_gather_rows(const int32_t *sel_row, int batch, int rows, const void 
 void launch_embed_prep(const int32_t *token, const TemplateDev &t, int batch, const void *tok_emb, const void *mask_emb, int d,
                        int vocab, const void *gain, float *x, void *h_frag, float *ssq, hipStream_t s) {
     const EmbedSource e = {token, t.is_mask, t.mask_index, (const uint16_t *)tok_emb, (const uint16_t *)mask_emb, t.rows, vocab};
-    hipLaunchKernelGGL(rmsnorm_prep_kernel<true>, dim3(batch * t.rows, (d / 4 + 255) / 256), dim3(256), 0, s, x, (const float *)nullptr, 0,
+    hipLaunchKernelGGL(rmsnorm_prep_kernel<true>, slab_grid(batch * t.rows, (d + 1023) / 1024), dim3(256), 0, s, x, (const float *)nullptr, 0,
                        batch * t.rows, d, (const uint16_t *)gain, (uint16_t *)h_frag, ssq, e);
 }
 void launch_rmsnorm_prep(float *x, const float *partial, int splits, int M, int d, const void *gain,
                          void *h_frag, float *ssq, hipStream_t s) {
-    const int chunks = (d / 4 + 255) / 256;
-    hipLaunchKernelGGL(rmsnorm_prep_kernel<false>, dim3(M, chunks), dim3(256), 0, s, x, partial, splits, M, d,
+    hipLaunchKernelGGL(rmsnorm_prep_kernel<false>, slab_grid(M, (d + 1023) / 1024), dim3(256), 0, s, x, partial, splits, M, d,
                        (const uint16_t *)gain, (uint16_t *)h_frag, ssq, EmbedSource{});
 }
 void launch_qkv_rope(const float *partial, int splits, int batch, const TemplateDev &t, int Hq,
@@ -384,7 +400,7 @@ void launch_qkv_rope(const float *partial, int splits, int batch, const Template
 void launch_silu_mul(const float *partial, int splits, int M, int F, void *act_frag, const RowScale &rs,
                      hipStream_t s) {
     const int n8 = ((F + 31) / 32) * 4;                       // threads (8 features each) per row
-    hipLaunchKernelGGL(silu_mul_kernel, dim3((n8 + 127) / 128, M), dim3(128), 0, s, partial, splits, M, F,
+    hipLaunchKernelGGL(silu_mul_kernel, slab_grid(M, (n8 + 127) / 128), dim3(128), 0, s, partial, splits, M, F,
                        (uint16_t *)act_frag, rs);
 }
 void launch_select(const float *logits, int batch, const TemplateDev &t, int vocab, int kmax,
