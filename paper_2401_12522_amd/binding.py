@@ -15,7 +15,7 @@ EXPORTS = [
     "bita_packed_bytes", "bita_pack_weight", "bita_model_create", "bita_model_destroy",
     "bita_workspace_bytes", "bita_tree_template_create", "bita_tree_template_destroy",
     "bita_tree_template_info", "bita_build_tree", "bita_verify_step", "bita_accept",
-    "bita_compact_kv", "bita_prefill_workspace_bytes", "bita_prefill_prepare", "bita_prefill", "bita_attention_workspace_bytes", "bita_tree_attention",
+    "bita_compact_kv", "bita_decode_step", "bita_prefill_workspace_bytes", "bita_prefill_prepare", "bita_prefill", "bita_attention_workspace_bytes", "bita_tree_attention",
     "bita_gemm_workspace_bytes", "bita_gemm", "bita_gemm_noalloc_max_scratch_bytes", "bita_gemm_noalloc_scratch_bytes",
     "bita_gemm_noalloc", "bita_select", "bita_tune_gemm", "bita_gemm_plan_info", "bita_gemm_plan_detail", "bita_profile_enable",
     "bita_profile_disable", "bita_profile_read", "bita_last_error",
@@ -46,6 +46,11 @@ class _KV(C.Structure):
                [("block_table", C.c_void_p)] + [(n, C.c_int32) for n in ("page_size", "n_pages", "max_pages")]
 
 
+class _StepOut(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in ("token", "argmax", "topk_ids", "topk_val", "logits", "path", "n_acc", "bonus", "emitted",
+                                           "next_group", "next_shift")]
+
+
 def lib():
     """Load libbita.so (once).  Raises if it is missing: the product has no fallback."""
     global _lib
@@ -74,6 +79,8 @@ def lib():
     L.bita_accept.argtypes = [vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp]
     L.bita_compact_kv.restype = C.c_int
     L.bita_compact_kv.argtypes = [vp, C.POINTER(_KV), vp, i32, vp, vp, i32, vp]
+    L.bita_decode_step.restype = C.c_int
+    L.bita_decode_step.argtypes = [vp, C.POINTER(_KV), vp, vp, vp, i32, i32, vp, vp, vp, i32, vp, sz, i32, C.POINTER(_StepOut), vp]
     L.bita_prefill_workspace_bytes.restype, L.bita_prefill_workspace_bytes.argtypes = sz, [vp, i32, i32]
     L.bita_prefill_prepare.restype, L.bita_prefill_prepare.argtypes = C.c_int, [vp, i32, i32]
     L.bita_prefill.restype = C.c_int
@@ -385,7 +392,18 @@ def prefill(model, kv, ctx_hint, tokens, chunk_rows, seq_len=None, workspace=Non
 
 
 def decode_step(model, kv, ctx_hint, tmpl, buf, batch, root_token, cand, group=None, shift=None):
-    """The four calls of one step, back to back on the current stream (no host sync)."""
+    """The four calls of one step on the current stream (no host sync), by the library's own call for all of them."""
+    if buf.path.shape[1] == tmpl.depth + 1:
+        d = kv.desc(ctx_hint)
+        ptr = lambda t: t.data_ptr() if t is not None else None                     # noqa: E731
+        has_masks = tmpl.n_groups > 0
+        out = _StepOut(ptr(buf.token), ptr(buf.argmax), ptr(buf.topk_ids) if has_masks else None, ptr(buf.topk_val) if has_masks else None,
+                       ptr(buf.logits), ptr(buf.path), ptr(buf.n_acc), ptr(buf.bonus), ptr(buf.emitted), ptr(buf.next_group), ptr(buf.next_shift))
+        cand_rows, kmax = (cand.shape[1], cand.shape[2]) if cand is not None else (0, 0)
+        _check(lib().bita_decode_step(model.handle, C.byref(d), tmpl.handle, _ptr(root_token), _ptr(cand), cand_rows, kmax, _ptr(group),
+                                      _ptr(shift), _ptr(kv.ctx_len), batch, _ptr(buf.workspace), buf.workspace.numel(), buf.kmax,
+                                      C.byref(out), _stream()))
+        return
     build_tree(tmpl, root_token, cand, group, shift, batch, buf.token)
     verify_step(model, kv, ctx_hint, tmpl, buf, batch)
     accept(tmpl, buf, batch)

@@ -245,7 +245,7 @@ static void timed_gemm(const void *a_frag, int M, int64_t K, const void *w, int6
 
 // ------------------------------------------------------------------------------------------
 struct WsLayout {
-    size_t x, h, q, attn_out, act, partial, part_o, part_ml, logits, ssq, kv_lo, total;
+    size_t x, h, q, attn_out, act, partial, part_o, part_ml, logits, ssq, kv_lo, ctx_start, total;
     size_t partial_bytes;
 };
 #define ATTN_MAX_SPLITS 32
@@ -277,6 +277,7 @@ static WsLayout ws_layout(const bita_config &c, int batch, int rows) {
     L.logits = take(M * c.vocab * 4);
     L.ssq = take(M * RMS_MAX_CHUNKS * 4);
     L.kv_lo = take(2 * M * c.n_kv_heads * c.head_dim * 2);   // low planes of one layer's pass-row K and V
+    L.ctx_start = take((size_t)batch * 4);
     L.total = off;
     return L;
 }
@@ -308,7 +309,7 @@ extern "C" size_t bita_workspace_bytes(const bita_model *m, int32_t batch, int32
 int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, const int32_t *d_token,
                 const int32_t *d_ctx_len, int32_t batch, void *d_workspace, size_t ws_bytes, int32_t kmax,
                 int32_t *d_argmax, int32_t *d_topk_ids, float *d_topk_val, float *d_logits, void *stream,
-                const PassTail *tail) {
+                const PassTail *tail, const BuildSource *build, int32_t **ctx_start) {
     if (!m || !kv || !t || !d_token || !d_ctx_len || !d_workspace || !d_argmax || batch <= 0)
         return bita_set_error(BITA_ERR_INVALID_ARG, "bita_verify_step: null argument or batch <= 0");
     const bita_config &c = m->cfg;
@@ -389,9 +390,14 @@ int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, c
         }
     };
 
+    BuildSource source = {};
+    if (build) {
+        source = *build;
+        source.ctx_start = *ctx_start = (int32_t *)(ws + L.ctx_start);
+    }
     int pending = 0;                                    // split-K partials waiting to be added to x
     for (int l = 0; l < c.n_layers; l++) {
-        if (l == 0) launch_embed_prep(d_token, td, batch, m->tok_emb, m->mask_emb, d, c.vocab, m->attn_norm[0], x, h, ssq, s);
+        if (l == 0) launch_embed_prep(d_token, source, td, batch, m->tok_emb, m->mask_emb, d, c.vocab, m->attn_norm[0], x, h, ssq, s);
         else launch_rmsnorm_prep(x, partial, pending, M, d, m->attn_norm[l], h, ssq, s);
         timed_gemm(h, M, d, m->wqkv[l], nqkv, partial, nqkv, p_qkv, s);
         void *kt = (unsigned char *)kv->k_tree + l * kv_layer_tree, *vt = (unsigned char *)kv->v_tree + l * kv_layer_tree;

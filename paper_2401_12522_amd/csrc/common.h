@@ -164,9 +164,13 @@ void launch_pack(const void *src, int64_t n_rows, int64_t k, void *dst, int64_t 
                  int64_t tile_stride, int64_t total_tiles, hipStream_t s);
 
 // Where the first layer's norm takes its rows from (see rmsnorm_prep_kernel).
+// A whole step (bita_decode_step) has the first layer's norm work out the rows' tokens itself, from what
+// bita_build_tree takes (root == nullptr: they are in `token` already), and leave every sequence's length
+// at the start of the step in ctx_start.
+struct BuildSource { const int32_t *root, *cand, *group, *shift; int cand_rows, kmax; int32_t *token; const int32_t *ctx_len; int32_t *ctx_start; };
 struct EmbedSource { const int32_t *token; const uint8_t *is_mask; const int32_t *mask_index; const uint16_t *tok_emb, *mask_emb; int rows, vocab; };
 // x = embeddings of the pass' rows, and the first norm's slab and sums of squares
-void launch_embed_prep(const int32_t *token, const TemplateDev &t, int batch, const void *tok_emb, const void *mask_emb, int d,
+void launch_embed_prep(const int32_t *token, const BuildSource &build, const TemplateDev &t, int batch, const void *tok_emb, const void *mask_emb, int d,
                        int vocab, const void *gain, float *x, void *h_frag, float *ssq, hipStream_t s);
 // x += sum of partials (optional), then h = rmsnorm(x) * gain as bf16 with row stride ldh
 // RMSNorm is split: the prep kernel writes x*gain (two planes, fragment order) and per-chunk
@@ -208,11 +212,23 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
 // goes on with those rows alone behind the K/V projection.  sel_row == nullptr: K/V only.  ws: a
 // workspace of bita_workspace_bytes(m, batch, 1).
 struct PassTail { const int32_t *sel_row; void *ws; };
-// bita_verify_step, with an optional tail (argmax is then [B], one per sequence; no top-k, no logits)
+// bita_verify_step, with an optional tail (argmax is then [B], one per sequence; no top-k, no logits), or working
+// the rows' tokens out itself (build; the lengths at the start of the step are then found at *ctx_start)
 int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, const int32_t *d_token,
                 const int32_t *d_ctx_len, int32_t batch, void *d_workspace, size_t ws_bytes, int32_t kmax,
                 int32_t *d_argmax, int32_t *d_topk_ids, float *d_topk_val, float *d_logits, void *stream,
-                const PassTail *tail);
+                const PassTail *tail, const BuildSource *build = nullptr, int32_t **ctx_start = nullptr);
+int page_map_of(const bita_kv *kv, int ctx_upper, PageMap *pm, const char *who);
+// token of row v of sequence b (bita_build_tree)
+__device__ __forceinline__ int tree_token(const BuildSource &s, const TemplateDev &t, int b, int v) {
+    if (v == 0) return s.root[b];
+    if (v >= t.n_tree) return t.mask_index[v];
+    const int g = s.group ? s.group[b] : 0, lvl = t.depth[v] - 1 + (s.shift ? s.shift[b] : 0), rank = t.rank[v];
+    const int row = g * t.n_mask + lvl;
+    // g < 0: the previous pass had no mask group to offer (accept writes -1 then): no drafts
+    return (g >= 0 && lvl >= 0 && lvl < t.n_mask && row < s.cand_rows && rank < s.kmax)
+               ? s.cand[((int64_t)b * s.cand_rows + row) * s.kmax + rank] : -1;
+}
 // row sel_row[b] of each sequence of `rows`: its columns of a two-plane slab (fragment order) and of
 // the residual stream, into a slab and a stream of `batch` rows
 void launch_gather_rows(const int32_t *sel_row, int batch, int rows, const void *a_frag, int k, const float *x, int d,

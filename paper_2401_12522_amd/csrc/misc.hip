@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void rmsnorm_prep_kernel(float *__restrict__ x
                                                            int splits, int M, int d,
                                                            const uint16_t *__restrict__ gain,
                                                            uint16_t *__restrict__ h_frag, float *__restrict__ ssq,
-                                                           EmbedSource e) {
+                                                           EmbedSource e, BuildSource build, TemplateDev t) {
     __shared__ float red[4];
     int row, chunk;
     if (!slab_block(M, (d + 1023) >> 10, row, chunk)) return;
@@ -61,7 +61,17 @@ __global__ __launch_bounds__(256) void rmsnorm_prep_kernel(float *__restrict__ x
         }
         float4 v;
         if constexpr (EMBED) {
-            const int r = row % e.rows, tok = e.token[row];
+            const int b = row / e.rows, r = row - b * e.rows;
+            int tok;
+            if (build.root) {
+                tok = tree_token(build, t, b, r);
+                if (c == 0) {
+                    build.token[row] = tok;
+                    if (r == 0) build.ctx_start[b] = build.ctx_len[b];
+                }
+            } else {
+                tok = e.token[row];
+            }
             const uint16_t *src = nullptr;
             if (e.is_mask[r]) src = e.mask_emb + (int64_t)e.mask_index[r] * d;
             else if (tok >= 0 && tok < e.vocab) src = e.tok_emb + (int64_t)tok * d;
@@ -375,16 +385,16 @@ void launch_gather_rows(const int32_t *sel_row, int batch, int rows, const void 
     hipLaunchKernelGGL(gather_rows_kernel, dim3(batch, (n + 255) / 256), dim3(256), 0, s, sel_row, rows, (const uint16_t *)a_frag, k,
                        x, d, (uint16_t *)a_out, x_out);
 }
-void launch_embed_prep(const int32_t *token, const TemplateDev &t, int batch, const void *tok_emb, const void *mask_emb, int d,
+void launch_embed_prep(const int32_t *token, const BuildSource &build, const TemplateDev &t, int batch, const void *tok_emb, const void *mask_emb, int d,
                        int vocab, const void *gain, float *x, void *h_frag, float *ssq, hipStream_t s) {
     const EmbedSource e = {token, t.is_mask, t.mask_index, (const uint16_t *)tok_emb, (const uint16_t *)mask_emb, t.rows, vocab};
     hipLaunchKernelGGL(rmsnorm_prep_kernel<true>, slab_grid(batch * t.rows, (d + 1023) / 1024), dim3(256), 0, s, x, (const float *)nullptr, 0,
-                       batch * t.rows, d, (const uint16_t *)gain, (uint16_t *)h_frag, ssq, e);
+                       batch * t.rows, d, (const uint16_t *)gain, (uint16_t *)h_frag, ssq, e, build, t);
 }
 void launch_rmsnorm_prep(float *x, const float *partial, int splits, int M, int d, const void *gain,
                          void *h_frag, float *ssq, hipStream_t s) {
     hipLaunchKernelGGL(rmsnorm_prep_kernel<false>, slab_grid(M, (d + 1023) / 1024), dim3(256), 0, s, x, partial, splits, M, d,
-                       (const uint16_t *)gain, (uint16_t *)h_frag, ssq, EmbedSource{});
+                       (const uint16_t *)gain, (uint16_t *)h_frag, ssq, EmbedSource{}, BuildSource{}, TemplateDev{});
 }
 void launch_qkv_rope(const float *partial, int splits, int batch, const TemplateDev &t, int Hq,
                      int Hkv, int hd, const int32_t *ctx_len, const float *rope_cos,

@@ -5,28 +5,9 @@
 // token[v] of the next pass: draft row at depth dv with sibling rank j carries the j-th
 // ranked prediction of mask (dv-1+shift) of the chosen group; rows without a prediction
 // are inactive (-1); mask rows carry their index in the group; row 0 is the last emitted token.
-__global__ void build_tree_kernel(TemplateDev t, const int32_t *__restrict__ root_token,
-                                  const int32_t *__restrict__ cand, const int32_t *__restrict__ group,
-                                  const int32_t *__restrict__ shift, int cand_rows, int kmax,
-                                  int32_t *__restrict__ token) {
+__global__ void build_tree_kernel(TemplateDev t, BuildSource src) {
     const int b = blockIdx.x;
-    const int g = group ? group[b] : 0;
-    const int sh = shift ? shift[b] : 0;
-    for (int v = threadIdx.x; v < t.rows; v += blockDim.x) {
-        int tok;
-        if (v == 0) {
-            tok = root_token[b];
-        } else if (v < t.n_tree) {
-            const int lvl = t.depth[v] - 1 + sh;
-            const int row = g * t.n_mask + lvl;
-            // g < 0: the previous pass had no mask group to offer (accept writes -1 then): no drafts
-            tok = (g >= 0 && lvl >= 0 && lvl < t.n_mask && row < cand_rows && t.rank[v] < kmax)
-                      ? cand[((int64_t)b * cand_rows + row) * kmax + t.rank[v]] : -1;
-        } else {
-            tok = t.mask_index[v];
-        }
-        token[(int64_t)b * t.rows + v] = tok;
-    }
+    for (int v = threadIdx.x; v < t.rows; v += blockDim.x) src.token[(int64_t)b * t.rows + v] = tree_token(src, t, b, v);
 }
 
 // One wavefront per sequence.  At node v with greedy token a, the lanes test rows
@@ -71,33 +52,35 @@ __global__ __launch_bounds__(64) void accept_kernel(TemplateDev t, const int32_t
     }
 }
 
+// Where a pass' K/V rows are and where the cache rows go.
+struct KvRows { uint4 *k_cache, *v_cache; const uint4 *k_tree, *v_tree; int batch, Hkv, smax, rows, row_u4; PageMap pm; };
+// cache[l][b][h][slot][j] <- tree[l][b][h][row][j], 16 bytes
+__device__ __forceinline__ void commit_granule(const KvRows &kv, int lh, int b, int row, int slot, int j) {
+    const int l = lh / kv.Hkv, h = lh - l * kv.Hkv;
+    const int64_t src = ((((int64_t)l * kv.batch + b) * kv.Hkv + h) * kv.rows + row) * kv.row_u4 + j;
+    int64_t dst = ((((int64_t)l * kv.batch + b) * kv.Hkv + h) * kv.smax + slot) * kv.row_u4 + j;
+    if (kv.pm.table) {                                  // page pools [L][n_pages][Hkv][page][hd]
+        const int page = min(max(kv.pm.table[(int64_t)b * kv.pm.max_pages + (slot >> kv.pm.page_lg)], 0), kv.pm.n_pages - 1);
+        dst = (((((int64_t)l * kv.pm.n_pages + page) * kv.Hkv + h) << kv.pm.page_lg) + (slot & ((1 << kv.pm.page_lg) - 1))) * kv.row_u4 + j;
+    }
+    const uint4 k = kv.k_tree[src], v = kv.v_tree[src];
+    kv.k_cache[dst] = k;
+    kv.v_cache[dst] = v;
+}
+
+#define COMMIT_THREADS 256
 // cache[l][b][h][ctx_len + i][:] <- tree[l][b][h][path[i]][:], 16 bytes per lane.
-// grid: (layer * kv-head, slot i, sequence).  ctx_len is advanced by a second tiny kernel so
+// grid: (layer * kv-head, rows of the path, sequence).  ctx_len is advanced by a second tiny kernel so
 // every workgroup of this one reads the old value.
-__global__ void compact_kv_kernel(uint4 *__restrict__ k_cache, uint4 *__restrict__ v_cache,
-                                  const uint4 *__restrict__ k_tree, const uint4 *__restrict__ v_tree,
-                                  const int32_t *__restrict__ path, int path_stride,
-                                  const int32_t *__restrict__ n_acc, const int32_t *__restrict__ ctx_len,
-                                  int batch, int Hkv, int smax, int rows, int row_u4, PageMap pm) {
-    const int lh = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
-    const int n = n_acc[b];
-    if (i >= n) return;
-    const int lc = ctx_len[b];
-    if (lc + n > smax) return;
+__global__ __launch_bounds__(COMMIT_THREADS) void compact_kv_kernel(KvRows kv, const int32_t *__restrict__ path, int path_stride,
+                                                                    const int32_t *__restrict__ n_acc, const int32_t *__restrict__ ctx_len) {
+    const int per_wg = COMMIT_THREADS / kv.row_u4, b = blockIdx.z;
+    const int i = blockIdx.y * per_wg + (int)threadIdx.x / kv.row_u4, j = threadIdx.x % kv.row_u4;
+    const int n = n_acc[b], lc = ctx_len[b];
+    if (i >= n || i >= path_stride || lc + n > kv.smax) return;
     const int src_row = path[(int64_t)b * path_stride + i];
-    if (src_row < 0 || src_row >= rows) return;
-    const int l = lh / Hkv, h = lh % Hkv;
-    const int64_t src = ((((int64_t)l * batch + b) * Hkv + h) * rows + src_row) * row_u4;
-    int64_t dst = ((((int64_t)l * batch + b) * Hkv + h) * smax + lc + i) * row_u4;
-    if (pm.table) {                                     // page pools [L][n_pages][Hkv][page][hd]
-        const int slot = lc + i;
-        const int page = min(max(pm.table[(int64_t)b * pm.max_pages + (slot >> pm.page_lg)], 0), pm.n_pages - 1);
-        dst = (((((int64_t)l * pm.n_pages + page) * Hkv + h) << pm.page_lg) + (slot & ((1 << pm.page_lg) - 1))) * row_u4;
-    }
-    for (int j = threadIdx.x; j < row_u4; j += blockDim.x) {
-        k_cache[dst + j] = k_tree[src + j];
-        v_cache[dst + j] = v_tree[src + j];
-    }
+    if (src_row < 0 || src_row >= kv.rows) return;
+    commit_granule(kv, blockIdx.x, b, src_row, lc + i, j);
 }
 __global__ void advance_ctx_kernel(const int32_t *__restrict__ n_acc, int32_t *__restrict__ ctx_len,
                                    int batch, int smax) {
@@ -105,18 +88,87 @@ __global__ void advance_ctx_kernel(const int32_t *__restrict__ n_acc, int32_t *_
     if (b < batch && ctx_len[b] + n_acc[b] <= smax) ctx_len[b] += n_acc[b];
 }
 
-extern "C" int bita_build_tree(const bita_tree_template *t, const int32_t *d_root_token,
-                               const int32_t *d_cand, int32_t cand_rows, int32_t kmax,
-                               const int32_t *d_group, const int32_t *d_shift, int32_t batch,
-                               int32_t *d_token, void *stream) {
+// Acceptance and commit in one launch (bita_decode_step): every workgroup walks the tree for itself, from copies in
+// LDS, and copies its share of the accepted rows; the first one of a sequence writes what the walk found and the
+// new length.  Nobody reads what another workgroup writes: the length comes from ctx_start, which the
+// first kernel of the step filled.  Three launches (acceptance walk, copies, lengths) and the first one's memory round
+// trip per level before.
+__global__ __launch_bounds__(COMMIT_THREADS) void accept_commit_kernel(TemplateDev t, const int32_t *__restrict__ token, const int32_t *__restrict__ argmax,
+                                                                       int32_t *__restrict__ path, int32_t *__restrict__ n_acc, int32_t *__restrict__ bonus,
+                                                                       int32_t *__restrict__ emitted, int32_t *__restrict__ next_group,
+                                                                       int32_t *__restrict__ next_shift, const int32_t *__restrict__ ctx_start,
+                                                                       int32_t *__restrict__ ctx_len, int n_lh, KvRows kv) {
+    __shared__ int32_t s_parent[BITA_MAX_ROWS], s_token[BITA_MAX_ROWS], s_argmax[BITA_MAX_ROWS], s_path[BITA_MAX_ROWS];
+    __shared__ int32_t s_len;
+    const int b = blockIdx.z, tid = threadIdx.x;
+    const int lc = ctx_start[b];
+    for (int i = tid; i < t.n_tree; i += COMMIT_THREADS) {
+        s_parent[i] = t.parent[i];
+        s_token[i] = token[(int64_t)b * t.rows + i];
+        s_argmax[i] = argmax[(int64_t)b * t.n_tree + i];
+    }
+    __syncthreads();
+    if (tid < 64) {
+        // as accept_kernel: the lowest active child of v that carries v's greedy token
+        int v = 0, len = 1;
+        if (tid == 0) s_path[0] = 0;
+        while (len <= t.depth_max) {
+            const int a = s_argmax[v];
+            int found = -1;
+            for (int base = v + 1; base < t.n_tree && found < 0; base += 64) {
+                const int c = base + tid;
+                const bool hit = c < t.n_tree && s_parent[c] == v && s_token[c] >= 0 && s_token[c] == a;
+                const unsigned long long m = __ballot(hit);
+                if (m) found = base + __ffsll((long long)m) - 1;
+            }
+            if (found < 0) break;
+            if (tid == 0) s_path[len] = found;
+            v = found;
+            len++;
+        }
+        if (tid == 0) s_len = len;
+    }
+    __syncthreads();
+    const int n = s_len, last = s_path[n - 1];
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        const int stride = t.depth_max + 1;
+        for (int i = tid; i < stride; i += COMMIT_THREADS) {
+            path[(int64_t)b * stride + i] = i < n ? s_path[i] : -1;
+            emitted[(int64_t)b * stride + i] = i < n ? s_argmax[s_path[i]] : -1;
+        }
+        if (tid == 0) {
+            n_acc[b] = n;
+            bonus[b] = s_argmax[last];
+            const int g = t.group_of_node[last];
+            if (next_group) next_group[b] = g >= 0 ? g : t.group_of_node[0];
+            if (next_shift) next_shift[b] = g >= 0 ? 0 : n - 1;
+            if (lc + n <= kv.smax) ctx_len[b] = lc + n;
+        }
+    }
+    const int per_wg = COMMIT_THREADS / kv.row_u4;
+    const int lh = blockIdx.x * per_wg + tid / kv.row_u4, j = tid % kv.row_u4;
+    if (lh >= n_lh || lc + n > kv.smax) return;
+    for (int i = blockIdx.y; i < n; i += gridDim.y) commit_granule(kv, lh, b, s_path[i], lc + i, j);
+}
+
+static int build_check(const bita_tree_template *t, const int32_t *d_root_token, const int32_t *d_cand, int32_t cand_rows, int32_t kmax,
+                       int32_t batch, const int32_t *d_token) {
     if (!t || !d_root_token || !d_token || batch <= 0)
         return bita_set_error(BITA_ERR_INVALID_ARG, "bita_build_tree: null argument or batch <= 0");
     if (t->dev.n_tree > 1 && (!d_cand || cand_rows <= 0 || kmax <= 0 || kmax > BITA_MAX_TOPK))
         return bita_set_error(BITA_ERR_INVALID_ARG,
                               "bita_build_tree: candidates needed, cand_rows > 0, 1 <= kmax <= %d",
                               BITA_MAX_TOPK);
-    hipLaunchKernelGGL(build_tree_kernel, dim3(batch), dim3(64), 0, (hipStream_t)stream, t->dev,
-                       d_root_token, d_cand, d_group, d_shift, cand_rows, kmax, d_token);
+    return BITA_OK;
+}
+
+extern "C" int bita_build_tree(const bita_tree_template *t, const int32_t *d_root_token,
+                               const int32_t *d_cand, int32_t cand_rows, int32_t kmax,
+                               const int32_t *d_group, const int32_t *d_shift, int32_t batch,
+                               int32_t *d_token, void *stream) {
+    if (int rc = build_check(t, d_root_token, d_cand, cand_rows, kmax, batch, d_token)) return rc;
+    const BuildSource src = {d_root_token, d_cand, d_group, d_shift, cand_rows, kmax, d_token, nullptr, nullptr};
+    hipLaunchKernelGGL(build_tree_kernel, dim3(batch), dim3(64), 0, (hipStream_t)stream, t->dev, src);
     BITA_HIP_CHECK(hipGetLastError());
     return BITA_OK;
 }
@@ -133,14 +185,54 @@ extern "C" int bita_accept(const bita_tree_template *t, const int32_t *d_token, 
     return BITA_OK;
 }
 
+static KvRows kv_rows(const bita_config &cfg, const bita_kv *kv, const PageMap &pm, int batch) {
+    return KvRows{(uint4 *)kv->k_cache, (uint4 *)kv->v_cache, (const uint4 *)kv->k_tree, (const uint4 *)kv->v_tree, batch,
+                  cfg.n_kv_heads, kv->smax, kv->rows, cfg.head_dim * 2 / 16, pm};
+}
 int compact_kv_launch(const bita_config &cfg, const bita_kv *kv, const PageMap &pm, const int32_t *d_path,
                       int path_stride, const int32_t *d_n_acc, int32_t *d_ctx_len, int batch, hipStream_t s) {
-    const int row_u4 = cfg.head_dim * 2 / 16;
-    dim3 grid(cfg.n_layers * cfg.n_kv_heads, path_stride, batch);
-    hipLaunchKernelGGL(compact_kv_kernel, grid, dim3(16), 0, s, (uint4 *)kv->k_cache, (uint4 *)kv->v_cache,
-                       (const uint4 *)kv->k_tree, (const uint4 *)kv->v_tree, d_path, path_stride, d_n_acc,
-                       d_ctx_len, batch, cfg.n_kv_heads, kv->smax, kv->rows, row_u4, pm);
+    const KvRows rows = kv_rows(cfg, kv, pm, batch);
+    const int per_wg = COMMIT_THREADS / rows.row_u4;
+    hipLaunchKernelGGL(compact_kv_kernel, dim3(cfg.n_layers * cfg.n_kv_heads, (path_stride + per_wg - 1) / per_wg, batch), dim3(COMMIT_THREADS),
+                       0, s, rows, d_path, path_stride, d_n_acc, d_ctx_len);
     hipLaunchKernelGGL(advance_ctx_kernel, dim3((batch + 63) / 64), dim3(64), 0, s, d_n_acc, d_ctx_len,
                        batch, kv->smax);
+    return BITA_OK;
+}
+
+// The four calls of a step with three launches less: the tokens are worked out by the first layer's norm, and
+// acceptance, copies and lengths are one kernel.  Each of the three cost its launch, 2.5 to 3.5 us whatever it did (four
+// calls / one, eager: two narrow layers, 12 rows 97 -> 83 us; two layers of 7B widths and the head, 68 rows 345 -> 336, one
+// row 244 -> 240; a layer of 13B widths and the head, 25 rows 202.6 -> 198.2).
+extern "C" int bita_decode_step(bita_model *m, const bita_kv *kv, const bita_tree_template *t, const int32_t *d_root_token,
+                                const int32_t *d_cand, int32_t cand_rows, int32_t cand_kmax, const int32_t *d_group, const int32_t *d_shift,
+                                int32_t *d_ctx_len, int32_t batch, void *d_workspace, size_t ws_bytes, int32_t kmax,
+                                const bita_step_out *out, void *stream) {
+    if (!out) return bita_set_error(BITA_ERR_INVALID_ARG, "bita_decode_step: null output descriptor");
+    if (int rc = build_check(t, d_root_token, d_cand, cand_rows, cand_kmax, batch, out->d_token)) return rc;
+    const bool outputs = out->d_argmax && out->d_path && out->d_n_acc && out->d_bonus && out->d_emitted;
+    const int stride = t->dev.depth_max + 1;
+    PageMap pm;
+    const bool commits = m && kv && d_ctx_len && outputs && kv->batch == batch && stride <= kv->rows && kv->ctx_hint >= 0 &&
+                         kv->ctx_hint <= kv->smax - stride && page_map_of(kv, kv->ctx_hint + stride, &pm, "bita_compact_kv") == BITA_OK;
+    if (!commits) {
+        // something of it will be refused: the calls before that one do their work, as they do one by one
+        if (int rc = bita_build_tree(t, d_root_token, d_cand, cand_rows, cand_kmax, d_group, d_shift, batch, out->d_token, stream)) return rc;
+        if (int rc = bita_verify_step(m, kv, t, out->d_token, d_ctx_len, batch, d_workspace, ws_bytes, kmax, out->d_argmax, out->d_topk_ids,
+                                      out->d_topk_val, out->d_logits, stream)) return rc;
+        if (int rc = bita_accept(t, out->d_token, out->d_argmax, batch, out->d_path, out->d_n_acc, out->d_bonus, out->d_emitted,
+                                 out->d_next_group, out->d_next_shift, stream)) return rc;
+        return bita_compact_kv(m, kv, out->d_path, stride, out->d_n_acc, d_ctx_len, batch, stream);
+    }
+    int32_t *ctx_start = nullptr;
+    const BuildSource build = {d_root_token, d_cand, d_group, d_shift, cand_rows, cand_kmax, out->d_token, d_ctx_len, nullptr};
+    if (int rc = verify_pass(m, kv, t, out->d_token, d_ctx_len, batch, d_workspace, ws_bytes, kmax, out->d_argmax, out->d_topk_ids,
+                             out->d_topk_val, out->d_logits, stream, nullptr, &build, &ctx_start)) return rc;
+    const KvRows rows = kv_rows(m->cfg, kv, pm, batch);
+    const int n_lh = m->cfg.n_layers * m->cfg.n_kv_heads, per_wg = COMMIT_THREADS / rows.row_u4;
+    hipLaunchKernelGGL(accept_commit_kernel, dim3((n_lh + per_wg - 1) / per_wg, stride < 4 ? stride : 4, batch), dim3(COMMIT_THREADS), 0,
+                       (hipStream_t)stream, t->dev, out->d_token, out->d_argmax, out->d_path, out->d_n_acc, out->d_bonus, out->d_emitted,
+                       out->d_next_group, out->d_next_shift, ctx_start, d_ctx_len, n_lh, rows);
+    BITA_HIP_CHECK(hipGetLastError());
     return BITA_OK;
 }
