@@ -696,38 +696,60 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
     // The passes begin at 6 m-tiles, but below 256 weight tiles at 8: a 16-tile workgroup is most of such
     // a matrix (96 x 256 x 688 10.5 us in the 8-tile form, 12.9; 96 x 1024 x 4096 13.5 and 14.8).
     int passes = m_tiles > (planes == 1 && NT >= 256 ? 5 : 7) ? (m_tiles + 4) / 5 : 1;
-    if (passes >= 2) p.variant = (NT >= 1024 && NT < 3000) ? 11 : 9;
+    // What a launch is estimated to take: the traffic through one CU's vector L1 (weights + activation slab of the
+    // workgroup's k range) times the number of rounds the workgroups take on the 256 CUs, plus the split-K
+    // partial sums.
+    auto estimate = [&](int mt, int n_pass, int tiles_wg, int *splits_out) {
+        const int64_t wgs_n = (NT + tiles_wg - 1) / tiles_wg;
+        int64_t sp = 256 / (wgs_n * n_pass);
+        if (sp > KS / 8) sp = KS / 8;
+        if (NT < 512 && sp > 8) sp = 8;
+        if (sp > 32) sp = 32;
+        if (g_force_splits > 0) sp = g_force_splits;
+        if (sp < 1) sp = 1;
+        const int64_t per = (KS + sp - 1) / sp;
+        sp = (KS + per - 1) / per;
+        const double per_wg = (double)(tiles_wg + planes * mt) * 1024.0 * (double)per;
+        const double rounds = (double)((wgs_n * n_pass * sp + 255) / 256);
+        double t = rounds * per_wg / 41e9;                              // ~17 B/clk through one CU's L1
+        if (sp > 1) t += 2.0 * (double)sp * m_rows * (double)n_rows * 4.0 / 4e12;
+        *splits_out = (int)sp;
+        return t;
+    };
+    // 14 waves (14 tiles per workgroup) put more workgroups on the CUs than 16 from 1024 to 2999 tiles, 5 to 10 % where both
+    // take as many rounds (22016 x 4096, 170 rows, 16 / 14 waves: 132 / 124 us; 272 rows 139 / 129), but a round more of
+    // them costs far more than that: 32000 x 4096, 150 rows 84 / 129 us, 300 rows 149 / 192, 440 rows 214 / 256; 27648 x 5120,
+    // 512 rows 260 / 308; 40960 x 2048, 240 rows 80 / 109; one plane 67 / 103, 119 / 148, 171 / 193, 202 / 228, 65 / 86.
+    // The estimate ranks the two right wherever they differ by more than 5 % (196 launches).
+    double t_five = 0.0;                                     // passes of 5 m-tiles (or the one pass of 6 or 7)
+    int sp_now = 1;
+    if (passes >= 2) {
+        p.variant = 9;
+        t_five = estimate(5, passes, 16, &sp_now);
+        if (NT >= 1024 && NT < 3000) {
+            int sp14 = 1;
+            const double t14 = estimate(5, passes, 14, &sp14);
+            if (t14 <= t_five || sp_now > 1) { p.variant = 11; t_five = t14; }   // (more splits than one: not measured, and more scratch)
+        }
+    } else {
+        t_five = estimate(m_tiles, 1, 8, &sp_now);
+    }
     p.mt_pass = 0;
     p.tall_tiles = 16;
-    // Tall passes (6 to 9 m-tiles per pass, variant 12): fewer passes over the weights and 16
-    // weight tiles per activation fragment, against fewer, fatter workgroups.  What decides is the
-    // traffic through one CU's vector L1 (weights + activation slab of the workgroup's k range) times
-    // the number of rounds the workgroups take on the 256 CUs, plus the split-K partial sums; the
-    // same estimate for both forms, the tall one taken where it predicts at least a fifth less
-    // (measured on the 7B-shaped matrices at 105 to 512 rows: the estimate ranks the forms right
-    // beyond that margin and the choice is then 12 to 36 % faster; inside it they are within 5 %).
+    // Tall passes (6 to 9 m-tiles per pass, variant 12): fewer passes over the weights and 16 weight tiles per
+    // activation fragment, against fewer, fatter workgroups.  The tall form is taken where the same estimate promises a
+    // fifth less than the others, or, with 10 us for what every launch costs besides, a seventh (what is less than that
+    // it does not resolve: 234 launches of 7B, 13B and 70B matrices at 84 to 512 rows; a fifth alone left these behind, before / now: 13B QKV, 272 rows 94 / 83 us, gate/up, 84 rows 70 / 65, 120
+    // rows 90 / 77, 400 rows 235 / 217; 7B down, 340 rows 73 / 69; 70B QKV, 204 rows 79 / 75).
     if (planes == 2 && m_tiles >= 6 && g_force_variant == -1) {
-        auto estimate = [&](int mt, int n_pass, int tiles_wg, int *splits_out) {
-            const int64_t wgs_n = (NT + tiles_wg - 1) / tiles_wg;
-            int64_t sp = 256 / (wgs_n * n_pass);
-            if (sp > KS / 8) sp = KS / 8;
-            if (NT < 512 && sp > 8) sp = 8;
-            if (sp > 32) sp = 32;
-            if (g_force_splits > 0) sp = g_force_splits;
-            if (sp < 1) sp = 1;
-            const int64_t per = (KS + sp - 1) / sp;
-            sp = (KS + per - 1) / per;
-            const double per_wg = (double)(tiles_wg + 2 * mt) * 1024.0 * (double)per;
-            const double rounds = (double)((wgs_n * n_pass * sp + 255) / 256);
-            double t = rounds * per_wg / 41e9;                              // ~17 B/clk through one CU's L1
-            if (sp > 1) t += 2.0 * (double)sp * m_rows * (double)n_rows * 4.0 / 4e12;
-            *splits_out = (int)sp;
-            return t;
-        };
-        int sp_now = 1;
-        const GemmVariant &vn = g_variants[m_tiles <= 7 ? 8 : p.variant];
-        const double t_now = estimate(m_tiles <= 7 ? m_tiles : 5, passes, vn.nw * vn.waves / vn.kgroups, &sp_now);
-        double t_best = 0.8 * t_now;
+        const double launch = 10e-6;
+        double t_ref = t_five;
+        // (a launch of 14-wave workgroups is what the tall forms were measured against where that is what the width
+        // suggests; they must also beat the 16-wave one)
+        if (passes >= 2 && NT >= 1024 && NT < 3000) t_ref = estimate(5, passes, 14, &sp_now);
+        const double fifth = 0.8 * t_ref, seventh = 0.86 * (t_ref + launch) - launch;
+        double t_best = fifth > seventh ? fifth : seventh;
+        if (t_best > 1.01 * t_five) t_best = 1.01 * t_five;
         // 16 or 12 weight tiles per workgroup: a launch whose 16-tile workgroups leave CUs idle (172 of
         // 256 at 272 rows of the 7B gate/up, 9 m-tiles) or take a nearly empty last round is cut finer
         // where the estimate falls by a twentieth (gate/up, K = 4096: 170 rows 77.5 -> 72.1 us,
@@ -739,9 +761,9 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
         // 96 243 -> 233, 105 260 -> 253, 112 261 -> 254, 120 267 -> 259, 128 271 -> 265, 134 300 -> 292,
         // 144 300 -> 294, four sequences of 68 454 -> 440).  Narrower workgroups were not built: at 12
         // tiles the activation reads already take five sixths of the LDS cycles that the multiplies last.
-        // More splits need more scratch: where they would not fit the static one of bita_gemm_noalloc the
-        // form is left out, so that it takes no shape away from that call (none of the 7B, 13B and 70B
-        // matrices up to 544 rows comes near).
+        // More splits need more scratch: where they would not fit the static one of bita_gemm_noalloc a form is
+        // left out, so that it takes no shape away from that call (none of the 7B, 13B and 70B matrices up to 544 rows
+        // comes near), but for 16-tile forms that promise a fifth, which never fitted.
         for (int cap = 9; cap >= 6; cap--) {
             const int n_pass = (m_tiles + cap - 1) / cap, mt = (m_tiles + n_pass - 1) / n_pass;
             if (mt < 6) continue;
@@ -750,7 +772,7 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
                 // (small matrices, fewer than half the CUs at 16 tiles, are latency: the shorter epilogue wins)
                 if (tiles == 12 && (NT + 15) / 16 * n_pass * sp < 128) continue;
                 const double t = estimate(mt, n_pass, tiles, &sp);
-                if (tiles == 12 && sp > 1 &&
+                if (sp > 1 && (tiles == 12 || t > fifth) &&
                     (((size_t)sp * m_rows * n_rows * 4 + 255) & ~(size_t)255) + frag_bytes(m_rows, k) > BITA_NOALLOC_SCRATCH_BYTES)
                     continue;
                 if (t < (tiles == 12 && p.mt_pass ? 0.95 : 1.0) * t_best) { t_best = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; p.tall_tiles = tiles; }

@@ -36,3 +36,20 @@ def test_one_plane_is_planned_for_the_passes_it_runs(m, n, k, splits):
         part = (plan["splits"] * m * n * 4 + 255) // 256 * 256 if plan["splits"] > 1 else 0
         assert L.bita_gemm_noalloc_scratch_bytes(m, n, k) >= part + frag
     assert L.bita_gemm_plan_detail(m, n, k, 3, out4) == -1
+
+
+@pytest.mark.parametrize("m,n,k", [(150, 32000, 4096), (300, 32000, 5120), (440, 32000, 4096), (512, 27648, 5120), (240, 40960, 2048),
+                                   (136, 16384, 17000), (160, 16384, 40000)])
+@pytest.mark.parametrize("planes", [1, 2])
+def test_passes_of_five_take_the_fewer_rounds(m, n, k, planes):
+    """Many rows of 1024 to 2999 tiles: 16 waves per workgroup where 14 would take a round more on the 256 CUs, unless
+    that means k splits, which the static scratch would have to hold."""
+    from paper_2401_12522_amd import binding as B
+    _lib()
+    plan = B.gemm_plan_info(m, n, k, planes)
+    passes, tiles = ((m + 15) // 16 + 4) // 5, n // 16
+    rounds = {t: -(-(-(-tiles // t) * passes) // 256) for t in (14, 16)}
+    splits = 256 // (-(-tiles // 16) * passes)
+    if plan["mt_pass"] == 0:
+        assert plan["variant"] == (11 if splits > 1 or rounds[14] * (14 + 5 * planes) <= rounds[16] * (16 + 5 * planes) else 9), plan
+        assert plan["splits"] == 1
