@@ -1,5 +1,5 @@
-"""Tree attention (GPU) where several query heads of a K/V head share a tile of 16 queries: every number of heads per
-K/V head that shares tiles differently, at row counts around a tile's rows, with few workgroups and with many, and
+"""Tree attention (GPU) where several query heads of a K/V head share a tile of 16 queries, and where none do: every number
+of heads per K/V head that shares tiles differently, at row counts around a tile's rows, with few workgroups and with many, and
 with the keys split between workgroups."""
 import math
 
@@ -12,7 +12,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("heads,kv_heads,hd", [(4, 2, 64), (8, 2, 64), (6, 1, 128), (8, 2, 128), (8, 1, 128), (24, 2, 64), (12, 1, 128), (16, 1, 128),
+@pytest.mark.parametrize("heads,kv_heads,hd", [(4, 4, 64), (4, 4, 128), (4, 2, 64), (8, 2, 64), (6, 1, 128), (8, 2, 128), (8, 1, 128), (24, 2, 64), (12, 1, 128), (16, 1, 128),
                                                (32, 1, 64)])
 @pytest.mark.parametrize("rows,batch,longest", [(1, 1, 2100), (2, 2, 40), (3, 70, 33), (5, 3, 300), (17, 2, 64), (33, 40, 31)])
 def test_heads_that_share_a_tile(heads, kv_heads, hd, rows, batch, longest):
