@@ -192,9 +192,15 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
     // A tile's 16 query lanes are 2^lg_rows rows of 2^lg_ht heads (one head per workgroup: 16 rows of it); the
     // workgroup's second tile has the same rows of the next heads.
-    const int n_mt = n_mt_lg & 0xFFFF, lg_ht = U > 1 ? n_mt_lg >> 16 : 0, lg_rows = 4 - lg_ht;
-    const int qh = w_in / n_mt, mt = n_mt - 1 - (w_in - qh * n_mt);          // long m-tiles first
+    const int n_mt = n_mt_lg & 0xFFFF, lg_ht = U > 1 ? (n_mt_lg >> 16) & 0xFF : 0, lg_rows = 4 - lg_ht;
+    const int qh = w_in / n_mt;
+    int mt = n_mt - 1 - (w_in - qh * n_mt);                                  // long m-tiles first
     const int b = group / Hkv, kvh = group - b * Hkv;
+    // One row per sequence is asked for (bit 24, known without a load, so that other launches do not wait for one): only
+    // its row tile is launched.  A prefill's last layer, 488 rows on 512, 32 heads: 27.7 -> 17.9 us, the other tiles'
+    // workgroups leaving behind their first chunk before.  (Two tiles per workgroup have no registers for it: a spill, 1 %
+    // of every launch.  They leave below.)
+    if (U == 1 && (n_mt_lg >> 24)) mt = min(max(only_row[b], 0), R - 1) >> lg_rows;
     const int h0 = kvh * qpk + (U > 1 ? qh << (1 + lg_ht) : qh);                // the workgroup's first head
 
     int Lc = ctx_len[b];
@@ -552,7 +558,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     att_wait<0>();                                      // the first chunk and the prologue's loads have landed
     // (looked at here, where the prologue's loads have landed anyway: ahead of them it cost 0.5 % of
     // every launch; the whole workgroup leaves together)
-    if (only_row && (min(max(only_row[b], 0), R - 1) >> lg_rows) != mt) return;
+    if (U > 1 && only_row && (min(max(only_row[b], 0), R - 1) >> lg_rows) != mt) return;
     // a tree row without a candidate (negative token) is absent from the pass: its output is zero
     int row_flags = (row_ok && mask_byte ? 1 : 0) | (row_ok && (mask_byte || tok_val >= 0) ? 2 : 0);
     asm volatile("" : "+v"(row_flags));                 // (looked at here, not inside the loop)
@@ -726,12 +732,12 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
         attr_set = true;
     }
     const size_t smem_bytes = C::SMEM + (PAGED ? (size_t)((pm.tbl_cap + 3) / 4) * 16 : 0);
-    const int per_wg = 16 >> lg_ht, n_mt = (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
+    const int per_wg = 16 >> lg_ht, n_mt = U == 1 && only_row ? 1 : (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     const int groups = batch * Hkv, per_group = (Hq / Hkv / U >> lg_ht) * n_mt * p.splits;
     const dim3 grid(8 * per_group, (groups + 7) / 8);
     hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, PAGED>), grid, dim3(W * 64), smem_bytes, s,
-                       ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16, p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
+                       ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16 | (U == 1 && only_row ? 1 << 24 : 0), p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
                        (const uint16_t *)k_cache, (const uint16_t *)v_cache,
                        (const uint16_t *)k_tree, (const uint16_t *)v_tree, (const uint16_t *)k_tree_lo,
                        (const uint16_t *)v_tree_lo, (const uint16_t *)prompt_k, (const uint16_t *)prompt_v, token,
@@ -763,7 +769,7 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
     // 159.5 / 136.3 us, 3 of 300 26.3 / 19.8; 32 heads, 2 of 800 22.5 / 17.9, 4 of 700 to 1400 35.4 / 30.6, 8 of 2000
     // 111 / 94.5, 170 rows on 1024 25.1 / 21.8, 488 rows on 512 50.8 / 43.8; but one sequence, 136 and 160 workgroups:
     // 64/8 heads 28.3 / 33.2, 32 heads 13.0 / 15.5).  Where one row per sequence is asked for, one row tile of each
-    // has work, the others leave.
+    // has work.
     const int rows_wg = 16 >> lg_ht, n_mt = only_row ? 1 : (t.rows + rows_wg - 1) / rows_wg;
     const bool four = (int64_t)batch * (pair ? Hq >> (1 + lg_ht) : Hq) * n_mt * p.splits > 256;
 #define ATT_LAUNCH_P(HD_, U_, W_, PG_) launch_attn_t<HD_, U_, W_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
