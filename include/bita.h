@@ -214,8 +214,8 @@ int bita_compact_kv(const bita_model *m, const bita_kv *kv, const int32_t *d_pat
 /* The four calls above as one, for a loop that has nothing to do between them: the same results in
  * the same buffers, in three launches less.  Arguments as theirs (cand_rows, cand_kmax: the extents of d_cand; kmax:
  * of the top-k outputs; the path's row length is the template's depth + 1); the outputs may be the inputs of
- * the next step, or of this one.  What one of the four would refuse is refused with its message, after the calls
- * before it have done their work. */
+ * the next step, or, d_token excepted, of this one.  What one of the four would refuse is refused with its message, after
+ * the calls before it have done their work. */
 typedef struct bita_step_out {
     int32_t *d_token, *d_argmax, *d_topk_ids;
     float *d_topk_val, *d_logits;

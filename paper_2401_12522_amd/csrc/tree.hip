@@ -162,13 +162,16 @@ static int build_check(const bita_tree_template *t, const int32_t *d_root_token,
     return BITA_OK;
 }
 
+static void launch_build_tree(const TemplateDev &t, const BuildSource &src, int batch, hipStream_t s) {
+    hipLaunchKernelGGL(build_tree_kernel, dim3(batch), dim3(64), 0, s, t, src);
+}
 extern "C" int bita_build_tree(const bita_tree_template *t, const int32_t *d_root_token,
                                const int32_t *d_cand, int32_t cand_rows, int32_t kmax,
                                const int32_t *d_group, const int32_t *d_shift, int32_t batch,
                                int32_t *d_token, void *stream) {
     if (int rc = build_check(t, d_root_token, d_cand, cand_rows, kmax, batch, d_token)) return rc;
     const BuildSource src = {d_root_token, d_cand, d_group, d_shift, cand_rows, kmax, d_token, nullptr, nullptr};
-    hipLaunchKernelGGL(build_tree_kernel, dim3(batch), dim3(64), 0, (hipStream_t)stream, t->dev, src);
+    launch_build_tree(t->dev, src, batch, (hipStream_t)stream);
     BITA_HIP_CHECK(hipGetLastError());
     return BITA_OK;
 }
@@ -227,7 +230,12 @@ extern "C" int bita_decode_step(bita_model *m, const bita_kv *kv, const bita_tre
     int32_t *ctx_start = nullptr;
     const BuildSource build = {d_root_token, d_cand, d_group, d_shift, cand_rows, cand_kmax, out->d_token, d_ctx_len, nullptr};
     if (int rc = verify_pass(m, kv, t, out->d_token, d_ctx_len, batch, d_workspace, ws_bytes, kmax, out->d_argmax, out->d_topk_ids,
-                             out->d_topk_val, out->d_logits, stream, nullptr, &build, &ctx_start)) return rc;
+                             out->d_topk_val, out->d_logits, stream, nullptr, &build, &ctx_start)) {
+        // refused ahead of its first kernel, which would have written the tokens: bita_build_tree had nothing against them
+        launch_build_tree(t->dev, build, batch, (hipStream_t)stream);
+        (void)hipGetLastError();
+        return rc;
+    }
     const KvRows rows = kv_rows(m->cfg, kv, pm, batch);
     const int n_lh = m->cfg.n_layers * m->cfg.n_kv_heads, per_wg = COMMIT_THREADS / rows.row_u4;
     hipLaunchKernelGGL(accept_commit_kernel, dim3((n_lh + per_wg - 1) / per_wg, stride < 4 ? stride : 4, batch), dim3(COMMIT_THREADS), 0,

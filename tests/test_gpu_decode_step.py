@@ -114,6 +114,37 @@ def test_a_full_cache_refuses_the_commit_alone():
         assert int(got[0][1].ctx_len[0]) == 30 + (0 if refused else int(got[0][0].n_acc[0]))
 
 
+@pytest.mark.parametrize("fault", ["workspace", "kmax", "position", "scratch rows"])
+def test_what_the_pass_refuses_leaves_the_tokens_built(fault):
+    """The pass refuses where the commit would not: the tokens are there all the same, nothing else is touched, and the
+    message is the pass' own."""
+    import paper_2401_12522_amd as bita
+    cfg = synth.get_config("tiny_gqa")
+    t = synth.attach_mask_groups(synth.random_tree(8, 3, 0), [0], cfg.n_mask)
+    tmpl = bita.TreeTemplate(t.parent, t.is_mask, t.n_tree, cfg.n_mask)
+    model = bita.Model(cfg, synth.SynthWeights(cfg, seed=3), max_pos=34 if fault == "position" else 200)
+    rng = np.random.default_rng(1)
+    root, cand = dev_i32(rng.integers(0, cfg.vocab, 2)), dev_i32(rng.integers(0, cfg.vocab, (2, cfg.n_mask, 4)))
+    got = []
+    for step in (lambda *a: bita.decode_step(*a, root, cand), lambda *a: _four(bita, *a, root, cand, None, None)):
+        kv = bita.KVState(cfg, cfg.n_layers, 2, 64, tmpl.rows + (fault == "scratch rows"))
+        kv.ctx_len.fill_(30)
+        buf = bita.StepBuffers(model, tmpl, 2, 4, want_logits=True)
+        for n in OUTPUTS:
+            getattr(buf, n).fill_(-7)
+        if fault == "workspace":
+            buf.workspace = buf.workspace[:1024]
+        if fault == "kmax":
+            buf.kmax = 99
+        with pytest.raises(bita.BitaError, match="bita_verify_step"):
+            step(model, kv, 30, tmpl, buf, 2)
+        torch.cuda.synchronize()
+        got.append((buf, kv))
+    _same(got[0][0], got[1][0], OUTPUTS)
+    _same(got[0][1], got[1][1], ("ctx_len", "k_cache", "v_cache"))
+    assert got[0][0].token[:, 0].tolist() == root.tolist() and int(got[0][0].n_acc[0]) == -7
+
+
 def test_outputs_of_a_step_feed_the_next_in_a_graph():
     import paper_2401_12522_amd as bita
     cfg = synth.get_config("tiny_gqa")
