@@ -245,7 +245,7 @@ static void timed_gemm(const void *a_frag, int M, int64_t K, const void *w, int6
 
 // ------------------------------------------------------------------------------------------
 struct WsLayout {
-    size_t x, h, q, attn_out, act, partial, part_o, part_ml, logits, ssq, kv_lo, ctx_start, total;
+    size_t x, h, q, attn_out, act, partial, part_o, part_ml, logits, ssq, kv_lo, total;
     size_t partial_bytes;
 };
 #define ATTN_MAX_SPLITS 32
@@ -277,7 +277,6 @@ static WsLayout ws_layout(const bita_config &c, int batch, int rows) {
     L.logits = take(M * c.vocab * 4);
     L.ssq = take(M * RMS_MAX_CHUNKS * 4);
     L.kv_lo = take(2 * M * c.n_kv_heads * c.head_dim * 2);   // low planes of one layer's pass-row K and V
-    L.ctx_start = take((size_t)batch * 4);
     L.total = off;
     return L;
 }
@@ -390,11 +389,7 @@ int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, c
         }
     };
 
-    BuildSource source = {};
-    if (build) {
-        source = *build;
-        source.ctx_start = *ctx_start = (int32_t *)(ws + L.ctx_start);
-    }
+    const BuildSource source = build ? *build : BuildSource{};
     int pending = 0;                                    // split-K partials waiting to be added to x
     for (int l = 0; l < c.n_layers; l++) {
         if (l == 0) launch_embed_prep(d_token, source, td, batch, m->tok_emb, m->mask_emb, d, c.vocab, m->attn_norm[0], x, h, ssq, s);
@@ -432,7 +427,10 @@ int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, c
         return BITA_OK;
     }
     head(M, pending, x, h, partial, ssq, logits, p_lm);
-    launch_select(logits, batch, td, c.vocab, kmax, d_argmax, n_sel_mask > 0 ? d_topk_ids : nullptr, d_topk_val, s);
+    // (the residual stream is done with once the final norm has read it: its memory holds the lengths)
+    if (build) *ctx_start = (int32_t *)x;
+    launch_select(logits, batch, td, c.vocab, kmax, d_argmax, n_sel_mask > 0 ? d_topk_ids : nullptr, d_topk_val, s, d_ctx_len,
+                  build ? *ctx_start : nullptr);
     BITA_HIP_CHECK(hipGetLastError());
     return BITA_OK;
 }

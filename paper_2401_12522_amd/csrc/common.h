@@ -165,9 +165,8 @@ void launch_pack(const void *src, int64_t n_rows, int64_t k, void *dst, int64_t 
 
 // Where the first layer's norm takes its rows from (see rmsnorm_prep_kernel).
 // A whole step (bita_decode_step) has the first layer's norm work out the rows' tokens itself, from what
-// bita_build_tree takes (root == nullptr: they are in `token` already), and leave every sequence's length
-// at the start of the step in ctx_start.
-struct BuildSource { const int32_t *root, *cand, *group, *shift; int cand_rows, kmax; int32_t *token; const int32_t *ctx_len; int32_t *ctx_start; };
+// bita_build_tree takes (root == nullptr: they are in `token` already).
+struct BuildSource { const int32_t *root, *cand, *group, *shift; int cand_rows, kmax; int32_t *token; };
 struct EmbedSource { const int32_t *token; const uint8_t *is_mask; const int32_t *mask_index; const uint16_t *tok_emb, *mask_emb; int rows, vocab; };
 // x = embeddings of the pass' rows, and the first norm's slab and sums of squares
 void launch_embed_prep(const int32_t *token, const BuildSource &build, const TemplateDev &t, int batch, const void *tok_emb, const void *mask_emb, int d,
@@ -185,8 +184,10 @@ void launch_qkv_rope(const float *partial, int splits, int batch, const Template
                      const RowScale &rs, hipStream_t s);
 void launch_silu_mul(const float *partial, int splits, int m_rows, int d_ffn, void *act_frag,
                      const RowScale &rs, hipStream_t s);
+// ctx_start: where a step that goes on to change the lengths has them copied to (nullptr: nowhere)
 void launch_select(const float *logits, int batch, const TemplateDev &t, int vocab, int kmax,
-                   int32_t *argmax, int32_t *topk_ids, float *topk_val, hipStream_t s);
+                   int32_t *argmax, int32_t *topk_ids, float *topk_val, hipStream_t s,
+                   const int32_t *ctx_len = nullptr, int32_t *ctx_start = nullptr);
 
 // Where the cache rows live: contiguous per sequence (table == nullptr) or in pages of
 // 1 << page_lg key slots, page ids per sequence in table[b][0 .. max_pages).  tbl_cap: table

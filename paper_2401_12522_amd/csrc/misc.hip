@@ -65,10 +65,7 @@ __global__ __launch_bounds__(256) void rmsnorm_prep_kernel(float *__restrict__ x
             int tok;
             if (build.root) {
                 tok = tree_token(build, t, b, r);
-                if (c == 0) {
-                    build.token[row] = tok;
-                    if (r == 0) build.ctx_start[b] = build.ctx_len[b];
-                }
+                if (c == 0) build.token[row] = tok;
             } else {
                 tok = e.token[row];
             }
@@ -292,12 +289,15 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k)
 __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const float *__restrict__ logits, TemplateDev t,
                                                                 int vocab, int kmax, int32_t *__restrict__ argmax,
                                                                 int32_t *__restrict__ topk_ids,
-                                                                float *__restrict__ topk_val) {
+                                                                float *__restrict__ topk_val,
+                                                                const int32_t *__restrict__ ctx_len,
+                                                                int32_t *__restrict__ ctx_start) {
     constexpr int NW = SELECT_THREADS / 64;
     __shared__ unsigned long long sk[2][NW];          // wave results, in turn: one barrier per winner
     const int b = blockIdx.y, wave = threadIdx.x >> 6;
     // mask rows (k winners) are dealt out first: theirs are the long workgroups
     const int n_mask_sel = gridDim.x - t.n_tree;
+    if (ctx_start && blockIdx.x == 0 && threadIdx.x == 0) ctx_start[b] = ctx_len[b];     // (see launch_select)
     const int sel = (int)blockIdx.x < n_mask_sel ? t.n_tree + blockIdx.x : blockIdx.x - n_mask_sel;   // 0..T-1 tree rows, then G*n mask rows
     const bool is_tree = sel < t.n_tree;
     const int r = is_tree ? sel : t.mask_rows[sel - t.n_tree];
@@ -414,8 +414,8 @@ void launch_silu_mul(const float *partial, int splits, int M, int F, void *act_f
                        (uint16_t *)act_frag, rs);
 }
 void launch_select(const float *logits, int batch, const TemplateDev &t, int vocab, int kmax,
-                   int32_t *argmax, int32_t *topk_ids, float *topk_val, hipStream_t s) {
+                   int32_t *argmax, int32_t *topk_ids, float *topk_val, hipStream_t s, const int32_t *ctx_len, int32_t *ctx_start) {
     const int n_sel = t.n_tree + (topk_ids ? t.n_groups * t.n_mask : 0);
     hipLaunchKernelGGL(select_kernel, dim3(n_sel, batch), dim3(SELECT_THREADS), 0, s, logits, t, vocab, kmax,
-                       argmax, topk_ids, topk_val);
+                       argmax, topk_ids, topk_val, ctx_len, ctx_start);
 }

@@ -91,7 +91,7 @@ __global__ void advance_ctx_kernel(const int32_t *__restrict__ n_acc, int32_t *_
 // Acceptance and commit in one launch (bita_decode_step): every workgroup walks the tree for itself, from copies in
 // LDS, and copies its share of the accepted rows; the first one of a sequence writes what the walk found and the
 // new length.  Nobody reads what another workgroup writes: the length comes from ctx_start, which the
-// first kernel of the step filled.  Three launches (acceptance walk, copies, lengths) and the first one's memory round
+// selection filled.  Three launches (acceptance walk, copies, lengths) and the first one's memory round
 // trip per level before.
 __global__ __launch_bounds__(COMMIT_THREADS) void accept_commit_kernel(TemplateDev t, const int32_t *__restrict__ token, const int32_t *__restrict__ argmax,
                                                                        int32_t *__restrict__ path, int32_t *__restrict__ n_acc, int32_t *__restrict__ bonus,
@@ -170,7 +170,7 @@ extern "C" int bita_build_tree(const bita_tree_template *t, const int32_t *d_roo
                                const int32_t *d_group, const int32_t *d_shift, int32_t batch,
                                int32_t *d_token, void *stream) {
     if (int rc = build_check(t, d_root_token, d_cand, cand_rows, kmax, batch, d_token)) return rc;
-    const BuildSource src = {d_root_token, d_cand, d_group, d_shift, cand_rows, kmax, d_token, nullptr, nullptr};
+    const BuildSource src = {d_root_token, d_cand, d_group, d_shift, cand_rows, kmax, d_token};
     launch_build_tree(t->dev, src, batch, (hipStream_t)stream);
     BITA_HIP_CHECK(hipGetLastError());
     return BITA_OK;
@@ -228,7 +228,7 @@ extern "C" int bita_decode_step(bita_model *m, const bita_kv *kv, const bita_tre
         return bita_compact_kv(m, kv, out->d_path, stride, out->d_n_acc, d_ctx_len, batch, stream);
     }
     int32_t *ctx_start = nullptr;
-    const BuildSource build = {d_root_token, d_cand, d_group, d_shift, cand_rows, cand_kmax, out->d_token, d_ctx_len, nullptr};
+    const BuildSource build = {d_root_token, d_cand, d_group, d_shift, cand_rows, cand_kmax, out->d_token};
     if (int rc = verify_pass(m, kv, t, out->d_token, d_ctx_len, batch, d_workspace, ws_bytes, kmax, out->d_argmax, out->d_topk_ids,
                              out->d_topk_val, out->d_logits, stream, nullptr, &build, &ctx_start)) {
         // refused ahead of its first kernel, which would have written the tokens: bita_build_tree had nothing against them

@@ -10,6 +10,8 @@ from gpu_util import dev_i32
 
 pytestmark = pytest.mark.gpu
 OUTPUTS = ("token", "argmax", "topk_ids", "topk_val", "logits", "path", "n_acc", "bonus", "emitted", "next_group", "next_shift")
+# model, sequences, rows; bytes for a pass of so many rows, and for a prefill in chunks of as many
+WORKSPACES = [("tiny", 1, 12, 636160, 762112), ("tiny_gqa", 3, 20, 3072256, 3289600), ("tiny", 2, 1, 171008, 343296)]
 
 
 def _four(bita, model, kv, hint, tmpl, buf, B, root, cand, group, shift):
@@ -143,6 +145,35 @@ def test_what_the_pass_refuses_leaves_the_tokens_built(fault):
     _same(got[0][0], got[1][0], OUTPUTS)
     _same(got[0][1], got[1][1], ("ctx_len", "k_cache", "v_cache"))
     assert got[0][0].token[:, 0].tolist() == root.tolist() and int(got[0][0].n_acc[0]) == -7
+
+
+@pytest.mark.parametrize("cfg_name,batch,rows,step_bytes,prefill_bytes", WORKSPACES)
+def test_a_step_needs_the_pass_workspace_and_no_more(cfg_name, batch, rows, step_bytes, prefill_bytes):
+    """Workspaces laid out for the pass alone hold the whole step: their sizes are what they were before there was a
+    call for it, and nothing is written behind them."""
+    import paper_2401_12522_amd as bita
+    from paper_2401_12522_amd import binding as L
+    cfg = synth.get_config(cfg_name)
+    model = bita.Model(cfg, synth.SynthWeights(cfg, seed=3), max_pos=200)
+    assert model.workspace_bytes(batch, rows) == step_bytes
+    assert L.lib().bita_prefill_workspace_bytes(model.handle, batch, rows) == prefill_bytes
+    parent = synth.random_tree(rows, 3, 0)
+    tmpl = bita.TreeTemplate(parent, np.zeros(rows, np.uint8), rows, cfg.n_mask)
+    rng = np.random.default_rng(rows)
+    root, cand = dev_i32(rng.integers(0, cfg.vocab, batch)), dev_i32(rng.integers(0, cfg.vocab, (batch, cfg.n_mask, 4)))
+    got = []
+    for step in (lambda *a: bita.decode_step(*a, root, cand), lambda *a: _four(bita, *a, root, cand, None, None)):
+        kv = bita.KVState(cfg, cfg.n_layers, batch, 100, rows)
+        kv.ctx_len.copy_(dev_i32(np.arange(batch) * 9 + 5))
+        buf = bita.StepBuffers(model, tmpl, batch, 4, want_logits=True)
+        memory = torch.full((step_bytes + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        buf.workspace = memory[:step_bytes]
+        step(model, kv, int(kv.ctx_len.max()), tmpl, buf, batch)
+        torch.cuda.synchronize()
+        assert bool((memory[step_bytes:] == 0x5A).all())
+        got.append((buf, kv))
+    _same(got[0][0], got[1][0], [n for n in OUTPUTS if not n.startswith("topk")])
+    _same(got[0][1], got[1][1], ("ctx_len", "k_cache", "v_cache"))
 
 
 def test_outputs_of_a_step_feed_the_next_in_a_graph():
