@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #define ATT_CHUNK 32            // key slots per chunk
+#define ATT_GRID_Y_LG 15        // log2 of the grid's y extent where the K/V heads are more (65535 at most are launched)
 
 // one all-zero K/V row (head dim <= 128): padding slots read it like any other row
 static __device__ uint4 g_att_zero_row[16] = {};
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, and known to be
     // ---- workgroup id -> (kv group, query head of the group, m-tile, split), kv groups dealt
     //      round-robin to the XCDs (grid x runs over the XCDs first)
-    const int group = (blockIdx.x & 7) + 8 * blockIdx.y;     // (sequence, kv head)
+    const int group = (blockIdx.x & 7) + 8 * (blockIdx.y + (blockIdx.z << ATT_GRID_Y_LG));     // (sequence, kv head)
     if (group >= batch * Hkv) return;
     int w_in = blockIdx.x >> 3, split = 0;
     if (n_splits > 1) {                                      // (each integer division is 25 scalar instructions)
@@ -735,7 +736,8 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
     const int per_wg = 16 >> lg_ht, n_mt = U == 1 && only_row ? 1 : (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     const int groups = batch * Hkv, per_group = (Hq / Hkv / U >> lg_ht) * n_mt * p.splits;
-    const dim3 grid(8 * per_group, (groups + 7) / 8);
+    const int per_xcd = (groups + 7) / 8, grid_y = per_xcd < 1 << ATT_GRID_Y_LG ? per_xcd : 1 << ATT_GRID_Y_LG;
+    const dim3 grid(8 * per_group, grid_y, (per_xcd + grid_y - 1) / grid_y);
     hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, PAGED>), grid, dim3(W * 64), smem_bytes, s,
                        ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16 | (U == 1 && only_row ? 1 << 24 : 0), p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
                        (const uint16_t *)k_cache, (const uint16_t *)v_cache,
