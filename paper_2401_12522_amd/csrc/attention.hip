@@ -716,6 +716,34 @@ AttnPlan attn_plan(int batch, int rows, int n_heads, int hd, int ctx_hint, int n
     return p;
 }
 
+// How a launch is cut into workgroups, from nothing but its sizes.
+AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, const AttnPlan &p, bool one_row) {
+    // Grouped-query models: a workgroup's two tiles of 16 queries share its chunk loads.  The tiles take as many heads
+    // of the K/V head's group as a power of two divides evenly, and so fewer rows: eight heads of 4 rows for 64/8 heads,
+    // 17 workgroups per K/V head for the 68 rows of a 64-node tree where pairs of heads with 16 rows each took 20
+    // (three of their four tiles over the last 16 rows held 4), a finer grain for the CUs, and fewer keys masked away at
+    // a row tile's end.  Pairs of heads / this, us: 68 rows, 8 sequences of 1024 to 4096 keys 157.0 / 136.3, 2 of 1000
+    // 28.4 / 27.1, one of 2048 29.6 / 28.3; 170 rows on 1024 34.1 / 29.6, 512 rows on 512 74.3 / 63.7, 25 rows, 4 of
+    // 2000 28.9 / 26.6, one row 14.2 / 14.0: never slower.
+    const int qpk = Hq / Hkv;
+    AttnTiles a;
+    a.tiles = qpk % 2 == 0 ? 2 : 1;
+    a.lg_ht = 0;
+    while (a.tiles == 2 && a.lg_ht < 3 && qpk % (4 << a.lg_ht) == 0) a.lg_ht++;
+    // Eight waves walk one workgroup's keys, or four: with four a CU holds two workgroups, one in its loop while the
+    // other is in its prologue or merge (6 us of a workgroup's time together), and the merge is half as wide.
+    // Four where the workgroups are more than the CUs, eight where each has a CU to itself and fewer waves would
+    // only make its walk longer (eight / four, 68 rows unless stated: 64/8 heads, 8 sequences of 1024 to 4096 keys
+    // 159.5 / 136.3 us, 3 of 300 26.3 / 19.8; 32 heads, 2 of 800 22.5 / 17.9, 4 of 700 to 1400 35.4 / 30.6, 8 of 2000
+    // 111 / 94.5, 170 rows on 1024 25.1 / 21.8, 488 rows on 512 50.8 / 43.8; but one sequence, 136 and 160 workgroups:
+    // 64/8 heads 28.3 / 33.2, 32 heads 13.0 / 15.5).  Where one row per sequence is asked for, one row tile of each
+    // has work.
+    const int rows_wg = 16 >> a.lg_ht, n_mt = one_row ? 1 : (rows + rows_wg - 1) / rows_wg;
+    a.workgroups = (int64_t)batch * (a.tiles == 2 ? Hq >> (1 + a.lg_ht) : Hq) * n_mt * p.splits;
+    a.waves = a.workgroups > 256 ? 4 : 8;
+    return a;
+}
+
 // lg_ht: log2 of the heads that share a tile (two heads per workgroup and more)
 template <int HD, int U, int W, bool PAGED>
 static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo, const void *k_cache, const void *v_cache,
@@ -753,36 +781,16 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            const void *prompt_v, const int32_t *ctx_len, const int32_t *token, int batch, int Hq, int Hkv, int hd,
                            int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
                            void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s, const int32_t *only_row) {
-    // Grouped-query models: a workgroup's two tiles of 16 queries share its chunk loads.  The tiles take as many heads
-    // of the K/V head's group as a power of two divides evenly, and so fewer rows: eight heads of 4 rows for 64/8 heads,
-    // 17 workgroups per K/V head for the 68 rows of a 64-node tree where pairs of heads with 16 rows each took 20
-    // (three of their four tiles over the last 16 rows held 4), a finer grain for the CUs, and fewer keys masked away at
-    // a row tile's end.  Pairs of heads / this, us: 68 rows, 8 sequences of 1024 to 4096 keys 157.0 / 136.3, 2 of 1000
-    // 28.4 / 27.1, one of 2048 29.6 / 28.3; 170 rows on 1024 34.1 / 29.6, 512 rows on 512 74.3 / 63.7, 25 rows, 4 of
-    // 2000 28.9 / 26.6, one row 14.2 / 14.0: never slower.
-    const int qpk = Hq / Hkv;
-    const bool pair = qpk % 2 == 0;
-    int lg_ht = 0;
-    while (pair && lg_ht < 3 && qpk % (4 << lg_ht) == 0) lg_ht++;
-    // Eight waves walk one workgroup's keys, or four: with four a CU holds two workgroups, one in its loop while the
-    // other is in its prologue or merge (6 us of a workgroup's time together), and the merge is half as wide.
-    // Four where the workgroups are more than the CUs, eight where each has a CU to itself and fewer waves would
-    // only make its walk longer (eight / four, 68 rows unless stated: 64/8 heads, 8 sequences of 1024 to 4096 keys
-    // 159.5 / 136.3 us, 3 of 300 26.3 / 19.8; 32 heads, 2 of 800 22.5 / 17.9, 4 of 700 to 1400 35.4 / 30.6, 8 of 2000
-    // 111 / 94.5, 170 rows on 1024 25.1 / 21.8, 488 rows on 512 50.8 / 43.8; but one sequence, 136 and 160 workgroups:
-    // 64/8 heads 28.3 / 33.2, 32 heads 13.0 / 15.5).  Where one row per sequence is asked for, one row tile of each
-    // has work.
-    const int rows_wg = 16 >> lg_ht, n_mt = only_row ? 1 : (t.rows + rows_wg - 1) / rows_wg;
-    const bool four = (int64_t)batch * (pair ? Hq >> (1 + lg_ht) : Hq) * n_mt * p.splits > 256;
+    const AttnTiles a = attn_tiles(batch, t.rows, Hq, Hkv, p, only_row != nullptr);
 #define ATT_LAUNCH_P(HD_, U_, W_, PG_) launch_attn_t<HD_, U_, W_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
-                                                   prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, lg_ht, s)
+                                                   prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, a.lg_ht, s)
 #define ATT_LAUNCH(HD_, U_) do { \
-        if (four) { if (pm.table) ATT_LAUNCH_P(HD_, U_, 4, true); else ATT_LAUNCH_P(HD_, U_, 4, false); } \
+        if (a.waves == 4) { if (pm.table) ATT_LAUNCH_P(HD_, U_, 4, true); else ATT_LAUNCH_P(HD_, U_, 4, false); } \
         else { if (pm.table) ATT_LAUNCH_P(HD_, U_, 8, true); else ATT_LAUNCH_P(HD_, U_, 8, false); } } while (0)
     if (hd == 128) {
-        if (pair) ATT_LAUNCH(128, 2); else ATT_LAUNCH(128, 1);
+        if (a.tiles == 2) ATT_LAUNCH(128, 2); else ATT_LAUNCH(128, 1);
     } else {
-        if (pair) ATT_LAUNCH(64, 2); else ATT_LAUNCH(64, 1);
+        if (a.tiles == 2) ATT_LAUNCH(64, 2); else ATT_LAUNCH(64, 1);
     }
 #undef ATT_LAUNCH_P
 #undef ATT_LAUNCH
