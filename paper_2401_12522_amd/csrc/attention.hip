@@ -724,12 +724,24 @@ AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, const AttnPlan &p, bo
     // (three of their four tiles over the last 16 rows held 4), a finer grain for the CUs, and fewer keys masked away at
     // a row tile's end.  Pairs of heads / this, us: 68 rows, 8 sequences of 1024 to 4096 keys 157.0 / 136.3, 2 of 1000
     // 28.4 / 27.1, one of 2048 29.6 / 28.3; 170 rows on 1024 34.1 / 29.6, 512 rows on 512 74.3 / 63.7, 25 rows, 4 of
-    // 2000 28.9 / 26.6, one row 14.2 / 14.0: never slower.
+    // 2000 28.9 / 26.6.
+    // Fewer rows than a tile's are another matter: a pair's tile then has no more queries than rows, and a wave that
+    // rescales only where one of its queries finds a new maximum does so less often.  Where the CUs of an XCD (32; its
+    // K/V heads stay on it) take the pairs' workgroups at once there is nothing to gain for it, and heads share a tile up
+    // to 4 queries only (pairs / shared as far as the heads go, warm: 64/8 heads, 5 rows on 1000 15.1 / 17.1, on 4096
+    // 20.1 / 21.9, 4 sequences of 2048 22.6 / 24.1, 8 rows on 2048 16.8 / 18.0; 32/8 heads, 8 rows on 1000 15.8 / 17.2;
+    // 32/1 heads, 3 rows on 1000 15.3 / 17.2; but one row 18.5 / 17.6 on 4096).  Where they queue, sharing wins
+    // (32/1 heads, 5 rows on 4096 46.5 / 29.2), if it leaves fewer workgroups (12/1 heads, 9 rows on 8000, 3 of each
+    // split either way: 45.8 / 48.7; from two full tiles on the finer grain pays by itself).
     const int qpk = Hq / Hkv;
     AttnTiles a;
     a.tiles = qpk % 2 == 0 ? 2 : 1;
     a.lg_ht = 0;
     while (a.tiles == 2 && a.lg_ht < 3 && qpk % (4 << a.lg_ht) == 0) a.lg_ht++;
+    auto per_kv_head = [&](int lg) { return (int64_t)(qpk / 2 >> lg) * ((rows + (16 >> lg) - 1) / (16 >> lg)) * p.splits; };
+    if (rows < 16 && ((int64_t)batch * Hkv + 7) / 8 * per_kv_head(0) <= 32)
+        while (a.lg_ht > 0 && rows << a.lg_ht > 4) a.lg_ht--;
+    if (rows < 32 && per_kv_head(a.lg_ht) >= per_kv_head(0)) a.lg_ht = 0;
     // Eight waves walk one workgroup's keys, or four: with four a CU holds two workgroups, one in its loop while the
     // other is in its prologue or merge (6 us of a workgroup's time together), and the merge is half as wide.
     // Four where the workgroups are more than the CUs, eight where each has a CU to itself and fewer waves would

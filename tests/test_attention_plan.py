@@ -26,6 +26,21 @@ def test_heads_rows_and_waves_of_a_workgroup(batch, rows, heads, kv_heads, ctx, 
     assert {k: plan[k] for k in expect} == expect, plan
 
 
+@pytest.mark.parametrize("batch,rows,heads,kv_heads,ctx,heads_wg", [
+    # the pairs' workgroups fit an XCD's 32 CUs: up to 4 queries share a tile
+    (1, 1, 64, 8, 2048, 8), (1, 2, 64, 8, 2048, 4), (1, 3, 64, 8, 2048, 2), (1, 5, 64, 8, 2048, 2), (4, 15, 64, 8, 2048, 2),
+    (1, 2, 32, 8, 1000, 4), (1, 8, 32, 8, 1000, 2), (1, 1, 32, 1, 100, 8), (1, 3, 32, 1, 1000, 2),
+    # they queue: as many as there are
+    (1, 5, 32, 1, 4096, 16), (12, 5, 64, 8, 2048, 8), (70, 3, 24, 2, 33, 4),
+    # but not where that leaves as many workgroups as before, as long as the rows are fewer than two tiles'
+    (1, 9, 12, 1, 8000, 2), (1, 16, 64, 8, 2048, 2), (1, 17, 64, 8, 2048, 8), (2, 25, 12, 1, 2048, 2), (1, 32, 64, 8, 2048, 8),
+])
+def test_heads_share_a_tile_where_that_saves_time(batch, rows, heads, kv_heads, ctx, heads_wg):
+    plan = _plan(batch, rows, heads, kv_heads, 128, ctx)
+    assert plan["heads"] == heads_wg, plan
+    assert plan["rows"] == 32 // heads_wg
+
+
 def test_plans_of_nothing_are_refused():
     from paper_2401_12522_amd import binding
     for bad in ((0, 1, 4, 4, 64, 0), (1, 1, 4, 3, 64, 0), (1, 1, 4, 4, 96, 0), (1, 1, 4, 4, 64, -1)):
