@@ -479,7 +479,7 @@ extern "C" int bita_attention_plan_info(int32_t batch, int32_t rows, int32_t n_h
         ctx_hint < 0 || n_prompt < 0 || page_size < 0)
         return bita_set_error(BITA_ERR_INVALID_ARG, "bita_attention_plan_info: bad argument");
     const AttnPlan p = attn_plan(batch, rows, n_heads, head_dim, ctx_hint, n_prompt);
-    const AttnTiles a = attn_tiles(batch, rows, n_heads, n_kv_heads, p, false);
+    const AttnTiles a = attn_tiles(batch, rows, n_heads, n_kv_heads, head_dim, p, page_size ? (ctx_hint + page_size - 1) / page_size : 0, false);
     out5[0] = p.splits; out5[1] = a.tiles << a.lg_ht; out5[2] = 16 >> a.lg_ht; out5[3] = a.waves;
     out5[4] = a.workgroups < INT32_MAX ? (int32_t)a.workgroups : INT32_MAX;
     return BITA_OK;

@@ -711,13 +711,19 @@ AttnPlan attn_plan(int batch, int rows, int n_heads, int hd, int ctx_hint, int n
     const int per = (n_chunks + splits - 1) / splits;
     splits = (n_chunks + per - 1) / per;
     p.splits = splits;
+    p.chunks = n_chunks;
     p.part_o_bytes = (size_t)batch * n_heads * splits * rows * hd * sizeof(float);
     p.part_ml_bytes = (size_t)batch * n_heads * splits * rows * 2 * sizeof(float);
     return p;
 }
 
-// How a launch is cut into workgroups, from nothing but its sizes.
-AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, const AttnPlan &p, bool one_row) {
+// How a launch is cut into workgroups, from nothing but its sizes.  table_entries: of a sequence's page table, 0 for a
+// contiguous cache.
+static size_t att_table_bytes(int entries) { return (size_t)((entries + 3) / 4) * 16; }
+static size_t att_smem_four(int hd, int tiles) {
+    return hd == 128 ? (tiles == 2 ? AttCfg<128, 2, 4>::SMEM : AttCfg<128, 1, 4>::SMEM) : (tiles == 2 ? AttCfg<64, 2, 4>::SMEM : AttCfg<64, 1, 4>::SMEM);
+}
+AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, int hd, const AttnPlan &p, int table_entries, bool one_row) {
     // Grouped-query models: a workgroup's two tiles of 16 queries share its chunk loads.  The tiles take as many heads
     // of the K/V head's group as a power of two divides evenly, and so fewer rows: eight heads of 4 rows for 64/8 heads,
     // 17 workgroups per K/V head for the 68 rows of a 64-node tree where pairs of heads with 16 rows each took 20
@@ -750,9 +756,23 @@ AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, const AttnPlan &p, bo
     // 111 / 94.5, 170 rows on 1024 25.1 / 21.8, 488 rows on 512 50.8 / 43.8; but one sequence, 136 and 160 workgroups:
     // 64/8 heads 28.3 / 33.2, 32 heads 13.0 / 15.5).  Where one row per sequence is asked for, one row tile of each
     // has work.
+    // Two workgroups of four waves have to fit a CU's LDS: with a large page table they do not, and one by itself
+    // takes half as long again as eight waves (a pass of 44 rows on 3841 pages of 16, 64/8 heads 653 / 436 us, on 3969 pages,
+    // 32 heads 586 / 395).  The same at the end of a launch whose last workgroups, up to 256 in an odd round of 256, come
+    // to one a CU: what that costs grows with the walk, what four waves save does not.  Paged walks lose beyond 17 chunks
+    // a round (four / eight, passes of 32 heads, 3 rounds: 360 rows on 5000 307 / 282, 133 rows, 2 of 5630 320 / 293, 74
+    // rows, 4 of 2367 195 / 186, 4 of 1292 136 / 137; 5 rounds: 127 rows, 5 of 4594 418 / 406, 204 rows, 3 of 1026 195 /
+    // 198; 64/8 heads, 3 rounds: 360 rows on 5000 371 / 347, 5 rounds: 68 rows, 8 of 2000 278 / 290), contiguous ones of
+    // one head per workgroup, unsplit, from 120 chunks in the upper half of the third round on (attention alone, 32 heads:
+    // 357 rows on 5360 117 / 106, 351 on 3102 74 / 70; but 285 on 6309 110 / 113), with pairs never (64/8 heads, 351 rows on
+    // 6806 187 / 195).
     const int rows_wg = 16 >> a.lg_ht, n_mt = one_row ? 1 : (rows + rows_wg - 1) / rows_wg;
     a.workgroups = (int64_t)batch * (a.tiles == 2 ? Hq >> (1 + a.lg_ht) : Hq) * n_mt * p.splits;
-    a.waves = a.workgroups > 256 ? 4 : 8;
+    const int64_t rounds = (a.workgroups + 255) / 256, walk = (p.chunks + p.splits - 1) / p.splits;
+    const bool fits = 2 * (att_smem_four(hd, a.tiles) + att_table_bytes(table_entries)) <= 160 * 1024;
+    const bool long_end = (rounds & 1) && (table_entries ? walk > 17 * rounds
+                                                         : a.tiles == 1 && p.splits == 1 && rounds == 3 && a.workgroups >= 640 && walk >= 120);
+    a.waves = rounds > 1 && fits && !long_end ? 4 : 8;
     return a;
 }
 
@@ -772,7 +792,7 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
                                   C::SMEM + (PAGED ? ATT_PAGE_TABLE_MAX * 4 : 0));
         attr_set = true;
     }
-    const size_t smem_bytes = C::SMEM + (PAGED ? (size_t)((pm.tbl_cap + 3) / 4) * 16 : 0);
+    const size_t smem_bytes = C::SMEM + (PAGED ? att_table_bytes(pm.tbl_cap) : 0);
     const int per_wg = 16 >> lg_ht, n_mt = U == 1 && only_row ? 1 : (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     const int groups = batch * Hkv, per_group = (Hq / Hkv / U >> lg_ht) * n_mt * p.splits;
@@ -793,7 +813,7 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            const void *prompt_v, const int32_t *ctx_len, const int32_t *token, int batch, int Hq, int Hkv, int hd,
                            int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
                            void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s, const int32_t *only_row) {
-    const AttnTiles a = attn_tiles(batch, t.rows, Hq, Hkv, p, only_row != nullptr);
+    const AttnTiles a = attn_tiles(batch, t.rows, Hq, Hkv, hd, p, pm.table ? pm.tbl_cap : 0, only_row != nullptr);
 #define ATT_LAUNCH_P(HD_, U_, W_, PG_) launch_attn_t<HD_, U_, W_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
                                                    prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, a.lg_ht, s)
 #define ATT_LAUNCH(HD_, U_) do { \

@@ -41,6 +41,22 @@ def test_heads_share_a_tile_where_that_saves_time(batch, rows, heads, kv_heads, 
     assert plan["rows"] == 32 // heads_wg
 
 
+@pytest.mark.parametrize("batch,rows,heads,kv_heads,ctx,page,waves", [
+    (1, 136, 32, 32, 1024, 0, 4), (1, 128, 32, 32, 1024, 0, 8),                                    # more workgroups than CUs
+    # two workgroups of four waves and their page tables in a CU's LDS: 3840 entries with two tiles, 3968 with one
+    (1, 96, 64, 8, 61440, 16, 4), (1, 96, 64, 8, 61441, 16, 8), (1, 17, 32, 32, 63488, 16, 4), (1, 17, 32, 32, 63489, 16, 8),
+    # an odd round of 256 at the end of long paged walks
+    (4, 68, 32, 32, 1292, 64, 4), (4, 68, 32, 32, 1400, 64, 4), (4, 68, 32, 32, 1500, 64, 8), (4, 68, 32, 32, 1500, 0, 4), (2, 133, 32, 32, 5630, 16, 8),
+    (2, 120, 32, 32, 5630, 16, 4), (3, 204, 32, 32, 1026, 16, 4), (5, 127, 32, 32, 4594, 16, 8), (8, 68, 64, 8, 2000, 64, 4),
+    (1, 360, 64, 8, 5000, 64, 8),
+    # and of long contiguous ones with one head per workgroup
+    (1, 357, 32, 32, 5360, 0, 8), (1, 285, 32, 32, 6309, 0, 4), (1, 357, 32, 32, 2000, 0, 4), (1, 351, 64, 8, 6806, 0, 4), (1, 512, 32, 32, 5360, 0, 4),
+])
+def test_four_waves_where_two_workgroups_share_a_cu(batch, rows, heads, kv_heads, ctx, page, waves):
+    plan = _plan(batch, rows, heads, kv_heads, 128, ctx, n_prompt=16, page_size=page)
+    assert plan["waves"] == waves, plan
+
+
 def test_plans_of_nothing_are_refused():
     from paper_2401_12522_amd import binding
     for bad in ((0, 1, 4, 4, 64, 0), (1, 1, 4, 3, 64, 0), (1, 1, 4, 4, 96, 0), (1, 1, 4, 4, 64, -1)):
