@@ -739,17 +739,22 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
     // Tall passes (6 to 9 m-tiles per pass, variant 12): fewer passes over the weights and 16 weight tiles per
     // activation fragment, against fewer, fatter workgroups.  The tall form is taken where the same estimate promises a
     // fifth less than the others, or, with 10 us for what every launch costs besides, a seventh (what is less than that
-    // it does not resolve: 234 launches of 7B, 13B and 70B matrices at 84 to 512 rows; a fifth alone left these behind, before / now: 13B QKV, 272 rows 94 / 83 us, gate/up, 84 rows 70 / 65, 120
-    // rows 90 / 77, 400 rows 235 / 217; 7B down, 340 rows 73 / 69; 70B QKV, 204 rows 79 / 75).
+    // it does not resolve.  A fifth alone left these behind, before / now: 13B gate/up, 81 rows 71 / 66 us, 117 rows 91 / 85, 409
+    // rows 239 / 215; 70B QKV, 208 rows 83 / 79; 7088 x 16128, 164 rows 113 / 91.  Over 117 launches of 81 to 512 rows that a
+    // seventh alone gives a tall form the median is 8 % less time; one pass of 7 m-tiles for two k splits instead of one
+    // neither gains nor loses, 3 % either way).
     if (planes == 2 && m_tiles >= 6 && g_force_variant == -1) {
         const double launch = 10e-6;
+        const int five_passes = passes, five_variant = p.variant, five_tiles = passes >= 2 ? 5 * passes : m_tiles;
         double t_ref = t_five;
         // (a launch of 14-wave workgroups is what the tall forms were measured against where that is what the width
-        // suggests; they must also beat the 16-wave one)
-        if (passes >= 2 && NT >= 1024 && NT < 3000) t_ref = estimate(5, passes, 14, &sp_now);
+        // suggests; what they have to beat where 16 waves are taken instead is below)
+        if (passes >= 2 && NT >= 1024 && NT < 3000) {
+            int sp14 = 1;
+            t_ref = estimate(5, passes, 14, &sp14);
+        }
         const double fifth = 0.8 * t_ref, seventh = 0.86 * (t_ref + launch) - launch;
         double t_best = fifth > seventh ? fifth : seventh;
-        if (t_best > 1.01 * t_five) t_best = 1.01 * t_five;
         // 16 or 12 weight tiles per workgroup: a launch whose 16-tile workgroups leave CUs idle (172 of
         // 256 at 272 rows of the 7B gate/up, 9 m-tiles) or take a nearly empty last round is cut finer
         // where the estimate falls by a twentieth (gate/up, K = 4096: 170 rows 77.5 -> 72.1 us,
@@ -775,8 +780,25 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
                 if (sp > 1 && (tiles == 12 || t > fifth) &&
                     (((size_t)sp * m_rows * n_rows * 4 + 255) & ~(size_t)255) + frag_bytes(m_rows, k) > BITA_NOALLOC_SCRATCH_BYTES)
                     continue;
-                if (t < (tiles == 12 && p.mt_pass ? 0.95 : 1.0) * t_best) { t_best = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; p.tall_tiles = tiles; }
+                // (in two passes 12 tiles that promise a fifth stand against 16 that promise a seventh: 12 of 15 such launches of
+                // 169 to 221 rows lost 1 to 6 % with 16, three gained 3 to 4; in one pass or three 16 gain more than they lose)
+                const bool stands = n_pass == 2 && t < fifth && t_best >= fifth;
+                if (t < (tiles == 12 && p.mt_pass && !stands ? 0.95 : 1.0) * t_best) { t_best = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; p.tall_tiles = tiles; }
             }
+        }
+        // Against the form that would run instead the estimate errs with the m-tiles that the passes execute.  Where the tall
+        // ones execute no more, a tie goes to them (19440 x 4552, 211 rows, 14 m-tiles for 15, estimates alike, tall / passes
+        // of 5 84 / 88 us; as many, 16720 x 2240, 508 rows 85 / 89, 17504 x 744, 490 rows 45.8 / 45.0).  Where they execute more
+        // it promises them too much: with a tenth or less the passes of 5 are 1 to 7 % faster (32000 x 8192, 301 rows, 21 for 20,
+        // estimates alike, 309 / 288; 40960 x 2048, 460 rows, 32 for 30, 0.92 of the other, 164 / 155), and with 0.87 of it
+        // from k = 2560 on (27648 x 5120, 538 rows, 36 for 35, 281 / 267; but 26928 x 1496, 547 rows 99 / 103, and with 0.865 of
+        // it 33312 x 3472, 524 rows 240 / 245).  Short k's, below 24 k-steps, are its own again (32048 x 432, 295 rows 33 / 35).
+        const bool more = p.mt_pass && passes * p.mt_pass > five_tiles;
+        if (t_best >= (!more || KS < 24 ? 1.01 : KS < 80 ? 0.9 : 0.87) * t_five) {
+            p.mt_pass = 0;
+            p.tall_tiles = 16;
+            passes = five_passes;
+            p.variant = five_variant;
         }
     }
     if (g_force_variant >= 0 && g_force_variant < GEMM_N_VARIANTS) p.variant = g_force_variant;

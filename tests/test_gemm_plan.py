@@ -45,11 +45,34 @@ def test_passes_of_five_take_the_fewer_rounds(m, n, k, planes):
     """Many rows of 1024 to 2999 tiles: 16 waves per workgroup where 14 would take a round more on the 256 CUs, unless
     that means k splits, which the static scratch would have to hold."""
     from paper_2401_12522_amd import binding as B
-    _lib()
-    plan = B.gemm_plan_info(m, n, k, planes)
+    _lib().bita_tune_gemm(-2, -1)               # without the tall forms, which two planes may take instead
+    try:
+        plan = B.gemm_plan_info(m, n, k, planes)
+    finally:
+        _lib().bita_tune_gemm(-1, -1)
     passes, tiles = ((m + 15) // 16 + 4) // 5, n // 16
     rounds = {t: -(-(-(-tiles // t) * passes) // 256) for t in (14, 16)}
     splits = 256 // (-(-tiles // 16) * passes)
-    if plan["mt_pass"] == 0:
-        assert plan["variant"] == (11 if splits > 1 or rounds[14] * (14 + 5 * planes) <= rounds[16] * (16 + 5 * planes) else 9), plan
-        assert plan["splits"] == 1
+    assert plan["variant"] == (11 if splits > 1 or rounds[14] * (14 + 5 * planes) <= rounds[16] * (16 + 5 * planes) else 9), plan
+    assert plan["mt_pass"] == 0 and plan["splits"] == 1
+
+
+@pytest.mark.parametrize("m,n,k,variant,mt_pass,tiles,splits", [
+    # a fifth or a seventh less than the other form
+    (170, 22016, 4096, 12, 6, 12, 1), (84, 27648, 5120, 12, 6, 16, 2), (120, 27648, 5120, 12, 8, 16, 2), (204, 10240, 8192, 12, 7, 16, 3),
+    (272, 15360, 5120, 9, 0, 0, 1), (340, 4096, 11008, 9, 0, 0, 3), (216, 10240, 8192, 9, 0, 0, 2),
+    # more m-tiles executed than in passes of 5: a tenth less than those asks for, an eighth from 80 k-steps on
+    (301, 32000, 8192, 9, 0, 0, 1), (300, 32000, 5120, 9, 0, 0, 1), (460, 40960, 2048, 9, 0, 0, 1), (538, 27648, 5120, 9, 0, 0, 1),
+    (547, 26928, 1496, 12, 9, 16, 1), (524, 33312, 3472, 12, 9, 12, 1), (459, 32000, 4096, 12, 8, 16, 1), (457, 57344, 8192, 12, 8, 16, 1),
+    (295, 32048, 432, 12, 7, 12, 1), (300, 32000, 736, 12, 7, 12, 1), (300, 32000, 744, 9, 0, 0, 1),
+    # as many or fewer: ties go to the tall form
+    (211, 19440, 4552, 12, 7, 12, 1), (508, 16720, 2240, 12, 7, 12, 1),
+    # 12 tiles that promise a fifth against 16 that promise a seventh: in two passes, in one, in three
+    (188, 4720, 11528, 12, 6, 12, 5), (182, 5648, 4968, 12, 6, 12, 4), (107, 12288, 4096, 12, 7, 16, 5), (330, 4720, 3336, 12, 7, 16, 4),
+    # a tall form of more k splits than the static scratch holds is left out, unless it promises a fifth by 16 tiles
+    (160, 16384, 40000, 11, 0, 0, 1), (136, 16384, 17000, 12, 9, 16, 4)])
+def test_tall_passes_where_they_are_faster(m, n, k, variant, mt_pass, tiles, splits):
+    from paper_2401_12522_amd import binding as B
+    _lib()
+    plan = B.gemm_plan_info(m, n, k)
+    assert (plan["variant"], plan["mt_pass"], plan["tall_tiles"], plan["splits"]) == (variant, mt_pass, tiles, splits), plan
