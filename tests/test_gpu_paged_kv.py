@@ -89,6 +89,53 @@ def test_paged_steps_are_bit_identical_to_contiguous(bita, cfg_name, n_layers, p
     assert spare and not paged.k_cache[:, spare].any() and not paged.v_cache[:, spare].any()
 
 
+@pytest.mark.parametrize("page", [16, 64])
+@pytest.mark.parametrize("cfg_name,lens,heads_wg", [("7b", [1400, 333, 1000, 77], 1), ("70b", [900, 128, 511], 8)])
+def test_paged_steps_of_more_workgroups_than_cus(bita, cfg_name, lens, heads_wg, page):
+    """64-node trees over several sequences of ragged lengths: four waves per workgroup, one head or eight, from pages as
+    from contiguous rows; and every sequence as by itself, where a workgroup has a CU to itself and eight waves."""
+    cfg = synth.get_config(cfg_name, n_layers=1)
+    B, hint, smax = len(lens), max(lens), 1536
+    tin = synth.attach_mask_groups(synth.full_branching_tree([4, 3, 2, 1], 64), [0], cfg.n_mask)
+    model = bita.Model(cfg, synth.SynthWeights(cfg, seed=2, device="cuda"), max_pos=smax + 64)
+    tmpl = bita.TreeTemplate(tin.parent, tin.is_mask, tin.n_tree, cfg.n_mask)
+    plan = lambda b, n, **k: bita.binding.attention_plan_info(b, tmpl.rows, cfg.n_heads, cfg.n_kv_heads, 128, n, cfg.n_prompt, **k)   # noqa: E731
+    for p in (plan(B, hint), plan(B, hint, page_size=page)):
+        assert (p["waves"], p["heads"], p["splits"]) == (4, heads_wg, 1) and p["workgroups"] > 256
+    flat = bita.KVState(cfg, 1, B, smax, tmpl.rows)
+    paged = bita.PagedKVState(cfg, 1, B, smax, tmpl.rows, page, n_pages=B * (smax // page) + 5, seed=7)
+    _random_cache(flat, lens, 3)
+    for b, n in enumerate(lens):
+        paged.load_contiguous(b, flat.k_cache[:, b], flat.v_cache[:, b], n)
+    start = flat.k_cache.clone(), flat.v_cache.clone()
+    rng = np.random.default_rng(11)
+    root, cand = dev_i32(rng.integers(0, cfg.vocab, B)), dev_i32(rng.integers(0, cfg.vocab, (B, cfg.n_mask, tmpl.kmax)))
+    a, p = [bita.StepBuffers(model, tmpl, B, tmpl.kmax, want_logits=True) for _ in range(2)]
+    for kv, buf in ((flat, a), (paged, p)):
+        bita.decode_step(model, kv, hint, tmpl, buf, B, root, cand)
+    torch.cuda.synchronize()
+    assert torch.isfinite(a.logits).all()
+    assert torch.equal(a.logits, p.logits), (a.logits - p.logits).abs().max().item()
+    for name in ("token", "argmax", "topk_ids", "topk_val", "path", "n_acc", "bonus", "emitted", "next_group", "next_shift"):
+        assert torch.equal(getattr(a, name), getattr(p, name)), name
+    for b in range(B):
+        k, v = paged.contiguous(b)
+        n = int(paged.ctx_len[b])
+        assert n == int(flat.ctx_len[b]) > lens[b]
+        assert torch.equal(k[:, :, :n], flat.k_cache[:, b, :, :n]) and torch.equal(v[:, :, :n], flat.v_cache[:, b, :, :n])
+    one, buf = bita.KVState(cfg, 1, 1, smax, tmpl.rows), bita.StepBuffers(model, tmpl, 1, tmpl.kmax, want_logits=True)
+    for b, n in enumerate(lens):
+        assert plan(1, n)["waves"] == 8
+        one.k_cache.copy_(start[0][:, b:b + 1])
+        one.v_cache.copy_(start[1][:, b:b + 1])
+        one.ctx_len.fill_(n)
+        bita.decode_step(model, one, n, tmpl, buf, 1, root[b:b + 1].clone(), cand[b:b + 1].clone())
+        torch.cuda.synchronize()
+        ref, got = buf.logits[0].double(), a.logits[b].double()
+        # each side's two-plane sums are within 1.3e-5 of 64 bits (measured at these widths), and within three times that of each other
+        assert float((got - ref).norm() / ref.norm()) < 4e-5, b
+
+
 @pytest.mark.parametrize("hd,heads,page_lg", [(128, 1, 23), (128, 1, 24), (128, 2, 24), (128, 1, 25), (64, 2, 24), (64, 1, 25)])
 def test_pages_whose_bytes_leave_32_bits(bita, hd, heads, page_lg):
     """One page larger than the sequence, of 2, 4 or 8 GiB per K/V head (4 GiB and its multiples are zero

@@ -106,6 +106,44 @@ def test_prefill_ragged_batch_in_two_calls(bita):
             assert got == argmax_low(last)
 
 
+@pytest.mark.parametrize("heads,kv_heads,hd,batch,chunk,longest", [
+    (8, 1, 128, 3, 40, 155), (16, 2, 64, 3, 64, 250), (32, 1, 64, 2, 33, 99),     # 4 rows a workgroup, 4, 2
+    (8, 1, 128, 3, 40, 131), (6, 1, 64, 2, 40, 60),                               # few rows, and heads that do not share tiles: 16
+    (64, 8, 64, 40, 48, 90), (64, 8, 128, 36, 33, 60),                            # more workgroups than CUs: four waves
+    (4, 4, 128, 3, 40, 131), (4, 4, 64, 70, 33, 90),                              # one head per workgroup: the one row tile alone
+    (8, 1, 64, 1, 40, 2000)])                                                     # the keys split between workgroups
+def test_the_token_after_a_prompt_is_that_of_passes_that_finish_every_row(bita, heads, kv_heads, hd, batch, chunk, longest):
+    """A prefill's last layer goes on with one row per sequence, and attention with the workgroups that hold it.  The
+    tokens after all rows of the last chunk, by a pass that finishes them all, are the reference, wherever each sequence ends."""
+    cfg = synth.get_config("tiny", n_heads=heads, n_kv_heads=kv_heads, head_dim=hd)
+    model = bita.Model(cfg, synth.SynthWeights(cfg, seed=6, device="cuda"), max_pos=longest + 64)
+    rng = np.random.default_rng(heads + chunk)
+    last = longest - (longest - 1) // chunk * chunk                               # rows of the last chunk
+    first = longest - last
+    toks = dev_i32(rng.integers(0, cfg.vocab, (batch, longest)))
+    ends = first + 1 + np.arange(batch) * 5 % last                                # every place of a tile
+    kv = bita.KVState(cfg, cfg.n_layers, batch, longest + 8, chunk)
+    nxt = bita.prefill(model, kv, 0, toks, chunk, seq_len=dev_i32(ends))
+    every = bita.KVState(cfg, cfg.n_layers, batch, longest + 8, chunk)
+    if first:
+        bita.prefill(model, every, 0, toks[:, :first].contiguous(), chunk)
+    every.resize_rows(cfg.n_layers, cfg, last)
+    tmpl = bita.TreeTemplate(np.arange(last, dtype=np.int32) - 1, np.zeros(last, np.uint8), last, cfg.n_mask)
+    buf = bita.StepBuffers(model, tmpl, batch, 1, want_logits=True)
+    buf.token.copy_(toks[:, first:])
+    bita.verify_step(model, every, first, tmpl, buf, batch)
+    torch.cuda.synchronize()
+    assert kv.ctx_len.cpu().tolist() == ends.tolist()
+    rows = torch.tensor(ends - first - 1, device="cuda")
+    logits = buf.logits[torch.arange(batch, device="cuda"), rows]
+    assert torch.isfinite(logits).all()
+    two = torch.topk(logits, 2).values
+    # (the two passes' sums are ordered differently: 4e-5 of a logit's size between them, and the cache's stored rows a unit here and there)
+    clear = (two[:, 0] - two[:, 1]) > 1e-2 * logits.abs().amax(1)
+    assert bool(clear.any())
+    assert torch.equal(nxt[clear], torch.argmax(logits, 1)[clear].int())
+
+
 def test_prefill_rejects_what_does_not_fit(bita):
     cfg = synth.get_config("tiny")
     w = synth.SynthWeights(cfg, seed=1)
