@@ -119,8 +119,9 @@ __global__ __launch_bounds__(256) void rmsnorm_prep_kernel(float *__restrict__ x
 // bf16 planes; only the hi planes of accepted rows are ever committed to the cache.
 // A thread takes four neighbouring rotation pairs of a head: 16-byte loads, 8-byte stores.  What bounds it
 // is the sums and planes it moves (512 rows of 96 heads: 50 MB); with one pair a thread, 4-byte loads and 2-byte
-// stores, they moved at 2.3 TB/s, now at 4.6 (rocprofv3, 7B widths: 512 rows 21.8 -> 11.0 us, 272 rows in two
-// k splits 14.3 -> 8.8, 170 rows 10.4 -> 6.7; 68 rows, where the launch and two round trips are most of it, 5.6 -> 5.8).
+// stores, they moved at 2.1 TB/s, now at 4.8 (rocprofv3, 7B widths: 512 rows 23.9 -> 10.6 us, 272 rows in two
+// k splits 14.2 -> 8.5, 170 rows 9.8 -> 6.1, 102 rows 7.5 -> 6.6; 13B 84 rows 7.6 -> 5.9; up to 84 rows of 7B, where the launch and
+// two round trips are most of it, the same within 0.1: 68 rows 5.6.  Two pairs a thread: 68 rows 5.4, but 170 rows 8.0, 512 17.6).
 #define ROPE_THREADS 128
 template <int HD>
 __global__ __launch_bounds__(ROPE_THREADS) void qkv_rope_kernel(
@@ -152,7 +153,8 @@ __global__ __launch_bounds__(ROPE_THREADS) void qkv_rope_kernel(
         float4 pl[8], ph[8];
 #pragma unroll
         for (int u = 0; u < 8; u++) {
-            const float *p = partial + ((int64_t)min(s0 + u, splits - 1) * M + row) * ncols + col;
+            if (u > 0 && s0 + u >= splits) continue;         // (reading the last one again instead cost 8 % of 512 rows in one split)
+            const float *p = partial + ((int64_t)(s0 + u) * M + row) * ncols + col;
             pl[u] = *reinterpret_cast<const float4 *>(p);
             ph[u] = *reinterpret_cast<const float4 *>(p + half);
         }
