@@ -696,6 +696,8 @@ AttnPlan attn_plan(int batch, int rows, int n_heads, int hd, int ctx_hint, int n
     AttnPlan p;
     const int n_mt = (rows + 15) / 16;
     const int n_chunks = (n_prompt + ctx_hint + ATT_CHUNK - 1) / ATT_CHUNK + n_mt;
+    // (tiles of 16 rows of every head: heads that share a workgroup make fewer of them, see attn_tiles, and the split stays what
+    // it is for heads by themselves)
     const int wgs = batch * n_heads * n_mt;
     // No key split while one workgroup's walk stays moderate (256 chunks = 8192 keys, 32 per
     // wave); beyond that, or when the row tiles alone leave most CUs idle on a long context,

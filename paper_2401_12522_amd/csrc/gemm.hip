@@ -720,7 +720,8 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
     // take as many rounds (22016 x 4096, 170 rows, 16 / 14 waves: 132 / 124 us; 272 rows 139 / 129), but a round more of
     // them costs far more than that: 32000 x 4096, 150 rows 84 / 129 us, 300 rows 149 / 192, 440 rows 214 / 256; 27648 x 5120,
     // 512 rows 260 / 308; 40960 x 2048, 240 rows 80 / 109; one plane 67 / 103, 119 / 148, 171 / 193, 202 / 228, 65 / 86.
-    // The estimate ranks the two right wherever they differ by more than 5 % (196 launches).
+    // (Passes of 5 by themselves: with two planes 440 and 512 rows take a tall form.)  The estimate ranks the two right
+    // wherever they differ by more than 5 % (196 launches).
     double t_five = 0.0;                                     // passes of 5 m-tiles (or the one pass of 6 or 7)
     int sp_now = 1;
     if (passes >= 2) {

@@ -14,8 +14,9 @@ __device__ __forceinline__ float wave_sum(float v) {
 // of the slab holds 16 bytes of each of eight rows, and consecutive workgroup ids go round-robin over the XCDs: with
 // the row as the id eight L2s held an eighth of every line each and wrote it to memory piece by piece.  The 16 rows of
 // a slab tile go to one XCD here, 8 ids apart (tile t of the (chunk, row tile) grid on XCD t % 8), so that their lines leave
-// whole.  Norm kernel, row as the id / this (rocprofv3): 512 rows of 4096 12.6 -> 10.4 us, first layer 10.0 -> 7.9; 272 rows
-// 9.2 -> 8.7, first layer 7.5 -> 6.8; 170 rows 7.8 -> 7.1; 68 rows of 8192 8.0 -> 6.8, of 4096 6.1 -> 5.6; fewer rows the same.
+// whole.  Norm kernel, row as the id / this (rocprofv3): 512 rows of 4096 12.4 -> 10.5 us, first layer 9.4 -> 9.1 (embeddings in
+// cache); 272 rows 8.6 -> 7.7, 170 rows 7.0 -> 6.3; 68 rows of 8192 8.0 -> 6.8, of 4096 6.2 -> 5.6; fewer rows the same.
+// Gating kernel, 7B widths: 102 rows 8.2 -> 7.1, 136 rows 9.4 -> 8.0.
 // Workgroups beyond the last row or chunk have nothing to do (false).
 __device__ __forceinline__ bool slab_block(int M, int chunks, int &row, int &chunk) {
     const int mt_n = (M + 15) >> 4, q = blockIdx.x >> 3, t = (q >> 4) * 8 + (blockIdx.x & 7);

@@ -204,9 +204,10 @@ int compact_kv_launch(const bita_config &cfg, const bita_kv *kv, const PageMap &
 }
 
 // The four calls of a step with three launches less: the tokens are worked out by the first layer's norm, and
-// acceptance, copies and lengths are one kernel.  Each of the three cost its launch, 2.5 to 3.5 us whatever it did (four
-// calls / one, eager: two narrow layers, 12 rows 97 -> 83 us; two layers of 7B widths and the head, 68 rows 345 -> 336, one
-// row 244 -> 240; a layer of 13B widths and the head, 25 rows 202.6 -> 198.2).
+// acceptance, copies and lengths are one kernel.  Each of the three cost 1.5 to 2 us whatever it did (four calls / one,
+// in turn in one process, eager: two narrow layers, 12 rows 80.8 / 74.7 us, of which the host issues 73.6 / 59.4; two layers of 7B
+// widths and the head, 68 rows 341 / 335, one row 245.6 / 240.3; a layer of 13B widths and the head, 25 rows 203.8 / 199.2, of 70B,
+// 68 rows 458 / 453; replayed from a graph two narrow layers 83.9 / 80.2, 13B 211.3 / 206.5).
 extern "C" int bita_decode_step(bita_model *m, const bita_kv *kv, const bita_tree_template *t, const int32_t *d_root_token,
                                 const int32_t *d_cand, int32_t cand_rows, int32_t cand_kmax, const int32_t *d_group, const int32_t *d_shift,
                                 int32_t *d_ctx_len, int32_t batch, void *d_workspace, size_t ws_bytes, int32_t kmax,
