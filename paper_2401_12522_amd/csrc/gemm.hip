@@ -72,6 +72,9 @@ __device__ __forceinline__ void lds_wait_frag(bf16x8 &a) {
     asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "n"(OUTSTANDING));
 }
 
+// (no use of the fragment is moved ahead of the wait before this)
+__device__ __forceinline__ void frag_use(bf16x8 &a) { asm volatile("" : "+v"(a)); }
+
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F &&f) {
     if constexpr (I < N) {
@@ -126,6 +129,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     float *__restrict__ out, int64_t ldo, GemmOutput direct) {
     using C = GemmCfg<MT, NW, SPLIT, KC, D, WAVES, KG, PACK>;
     constexpr int WN = C::WN;
+    // Which loop: the two k groups in turns (below), or both at once.  Turns from 6 m-tiles on, and with passes of 5 on the
+    // forms that many rows take (14 and 16 waves) or with one plane; the packed 5 of a 64-node tree and the forms that 73 to 80
+    // rows of two planes take gain nothing by it (68 rows, both at once / turns: 12288 x 4096 30.4 / 30.9 us, 32000 x 4096 54.2 /
+    // 54.5, 57344 x 8192 154 / 153; 80 rows: 32000 x 4096 56.0 / 56.6, 8192 x 8192 37.5 / 38.2).
+    constexpr bool TURNS = KG == 2 && KC == 1 && (MT > 5 || (MT == 5 && !PACK && (WAVES >= 14 || !SPLIT)));
+    constexpr int SUB = MT > 5 ? 2 : 1;                        // reads and multiplies of a k-step: all at once, or plane by plane
     extern __shared__ __attribute__((aligned(16))) uint4 smem_u4[];   // [KG][D][NFRAG][64] + dump slot
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -245,48 +254,24 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
             // a k group whose share of the range is shorter than the others' skips the k-steps
             // past its end (wave-uniform)
             if (ks_begin + stage * KC + s >= ks_end) continue;
-            if constexpr (MT <= 5) {
-                // all LDS reads of the k-step are issued before its first MFMA; fragment f is
-                // waited for with the NF-1-f later reads still in flight
-                constexpr int NF = C::PL * MT - (PACK ? 1 : 0);
-                static_assert(NF <= 16, "lgkmcnt range");
-                bf16x8 a[NF];
-                static_for<0, NF>([&](auto f_c) {
-                    constexpr int F = decltype(f_c)::value;
-                    a[F] = lds_read_frag<((SLOT * C::NFRAG + F * KC) * 64) * 16>(lds_lane_base + s * 1024);
-                });
-                static_for<0, NF>([&](auto f_c) {
-                    constexpr int F = decltype(f_c)::value, i = F % MT;
-                    lds_wait_frag<NF - 1 - F>(a[F]);
+            // all LDS reads of the k-step are issued before its first MFMA; fragment f is
+            // waited for with the NF-1-f later reads still in flight
+            constexpr int NF = C::PL * MT - (PACK ? 1 : 0);
+            static_assert(NF <= 16, "lgkmcnt range");
+            bf16x8 a[NF];
+            static_for<0, NF>([&](auto f_c) {
+                constexpr int F = decltype(f_c)::value;
+                a[F] = lds_read_frag<((SLOT * C::NFRAG + F * KC) * 64) * 16>(lds_lane_base + s * 1024);
+            });
+            static_for<0, NF>([&](auto f_c) {
+                constexpr int F = decltype(f_c)::value, i = F % MT;
+                lds_wait_frag<NF - 1 - F>(a[F]);
 #pragma unroll
-                    for (int j = 0; j < NW; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            a[F], __builtin_bit_cast(bf16x8, w[SLOT][j][s]), acc[i][j], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);          // keeps the next fragment's wait behind these MFMAs
-                });
-            } else {
-                // tall passes (6 to 10 m-tiles): the fragments of a k-step are read in batches of
-                // AB, so that the accumulators (MT x NW tiles) leave room for them
-                static_assert(!PACK, "tall passes never pack");
-                constexpr int NF = C::PL * MT, AB = 4, NB = (NF + AB - 1) / AB;
-                static_for<0, NB>([&](auto b_c) {
-                    constexpr int B0 = decltype(b_c)::value * AB, BN = (NF - B0) < AB ? (NF - B0) : AB;
-                    bf16x8 a[BN];
-                    static_for<0, BN>([&](auto f_c) {
-                        constexpr int F = B0 + decltype(f_c)::value;
-                        a[F - B0] = lds_read_frag<((SLOT * C::NFRAG + F * KC) * 64) * 16>(lds_lane_base + s * 1024);
-                    });
-                    static_for<0, BN>([&](auto f_c) {
-                        constexpr int F = B0 + decltype(f_c)::value, i = F % MT;
-                        lds_wait_frag<BN - 1 - (F - B0)>(a[F - B0]);
-#pragma unroll
-                        for (int j = 0; j < NW; j++)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                a[F - B0], __builtin_bit_cast(bf16x8, w[SLOT][j][s]), acc[i][j], 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
-                    });
-                });
-            }
+                for (int j = 0; j < NW; j++)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        a[F], __builtin_bit_cast(bf16x8, w[SLOT][j][s]), acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);          // keeps the next fragment's wait behind these MFMAs
+            });
         }
     };
     // One pipeline step for stage c living in slot U: wait for its data (leaving the D-2 newer
@@ -332,11 +317,129 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
                                  : reinterpret_cast<const float4 *>(A_frag);
         my_row_sums.q0 = src[0]; my_row_sums.q1 = src[1]; my_row_sums.q2 = src[2]; my_row_sums.q3 = src[3];
     }
-    static_for<0, D - 1>([&](auto u_c) { issue(u_c, decltype(u_c)::value); });
+    static_for<0, D - 1>([&](auto u_c) {
+        issue(u_c, decltype(u_c)::value);
+        if constexpr (TURNS) __builtin_amdgcn_sched_barrier(0);   // (stage by stage: the waits below count them)
+    });
     float my_row_scale = 0.f;
     if constexpr (DIRECT) {
         if (direct.kind != GEMM_OUT_PARTIAL && m_base + (tid % (MT * 16)) < M) my_row_scale = row_scale_finish(direct.rs, my_row_sums);
     }
+    if constexpr (TURNS) {
+        // The k groups in turns: a phase ends at a barrier, and in each of them one group multiplies from registers while the
+        // other, a phase behind, reads its next fragments from LDS and issues its loads.  Every SIMD holds waves of
+        // both, so its matrix core always has one that waits for nothing (16 cycles an instruction, 58 cycles a phase
+        // for barrier, wait and branch).  With both groups at once (the loop below) all waves read behind the same barrier and
+        // the cores idled for that long, about 700 cycles of each k-step however many instructions it had.  Cycles per
+        // k-step, at once / turns, of them multiplies: 9 m-tiles x 12 tiles 2490 / 1930, 1728; 9 x 16 3150 / 2470, 2304; 8 x 12
+        // 2215 / 1690, 1536; 8 x 16 2800 / 2240, 2048.  What bounds it now is the card's power: the clock falls from 1.65-1.95 to
+        // 1.4-1.65 GHz (with activations of zeros it is 2.35).  Calls, us: 22016 x 4096, 240 rows 93.8 / 75.8, 272 rows 101 / 90, 512
+        // rows 165 / 151; 12288 x 4096, 512 rows 94.8 / 81.0; 57344 x 8192, 96 rows 180 / 169, 512 rows 781 / 698; 8192 x 28672, 272
+        // rows 235 / 216; passes of 5: 8192 x 28672, 300 rows 268 / 250, 4096 x 11008, 340 rows 74.1 / 69.7, one plane:
+        // 22016 x 4096, 20 rows 37 / 34.
+        // What is in the multiplying phase besides its instructions costs the launch as it stands: 9 waits instead of one 7 %,
+        // the next stage's addresses 17 %.  A higher wave priority there changes nothing.
+        constexpr int NF = C::NFRAG, PER = (NF + SUB - 1) / SUB;     // fragments of a k-step, read at a time
+        typedef const __attribute__((address_space(1))) unsigned char *gptr;
+        typedef uint32_t __attribute__((ext_vector_type(4))) u32x4_t;
+        bf16x8 a[PER];
+        // Addresses: what stays the same from stage to stage here; a stage adds one offset per operand, worked out at the end
+        // of a reading phase.
+        gptr w_src[NW], a_src[C::FPW];
+#pragma unroll
+        for (int j = 0; j < NW; j++) w_src[j] = (gptr)(Wp + (int64_t)min(t0 + j, NT - 1) * 128);
+#pragma unroll
+        for (int i = 0; i < C::FPW; i++) {
+            const int fc = min(i * WN + wn, NF - 1), mtg = min(bz * MT + fc % MT, m_tiles - 1);
+            a_src[i] = (gptr)(A_frag + ((int64_t)(fc / MT) * planes_stride_f + mtg) * 64 + (mtg == m_tiles - 1 ? lane_last : lane));
+            asm("" : "+v"(a_src[i]));
+        }
+        int64_t w_at = 0, a_at = 0;                                  // of the next stage to issue
+        auto place = [&](int stage) __attribute__((always_inline)) {
+            const int ks = min(ks_begin + stage, KS - 1);
+            w_at = packed_block(0, ks, NT) << 10;
+            a_at = (int64_t)ks * m_tiles << 10;
+            asm volatile("" : "+s"(w_at), "+s"(a_at));
+        };
+        auto fetch_a = [&](auto slot_c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < C::FPW; i++) {
+                const int f = i * WN + wn;
+                uint4 *dst = f < NF ? a_lds + (decltype(slot_c)::value * NF + f) * 64 : dump;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(a_src[i] + a_at),
+                                                 (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+            }
+        };
+        auto fetch_w = [&](auto slot_c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < NW; j++) {
+                const u32x4_t q = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4_t *)(w_src[j] + w_at + lane * 16));
+                w[decltype(slot_c)::value][j][0] = make_uint4(q.x, q.y, q.z, q.w);
+            }
+        };
+        auto swap = [&]() __attribute__((always_inline)) {           // end of a phase
+            __builtin_amdgcn_sched_barrier(0);
+            wg_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto read = [&](auto slot_c, auto sub_c) __attribute__((always_inline)) {
+            constexpr int SLOT = decltype(slot_c)::value, F0 = decltype(sub_c)::value * PER;
+            static_for<0, (NF - F0 < PER ? NF - F0 : PER)>([&](auto f_c) {
+                constexpr int F = decltype(f_c)::value;
+                a[F] = lds_read_frag<(SLOT * NF + F0 + F) * 1024>(lds_lane_base);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto multiply = [&](auto slot_c, auto sub_c, bool live) __attribute__((always_inline)) {
+            constexpr int SLOT = decltype(slot_c)::value, F0 = decltype(sub_c)::value * PER, N = NF - F0 < PER ? NF - F0 : PER;
+            lds_wait_frag<0>(a[0]);                                  // (one wait for all)
+            static_for<1, N>([&](auto f_c) { frag_use(a[decltype(f_c)::value]); });
+            if (!live) return;                                       // (wave-uniform)
+            static_for<0, N>([&](auto f_c) {
+                constexpr int F = decltype(f_c)::value, I = (F0 + F) % MT;
+#pragma unroll
+                for (int j = 0; j < NW; j++)
+                    acc[I][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[F], __builtin_bit_cast(bf16x8, w[SLOT][j][0]), acc[I][j], 0, 0, 0);
+            });
+        };
+        // (LEFT: loads that may still be in flight behind the next stage's)
+        auto step = [&](auto u_c, int stage, auto more_c, auto left_c) __attribute__((always_inline)) {
+            constexpr int U = decltype(u_c)::value, PRE = (U + D - 1) % D;
+            constexpr bool MORE = decltype(more_c)::value;
+            const bool live = ks_begin + stage < ks_end;             // a k group whose share of the range is shorter than the other's
+            static_for<0, SUB>([&](auto sub_c) {
+                constexpr int S = decltype(sub_c)::value;
+                read(u_c, sub_c);
+                if constexpr (MORE && S == 0) fetch_a(std::integral_constant<int, PRE>{});
+                if constexpr (MORE && S == SUB - 1) {
+                    fetch_w(std::integral_constant<int, PRE>{});
+                    place(stage + D);
+                }
+                swap();
+                multiply(u_c, sub_c, live);
+                if constexpr (S == SUB - 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    wait_vmcnt_lds<decltype(left_c)::value>();
+                }
+                swap();
+            });
+        };
+        place(D - 1);
+        wait_vmcnt_lds<(D - 2) * C::LOADS>();
+        swap();
+        if (kg & 1) swap();
+        int c = 0;
+        for (; c + D <= n_stages; c += D)
+            static_for<0, D>([&](auto u_c) {
+                step(u_c, c + decltype(u_c)::value, std::true_type{}, std::integral_constant<int, (D - 2) * C::LOADS>{});
+            });
+        static_for<0, D - 1>([&](auto u_c) {
+            constexpr int U = decltype(u_c)::value;
+            if (c + U < n_stages)
+                step(u_c, c + U, std::false_type{}, std::integral_constant<int, (D - 3 - U > 0 ? D - 3 - U : 0) * C::LOADS>{});
+        });
+        if (!(kg & 1)) swap();
+    } else {
     int c;
     if (KG > 1 && (kg & 1)) c = main_loop(std::true_type{});
     else c = main_loop(std::false_type{});
@@ -352,6 +455,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
             compute(u_c, c + U);
         }
     });
+    }
 
     if constexpr (KG > 1) {
         // sum the k groups through LDS, group by group in a fixed order; group 0 stores

@@ -34,6 +34,23 @@ def test_gemm_rows_of_twelve_tiles(M, N, K, tiles, mt_pass, splits):
     assert float((out - ref).abs().max()) <= 2e-5 * scale + 1e-6         # fp32 accumulation, as everywhere
 
 
+@pytest.mark.parametrize("M,N,planes", [(272, 22016, 2), (112, 57344, 2), (150, 4096, 2), (300, 12288, 2), (20, 22016, 1), (300, 12288, 1)])
+@pytest.mark.parametrize("K", [32, 64, 96, 160, 224, 232])
+def test_k_groups_in_turns_at_short_k(M, N, planes, K):
+    """Fewer k-steps than pipeline stages, remainders of the pipeline's round, and a second k group with fewer k-steps
+    than the first, or none: tall passes, passes of 5, one plane."""
+    import paper_2401_12522_amd as bita
+    g = torch.Generator().manual_seed(N + K + M)
+    a32 = torch.randn(M, K, generator=g)
+    hi = a32.to(torch.bfloat16)
+    lo = (a32 - hi.float()).to(torch.bfloat16) if planes == 2 else None
+    w = (torch.randn(N, K, generator=g) * 0.05).to(torch.bfloat16)
+    out = bita.gemm(hi.cuda(), bita.pack_weight(w.cuda()), N, a_lo=lo.cuda() if planes == 2 else None).cpu().double()
+    ref = (hi.double() + (lo.double() if planes == 2 else 0.0)) @ w.double().T
+    assert torch.isfinite(out).all()
+    assert float((out - ref).abs().max()) <= 2e-5 * float(ref.abs().max()) + 1e-6
+
+
 @pytest.mark.parametrize("d_ffn,batch,tiles", [(11008, 4, 12), (10976, 3, 12), (11024, 4, 12), (6160, 8, 16), (6128, 8, 12), (11520, 5, 12)])
 def test_gated_output_of_twelve_tile_workgroups(d_ffn, batch, tiles):
     """One layer with a wide FFN on passes of 68 rows x batch; the pass with the widths' own launch shapes
