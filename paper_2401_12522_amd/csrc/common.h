@@ -135,7 +135,7 @@ __device__ __forceinline__ float row_scale_finish(const RowScale &rs, const RowS
     return 1.0f / sqrtf(tot * rs.inv_d + rs.eps);
 }
 __device__ __forceinline__ float row_scale(const RowScale &rs, int m) { return row_scale_finish(rs, row_scale_fetch(rs, m)); }
-// mt_pass: m-tiles per row pass of a tall launch (6..9), 0 = the variant's own row handling;
+// mt_pass: m-tiles per row pass of a tall launch (6..11), 0 = the variant's own row handling;
 // tall_tiles: weight tiles per workgroup of a tall launch (16 or 12)
 struct GemmPlan { int splits, ksteps_per_split, variant, mt_pass, tall_tiles; };
 // What a GEMM launch with a single split (complete sums in its accumulators) may do instead of

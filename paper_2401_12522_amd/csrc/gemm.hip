@@ -385,8 +385,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         auto read = [&](auto slot_c, auto sub_c) __attribute__((always_inline)) {
             constexpr int SLOT = decltype(slot_c)::value, F0 = decltype(sub_c)::value * PER;
             static_for<0, (NF - F0 < PER ? NF - F0 : PER)>([&](auto f_c) {
-                constexpr int F = decltype(f_c)::value;
-                a[F] = lds_read_frag<(SLOT * NF + F0 + F) * 1024>(lds_lane_base);
+                constexpr int F = decltype(f_c)::value, AT = (SLOT * NF + F0 + F) * 1024, HIGH = AT < 65536 ? 0 : 32768;   // (16-bit offsets)
+                a[F] = lds_read_frag<AT - HIGH>(lds_lane_base + HIGH);
             });
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -755,7 +755,7 @@ struct GemmVariant { int nw, waves, depth, kgroups; };
 static const GemmVariant g_variants[] = {
     {1, 4, 4, 1}, {2, 4, 4, 1}, {4, 4, 4, 1}, {2, 8, 6, 1}, {4, 8, 6, 1},
     {2, 8, 4, 2}, {4, 8, 4, 2}, {1, 8, 4, 2}, {2, 8, 3, 2}, {2, 16, 3, 2}, {2, 6, 3, 2}, {2, 14, 3, 2},
-    {4, 8, 3, 2},     // 12: tall passes (6 to 9 m-tiles per pass), 16 tiles per k group (or 12: GemmPlan::tall_tiles)
+    {4, 8, 3, 2},     // 12: tall passes (6 to 11 m-tiles per pass), 16 tiles per k group (or 12: GemmPlan::tall_tiles; always from 10 m-tiles on)
 };
 #define GEMM_N_VARIANTS ((int)(sizeof(g_variants) / sizeof(g_variants[0])))
 static int g_force_variant = -1, g_force_splits = -1;
@@ -905,6 +905,22 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
             passes = five_passes;
             p.variant = five_variant;
         }
+        // Passes of 10 and 11 m-tiles, on 12 weight tiles, where the estimate falls by another tenth: row counts that 6 to 9 fill
+        // badly (300 rows as 2 passes of 10 instead of 4 of 5: 22016 x 4096 128.7 -> 94.5 us, 12288 x 4096 70.1 -> 63.8, 7088 x
+        // 16128 140 -> 127; 340 as 2 of 11: 22016 x 4096 130.6 -> 102.7; 152 as one of 10: 40960 x 2048 74.0 -> 51.8; over 21
+        // matrices at 25 row counts 23 launches, all within 1 % or faster; at 0.92 two of 26 are 3 and 7 % slower).
+        const GemmVariant &v = g_variants[p.variant];
+        int sp = 1;
+        double t_now = estimate(p.mt_pass ? p.mt_pass : 5, passes, p.mt_pass ? p.tall_tiles : v.nw * v.waves / v.kgroups, &sp);
+        t_now *= 0.9;
+        for (int mt = 10; mt <= 11 && passes >= 2; mt++) {
+            const int n_pass = (m_tiles + mt - 1) / mt;
+            if ((m_tiles + n_pass - 1) / n_pass != mt) continue;
+            const double t = estimate(mt, n_pass, 12, &sp);
+            if ((NT + 15) / 16 * n_pass * sp < 128 || t >= t_now) continue;
+            if (sp > 1 && (((size_t)sp * m_rows * n_rows * 4 + 255) & ~(size_t)255) + frag_bytes(m_rows, k) > BITA_NOALLOC_SCRATCH_BYTES) continue;
+            t_now = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; p.tall_tiles = 12;
+        }
     }
     if (g_force_variant >= 0 && g_force_variant < GEMM_N_VARIANTS) p.variant = g_force_variant;
     const GemmVariant &v = g_variants[p.variant];
@@ -1009,7 +1025,12 @@ void launch_gemm(const void *a_frag, bool two_planes, int M, int64_t K, const vo
             } else if (d) launch_gemm_t<MT_, 4, true, 8, 3, 2, true>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
             else launch_gemm_t<MT_, 4, true, 8, 3, 2, false>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
             return;
-        switch (p.mt_pass) { TALL(6) TALL(7) TALL(8) TALL(9) }
+#define TALL12(MT_) case MT_: \
+            if (d) launch_gemm_t<MT_, 3, true, 8, 3, 2, true>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
+            else launch_gemm_t<MT_, 3, true, 8, 3, 2, false>(a_frag, M, K, w, N, out, ldo, p, s, direct); \
+            return;
+        switch (p.mt_pass) { TALL(6) TALL(7) TALL(8) TALL(9) TALL12(10) TALL12(11) }
+#undef TALL12
 #undef TALL
     }
     if (M <= 16) {
