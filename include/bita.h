@@ -345,7 +345,9 @@ int bita_gemm_plan_info(int32_t m_rows, int64_t n_rows, int64_t k, int32_t *out4
  * weight tiles (16 columns each) per workgroup of a tall launch, 16 or 12, 0 where the launch is not tall. */
 int bita_gemm_plan_detail(int32_t m_rows, int64_t n_rows, int64_t k, int32_t planes, int32_t *out5);
 /* How tree attention over these sizes is cut into workgroups (for tests and reports; page_size 0: contiguous cache):
- * out5 (HOST) = {key splits, query heads per workgroup, rows per workgroup, waves per workgroup, workgroups}. */
+ * out5 (HOST) = {key splits, query heads per workgroup, rows per workgroup, waves per workgroup, workgroups}, before
+ * neighbouring row tiles of a head are joined to workgroups that share chunks, which launches with one head per workgroup
+ * and many workgroups do. */
 int bita_attention_plan_info(int32_t batch, int32_t rows, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
                              int32_t ctx_hint, int32_t n_prompt, int32_t page_size, int32_t *out5);
 

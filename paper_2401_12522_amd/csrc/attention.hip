@@ -12,6 +12,9 @@
 //    per workgroup no split over the keys is needed to fill the chip at the verify shapes,
 //    so the output is normalised and written in place (no partial results, no second kernel)
 //    unless the context is long enough for the planner to ask for key splits.
+//  * Where many workgroups of single heads would queue, two or four neighbouring row tiles of a head run as one workgroup
+//    whose waves share every chunk (T below): each fetches its part of it into one of two buffers of the key group,
+//    and a barrier per chunk keeps them in step.
 //  * Workgroups that read the same K/V head are placed on the same XCD (consecutive workgroup
 //    ids go round-robin over the 8 XCDs), so a head's K/V comes from HBM once and from that
 //    XCD's L2 for the other m-tiles and query heads of the group.
@@ -129,8 +132,8 @@ __device__ __forceinline__ void lds_wait_all(u32x4 (&k)[2][N], s16x4 (&v)[M][2])
     }
 }
 
-// U tiles of 16 queries and W waves per workgroup
-template <int HD, int U, int W>
+// U tiles of 16 queries per wave, W waves per workgroup, of which T neighbours share every chunk
+template <int HD, int U, int W, int T = 1>
 struct AttCfg {
     static constexpr int KSN = HD / 32;                       // k-steps of the QK^T contraction
     static constexpr int NTN = HD / 16;                       // 16-wide tiles of the head dimension
@@ -139,7 +142,10 @@ struct AttCfg {
     static constexpr int NVI = ATT_CHUNK / RPI;               // such instructions per chunk
     static constexpr int KV_BYTES = ATT_CHUNK * HD * 2;       // the K (or V) rows of one chunk
     static constexpr int CHUNK_BYTES = 2 * KV_BYTES;          // one ring slot: [K rows | V rows]
-    static constexpr int RING_BYTES = W * CHUNK_BYTES;       // one buffer per wave
+    static constexpr int G = W / T;                           // key groups: waves, or sets of T, with chunks of their own
+    static constexpr int IPW = NVI / T;                       // load instructions (K, and V) per wave and chunk
+    static constexpr int BUFS = T > 1 ? 2 : 1;                // chunk buffers per key group
+    static constexpr int RING_BYTES = G * BUFS * CHUNK_BYTES;
     // the merge: every wave's tiles over the chunk buffers, and behind them its rows' maxima and sums
     static constexpr int MERGE_BYTES = U * W * NTN * 64 * 16, ML_BYTES = 2 * U * W * 16 * 4;
     static constexpr int ML = RING_BYTES > MERGE_BYTES ? RING_BYTES : MERGE_BYTES;
@@ -162,7 +168,7 @@ __device__ __forceinline__ constexpr int att_swizzle_k(int rho) { return HD == 1
 // PAGED: the cache operands are page pools [n_pages][Hkv][page][HD] and key slot s of sequence b
 // lives in page table[b][s >> page_lg] at row s & (page - 1); the sequence's table entries are
 // copied to LDS (behind the chunk buffers) once per workgroup.
-template <int HD, int U, int W, bool PAGED>
+template <int HD, int U, int W, int T, bool PAGED>
 __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void tree_attn_kernel(
     // the first 14 dwords arrive in scalar registers with the wave (kernel-argument preload):
     // what the workgroup needs to find its work and to issue its first loads comes first
@@ -175,7 +181,8 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int32_t *__restrict__ token, float scale_log2, float *__restrict__ part_o, float *__restrict__ part_ml,
     uint16_t *__restrict__ out, uint16_t *__restrict__ out_lo, int as_fragments, int m_tiles_out, PageMap pm,
     const int32_t *__restrict__ only_row) {
-    using C = AttCfg<HD, U, W>;
+    using C = AttCfg<HD, U, W, T>;
+    constexpr int G = C::G, IPW = C::IPW;
     constexpr int KSN = C::KSN, NTN = C::NTN, GPR = C::GPR, RPI = C::RPI, NVI = C::NVI;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -195,7 +202,8 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // workgroup's second tile has the same rows of the next heads.
     const int n_mt = n_mt_lg & 0xFFFF, lg_ht = U > 1 ? (n_mt_lg >> 16) & 0xFF : 0, lg_rows = 4 - lg_ht;
     const int qh = w_in / n_mt;
-    int mt = n_mt - 1 - (w_in - qh * n_mt);                                  // long m-tiles first
+    int mt = n_mt - 1 - (w_in - qh * n_mt);                                  // long m-tiles (sets of T of them) first
+    const int kgrp = T > 1 ? wave / T : wave, tsub = T > 1 ? wave % T : 0;   // key group, tile of the set
     const int turn = group / Hkv, kvh = group - turn * Hkv;
     // Sequences take their turns longest first where the host asks for it (bit 25): lane 8i + j compares sequences i and j.
     int b = turn, Lc;
@@ -214,7 +222,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // its row tile is launched.  A prefill's last layer, 488 rows on 512, 32 heads: 27.7 -> 17.9 us, the other tiles'
     // workgroups leaving behind their first chunk before.  (Two tiles per workgroup have no registers for it: a spill, 1 %
     // of every launch.  They leave below.)
-    if (U == 1 && (n_mt_lg >> 24 & 1)) mt = min(max(only_row[b], 0), R - 1) >> lg_rows;
+    if (U == 1 && T == 1 && (n_mt_lg >> 24 & 1)) mt = min(max(only_row[b], 0), R - 1) >> lg_rows;
     const int h0 = kvh * qpk + (U > 1 ? qh << (1 + lg_ht) : qh);                // the workgroup's first head
 
     const int32_t *tbl = reinterpret_cast<const int32_t *>(smem + C::SMEM);
@@ -229,16 +237,16 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             dst[i] = min(max(pm.table[(int64_t)b * pm.max_pages + i], 0), pm.n_pages - 1);
         __syncthreads();
     }
-    const int row0 = mt << lg_rows;
+    const int row0 = (mt * T + tsub) << lg_rows, row_end = min(R, (mt + 1) * T << lg_rows);   // of the wave, of the workgroup
     const int n_ctx_keys = P + Lc;
     const int n_cc = (n_ctx_keys + ATT_CHUNK - 1) / ATT_CHUNK;           // chunks over [prefix | cache]
-    const int n_tc = min((R + 15) >> 4, ((row0 + (1 << lg_rows) - 1) >> 4) + 1);   // chunks over the pass rows
+    const int n_tc = (row_end + 15) >> 4;                                // chunks over the pass rows
     const int n_chunks = n_cc + n_tc;
     const int per_split = (n_chunks + n_splits - 1) / n_splits;
     const int chunk_begin = split * per_split;
     const int chunk_end = min(n_chunks, chunk_begin + per_split);
-    // this wave's chunks: chunk_begin + wave + W * i, i < n_my
-    const int n_my = max(0, (chunk_end - chunk_begin - wave + W - 1) / W);
+    // this wave's chunks: chunk_begin + kgrp + G * i, i < n_my (waves that share go round as often as the first key group)
+    const int n_my = max(0, (chunk_end - chunk_begin - kgrp + G - 1) / G);
 
     const uint16_t *pk = prompt_k + (int64_t)kvh * P * HD, *pv = prompt_v + (int64_t)kvh * P * HD;
     const int64_t page_stride = (int64_t)Hkv * HD << page_lg;           // elements per page (all kv heads)
@@ -297,7 +305,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         l_run[u] = 0.f;
     }
 
-    unsigned char *v_ring = smem + wave * C::CHUNK_BYTES;              // this wave's private chunk buffer
+    unsigned char *v_ring = smem + kgrp * (C::BUFS * C::CHUNK_BYTES);  // the key group's chunk buffer, or two that take turns
     // LDS addresses of this lane's transposed V reads inside ring slot 0: lane (g, c) addresses
     // V[slot 8g + 4half + c/4][16nt + 4(c%4) .. +4] and receives V[slots 8g + 4half .. +4][16nt + c]
     // ... and of its K fragment reads: sub-tile tt, k-step ks = row 16tt + c, granule 4ks + g
@@ -330,8 +338,10 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // per operand plus the constant lane offsets; the other cases select per lane.
     typedef const __attribute__((address_space(1))) unsigned char *gptr;   // keeps the loads global, not flat
     uint64_t anc_next = 0;                                              // ancestor bits for the stage in flight
-    auto emit = [&](int i, int iv) __attribute__((always_inline)) {
-        const int chunk = chunk_begin + wave + W * i;
+    auto emit = [&](int i, int j_iv) __attribute__((always_inline)) {
+        const int iv = T > 1 ? tsub * IPW + j_iv : j_iv;
+        unsigned char *buf = T > 1 ? v_ring + (i & 1) * C::CHUNK_BYTES : v_ring;
+        const int chunk = chunk_begin + kgrp + G * i;
         const int base = chunk * ATT_CHUNK;
         const uint32_t k_gran_iv = ((lane % GPR) ^ att_swizzle_k<HD>((iv & 3) * RPI + v_lane_row)) * 16;
         const uint32_t v_gran_iv = ((lane % GPR) ^ att_swizzle<HD>((iv & 1) * RPI + v_lane_row)) * 16;
@@ -362,10 +372,10 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             v_src = (gptr)(reinterpret_cast<const unsigned char *>(vrow) + v_gran_iv);
         }
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)k_src,
-                                         (__attribute__((address_space(3))) void *)(v_ring + iv * 1024), 16, 0, 0);
+                                         (__attribute__((address_space(3))) void *)(buf + iv * 1024), 16, 0, 0);
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)v_src,
-                                         (__attribute__((address_space(3))) void *)(v_ring + C::KV_BYTES + iv * 1024), 16, 0, 0);
-        if (iv == NVI - 1) anc_next = *(const __attribute__((address_space(1))) uint64_t *)a_src;
+                                         (__attribute__((address_space(3))) void *)(buf + C::KV_BYTES + iv * 1024), 16, 0, 0);
+        if (j_iv == IPW - 1) anc_next = *(const __attribute__((address_space(1))) uint64_t *)a_src;
     };
 
     // The same two loads for a chunk known to lie wholly inside the cache (all but a handful), as
@@ -383,14 +393,15 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     uint32_t k_off[4], v_off[2];
 #pragma unroll
     for (int par = 0; par < 4; par++) {
-        const int rho = par * RPI + v_lane_row;                         // (source granule, in bytes, at this lane's position)
+        const int rho = ((T > 1 ? tsub * IPW : 0) + par) * RPI + v_lane_row;                         // (source granule, in bytes, at this lane's position)
         k_off[par] = (uint32_t)lane_slot * (HD * 2) + ((lane % GPR) ^ att_swizzle_k<HD>(rho)) * 16;
         if (par < 2) v_off[par] = (uint32_t)lane_slot * (HD * 2) + ((lane % GPR) ^ att_swizzle<HD>(rho)) * 16;
     }
-    auto emit_cache = [&](__amdgpu_buffer_rsrc_t kr, __amdgpu_buffer_rsrc_t vr, uint32_t chunk_bytes, int iv) __attribute__((always_inline)) {
+    auto emit_cache = [&](__amdgpu_buffer_rsrc_t kr, __amdgpu_buffer_rsrc_t vr, uint32_t chunk_bytes, unsigned char *buf, int j) __attribute__((always_inline)) {
+        const int iv = T > 1 ? tsub * IPW + j : j;
         const uint32_t at = chunk_bytes + (uint32_t)att_slot_of_row(iv * RPI) * (HD * 2);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void *)(v_ring + iv * 1024), 16, k_off[iv & 3], at, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void *)(v_ring + C::KV_BYTES + iv * 1024), 16, v_off[iv & 1], at, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void *)(buf + iv * 1024), 16, k_off[j & 3], at, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void *)(buf + C::KV_BYTES + iv * 1024), 16, v_off[j & 1], at, 0, 0);
     };
 
     // One chunk.  Its K and V fragments are all pulled into registers first, which frees the
@@ -398,11 +409,15 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // with the QK^T matrix instructions, and have the rest of the step to land.
     auto compute = [&](int i, bool more) __attribute__((always_inline)) {
         const uint64_t anc_cur = anc_next;
-        const int chunk = chunk_begin + wave + W * i;
+        const int chunk = chunk_begin + kgrp + G * i;
         const bool tree_chunk = chunk >= n_cc;
         const int base = chunk * ATT_CHUNK;
         u32x4 kf[2][KSN];
         uint32_t ka = k_addr, va = v_addr;
+        if constexpr (T > 1) {
+            ka += (i & 1) * C::CHUNK_BYTES;
+            va += (i & 1) * C::CHUNK_BYTES;
+        }
         if constexpr (U > 1 && HD == 128) asm volatile("" : "+v"(ka), "+v"(va));   // (the derived addresses are not kept across chunks)
 #pragma unroll
         for (int ks = 0; ks < KSN; ks++) {
@@ -429,7 +444,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 s_acc[u][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qf[u][1][ks], s_acc[u][tt], 0, 0, 0);
             }
         };
-        const int base_n = base + W * ATT_CHUNK;                 // the wave's next chunk
+        const int base_n = base + G * ATT_CHUNK;                 // the wave's next chunk
         if (more && base_n >= P && base_n + ATT_CHUNK <= desc_end && one_page(base_n - P)) {   // wave-uniform
             // contiguous: one descriptor for the sequence's slots; paged: one for the chunk's page
             const int64_t first = PAGED ? (int64_t)__builtin_amdgcn_readfirstlane(tbl[(base_n - P) >> page_lg]) * page_stride : 0;
@@ -440,9 +455,10 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)(ck + first), 0, span, 0x00027000);
             const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)(cv + first), 0, span, 0x00027000);
             const uint32_t chunk_bytes = slot * (HD * 2);
+            unsigned char *buf = T > 1 ? v_ring + ((i + 1) & 1) * C::CHUNK_BYTES : v_ring;
 #pragma unroll
             for (int iv = 0; iv < NVI; iv++) {
-                emit_cache(kr, vr, chunk_bytes, iv);
+                if (iv < IPW) emit_cache(kr, vr, chunk_bytes, buf, iv);
                 __builtin_amdgcn_sched_barrier(0);
                 qk(iv);
                 __builtin_amdgcn_sched_barrier(0);
@@ -451,7 +467,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         } else if constexpr (U == 1 || HD == 64) {
 #pragma unroll
             for (int iv = 0; iv < NVI; iv++) {
-                if (more) emit(i + 1, iv);
+                if (iv < IPW && more) emit(i + 1, iv);
                 __builtin_amdgcn_sched_barrier(0);
                 qk(iv);
                 __builtin_amdgcn_sched_barrier(0);
@@ -461,7 +477,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             // between them they cost the registers (a reload per chunk) and most of the instructions
             if (more) {
 #pragma unroll 1
-                for (int iv = 0; iv < NVI; iv++) emit(i + 1, iv);
+                for (int iv = 0; iv < IPW; iv++) emit(i + 1, iv);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -566,7 +582,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // ---- per-wave loop: one chunk in flight behind the one being multiplied -------------------
     if (n_my > 0) {
 #pragma unroll
-        for (int iv = 0; iv < NVI; iv++) emit(0, iv);
+        for (int iv = 0; iv < IPW; iv++) emit(0, iv);
     }
     att_wait<0>();                                      // the first chunk and the prologue's loads have landed
     // (looked at here, where the prologue's loads have landed anyway: ahead of them it cost 0.5 % of
@@ -577,9 +593,28 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     asm volatile("" : "+v"(row_flags));                 // (looked at here, not inside the loop)
     row_mask = (row_flags & 1) != 0;
     const bool row_present = (row_flags & 2) != 0;
-    for (int i = 0; i < n_my; i++) {
-        compute(i, i + 1 < n_my);
-        att_wait<0>();                                  // the next chunk has landed
+    if constexpr (T == 1) {
+        for (int i = 0; i < n_my; i++) {
+            compute(i, i + 1 < n_my);
+            att_wait<0>();                              // the next chunk has landed
+        }
+    } else {
+        // A barrier per chunk: every sharing wave's part of it has landed, and all have read the buffer that is refilled
+        // next.  A wave whose rows are past the pass, or before all rows of a chunk, only loads its part.
+        const int n_round = max(0, (chunk_end - chunk_begin + G - 1) / G);
+        for (int i = 0; i < n_round; i++) {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            const int chunk = chunk_begin + kgrp + G * i;
+            if (i < n_my && row0 < R && (chunk < n_cc || ((chunk - n_cc) << 4) < row0 + (1 << lg_rows))) {
+                compute(i, i + 1 < n_my);
+            } else if (i + 1 < n_my) {
+#pragma unroll 1
+                for (int iv = 0; iv < IPW; iv++) emit(i + 1, iv);
+            }
+            att_wait<0>();
+        }
     }
 
     // ---- merge the wavefronts (disjoint key subsets): every wave leaves its maxima and sums, then its
@@ -605,11 +640,11 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     for (int u = 0; u < U; u++) {
         m_tot[u] = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < W; w++) m_tot[u] = fmaxf(m_tot[u], sm[(u * W + w) * 16 + c_m]);
+        for (int w = 0; w < G; w++) m_tot[u] = fmaxf(m_tot[u], sm[(u * W + w * T + tsub) * 16 + c_m]);
         const float m_use = (m_tot[u] == -INFINITY) ? 0.f : m_tot[u];
         l_tot[u] = 0.f;
 #pragma unroll
-        for (int w = 0; w < W; w++) l_tot[u] += sl[(u * W + w) * 16 + c_m] * fast_exp2(sm[(u * W + w) * 16 + c_m] - m_use);
+        for (int w = 0; w < G; w++) l_tot[u] += sl[(u * W + w * T + tsub) * 16 + c_m] * fast_exp2(sm[(u * W + w * T + tsub) * 16 + c_m] - m_use);
         const float f = fast_exp2(m_run[u] - m_use);
 #pragma unroll
         for (int nt = 0; nt < NTN; nt++)
@@ -622,11 +657,11 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     for (int u = 0; u < U; u++) {
         const int h = hq_m + (u << lg_ht);
 #pragma unroll
-        for (int nt = wave; nt < NTN; nt += W) {     // this wave's columns of the head, 16 at a time
-            float4 o = region[(u * W * NTN + nt) * 64 + lane_m];
+        for (int nt = kgrp; nt < NTN; nt += G) {     // this wave's columns of the head, 16 at a time
+            float4 o = region[((u * W + tsub) * NTN + nt) * 64 + lane_m];
 #pragma unroll
-            for (int w = 1; w < W; w++) {
-                const float4 v = region[((u * W + w) * NTN + nt) * 64 + lane_m];
+            for (int w = 1; w < G; w++) {
+                const float4 v = region[((u * W + w * T + tsub) * NTN + nt) * 64 + lane_m];
                 o.x += v.x; o.y += v.y; o.z += v.z; o.w += v.w;
             }
             // ---- lane (g, c) holds O[row rq][hd 16nt + 4g .. +4] -----------------------------------
@@ -787,27 +822,52 @@ AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, int hd, const AttnPla
     const bool long_end = (rounds & 1) && (table_entries ? walk > 17 * rounds
                                                          : a.tiles == 1 && p.splits == 1 && rounds == 3 && a.workgroups >= 640 && walk >= 120);
     a.waves = rounds > 1 && fits && !long_end ? 4 : 8;
+    // Where workgroups of one head and four waves queue (512 are held at once) two or four neighbouring row tiles of a head can
+    // run as one workgroup whose waves share every chunk: half or a quarter of the loads, which bound these launches, and of
+    // the workgroups, but a barrier per chunk, and a longer walk for every wave.  A round of such workgroups, full or not, takes
+    // 1.5 or 2.55 times as long as one of single tiles (several sequences, 128-wide heads; of a single tiles' last round half counts
+    // as its share), so two tiles pay where they save a round or most of one, four where two still queue.  single / shared, us, 32 heads
+    // unless stated: 68 rows, 4 sequences up to 900 keys 31.8 / 26.6, 5 of 900 36.5 / 27.4, 5 of 2200 66.8 / 52.8, 8 of 900
+    // (four tiles) 52.4 / 43.8, 40 rows, 8 of 900 38.8 / 29.2, 100 rows, 3 of 900 30.9 / 26.5, 256 rows, 2 of 1000 46.0 / 37.0, 40 heads,
+    // 25 rows, 8 of 1000 36.1 / 31.4; but 68 rows, 6 of 900 (960 workgroups, 576 shared) 38.9 / 41.6 and, four tiles, 100 rows,
+    // 5 of 2200 77.1 / 80.4, which the rule leaves out.  64-wide heads lose (4 heads, 32 sequences of 1000 21.4 / 22.2).  One sequence's tiles differ in length and queue well by themselves
+    // (300 rows on 512 26.7 / 29.9): only where eight waves over four tiles leave no queue from 960 on do they gain (512 rows
+    // on 512 45.5 / 42.3, on 1500 66.5 / 60.9, 40 heads, 384 rows on 512 40.7 / 36.3).
+    a.share = 1;
+    if (a.tiles == 1 && a.waves == 4 && hd == 128 && p.splits == 1 && !one_row) {
+        auto shared = [&](int t) { return (int64_t)batch * Hq * ((n_mt + t - 1) / t); };
+        auto rounds_of = [](int64_t wgs) { return (double)((wgs + 511) / 512); };
+        if (batch == 1) {
+            if (a.workgroups >= 960 && shared(4) <= 256) a.share = 4;
+        } else if (a.workgroups > 512) {
+            double best = 0.97 * 0.5 * ((double)a.workgroups / 512.0 + rounds_of(a.workgroups));
+            for (int t : {2, 4}) {
+                const double c = (t == 2 ? 1.5 : 2.55) * rounds_of(shared(t));
+                if (c < best) { best = c; a.share = t; }
+            }
+        }
+    }
     return a;
 }
 
 // lg_ht: log2 of the heads that share a tile (two heads per workgroup and more)
-template <int HD, int U, int W, bool PAGED>
+template <int HD, int U, int W, int T, bool PAGED>
 static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo, const void *k_cache, const void *v_cache,
                           const void *k_tree, const void *v_tree, const void *k_tree_lo, const void *v_tree_lo,
                           const void *prompt_k, const void *prompt_v, const int32_t *ctx_len, const int32_t *token,
                           int batch, int Hq,
                           int Hkv, int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
                           void *out_lo, bool out_as_fragments, const PageMap &pm, const int32_t *only_row, int lg_ht, hipStream_t s) {
-    using C = AttCfg<HD, U, W>;
+    using C = AttCfg<HD, U, W, T>;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)tree_attn_kernel<HD, U, W, PAGED>,
+        (void)hipFuncSetAttribute((const void *)tree_attn_kernel<HD, U, W, T, PAGED>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   C::SMEM + (PAGED ? ATT_PAGE_TABLE_MAX * 4 : 0));
         attr_set = true;
     }
     const size_t smem_bytes = C::SMEM + (PAGED ? att_table_bytes(pm.tbl_cap) : 0);
-    const int per_wg = 16 >> lg_ht, n_mt = U == 1 && only_row ? 1 : (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
+    const int per_wg = T * 16 >> lg_ht, n_mt = U == 1 && T == 1 && only_row ? 1 : (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     const int groups = batch * Hkv, per_group = (Hq / Hkv / U >> lg_ht) * n_mt * p.splits;
     const int per_xcd = (groups + 7) / 8, grid_y = per_xcd < 1 << ATT_GRID_Y_LG ? per_xcd : 1 << ATT_GRID_Y_LG;
@@ -819,8 +879,8 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
     // up to 8 % as often as it won.)
     const bool ranked = U > 1 && batch > 1 && batch <= 8 && (int64_t)groups * per_group > (W == 4 ? 512 : 256);
     const dim3 grid(8 * per_group, grid_y, (per_xcd + grid_y - 1) / grid_y);
-    hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, PAGED>), grid, dim3(W * 64), smem_bytes, s,
-                       ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16 | (U == 1 && only_row ? 1 << 24 : 0) | (ranked ? 1 << 25 : 0), p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
+    hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, T, PAGED>), grid, dim3(W * 64), smem_bytes, s,
+                       ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16 | (U == 1 && T == 1 && only_row ? 1 << 24 : 0) | (ranked ? 1 << 25 : 0), p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
                        (const uint16_t *)k_cache, (const uint16_t *)v_cache,
                        (const uint16_t *)k_tree, (const uint16_t *)v_tree, (const uint16_t *)k_tree_lo,
                        (const uint16_t *)v_tree_lo, (const uint16_t *)prompt_k, (const uint16_t *)prompt_v, token,
@@ -835,18 +895,23 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
                            void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s, const int32_t *only_row) {
     const AttnTiles a = attn_tiles(batch, t.rows, Hq, Hkv, hd, p, pm.table ? pm.tbl_cap : 0, only_row != nullptr);
-#define ATT_LAUNCH_P(HD_, U_, W_, PG_) launch_attn_t<HD_, U_, W_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
+#define ATT_LAUNCH_P(HD_, U_, W_, T_, PG_) launch_attn_t<HD_, U_, W_, T_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
                                                    prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, a.lg_ht, s)
 #define ATT_LAUNCH(HD_, U_) do { \
-        if (a.waves == 4) { if (pm.table) ATT_LAUNCH_P(HD_, U_, 4, true); else ATT_LAUNCH_P(HD_, U_, 4, false); } \
-        else { if (pm.table) ATT_LAUNCH_P(HD_, U_, 8, true); else ATT_LAUNCH_P(HD_, U_, 8, false); } } while (0)
-    if (hd == 128) {
+        if (a.waves == 4) { if (pm.table) ATT_LAUNCH_P(HD_, U_, 4, 1, true); else ATT_LAUNCH_P(HD_, U_, 4, 1, false); } \
+        else { if (pm.table) ATT_LAUNCH_P(HD_, U_, 8, 1, true); else ATT_LAUNCH_P(HD_, U_, 8, 1, false); } } while (0)
+#define ATT_SHARED(W_, T_) do { if (pm.table) ATT_LAUNCH_P(128, 1, W_, T_, true); else ATT_LAUNCH_P(128, 1, W_, T_, false); } while (0)
+    if (a.share == 2) ATT_SHARED(4, 2);
+    else if (a.share == 4 && batch > 1) ATT_SHARED(4, 4);
+    else if (a.share == 4) ATT_SHARED(8, 4);
+    else if (hd == 128) {
         if (a.tiles == 2) ATT_LAUNCH(128, 2); else ATT_LAUNCH(128, 1);
     } else {
         if (a.tiles == 2) ATT_LAUNCH(64, 2); else ATT_LAUNCH(64, 1);
     }
 #undef ATT_LAUNCH_P
 #undef ATT_LAUNCH
+#undef ATT_SHARED
     if (p.splits > 1) {
         const int heads_per_block = (256 / (hd / 4)) < Hq ? (256 / (hd / 4)) : Hq;
         hipLaunchKernelGGL(attn_merge_kernel, dim3(only_row ? 1 : t.rows, (Hq + heads_per_block - 1) / heads_per_block, batch),
