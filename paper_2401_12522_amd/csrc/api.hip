@@ -394,10 +394,18 @@ int verify_pass(bita_model *m, const bita_kv *kv, const bita_tree_template *t, c
     for (int l = 0; l < c.n_layers; l++) {
         if (l == 0) launch_embed_prep(d_token, source, td, batch, m->tok_emb, m->mask_emb, d, c.vocab, m->attn_norm[0], x, h, ssq, s);
         else launch_rmsnorm_prep(x, partial, pending, M, d, m->attn_norm[l], h, ssq, s);
-        timed_gemm(h, M, d, m->wqkv[l], nqkv, partial, nqkv, p_qkv, s);
         void *kt = (unsigned char *)kv->k_tree + l * kv_layer_tree, *vt = (unsigned char *)kv->v_tree + l * kv_layer_tree;
-        launch_qkv_rope(partial, p_qkv.splits, batch, td, c.n_heads, c.n_kv_heads, hd, d_ctx_len, m->rope_cos,
-                        m->rope_sin, c.max_pos, q, q_lo, kt, vt, k_lo, v_lo, rs_norm, s);
+        // with a single split the QKV product rotates and stores its columns itself
+        if (gemm_direct_output_possible(p_qkv, GEMM_OUT_ROPE)) {
+            const GemmOutput rotated = {GEMM_OUT_ROPE, rs_norm, nullptr, 0,
+                                        {d_ctx_len, td.depth, m->rope_cos, m->rope_sin, (uint16_t *)q, (uint16_t *)q_lo, (uint16_t *)kt, (uint16_t *)vt,
+                                         (uint16_t *)k_lo, (uint16_t *)v_lo, td.rows, c.n_heads, c.n_kv_heads, hd, c.max_pos}};
+            timed_gemm(h, M, d, m->wqkv[l], nqkv, partial, nqkv, p_qkv, s, &rotated);
+        } else {
+            timed_gemm(h, M, d, m->wqkv[l], nqkv, partial, nqkv, p_qkv, s);
+            launch_qkv_rope(partial, p_qkv.splits, batch, td, c.n_heads, c.n_kv_heads, hd, d_ctx_len, m->rope_cos,
+                            m->rope_sin, c.max_pos, q, q_lo, kt, vt, k_lo, v_lo, rs_norm, s);
+        }
         const bool tail_layer = tail && l == c.n_layers - 1;
         if (tail_layer && !tail->sel_row) break;         // nobody asks for anything but the rows' K/V
         launch_tree_attention(td, q, q_lo, (unsigned char *)kv->k_cache + l * kv_layer_cache,

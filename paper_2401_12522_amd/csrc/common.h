@@ -142,8 +142,22 @@ struct GemmPlan { int splits, ksteps_per_split, variant, mt_pass, tall_tiles; };
 // storing fp32 partials: apply the deferred RMSNorm row factor and store the result, or apply it
 // and the SwiGLU gating to its tile-interleaved gate/up columns and store the next GEMM's
 // activation slab (two bf16 planes, fragment order).
-enum { GEMM_OUT_PARTIAL = 0, GEMM_OUT_SCALED = 1, GEMM_OUT_SILU = 2 };
-struct GemmOutput { int kind; RowScale rs; uint16_t *act_frag; int d_ffn; };
+// GEMM_OUT_ROPE: apply it to the QKV columns, rotate q and k by the row's position and store both planes of q, k and v where
+// qkv_rope_kernel would (the same arithmetic, bit for bit).
+enum { GEMM_OUT_PARTIAL = 0, GEMM_OUT_SCALED = 1, GEMM_OUT_SILU = 2, GEMM_OUT_ROPE = 3 };
+struct RopeOutput {
+    const int32_t *ctx_len, *depth;                 // [B], [R]
+    const float *cos, *sin;                         // [max_pos][hd/2]
+    uint16_t *q, *q_lo, *k, *v, *k_lo, *v_lo;       // [B][R][Hq][hd], [B][Hkv][R][hd]
+    int R, Hq, Hkv, hd, max_pos;
+};
+struct GemmOutput { int kind; RowScale rs; uint16_t *act_frag; int d_ffn; RopeOutput rope; };
+// one rotation pair, rounded the same wherever it is done
+__device__ __forceinline__ void rope_pair(float &x, float &y, float c, float s) {
+    const float nx = __builtin_fmaf(x, c, -(y * s)), ny = __builtin_fmaf(y, c, x * s);
+    x = nx;
+    y = ny;
+}
 bool gemm_direct_output_possible(const GemmPlan &p, int kind);
 void gemm_force_plan(int variant, int splits);   // tuning aid: < 0 restores the heuristic
 // Device bytes of the static scratch behind bita_gemm_noalloc.  The planner knows it because a shape's

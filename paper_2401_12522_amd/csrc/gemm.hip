@@ -90,7 +90,7 @@ __device__ __forceinline__ void static_for(F &&f) {
 // through LDS at the end: twice the waves per partial sum written.
 // PACK: the slab's last m-tile (the pass' tile MT-1) keeps both planes of its rows in its high
 // plane's fragment (frag_pack_offset): the stage has one fragment less, the last of the list.
-template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool PACK = false>
+template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool PACK = false, bool ROPE = false>
 struct GemmCfg {
     static_assert(!PACK || (SPLIT && KC == 1), "packing folds the low plane into the high one");
     static constexpr int WN = WAVES / KG;                       // waves side by side along N
@@ -107,7 +107,10 @@ struct GemmCfg {
     // start 16 banks apart)
     static constexpr int ROW3 = 52;
     static constexpr int STAGE = NW % 2 == 0 ? 2 * (WN * NW * 8 / 16) * MT * 512 : NW == 3 ? WN * MT * 16 * ROW3 * 4 : 0;
-    static constexpr int SMEM = (RING > MERGE ? (RING > STAGE ? RING : STAGE) : (MERGE > STAGE ? MERGE : STAGE)) + 1024;
+    // ... or (rotated QKV columns, any form of two k groups) each wave's sums as rows, 4 floats apart as above
+    static constexpr int ROW = NW * 16 + 4, ROWS = ROPE ? WN * MT * 16 * ROW * 4 : 0;
+    static constexpr int OUT = STAGE > ROWS ? STAGE : ROWS;
+    static constexpr int SMEM = (RING > MERGE ? (RING > OUT ? RING : OUT) : (MERGE > OUT ? MERGE : OUT)) + 1024;
     static_assert((D - 2) * LOADS < 64, "vmcnt counter range");
 };
 
@@ -118,16 +121,18 @@ struct GemmCfg {
 // (68 rows x 22016, 6 MB: 45.2 us plain, 45.5).  The logits of a direct launch go through at every size,
 // though it hardly matters there (one layer and the head, through / plain: 7B, 1 row 149.1 / 149.1 us,
 // 48 rows 196.5 / 197.0, 68 rows 204.8 / 204.0, four sequences of 68 431.4 / 430.2; 13B, 25 rows 213.8 / 214.8).
-template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool DIRECT, bool PACK, bool THROUGH>
+// ROPE: a direct launch that rotates and stores the QKV columns (instantiations of their own: as one more case of the direct
+// ones its code cost gate/up and the LM head of a 64-node step 0.5 %).
+template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool DIRECT, bool PACK, bool THROUGH, bool ROPE>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // The first 14 dwords of the argument block arrive in scalar registers with the wave
     // (kernel-argument preload); everything the first loads depend on is among them, the grid's
     // extent included: read through gridDim it costs one dependent scalar load per component
     // before the first weight load can be issued.
     const uint4 *__restrict__ A_frag, const uint4 *__restrict__ Wp, int planes_stride_f, int M, int m_tiles,
-    int NT, int KS, int ksteps_per_split, int grid_x, int grid_y, int grid_z,
+    int NT, int KS, int ksteps_per_split, int grid_x, int grid_y, int grid_z, int head_tiles,
     float *__restrict__ out, int64_t ldo, GemmOutput direct) {
-    using C = GemmCfg<MT, NW, SPLIT, KC, D, WAVES, KG, PACK>;
+    using C = GemmCfg<MT, NW, SPLIT, KC, D, WAVES, KG, PACK, ROPE>;
     constexpr int WN = C::WN;
     // Which loop: the two k groups in turns (below), or both at once.  Turns from 6 m-tiles on, and with passes of 5 on the
     // forms that many rows take (14 and 16 waves) or with one plane; the packed 5 of a 64-node tree and the forms that 73 to 80
@@ -180,6 +185,18 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         }
     }
     const int t0 = (bx * WN + wn) * NW;
+    // The weight tile behind column tile t: itself, or, for columns that are rotated in pairs half a head apart, the two tiles of a
+    // pair one after the other, so that a workgroup (an even number of tiles) holds whole pairs.
+    int tile_of[NW];
+#pragma unroll
+    for (int j = 0; j < NW; j++) {
+        const int t = min(t0 + j, NT - 1);
+        tile_of[j] = t;
+        if constexpr (ROPE) {
+            const int r = t & (head_tiles - 1);
+            tile_of[j] = t - r + (r >> 1) + (r & 1) * (head_tiles >> 1);
+        }
+    }
     // the workgroup's k range, cut into KG contiguous parts of equal stage count
     const int wg_begin = by * ksteps_per_split;
     const int wg_end = min(KS, wg_begin + ksteps_per_split);
@@ -223,7 +240,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         for (int j = 0; j < NW; j++)
 #pragma unroll
             for (int s = 0; s < KC; s++) {
-                const int t = min(t0 + j, NT - 1), ks = min(ks0 + s, KS - 1);
+                const int t = tile_of[j], ks = min(ks0 + s, KS - 1);
                 typedef uint32_t __attribute__((ext_vector_type(4))) u32x4_t;
                 const u32x4_t q = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Wp + packed_block(t, ks, NT) * 64 + lane));
                 w[SLOT][j][s] = make_uint4(q.x, q.y, q.z, q.w);
@@ -347,7 +364,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         // of a reading phase.
         gptr w_src[NW], a_src[C::FPW];
 #pragma unroll
-        for (int j = 0; j < NW; j++) w_src[j] = (gptr)(Wp + (int64_t)min(t0 + j, NT - 1) * 128);
+        for (int j = 0; j < NW; j++) w_src[j] = (gptr)(Wp + (int64_t)tile_of[j] * 128);
 #pragma unroll
         for (int i = 0; i < C::FPW; i++) {
             const int fc = min(i * WN + wn, NF - 1), mtg = min(bz * MT + fc % MT, m_tiles - 1);
@@ -483,8 +500,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
             }
         }
         // (three tiles per wave: gate and up of a feature sit in different waves, the gating below is done
-        // by all waves from LDS)
-        if (kg != 0 && !(NW == 3 && DIRECT && direct.kind == GEMM_OUT_SILU)) return;
+        // by all waves from LDS, as is the rotation)
+        if (kg != 0 && !ROPE && !(NW == 3 && DIRECT && direct.kind == GEMM_OUT_SILU)) return;
     }
     if constexpr (PACK) {
         // the packed tile's low-plane products sit pack_off rows (pack_off / 4 lane groups)
@@ -579,7 +596,77 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         for (int i = 0; i < MT; i++)
 #pragma unroll
             for (int r = 0; r < 4; r++) sc[i][r] = scale_lds[i * 16 + 4 * g + r];
-        if (direct.kind == GEMM_OUT_SCALED) {
+        if constexpr (ROPE) {
+            // The workgroup's sums as rows in LDS, then eight rotation pairs of a row per item, the items of a row next to each
+            // other: 16-byte stores, up to 128 contiguous bytes of a head's half.  The sums' trip through memory (25 MB at 512 rows of
+            // 7B) and a launch less than qkv_rope_kernel behind a plain epilogue: prefill of 1000 tokens in chunks of 512, 2 layers
+            // 1142 -> 1096 us; two narrow layers 81.4 -> 78.6 replayed, 82.5 -> 76.6 eager.
+            static_assert(KG == 2, "the forms of two k groups");
+            constexpr int PAIRS = WN * NW / 2, ITEMS = PAIRS * 2, PIECE = MT * 16 * C::ROW;
+            static_assert(WN * NW % 2 == 0, "whole pairs");
+            const RopeOutput &o = direct.rope;
+            float *stage = reinterpret_cast<float *>(smem_u4);
+            if (kg == 0) {
+#pragma unroll
+                for (int i = 0; i < MT; i++)
+#pragma unroll
+                    for (int j = 0; j < NW; j++)
+#pragma unroll
+                        for (int r = 0; r < 4; r++) stage[wn * PIECE + (i * 16 + 4 * g + r) * C::ROW + j * 16 + cc] = acc[i][j][r];
+            }
+            __syncthreads();
+            const int half = o.hd >> 1, lg = o.hd == 128 ? 2 : 1;                       // (pairs of tiles per head: 4 or 2)
+            for (int idx = tid; idx < MT * 16 * ITEMS; idx += WAVES * 64) {
+                const int row = idx / ITEMS, item = idx % ITEMS, pr = item >> 1, oct = (item & 1) * 8;
+                const int m = m_base + row, pair = bx * PAIRS + pr, head = pair >> lg, at = (pair & ((1 << lg) - 1)) * 16 + oct;
+                if (m >= M || head >= o.Hq + 2 * o.Hkv) continue;
+                const int b = m / o.R, r = m - b * o.R;
+                int pos = o.ctx_len[b] + o.depth[r];
+                pos = pos < o.max_pos ? pos : o.max_pos - 1;                            // host checks capacity; stay in bounds
+                const float4 *ct = reinterpret_cast<const float4 *>(o.cos + (int64_t)pos * half + at), *st = reinterpret_cast<const float4 *>(o.sin + (int64_t)pos * half + at);
+                const float4 c0 = ct[0], c1 = ct[1], s0 = st[0], s1 = st[1];
+                const float c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w}, sn[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+                const float *xs = stage + 2 * pr / NW * PIECE + row * C::ROW + 2 * pr % NW * 16 + oct;
+                const float *ys = stage + (2 * pr + 1) / NW * PIECE + row * C::ROW + (2 * pr + 1) % NW * 16 + oct;
+                const float4 x0 = *reinterpret_cast<const float4 *>(xs), x1 = *reinterpret_cast<const float4 *>(xs + 4);
+                const float4 y0 = *reinterpret_cast<const float4 *>(ys), y1 = *reinterpret_cast<const float4 *>(ys + 4);
+                const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w}, yv[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
+                const float rsc = scale_lds[row];
+                uint32_t hi[2][4], lo[2][4];
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    uint16_t h[2][2], l[2][2];
+#pragma unroll
+                    for (int f = 0; f < 2; f++) {
+                        float x = xv[e + f] * rsc, y = yv[e + f] * rsc;
+                        if (head < o.Hq + o.Hkv) rope_pair(x, y, c[e + f], sn[e + f]);
+                        split_bf16(x, h[0][f], l[0][f]);
+                        split_bf16(y, h[1][f], l[1][f]);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 2; k++) {
+                        hi[k][e >> 1] = h[k][0] | ((uint32_t)h[k][1] << 16);
+                        lo[k][e >> 1] = l[k][0] | ((uint32_t)l[k][1] << 16);
+                    }
+                }
+                uint16_t *dst, *dst_lo;
+                if (head < o.Hq) {
+                    const int64_t off = ((int64_t)m * o.Hq + head) * o.hd + at;
+                    dst = o.q + off;
+                    dst_lo = o.q_lo + off;
+                } else {
+                    const int kh = head - o.Hq;
+                    const bool key = kh < o.Hkv;
+                    const int64_t off = (((int64_t)b * o.Hkv + (key ? kh : kh - o.Hkv)) * o.R + r) * o.hd + at;
+                    dst = (key ? o.k : o.v) + off;
+                    dst_lo = (key ? o.k_lo : o.v_lo) + off;
+                }
+                *reinterpret_cast<uint4 *>(dst) = make_uint4(hi[0][0], hi[0][1], hi[0][2], hi[0][3]);
+                *reinterpret_cast<uint4 *>(dst + half) = make_uint4(hi[1][0], hi[1][1], hi[1][2], hi[1][3]);
+                *reinterpret_cast<uint4 *>(dst_lo) = make_uint4(lo[0][0], lo[0][1], lo[0][2], lo[0][3]);
+                *reinterpret_cast<uint4 *>(dst_lo + half) = make_uint4(lo[1][0], lo[1][1], lo[1][2], lo[1][3]);
+            }
+        } else if (direct.kind == GEMM_OUT_SCALED) {
             // (the row factors sit in the dump slot behind the ring, outside the staging regions)
             store_tiles(out, [&](int i, int j, int r) { return acc[i][j][r] * sc[i][r]; });
         } else if constexpr (NW == 3) {
@@ -939,9 +1026,15 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
     return p;
 }
 
-template <int MT, int NW, bool SPLIT, int WAVES, int D, int KG, bool DIRECT, bool PACK = false, bool THROUGH = DIRECT>
+template <int MT, int NW, bool SPLIT, int WAVES, int D, int KG, bool DIRECT, bool PACK = false, bool THROUGH = DIRECT, bool ROPE = false>
 static void launch_gemm_t(const void *a_frag, int M, int64_t K, const void *w, int64_t N, float *out, int64_t ldo,
                           const GemmPlan &p, hipStream_t s, const GemmOutput &direct) {
+    if constexpr (DIRECT && SPLIT && KG == 2 && !ROPE && (NW > 2 || WAVES == 8 || WAVES == 16) && D == 3) {
+        if (direct.kind == GEMM_OUT_ROPE) {                    // (the forms that gemm_direct_output_possible says)
+            launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, THROUGH, true>(a_frag, M, K, w, N, out, ldo, p, s, direct);
+            return;
+        }
+    }
     if constexpr (MT > 1 && SPLIT && KG > 1 && !THROUGH) {
         if (p.splits > 1 && (int64_t)p.splits * M * ldo * 4 >= (8 << 20) && ldo <= GEMM_THROUGH_MAX_LD) {
             launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, true>(a_frag, M, K, w, N, out, ldo, p, s, direct);
@@ -949,18 +1042,18 @@ static void launch_gemm_t(const void *a_frag, int M, int64_t K, const void *w, i
         }
     }
     constexpr int KC = 1;
-    using C = GemmCfg<MT, NW, SPLIT, KC, D, WAVES, KG, PACK>;
+    using C = GemmCfg<MT, NW, SPLIT, KC, D, WAVES, KG, PACK, ROPE>;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH>,
+        (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH, ROPE>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
         attr_set = true;
     }
     const int NT = (int)(N / 16), KS = (int)((K + 31) / 32), m_tiles = (M + 15) / 16;
     dim3 grid((NT + C::WN * NW - 1) / (C::WN * NW), p.splits, (m_tiles + MT - 1) / MT);
-    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH>), grid, dim3(WAVES * 64), C::SMEM, s,
+    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH, ROPE>), grid, dim3(WAVES * 64), C::SMEM, s,
                        (const uint4 *)a_frag, (const uint4 *)w, KS * m_tiles, M, m_tiles, NT, KS, p.ksteps_per_split,
-                       (int)grid.x, (int)grid.y, (int)grid.z, out, ldo, direct);
+                       (int)grid.x, (int)grid.y, (int)grid.z, ROPE ? direct.rope.hd / 16 : 0, out, ldo, direct);
 }
 
 template <int MT, bool SPLIT>
@@ -1056,7 +1149,8 @@ void launch_gemm(const void *a_frag, bool two_planes, int M, int64_t K, const vo
     else launch_gemm_v<5, false>(a_frag, M, K, w, N, out, ldo, q, s, direct);
 }
 bool gemm_direct_output_possible(const GemmPlan &p, int kind) {
-    (void)kind;
+    // rotated columns: the forms that plans with a single split and QKV-like widths take
+    if (kind == GEMM_OUT_ROPE) return p.splits == 1 && (p.variant == 8 || p.variant == 9 || p.variant == 12);
     // the k-group shapes with whole gate/up tile pairs per wave, or (12, tall) per workgroup: its waves
     // hold four tiles, or three that are gated from LDS
     return p.splits == 1 && (p.variant == 5 || p.variant == 6 || p.variant >= 8);

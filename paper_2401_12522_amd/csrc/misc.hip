@@ -184,11 +184,7 @@ __global__ __launch_bounds__(ROPE_THREADS) void qkv_rope_kernel(
 #pragma unroll
     for (int e = 0; e < 4; e++) {
         float x = lo[e] * sc, y = hi[e] * sc;
-        if (head < Hq + Hkv) {
-            const float nx = x * c[e] - y * sn[e], ny = y * c[e] + x * sn[e];
-            x = nx;
-            y = ny;
-        }
+        if (head < Hq + Hkv) rope_pair(x, y, c[e], sn[e]);
         split_bf16(x, a_hi[e], a_lo[e]);
         split_bf16(y, b_hi[e], b_lo[e]);
     }
