@@ -880,7 +880,7 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
     // workgroups.  The passes fill the CUs, so fewer k splits are needed, and the widest
     // workgroups (16 waves, or 14 on the gate/up-like widths) share each activation fragment
     // among the most weight tiles.
-    // A single-plane slab has no forms of 6 to 9 m-tiles, neither the one-pass nor the tall ones.  It was
+    // A single-plane slab has no forms of 6 to 11 m-tiles, neither the one-pass nor the tall ones.  It was
     // given their plans and ran them in passes of 5; planned as what it is (whole calls, one plane,
     // splits and workgroups for two planes -> its own): 96 x 22016 x 4096 65.9 -> 56.0 us, 128 rows
     // 70.4 -> 58.8, 272 rows 108.6 -> 99.6; 272 x 12288 x 4096 66.4 -> 54.1; 170 x 4096 x 11008 51.9 -> 42.1.
