@@ -242,7 +242,7 @@ int bita_decode_step(bita_model *m, const bita_kv *kv, const bita_tree_template 
  *                its own row count), kv->ctx_hint an upper bound of ctx_len on
  *                entry
  *   chunk_rows   1..BITA_MAX_ROWS
- *   d_workspace  bita_prefill_workspace_bytes(m, batch, chunk_rows) bytes
+ *   d_workspace  bita_prefill_workspace_bytes(m, batch, chunk_rows) bytes, for any n_tokens
  *   d_next_token [B] or NULL    greedy token that follows each sequence's last
  *                               context token (untouched for empty sequences)
  * The chain templates (at most two row counts per call: chunk_rows and the ragged last

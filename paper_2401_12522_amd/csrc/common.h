@@ -105,8 +105,9 @@ struct bita_model {
     float *rope_cos = nullptr, *rope_sin = nullptr;     // [max_pos][hd/2]
     // chain templates of the prefill chunks by row count, created once and kept until the
     // handle is destroyed (the enqueued kernels read their device arrays)
-    std::mutex chain_mutex;
+    mutable std::mutex chain_mutex;
     std::map<int, bita_tree_template *> chains;
+    mutable std::map<std::pair<int, int>, size_t> chunk_bytes;   // workspace of a prefill's passes by (batch, chunk rows)
 };
 
 // ---- kernel launchers (each only enqueues) --------------------------------------
@@ -160,6 +161,7 @@ __device__ __forceinline__ void rope_pair(float &x, float &y, float c, float s) 
 }
 bool gemm_direct_output_possible(const GemmPlan &p, int kind);
 void gemm_force_plan(int variant, int splits);   // tuning aid: < 0 restores the heuristic
+bool gemm_plan_forced();
 // Device bytes of the static scratch behind bita_gemm_noalloc.  The planner knows it because a shape's
 // plan, and with it the result's last bits, is the same for every caller.
 #define BITA_NOALLOC_SCRATCH_BYTES (32u << 20)

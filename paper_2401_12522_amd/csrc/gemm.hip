@@ -848,6 +848,7 @@ static const GemmVariant g_variants[] = {
 static int g_force_variant = -1, g_force_splits = -1;
 // variant: >= 0 forces that workgroup shape, -1 the heuristic, -2 the heuristic without tall passes
 void gemm_force_plan(int variant, int splits) { g_force_variant = variant < -2 ? -1 : variant; g_force_splits = splits; }
+bool gemm_plan_forced() { return g_force_variant != -1 || g_force_splits > 0; }
 
 GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
     GemmPlan p;

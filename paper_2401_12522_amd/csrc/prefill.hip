@@ -3,6 +3,7 @@
 // parent is row i-1, no mask rows) makes the verify pass a causal forward over
 // [cache ‖ chunk]; committing rows 0..m-1 in order appends the chunk to the cache.
 #include "common.h"
+#include <algorithm>
 #include <vector>
 
 // One launch per chunk: the chunk's token rows (gathered from the [B][n_tokens] input, -1 =
@@ -36,11 +37,11 @@ __global__ void prefill_pick_kernel(const int32_t *__restrict__ argmax, const in
 
 namespace {
 struct PrefillWs { size_t step, tok, argmax, path, n_acc, sel_row, tail, total; };
-PrefillWs prefill_layout(const bita_model *m, int batch, int chunk_rows) {
+PrefillWs prefill_layout(const bita_model *m, int batch, int chunk_rows, size_t step_bytes) {
     PrefillWs L;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
-    L.step = take(bita_workspace_bytes(m, batch, chunk_rows));
+    L.step = take(step_bytes);
     L.tok = take((size_t)batch * chunk_rows * 4);
     L.argmax = take((size_t)batch * 4);
     L.path = take((size_t)batch * chunk_rows * 4);
@@ -49,6 +50,22 @@ PrefillWs prefill_layout(const bita_model *m, int batch, int chunk_rows) {
     L.tail = take(bita_workspace_bytes(m, batch, 1));
     L.total = off;
     return L;
+}
+// What the passes over chunks of up to chunk_rows rows need.  Not the longest chunk's alone: a product of fewer rows may be
+// cut into more k splits, and its partial sums then take more (7B widths, LM head: 144 rows in two splits 37 MB, 145 in one
+// 19 MB).  Planning every row count takes the host 0.45 ms at 512, so the answer stays with the model; not while the launch
+// shapes are forced.
+size_t chunk_workspace(const bita_model *m, int batch, int chunk_rows) {
+    auto most = [&] {
+        size_t bytes = 0;
+        for (int rows = 1; rows <= chunk_rows; rows++) bytes = std::max(bytes, bita_workspace_bytes(m, batch, rows));
+        return bytes;
+    };
+    if (gemm_plan_forced()) return most();
+    std::lock_guard<std::mutex> lock(m->chain_mutex);
+    size_t &bytes = m->chunk_bytes[{batch, chunk_rows}];
+    if (!bytes) bytes = most();
+    return bytes;
 }
 // The model's chain template of `rows` rows.  Created (device allocation and a blocking copy) the
 // first time a row count is asked for, unless may_create is false: then a missing template is an
@@ -85,7 +102,7 @@ extern "C" int bita_prefill_prepare(bita_model *m, int32_t n_tokens, int32_t chu
 
 extern "C" size_t bita_prefill_workspace_bytes(const bita_model *m, int32_t batch, int32_t chunk_rows) {
     if (!m || batch <= 0 || chunk_rows <= 0 || chunk_rows > BITA_MAX_ROWS) return 0;
-    return prefill_layout(m, batch, chunk_rows).total;
+    return prefill_layout(m, batch, chunk_rows, chunk_workspace(m, batch, chunk_rows)).total;
 }
 
 extern "C" int bita_prefill(bita_model *m, const bita_kv *kv, const int32_t *d_tokens, int32_t n_tokens,
@@ -104,7 +121,10 @@ extern "C" int bita_prefill(bita_model *m, const bita_kv *kv, const int32_t *d_t
     if ((int64_t)kv->ctx_hint + n_tokens > m->cfg.max_pos)
         return bita_set_error(BITA_ERR_CAPACITY, "bita_prefill: position %lld beyond rotary table (%d)",
                               (long long)kv->ctx_hint + n_tokens - 1, m->cfg.max_pos);
-    const PrefillWs L = prefill_layout(m, batch, chunk_rows);
+    // (the two row counts of this call: full chunks and the ragged last one)
+    const int last_rows = n_tokens % chunk_rows;
+    const size_t step_bytes = std::max(bita_workspace_bytes(m, batch, chunk_rows), last_rows ? bita_workspace_bytes(m, batch, last_rows) : 0);
+    const PrefillWs L = prefill_layout(m, batch, chunk_rows, step_bytes);
     if (ws_bytes < L.total)
         return bita_set_error(BITA_ERR_CAPACITY, "bita_prefill: workspace %zu < %zu bytes", ws_bytes, L.total);
     if (n_tokens == 0) return BITA_OK;

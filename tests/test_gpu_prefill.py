@@ -379,3 +379,58 @@ def test_next_token_behind_a_split_key_axis(bita, cfg_name, batch, n):
         assert torch.equal(kv[0].v_cache[:, b, :, :ctx + lens[b]], kv[1].v_cache[:, b, :, :ctx + lens[b]])
         assert np.isfinite(last[b]).all()
         assert nxt[b] == argmax_low(last[b]) or _margin(last[b]) < 2e-4, b     # (both sides within 1e-4 of exact logits)
+
+
+def _handle_of_sizes(cfg):
+    """A model handle that is asked for sizes only: every weight pointer is the same few bytes."""
+    from paper_2401_12522_amd import binding as B
+    some = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    w, handle = B._Weights(), B.C.c_void_p()
+    for name, kind in B._Weights._fields_:
+        setattr(w, name, some.data_ptr() if kind is B.C.c_void_p else (B.C.c_void_p * 1)(some.data_ptr()))
+    c = B._Config(1, cfg.d_model, cfg.n_heads, cfg.n_kv_heads, cfg.head_dim, cfg.d_ffn, cfg.vocab, cfg.n_prompt, cfg.n_mask, 16,
+                  cfg.rms_eps, cfg.rope_theta)
+    B._check(B.lib().bita_model_create(B.C.byref(c), B.C.byref(w), B.C.byref(handle)))
+    return handle
+
+
+@pytest.mark.parametrize("cfg_name,over", [("tiny_gqa", {}), ("7b", {}), ("13b", {}), ("70b", {}), ("7b", dict(vocab=512))])
+@pytest.mark.parametrize("batch", [1, 2, 3, 4])
+def test_the_workspace_of_a_chunk_size_holds_every_shorter_chunk(bita, cfg_name, over, batch):
+    """A pass of fewer rows may need more than one of more (more k splits): what a prefill of some chunk size is given has
+    to hold any last chunk."""
+    from paper_2401_12522_amd import binding as B
+    handle, longest = _handle_of_sizes(synth.get_config(cfg_name, n_layers=1, **over)), 512 // batch
+    try:
+        needs = [B.lib().bita_workspace_bytes(handle, batch, r) for r in range(1, longest + 1)]
+        fewer_need_more = [r for r in range(2, longest + 1) if needs[r - 1] < max(needs[:r - 1])]
+        assert bool(fewer_need_more) == (cfg_name in ("7b", "13b") or (cfg_name, batch) == ("70b", 1))
+        for chunk in fewer_need_more + [1, 17, longest]:
+            for _ in range(2):
+                assert B.lib().bita_prefill_workspace_bytes(handle, batch, chunk) >= max(needs[:chunk]) + needs[0], chunk
+    finally:
+        B.lib().bita_model_destroy(handle)
+
+
+@pytest.mark.parametrize("cfg_name,chunk,n,batch", [("7b", 145, 289, 1), ("7b", 73, 145, 2), ("13b", 89, 177, 1)])
+def test_a_last_chunk_that_needs_more_than_the_full_ones(bita, cfg_name, chunk, n, batch):
+    """Widths where one row less than a chunk needs a larger workspace.  The call runs in the workspace it is given, as
+    chunks of another size do, and one that is smaller than its own two chunk sizes need is refused before anything is enqueued."""
+    from paper_2401_12522_amd import binding as B
+    cfg = synth.get_config(cfg_name, n_layers=1)
+    model = bita.Model(cfg, synth.SynthWeights(cfg, seed=4, device="cuda"), max_pos=512)
+    assert model.workspace_bytes(batch, n % chunk) > model.workspace_bytes(batch, chunk)
+    toks = dev_i32(np.random.default_rng(n).integers(0, cfg.vocab, size=(batch, n)))
+    kv, other = bita.KVState(cfg, 1, batch, 512, chunk), bita.KVState(cfg, 1, batch, 512, 64)
+    ws = bita.prefill_workspace(model, batch, chunk)
+    bita.prefill(model, kv, 0, toks, chunk, workspace=ws)
+    bita.prefill(model, other, 0, toks, 64)
+    torch.cuda.synchronize()
+    assert kv.ctx_len.tolist() == other.ctx_len.tolist() == [n] * batch
+    for a, b in ((kv.k_cache, other.k_cache), (kv.v_cache, other.v_cache)):
+        assert bool(((a.float() - b.float()).abs() <= 2.0 ** -7 * b.float().abs() + 1e-5).all())   # one unit of bf16
+    kv.ctx_len.zero_()
+    rc = B.lib().bita_prefill(model.handle, B.C.byref(kv.desc(0)), B._ptr(toks), n, None, B._ptr(kv.ctx_len), batch, chunk,
+                              B._ptr(ws), model.workspace_bytes(batch, n % chunk), None, B._stream())
+    torch.cuda.synchronize()
+    assert rc == -3 and kv.ctx_len.tolist() == [0] * batch       # (the tokens and the last rows need room of their own)
