@@ -204,27 +204,15 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int qh = w_in / n_mt;
     int mt = n_mt - 1 - (w_in - qh * n_mt);                                  // long m-tiles (sets of T of them) first
     const int kgrp = T > 1 ? wave / T : wave, tsub = T > 1 ? wave % T : 0;   // key group, tile of the set
-    const int turn = group / Hkv, kvh = group - turn * Hkv;
-    // Sequences take their turns longest first where the host asks for it (bit 25): lane 8i + j compares sequences i and j.
-    int b = turn, Lc;
-    if (U > 1 && (n_mt_lg >> 25 & 1)) {
-        const int i = lane >> 3, j = lane & 7;
-        const int mine = ctx_len[min(i, batch - 1)], other = ctx_len[min(j, batch - 1)];
-        const uint64_t before = __builtin_amdgcn_ballot_w64(j < batch && (other > mine || (other == mine && j < i)));
-        const int place = __popc((uint32_t)(before >> (8 * i)) & 0xFFu);
-        const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(i < batch && place == turn));
-        b = at >> 3;
-        Lc = __builtin_amdgcn_readlane(mine, at);
-    } else {
-        Lc = ctx_len[b];
-    }
+    const int b = group / Hkv, kvh = group - b * Hkv;
     // One row per sequence is asked for (bit 24, known without a load, so that other launches do not wait for one): only
     // its row tile is launched.  A prefill's last layer, 488 rows on 512, 32 heads: 27.7 -> 17.9 us, the other tiles'
     // workgroups leaving behind their first chunk before.  (Two tiles per workgroup have no registers for it: a spill, 1 %
     // of every launch.  They leave below.)
-    if (U == 1 && T == 1 && (n_mt_lg >> 24 & 1)) mt = min(max(only_row[b], 0), R - 1) >> lg_rows;
+    if (U == 1 && T == 1 && (n_mt_lg >> 24)) mt = min(max(only_row[b], 0), R - 1) >> lg_rows;
     const int h0 = kvh * qpk + (U > 1 ? qh << (1 + lg_ht) : qh);                // the workgroup's first head
 
+    int Lc = ctx_len[b];
     const int32_t *tbl = reinterpret_cast<const int32_t *>(smem + C::SMEM);
     const int page_lg = pm.page_lg, page_mask = (1 << pm.page_lg) - 1;
     if (PAGED) {
@@ -870,17 +858,13 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
     const int per_wg = T * 16 >> lg_ht, n_mt = U == 1 && T == 1 && only_row ? 1 : (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     const int groups = batch * Hkv, per_group = (Hq / Hkv / U >> lg_ht) * n_mt * p.splits;
+    // (Sequences in the batch's order.  Longest first, ranked from the lengths by every workgroup of a launch that queues, cost
+    // equal lengths 1 % (64/8 heads 1.011 of the time over 24 launches, 64/1 heads 1.008) and gave unequal ones nothing on the whole:
+    // lengths within a factor of two 0.996 and 1.005, of four and more 0.995, single launches 0.86 to 1.11.)
     const int per_xcd = (groups + 7) / 8, grid_y = per_xcd < 1 << ATT_GRID_Y_LG ? per_xcd : 1 << ATT_GRID_Y_LG;
-    // Where workgroups queue for the CUs (512 of four waves are held at once, 256 of eight) sequences of different lengths start
-    // longest first, so that the last workgroups are short: 64/8 heads, 68 rows, 8 sequences of 4096 and seven between 1024
-    // and 4096 keys, five draws, in the batch's order / longest first: 139.6 / 132.2, 142.2 / 137.0, 130.0 / 127.4, 153.4 / 133.2 us; of
-    // equal lengths 74.0 / 74.0 (four of 2048), 74.6 / 76.0 (eight of 1024).  Up to 8 sequences: one comparison a lane.  (A loop over
-    // 64 cost every workgroup half a microsecond; and one head per workgroup, whose launches are bound by what they load, lost
-    // up to 8 % as often as it won.)
-    const bool ranked = U > 1 && batch > 1 && batch <= 8 && (int64_t)groups * per_group > (W == 4 ? 512 : 256);
     const dim3 grid(8 * per_group, grid_y, (per_xcd + grid_y - 1) / grid_y);
     hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, T, PAGED>), grid, dim3(W * 64), smem_bytes, s,
-                       ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16 | (U == 1 && T == 1 && only_row ? 1 << 24 : 0) | (ranked ? 1 << 25 : 0), p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
+                       ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16 | (U == 1 && T == 1 && only_row ? 1 << 24 : 0), p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
                        (const uint16_t *)k_cache, (const uint16_t *)v_cache,
                        (const uint16_t *)k_tree, (const uint16_t *)v_tree, (const uint16_t *)k_tree_lo,
                        (const uint16_t *)v_tree_lo, (const uint16_t *)prompt_k, (const uint16_t *)prompt_v, token,

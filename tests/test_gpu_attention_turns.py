@@ -1,5 +1,5 @@
-"""Tree attention (GPU) of several sequences with grouped heads and more workgroups than the CUs hold at once, which start by
-the sequences' lengths: a sequence's output does not depend on its place in the batch or on the others' lengths."""
+"""Tree attention (GPU) of several sequences of unequal lengths with grouped heads and more workgroups than the CUs hold at
+once: a sequence's output does not depend on its place in the batch or on the others' lengths."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("rows,lens", [(130, [40, 300]), (130, [77, 77]), (90, [5, 0, 400]), (70, [64, 64, 63, 65]), (41, [31, 500, 0, 500, 32, 33, 1]),
                                        (33, [1, 2, 3, 4, 5, 6, 7, 300]), (33, [300] * 8), (33, [9, 200, 8, 200, 7, 100, 200, 0])])
-def test_sequences_start_longest_first(rows, lens, hd):
+def test_a_sequence_in_any_place_of_the_batch(rows, lens, hd):
     import paper_2401_12522_amd as bita
     heads, kv_heads, B, smax, P = 64, 8, len(lens), max(lens) + 1, 5
     tin = synth.attach_mask_groups(synth.random_tree(rows, 4, rows), [0], 4)
