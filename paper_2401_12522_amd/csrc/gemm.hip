@@ -994,18 +994,25 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
             p.variant = five_variant;
         }
         // Passes of 10 and 11 m-tiles, on 12 weight tiles, where the estimate falls by another tenth: row counts that 6 to 9 fill
-        // badly (300 rows as 2 passes of 10 instead of 4 of 5: 22016 x 4096 128.7 -> 94.5 us, 12288 x 4096 70.1 -> 63.8, 7088 x
-        // 16128 140 -> 127; 340 as 2 of 11: 22016 x 4096 130.6 -> 102.7; 152 as one of 10: 40960 x 2048 74.0 -> 51.8; over 21
-        // matrices at 25 row counts 23 launches, all within 1 % or faster; at 0.92 two of 26 are 3 and 7 % slower).
+        // badly.  Without / with them, us: 22016 x 4096, 300 rows (2 passes of 10 for 4 of 5) 132.1 / 100.0, 340 (2 of 11 for 5) 136.2 /
+        // 109.0, 145 to 160 rows (one of 10 in two k splits for 2 passes of 5 in one) 75.0 / 66.5; 12288 x 4096, 150 rows (4 splits for 2)
+        // 48.7 / 46.8, 289 rows 73.6 / 66.6; 27648 x 5120, 480 rows 243 / 222; 40960 x 2048, 152 rows 76.1 / 58.7, 170 (one of 11 for two
+        // of 6) 69.9 / 63.1; 11008 x 8192, 147 rows 84.8 / 64.1.  Of 34 launches that take them the slowest are 1 to 2 % behind, within
+        // what one plan differs from itself (16720 x 2240, 145 rows 41.0 / 41.9).  More k splits mean a gating or a rotation in a kernel
+        // of its own, which the estimate leaves out, and it pays all the same in place of passes of 5 (two 7B layers and a small head, 145
+        // rows 413 / 397, 150 418 / 405, 160 423 / 410, 289 646 / 567; of 13B widths, 470 rows 1198 / 1153), but not in place of two passes of 6
+        // (22016 x 4096, 161 rows 67.4 / 69.3, 166 rows 68.0 / 71.9, the two layers 414 / 418 and 416 / 422; 19440 x 4552, 176 rows
+        // 72.8 / 78.1; but 20480 x 6144, 170 rows 96.0 / 92.5): a tall form gives way only to one of no more splits.
         const GemmVariant &v = g_variants[p.variant];
         int sp = 1;
         double t_now = estimate(p.mt_pass ? p.mt_pass : 5, passes, p.mt_pass ? p.tall_tiles : v.nw * v.waves / v.kgroups, &sp);
         t_now *= 0.9;
+        const int tall_splits = p.mt_pass ? sp : 32;
         for (int mt = 10; mt <= 11 && passes >= 2; mt++) {
             const int n_pass = (m_tiles + mt - 1) / mt;
             if ((m_tiles + n_pass - 1) / n_pass != mt) continue;
             const double t = estimate(mt, n_pass, 12, &sp);
-            if ((NT + 15) / 16 * n_pass * sp < 128 || t >= t_now) continue;
+            if ((NT + 15) / 16 * n_pass * sp < 128 || t >= t_now || sp > tall_splits) continue;
             if (sp > 1 && (((size_t)sp * m_rows * n_rows * 4 + 255) & ~(size_t)255) + frag_bytes(m_rows, k) > BITA_NOALLOC_SCRATCH_BYTES) continue;
             t_now = t; p.mt_pass = mt; passes = n_pass; p.variant = 12; p.tall_tiles = 12;
         }

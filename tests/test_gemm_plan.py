@@ -76,3 +76,20 @@ def test_tall_passes_where_they_are_faster(m, n, k, variant, mt_pass, tiles, spl
     _lib()
     plan = B.gemm_plan_info(m, n, k)
     assert (plan["variant"], plan["mt_pass"], plan["tall_tiles"], plan["splits"]) == (variant, mt_pass, tiles, splits), plan
+
+
+@pytest.mark.parametrize("m,n,k,mt_pass,splits", [
+    # in place of passes of 5, with more k splits too
+    (145, 22016, 4096, 10, 2), (160, 22016, 4096, 10, 2), (150, 12288, 4096, 10, 4), (289, 12288, 4096, 10, 2), (150, 20480, 6144, 10, 2),
+    (300, 22016, 4096, 10, 1), (340, 22016, 4096, 11, 1), (470, 27648, 5120, 10, 1), (152, 40960, 2048, 10, 1),
+    # in place of two passes of 6 m-tiles with as many splits, but not with more
+    (161, 40960, 2048, 11, 1), (176, 40960, 2048, 11, 1), (161, 22016, 4096, 6, 1), (166, 22016, 4096, 6, 1), (161, 19440, 4552, 6, 1),
+    (176, 19440, 4552, 6, 1), (170, 20480, 6144, 6, 1),
+    # left with passes of 5
+    (300, 12288, 4096, 0, 1), (300, 7088, 16128, 0, 2)])
+def test_passes_of_ten_and_eleven(m, n, k, mt_pass, splits):
+    from paper_2401_12522_amd import binding as B
+    _lib()
+    plan = B.gemm_plan_info(m, n, k)
+    assert (plan["mt_pass"], plan["splits"]) == (mt_pass, splits), plan
+    assert plan["tall_tiles"] == (12 if mt_pass else 0)
