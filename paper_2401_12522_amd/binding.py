@@ -15,7 +15,7 @@ EXPORTS = [
     "bita_packed_bytes", "bita_pack_weight", "bita_model_create", "bita_model_destroy",
     "bita_workspace_bytes", "bita_tree_template_create", "bita_tree_template_destroy",
     "bita_tree_template_info", "bita_build_tree", "bita_verify_step", "bita_accept",
-    "bita_compact_kv", "bita_decode_step", "bita_prefill_workspace_bytes", "bita_prefill_prepare", "bita_prefill", "bita_attention_workspace_bytes", "bita_attention_plan_info", "bita_tree_attention",
+    "bita_compact_kv", "bita_decode_step", "bita_prefill_workspace_bytes", "bita_prefill_prepare", "bita_prefill", "bita_attention_workspace_bytes", "bita_attention_plan_info", "bita_attention_launch_info", "bita_tree_attention",
     "bita_gemm_workspace_bytes", "bita_gemm", "bita_gemm_noalloc_max_scratch_bytes", "bita_gemm_noalloc_scratch_bytes",
     "bita_gemm_noalloc", "bita_select", "bita_tune_gemm", "bita_gemm_plan_info", "bita_gemm_plan_detail", "bita_profile_enable",
     "bita_profile_disable", "bita_profile_read", "bita_last_error",
@@ -99,6 +99,7 @@ def lib():
     L.bita_gemm_plan_info.restype, L.bita_gemm_plan_info.argtypes = C.c_int, [i32, i64, i64, vp]
     L.bita_gemm_plan_detail.restype, L.bita_gemm_plan_detail.argtypes = C.c_int, [i32, i64, i64, i32, vp]
     L.bita_attention_plan_info.restype, L.bita_attention_plan_info.argtypes = C.c_int, [i32] * 8 + [vp]
+    L.bita_attention_launch_info.restype, L.bita_attention_launch_info.argtypes = C.c_int, [i32] * 8 + [vp]
     L.bita_profile_enable.restype, L.bita_profile_enable.argtypes = C.c_int, [i32]
     L.bita_profile_disable.restype, L.bita_profile_disable.argtypes = None, []
     L.bita_profile_read.restype, L.bita_profile_read.argtypes = C.c_int, [i32, vp, vp, vp]
@@ -454,10 +455,19 @@ def gemm_plan_info(m_rows, n_rows, k, planes=2):
 
 
 def attention_plan_info(batch, rows, heads, kv_heads, head_dim, ctx_hint, n_prompt=0, page_size=0):
-    """{splits, heads, rows, waves (of a workgroup), workgroups} that tree attention over these sizes launches."""
+    """{splits, heads, rows, waves (of a workgroup), workgroups} that tree attention over these sizes is cut into, before
+    neighbouring row tiles of a head are joined to workgroups that share chunks (attention_launch_info)."""
     out = (C.c_int32 * 5)()
     _check(lib().bita_attention_plan_info(batch, rows, heads, kv_heads, head_dim, int(ctx_hint), n_prompt, page_size, out))
     return dict(splits=out[0], heads=out[1], rows=out[2], waves=out[3], workgroups=out[4])
+
+
+def attention_launch_info(batch, rows, heads, kv_heads, head_dim, ctx_hint, n_prompt=0, page_size=0):
+    """{splits, heads, rows, waves (of a workgroup), workgroups, share (row tiles that share chunks in one)} that tree
+    attention over these sizes launches."""
+    out = (C.c_int32 * 6)()
+    _check(lib().bita_attention_launch_info(batch, rows, heads, kv_heads, head_dim, int(ctx_hint), n_prompt, page_size, out))
+    return dict(splits=out[0], heads=out[1], rows=out[2], waves=out[3], workgroups=out[4], share=out[5])
 
 
 def select(tmpl, logits, kmax):

@@ -481,13 +481,34 @@ extern "C" size_t bita_attention_workspace_bytes(int32_t batch, int32_t rows, in
     return align_up(p.part_o_bytes, 256) + align_up(p.part_ml_bytes, 256);
 }
 
+static int attention_tiles(const char *who, int32_t batch, int32_t rows, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
+                           int32_t ctx_hint, int32_t n_prompt, int32_t page_size, const int32_t *out, AttnPlan *p, AttnTiles *a) {
+    if (!out || batch <= 0 || rows <= 0 || n_heads <= 0 || n_kv_heads <= 0 || n_heads % n_kv_heads || (head_dim != 64 && head_dim != 128) ||
+        ctx_hint < 0 || n_prompt < 0 || page_size < 0)
+        return bita_set_error(BITA_ERR_INVALID_ARG, "%s: bad argument", who);
+    *p = attn_plan(batch, rows, n_heads, head_dim, ctx_hint, n_prompt);
+    *a = attn_tiles(batch, rows, n_heads, n_kv_heads, head_dim, *p, page_size ? (ctx_hint + page_size - 1) / page_size : 0, false);
+    return BITA_OK;
+}
+
+extern "C" int bita_attention_launch_info(int32_t batch, int32_t rows, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
+                                          int32_t ctx_hint, int32_t n_prompt, int32_t page_size, int32_t *out6) {
+    AttnPlan p;
+    AttnTiles a;
+    if (int rc = attention_tiles("bita_attention_launch_info", batch, rows, n_heads, n_kv_heads, head_dim, ctx_hint, n_prompt, page_size, out6, &p, &a))
+        return rc;
+    out6[0] = p.splits; out6[1] = a.tiles << a.lg_ht; out6[2] = a.share * 16 >> a.lg_ht; out6[3] = a.share_waves;
+    out6[4] = a.launched_workgroups < INT32_MAX ? (int32_t)a.launched_workgroups : INT32_MAX;
+    out6[5] = a.share;
+    return BITA_OK;
+}
+
 extern "C" int bita_attention_plan_info(int32_t batch, int32_t rows, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
                                         int32_t ctx_hint, int32_t n_prompt, int32_t page_size, int32_t *out5) {
-    if (!out5 || batch <= 0 || rows <= 0 || n_heads <= 0 || n_kv_heads <= 0 || n_heads % n_kv_heads || (head_dim != 64 && head_dim != 128) ||
-        ctx_hint < 0 || n_prompt < 0 || page_size < 0)
-        return bita_set_error(BITA_ERR_INVALID_ARG, "bita_attention_plan_info: bad argument");
-    const AttnPlan p = attn_plan(batch, rows, n_heads, head_dim, ctx_hint, n_prompt);
-    const AttnTiles a = attn_tiles(batch, rows, n_heads, n_kv_heads, head_dim, p, page_size ? (ctx_hint + page_size - 1) / page_size : 0, false);
+    AttnPlan p;
+    AttnTiles a;
+    if (int rc = attention_tiles("bita_attention_plan_info", batch, rows, n_heads, n_kv_heads, head_dim, ctx_hint, n_prompt, page_size, out5, &p, &a))
+        return rc;
     out5[0] = p.splits; out5[1] = a.tiles << a.lg_ht; out5[2] = 16 >> a.lg_ht; out5[3] = a.waves;
     out5[4] = a.workgroups < INT32_MAX ? (int32_t)a.workgroups : INT32_MAX;
     return BITA_OK;

@@ -822,6 +822,7 @@ AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, int hd, const AttnPla
     // (300 rows on 512 26.7 / 29.9): only where eight waves over four tiles leave no queue from 960 on do they gain (512 rows
     // on 512 45.5 / 42.3, on 1500 66.5 / 60.9, 40 heads, 384 rows on 512 40.7 / 36.3).
     a.share = 1;
+    a.launched_workgroups = a.workgroups;
     if (a.tiles == 1 && a.waves == 4 && hd == 128 && p.splits == 1 && !one_row) {
         auto shared = [&](int t) { return (int64_t)batch * Hq * ((n_mt + t - 1) / t); };
         auto rounds_of = [](int64_t wgs) { return (double)((wgs + 511) / 512); };
@@ -834,7 +835,9 @@ AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, int hd, const AttnPla
                 if (c < best) { best = c; a.share = t; }
             }
         }
+        a.launched_workgroups = shared(a.share);
     }
+    a.share_waves = a.share == 4 && batch == 1 ? 8 : a.waves;
     return a;
 }
 
@@ -886,7 +889,7 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
         else { if (pm.table) ATT_LAUNCH_P(HD_, U_, 8, 1, true); else ATT_LAUNCH_P(HD_, U_, 8, 1, false); } } while (0)
 #define ATT_SHARED(W_, T_) do { if (pm.table) ATT_LAUNCH_P(128, 1, W_, T_, true); else ATT_LAUNCH_P(128, 1, W_, T_, false); } while (0)
     if (a.share == 2) ATT_SHARED(4, 2);
-    else if (a.share == 4 && batch > 1) ATT_SHARED(4, 4);
+    else if (a.share == 4 && a.share_waves == 4) ATT_SHARED(4, 4);
     else if (a.share == 4) ATT_SHARED(8, 4);
     else if (hd == 128) {
         if (a.tiles == 2) ATT_LAUNCH(128, 2); else ATT_LAUNCH(128, 1);

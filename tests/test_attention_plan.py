@@ -57,8 +57,37 @@ def test_four_waves_where_two_workgroups_share_a_cu(batch, rows, heads, kv_heads
     assert plan["waves"] == waves, plan
 
 
+def _launch(*a, **k):
+    from paper_2401_12522_amd import binding
+    _plan(*a, **k)                                  # (builds the library where it is missing)
+    return binding.attention_launch_info(*a, **k)
+
+
+@pytest.mark.parametrize("batch,rows,heads,kv_heads,hd,ctx,page,share,waves,workgroups", [
+    # two tiles where that saves a round or most of one, four where two would still queue
+    (4, 68, 32, 32, 128, 900, 0, 2, 4, 384), (4, 68, 32, 32, 128, 1400, 64, 2, 4, 384), (5, 68, 32, 32, 128, 2200, 0, 2, 4, 480),
+    (3, 100, 32, 32, 128, 900, 0, 2, 4, 384), (2, 256, 32, 32, 128, 1000, 0, 2, 4, 512), (8, 25, 40, 40, 128, 1000, 0, 2, 4, 320),
+    (8, 68, 32, 32, 128, 900, 0, 4, 4, 512), (8, 68, 32, 32, 128, 100, 16, 4, 4, 512),
+    (6, 68, 32, 32, 128, 900, 0, 1, 4, 960), (5, 100, 32, 32, 128, 2200, 0, 1, 4, 1120),
+    # up to 512 single tiles do not queue, eight waves, pairs of heads, 64-wide heads and key splits never share
+    (3, 68, 32, 32, 128, 900, 0, 1, 4, 480), (4, 68, 32, 32, 128, 1500, 64, 1, 8, 640), (8, 68, 64, 8, 128, 2000, 0, 1, 4, 1088),
+    (32, 68, 4, 4, 64, 1000, 0, 1, 4, 640), (1, 1, 32, 32, 128, 4096, 0, 1, 8, 256),
+    # one sequence: eight waves over four tiles where that leaves one round
+    (1, 512, 32, 32, 128, 512, 0, 4, 8, 256), (1, 465, 32, 32, 128, 0, 64, 4, 8, 256), (1, 464, 32, 32, 128, 512, 0, 1, 4, 928),
+    (1, 384, 40, 40, 128, 512, 0, 4, 8, 240), (1, 368, 40, 40, 128, 512, 0, 1, 4, 920), (1, 385, 40, 40, 128, 512, 0, 1, 4, 1000)])
+def test_which_row_tiles_share_chunks(batch, rows, heads, kv_heads, hd, ctx, page, share, waves, workgroups):
+    args, kw = (batch, rows, heads, kv_heads, hd, ctx), dict(n_prompt=16 if batch > 1 else 0, page_size=page)
+    plan, launch = _plan(*args, **kw), _launch(*args, **kw)
+    assert (launch["share"], launch["waves"], launch["workgroups"]) == (share, waves, workgroups), launch
+    assert (launch["splits"], launch["heads"], launch["rows"]) == (plan["splits"], plan["heads"], share * plan["rows"])
+    if share == 1:
+        assert all(launch[k] == plan[k] for k in plan)
+
+
 def test_plans_of_nothing_are_refused():
     from paper_2401_12522_amd import binding
     for bad in ((0, 1, 4, 4, 64, 0), (1, 1, 4, 3, 64, 0), (1, 1, 4, 4, 96, 0), (1, 1, 4, 4, 64, -1)):
         with pytest.raises(binding.BitaError, match="bita_attention_plan_info"):
             _plan(*bad)
+        with pytest.raises(binding.BitaError, match="bita_attention_launch_info"):
+            binding.attention_launch_info(*bad)

@@ -12,13 +12,13 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows,lens,heads,chain", [
-    (68, [300, 0, 33, 129], 32, False),                                     # two tiles, five tiles a head
-    (68, [95, 96, 97, 1, 31], 32, False), (41, [64, 65, 63, 32, 31, 33, 2, 0], 32, False), (97, [200, 17, 90], 32, False),
-    (68, [40, 300, 0, 1, 31, 32, 33, 64], 32, False),                       # four tiles, no key groups
-    (256, [100, 77], 32, True), (250, [7, 161], 32, True),                  # causal rows, two tiles
-    (512, [0], 32, True), (490, [300], 32, True), (481, [1], 32, True), (379, [45], 40, True)])   # four tiles on eight waves
-def test_tiles_that_share_chunks(rows, lens, heads, chain):
+@pytest.mark.parametrize("rows,lens,heads,chain,share,waves", [
+    (68, [300, 0, 33, 129], 32, False, 2, 4),                               # two tiles, five tiles a head
+    (68, [95, 96, 97, 1, 31], 32, False, 2, 4), (41, [64, 65, 63, 32, 31, 33, 2, 0], 32, False, 2, 4), (97, [200, 17, 90], 32, False, 2, 4),
+    (68, [40, 300, 0, 1, 31, 32, 33, 64], 32, False, 4, 4),                 # four tiles, no key groups
+    (256, [100, 77], 32, True, 2, 4), (250, [7, 161], 32, True, 2, 4),      # causal rows, two tiles
+    (512, [0], 32, True, 4, 8), (490, [300], 32, True, 4, 8), (481, [1], 32, True, 4, 8), (379, [45], 40, True, 4, 8)])   # four tiles on eight waves
+def test_tiles_that_share_chunks(rows, lens, heads, chain, share, waves):
     import paper_2401_12522_amd as bita
     hd, B, P, longest = 128, len(lens), 0 if chain else 5, max(lens)
     if chain:
@@ -29,6 +29,8 @@ def test_tiles_that_share_chunks(rows, lens, heads, chain):
     R = len(parent)
     plan = bita.binding.attention_plan_info(B, R, heads, heads, hd, longest, P)
     assert plan["waves"] == 4 and plan["splits"] == 1 and plan["workgroups"] > 512, plan
+    launch = bita.binding.attention_launch_info(B, R, heads, heads, hd, longest, P)
+    assert (launch["share"], launch["waves"]) == (share, waves), launch
     tmpl = bita.TreeTemplate(parent, is_mask, n_tree, 4)
     g = torch.Generator(device="cuda").manual_seed(rows + B)
     b16 = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)   # noqa: E731
@@ -57,3 +59,36 @@ def test_tiles_that_share_chunks(rows, lens, heads, chain):
             p = torch.softmax(((q[b, :, h].double() @ torch.cat(keys).T) / math.sqrt(hd)).masked_fill(~seen, -math.inf), -1)
             err = float((out[b, :, h] - p @ torch.cat(vals)).abs().max())
             assert err < 1e-4, (b, n, h, err)                                # the kernel tests' two-plane regression bound
+
+
+@pytest.mark.parametrize("rows,lens,page,share,waves", [
+    (68, [300, 0, 33, 129], 16, 2, 4), (68, [40, 300, 0, 1, 31, 32, 33, 64], 16, 4, 4), (97, [200, 17, 90, 128, 64, 65, 127, 63], 64, 4, 4),
+    (512, [0], 16, 4, 8), (490, [300], 64, 4, 8), (481, [45], 32, 4, 8)])
+def test_tiles_that_share_chunks_of_a_paged_cache(rows, lens, page, share, waves):
+    """A pass over shuffled pages gives the rows of a pass over the contiguous cache bit for bit (page sizes below, at and above
+    a chunk's, empty and full last pages)."""
+    import paper_2401_12522_amd as bita
+    cfg, B, smax = synth.get_config("7b", n_layers=1, d_model=256, vocab=512, d_ffn=256), len(lens), 384
+    model = bita.Model(cfg, synth.SynthWeights(cfg, seed=6, device="cuda"), max_pos=1024)
+    parent = np.arange(rows, dtype=np.int32) - 1 if B == 1 else synth.random_tree(rows, 4, rows)
+    tmpl = bita.TreeTemplate(parent, np.zeros(rows, np.uint8), rows, cfg.n_mask)
+    for ps in (0, page):
+        launch = bita.binding.attention_launch_info(B, rows, cfg.n_heads, cfg.n_kv_heads, cfg.head_dim, max(lens), cfg.n_prompt, ps)
+        assert (launch["share"], launch["waves"]) == (share, waves), launch
+    flat, paged = bita.KVState(cfg, 1, B, smax, rows), bita.PagedKVState(cfg, 1, B, smax, rows, page, n_pages=B * (smax // page) + 3, seed=5)
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    for b, n in enumerate(lens):
+        flat.k_cache[:, b, :, :n] = torch.randn((1, cfg.n_kv_heads, n, cfg.head_dim), device="cuda", generator=g).to(torch.bfloat16)
+        flat.v_cache[:, b, :, :n] = torch.randn((1, cfg.n_kv_heads, n, cfg.head_dim), device="cuda", generator=g).to(torch.bfloat16)
+        paged.load_contiguous(b, flat.k_cache[:, b], flat.v_cache[:, b], n)
+        flat.ctx_len[b] = n
+    paged.ctx_len.copy_(flat.ctx_len)
+    got = []
+    for kv in (flat, paged):
+        buf = bita.StepBuffers(model, tmpl, B, 1, want_logits=True)
+        buf.token.copy_(torch.randint(0, cfg.vocab, tuple(buf.token.shape), dtype=torch.int32, generator=torch.Generator().manual_seed(1)))
+        bita.verify_step(model, kv, max(lens), tmpl, buf, B)
+        got.append(buf)
+    torch.cuda.synchronize()
+    assert torch.isfinite(got[0].logits).all()
+    assert torch.equal(got[0].logits, got[1].logits) and torch.equal(flat.k_tree, paged.k_tree)
