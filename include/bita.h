@@ -350,10 +350,10 @@ int bita_gemm_plan_detail(int32_t m_rows, int64_t n_rows, int64_t k, int32_t pla
  * and many workgroups do. */
 int bita_attention_plan_info(int32_t batch, int32_t rows, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
                              int32_t ctx_hint, int32_t n_prompt, int32_t page_size, int32_t *out5);
-/* The same as it is launched: out6 (HOST) = {key splits, query heads per workgroup, rows per workgroup, waves per workgroup,
- * workgroups, row tiles of a head that share chunks in one workgroup (1: none do)}. */
+/* The same as it is launched: out7 (HOST) = {key splits, query heads per workgroup, rows per workgroup, waves per workgroup,
+ * workgroups, row tiles of a head that share chunks in one workgroup (1: none do), 1 where the sequences start longest first}. */
 int bita_attention_launch_info(int32_t batch, int32_t rows, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
-                               int32_t ctx_hint, int32_t n_prompt, int32_t page_size, int32_t *out6);
+                               int32_t ctx_hint, int32_t n_prompt, int32_t page_size, int32_t *out7);
 
 const char *bita_last_error(void);
 

@@ -463,11 +463,11 @@ def attention_plan_info(batch, rows, heads, kv_heads, head_dim, ctx_hint, n_prom
 
 
 def attention_launch_info(batch, rows, heads, kv_heads, head_dim, ctx_hint, n_prompt=0, page_size=0):
-    """{splits, heads, rows, waves (of a workgroup), workgroups, share (row tiles that share chunks in one)} that tree
-    attention over these sizes launches."""
-    out = (C.c_int32 * 6)()
+    """{splits, heads, rows, waves (of a workgroup), workgroups, share (row tiles that share chunks in one), ranked
+    (sequences start longest first)} that tree attention over these sizes launches."""
+    out = (C.c_int32 * 7)()
     _check(lib().bita_attention_launch_info(batch, rows, heads, kv_heads, head_dim, int(ctx_hint), n_prompt, page_size, out))
-    return dict(splits=out[0], heads=out[1], rows=out[2], waves=out[3], workgroups=out[4], share=out[5])
+    return dict(splits=out[0], heads=out[1], rows=out[2], waves=out[3], workgroups=out[4], share=out[5], ranked=bool(out[6]))
 
 
 def select(tmpl, logits, kmax):

@@ -492,14 +492,14 @@ static int attention_tiles(const char *who, int32_t batch, int32_t rows, int32_t
 }
 
 extern "C" int bita_attention_launch_info(int32_t batch, int32_t rows, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
-                                          int32_t ctx_hint, int32_t n_prompt, int32_t page_size, int32_t *out6) {
+                                          int32_t ctx_hint, int32_t n_prompt, int32_t page_size, int32_t *out7) {
     AttnPlan p;
     AttnTiles a;
-    if (int rc = attention_tiles("bita_attention_launch_info", batch, rows, n_heads, n_kv_heads, head_dim, ctx_hint, n_prompt, page_size, out6, &p, &a))
+    if (int rc = attention_tiles("bita_attention_launch_info", batch, rows, n_heads, n_kv_heads, head_dim, ctx_hint, n_prompt, page_size, out7, &p, &a))
         return rc;
-    out6[0] = p.splits; out6[1] = a.tiles << a.lg_ht; out6[2] = a.share * 16 >> a.lg_ht; out6[3] = a.share_waves;
-    out6[4] = a.launched_workgroups < INT32_MAX ? (int32_t)a.launched_workgroups : INT32_MAX;
-    out6[5] = a.share;
+    out7[0] = p.splits; out7[1] = a.tiles << a.lg_ht; out7[2] = a.share * 16 >> a.lg_ht; out7[3] = a.share_waves;
+    out7[4] = a.launched_workgroups < INT32_MAX ? (int32_t)a.launched_workgroups : INT32_MAX;
+    out7[5] = a.share; out7[6] = a.ranked;
     return BITA_OK;
 }
 

@@ -168,7 +168,8 @@ __device__ __forceinline__ constexpr int att_swizzle_k(int rho) { return HD == 1
 // PAGED: the cache operands are page pools [n_pages][Hkv][page][HD] and key slot s of sequence b
 // lives in page table[b][s >> page_lg] at row s & (page - 1); the sequence's table entries are
 // copied to LDS (behind the chunk buffers) once per workgroup.
-template <int HD, int U, int W, int T, bool PAGED>
+// RANKED: the sequences take their turns longest first (up to 8 of them).
+template <int HD, int U, int W, int T, bool PAGED, bool RANKED>
 __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void tree_attn_kernel(
     // the first 14 dwords arrive in scalar registers with the wave (kernel-argument preload):
     // what the workgroup needs to find its work and to issue its first loads comes first
@@ -204,7 +205,19 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int qh = w_in / n_mt;
     int mt = n_mt - 1 - (w_in - qh * n_mt);                                  // long m-tiles (sets of T of them) first
     const int kgrp = T > 1 ? wave / T : wave, tsub = T > 1 ? wave % T : 0;   // key group, tile of the set
-    const int b = group / Hkv, kvh = group - b * Hkv;
+    const int turn = group / Hkv, kvh = group - turn * Hkv;
+    int b = turn, Lc;
+    if constexpr (RANKED) {                                                     // lane 8i + j compares sequences i and j
+        const int i = lane >> 3, j = lane & 7;
+        const int mine = ctx_len[min(i, batch - 1)], other = ctx_len[min(j, batch - 1)];
+        const uint64_t before = __builtin_amdgcn_ballot_w64(j < batch && (other > mine || (other == mine && j < i)));
+        const int place = __popc((uint32_t)(before >> (8 * i)) & 0xFFu);
+        const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(i < batch && place == turn));
+        b = at >> 3;
+        Lc = __builtin_amdgcn_readlane(mine, at);
+    } else {
+        Lc = ctx_len[b];
+    }
     // One row per sequence is asked for (bit 24, known without a load, so that other launches do not wait for one): only
     // its row tile is launched.  A prefill's last layer, 488 rows on 512, 32 heads: 27.7 -> 17.9 us, the other tiles'
     // workgroups leaving behind their first chunk before.  (Two tiles per workgroup have no registers for it: a spill, 1 %
@@ -212,7 +225,6 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     if (U == 1 && T == 1 && (n_mt_lg >> 24)) mt = min(max(only_row[b], 0), R - 1) >> lg_rows;
     const int h0 = kvh * qpk + (U > 1 ? qh << (1 + lg_ht) : qh);                // the workgroup's first head
 
-    int Lc = ctx_len[b];
     const int32_t *tbl = reinterpret_cast<const int32_t *>(smem + C::SMEM);
     const int page_lg = pm.page_lg, page_mask = (1 << pm.page_lg) - 1;
     if (PAGED) {
@@ -838,11 +850,21 @@ AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, int hd, const AttnPla
         a.launched_workgroups = shared(a.share);
     }
     a.share_waves = a.share == 4 && batch == 1 ? 8 : a.waves;
+    // Where pairs of heads queue (512 workgroups of four waves are held at once, 256 of eight) and an XCD walks several sequences one
+    // after the other, the longest start first, so that the last workgroups are short: instantiations of their own (as a branch
+    // of the others the ranking cost every launch 0.5 %), up to 8 sequences (one comparison a lane; a loop over 64 cost a workgroup half a
+    // microsecond), from walks of 64 chunks on.  Ranking costs a workgroup some 0.3 us: with 1024 keys that was 1.4 % of equal
+    // lengths' time against 1 % that unequal ones gained, with 512 keys a loss for all, with one K/V head, whose sequences lie on an XCD each,
+    // nothing but the cost.  From 2048 keys on, time of the batch's order, 64/8, 32/4 and 64/16 heads: equal lengths 1.004 (48 launches), lengths
+    // within a factor of two 0.981 (58; 0.87 to 1.10 by the draw), of four 0.949 (38; 0.80 to 1.11); 64/8 heads, 68 rows, 8 of 1024 to
+    // 4096 keys, 40 draws 0.957 (125 -> 120 us); paged, whole passes, 0.96 and equal lengths 0.995.  (One head per workgroup, whose launches
+    // are bound by what they load, lost up to 8 % as often as it won; key splits are not measured.)
+    a.ranked = a.tiles == 2 && p.splits == 1 && a.workgroups > (a.waves == 4 ? 512 : 256) && batch <= 8 && (int64_t)batch * Hkv > 8 && walk >= 64;
     return a;
 }
 
 // lg_ht: log2 of the heads that share a tile (two heads per workgroup and more)
-template <int HD, int U, int W, int T, bool PAGED>
+template <int HD, int U, int W, int T, bool PAGED, bool RANKED = false>
 static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo, const void *k_cache, const void *v_cache,
                           const void *k_tree, const void *v_tree, const void *k_tree_lo, const void *v_tree_lo,
                           const void *prompt_k, const void *prompt_v, const int32_t *ctx_len, const int32_t *token,
@@ -852,7 +874,7 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
     using C = AttCfg<HD, U, W, T>;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)tree_attn_kernel<HD, U, W, T, PAGED>,
+        (void)hipFuncSetAttribute((const void *)tree_attn_kernel<HD, U, W, T, PAGED, RANKED>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   C::SMEM + (PAGED ? ATT_PAGE_TABLE_MAX * 4 : 0));
         attr_set = true;
@@ -861,12 +883,9 @@ static void launch_attn_t(const TemplateDev &t, const void *q, const void *q_lo,
     const int per_wg = T * 16 >> lg_ht, n_mt = U == 1 && T == 1 && only_row ? 1 : (t.rows + per_wg - 1) / per_wg;      // rows of a workgroup
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     const int groups = batch * Hkv, per_group = (Hq / Hkv / U >> lg_ht) * n_mt * p.splits;
-    // (Sequences in the batch's order.  Longest first, ranked from the lengths by every workgroup of a launch that queues, cost
-    // equal lengths 1 % (64/8 heads 1.011 of the time over 24 launches, 64/1 heads 1.008) and gave unequal ones nothing on the whole:
-    // lengths within a factor of two 0.996 and 1.005, of four and more 0.995, single launches 0.86 to 1.11.)
     const int per_xcd = (groups + 7) / 8, grid_y = per_xcd < 1 << ATT_GRID_Y_LG ? per_xcd : 1 << ATT_GRID_Y_LG;
     const dim3 grid(8 * per_group, grid_y, (per_xcd + grid_y - 1) / grid_y);
-    hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, T, PAGED>), grid, dim3(W * 64), smem_bytes, s,
+    hipLaunchKernelGGL((tree_attn_kernel<HD, U, W, T, PAGED, RANKED>), grid, dim3(W * 64), smem_bytes, s,
                        ctx_len, batch, Hq / Hkv, Hkv, n_mt | lg_ht << 16 | (U == 1 && T == 1 && only_row ? 1 << 24 : 0), p.splits, P, t.rows, smax, (const uint16_t *)q, (const uint16_t *)q_lo, t,
                        (const uint16_t *)k_cache, (const uint16_t *)v_cache,
                        (const uint16_t *)k_tree, (const uint16_t *)v_tree, (const uint16_t *)k_tree_lo,
@@ -882,13 +901,18 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
                            int P, int smax, const AttnPlan &p, float *part_o, float *part_ml, void *out,
                            void *out_lo, bool out_as_fragments, const PageMap &pm, hipStream_t s, const int32_t *only_row) {
     const AttnTiles a = attn_tiles(batch, t.rows, Hq, Hkv, hd, p, pm.table ? pm.tbl_cap : 0, only_row != nullptr);
-#define ATT_LAUNCH_P(HD_, U_, W_, T_, PG_) launch_attn_t<HD_, U_, W_, T_, PG_>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
+#define ATT_LAUNCH_P(HD_, U_, W_, T_, ...) launch_attn_t<HD_, U_, W_, T_, __VA_ARGS__>(t, q, q_lo, k_cache, v_cache, k_tree, v_tree, k_tree_lo, v_tree_lo, prompt_k, \
                                                    prompt_v, ctx_len, token, batch, Hq, Hkv, P, smax, p, part_o, part_ml, out, out_lo, out_as_fragments, pm, only_row, a.lg_ht, s)
 #define ATT_LAUNCH(HD_, U_) do { \
         if (a.waves == 4) { if (pm.table) ATT_LAUNCH_P(HD_, U_, 4, 1, true); else ATT_LAUNCH_P(HD_, U_, 4, 1, false); } \
         else { if (pm.table) ATT_LAUNCH_P(HD_, U_, 8, 1, true); else ATT_LAUNCH_P(HD_, U_, 8, 1, false); } } while (0)
 #define ATT_SHARED(W_, T_) do { if (pm.table) ATT_LAUNCH_P(128, 1, W_, T_, true); else ATT_LAUNCH_P(128, 1, W_, T_, false); } while (0)
-    if (a.share == 2) ATT_SHARED(4, 2);
+#define ATT_RANKED(HD_) do { \
+        if (a.waves == 4) { if (pm.table) ATT_LAUNCH_P(HD_, 2, 4, 1, true, true); else ATT_LAUNCH_P(HD_, 2, 4, 1, false, true); } \
+        else { if (pm.table) ATT_LAUNCH_P(HD_, 2, 8, 1, true, true); else ATT_LAUNCH_P(HD_, 2, 8, 1, false, true); } } while (0)
+    if (a.ranked && hd == 128) ATT_RANKED(128);
+    else if (a.ranked) ATT_RANKED(64);
+    else if (a.share == 2) ATT_SHARED(4, 2);
     else if (a.share == 4 && a.share_waves == 4) ATT_SHARED(4, 4);
     else if (a.share == 4) ATT_SHARED(8, 4);
     else if (hd == 128) {
@@ -899,6 +923,7 @@ void launch_tree_attention(const TemplateDev &t, const void *q, const void *q_lo
 #undef ATT_LAUNCH_P
 #undef ATT_LAUNCH
 #undef ATT_SHARED
+#undef ATT_RANKED
     if (p.splits > 1) {
         const int heads_per_block = (256 / (hd / 4)) < Hq ? (256 / (hd / 4)) : Hq;
         hipLaunchKernelGGL(attn_merge_kernel, dim3(only_row ? 1 : t.rows, (Hq + heads_per_block - 1) / heads_per_block, batch),

@@ -214,8 +214,8 @@ struct AttnPlan { int splits, chunks; size_t part_o_bytes, part_ml_bytes; };
 AttnPlan attn_plan(int batch, int rows, int n_heads, int hd, int ctx_hint, int n_prompt);
 // tiles of 16 queries per workgroup, log2 of the heads that share one, waves per workgroup; one_row: of each sequence.
 // share: how many neighbouring workgroups of a head are launched as one of share_waves waves that share chunks (1: none, and
-// launched_workgroups = workgroups, share_waves = waves)
-struct AttnTiles { int tiles, lg_ht, waves, share, share_waves; int64_t workgroups, launched_workgroups; };
+// launched_workgroups = workgroups, share_waves = waves).  ranked: the longest sequences' workgroups start first
+struct AttnTiles { int tiles, lg_ht, waves, share, share_waves; bool ranked; int64_t workgroups, launched_workgroups; };
 AttnTiles attn_tiles(int batch, int rows, int n_heads, int n_kv_heads, int hd, const AttnPlan &p, int table_entries, bool one_row);
 // k_tree_lo / v_tree_lo: low bf16 plane of the pass rows' K/V (nullable); out_lo: low plane of
 // the row-major output (nullable; unused when the output is written as fragments)

@@ -84,6 +84,17 @@ def test_which_row_tiles_share_chunks(batch, rows, heads, kv_heads, hd, ctx, pag
         assert all(launch[k] == plan[k] for k in plan)
 
 
+@pytest.mark.parametrize("batch,rows,heads,kv_heads,hd,ctx,page,ranked", [
+    (8, 68, 64, 8, 128, 4096, 0, True), (8, 68, 64, 8, 64, 4096, 64, True), (2, 170, 64, 8, 128, 3000, 0, True), (8, 130, 16, 2, 64, 3000, 0, True),
+    (8, 68, 64, 8, 128, 1841, 0, True), (8, 68, 64, 8, 128, 1840, 0, False),                     # 64 chunks
+    (9, 68, 64, 8, 128, 4096, 0, False), (3, 68, 64, 8, 128, 4096, 0, False), (1, 300, 64, 8, 128, 4096, 0, False),   # one lane a pair; no queue
+    (8, 68, 64, 1, 128, 4096, 0, False), (4, 137, 32, 2, 128, 4096, 0, False),                   # an XCD walks one sequence only
+    (8, 68, 64, 8, 128, 20000, 0, False), (4, 68, 32, 32, 128, 4096, 0, False)])                 # key splits, single heads
+def test_sequences_start_longest_first_on_long_walks_that_queue(batch, rows, heads, kv_heads, hd, ctx, page, ranked):
+    launch = _launch(batch, rows, heads, kv_heads, hd, ctx, n_prompt=16, page_size=page)
+    assert launch["ranked"] is ranked, launch
+
+
 def test_plans_of_nothing_are_refused():
     from paper_2401_12522_amd import binding
     for bad in ((0, 1, 4, 4, 64, 0), (1, 1, 4, 3, 64, 0), (1, 1, 4, 4, 96, 0), (1, 1, 4, 4, 64, -1)):
