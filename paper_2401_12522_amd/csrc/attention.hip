@@ -830,9 +830,16 @@ AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, int hd, const AttnPla
     // unless stated: 68 rows, 4 sequences up to 900 keys 31.8 / 26.6, 5 of 900 36.5 / 27.4, 5 of 2200 66.8 / 52.8, 8 of 900
     // (four tiles) 52.4 / 43.8, 40 rows, 8 of 900 38.8 / 29.2, 100 rows, 3 of 900 30.9 / 26.5, 256 rows, 2 of 1000 46.0 / 37.0, 40 heads,
     // 25 rows, 8 of 1000 36.1 / 31.4; but 68 rows, 6 of 900 (960 workgroups, 576 shared) 38.9 / 41.6 and, four tiles, 100 rows,
-    // 5 of 2200 77.1 / 80.4, which the rule leaves out.  64-wide heads lose (4 heads, 32 sequences of 1000 21.4 / 22.2).  One sequence's tiles differ in length and queue well by themselves
-    // (300 rows on 512 26.7 / 29.9): only where eight waves over four tiles leave no queue from 960 on do they gain (512 rows
-    // on 512 45.5 / 42.3, on 1500 66.5 / 60.9, 40 heads, 384 rows on 512 40.7 / 36.3).
+    // 5 of 2200 77.1 / 80.4, which the rule leaves out.  64-wide heads lose (4 heads, 32 sequences of 1000 21.4 / 22.2).
+    // Up to 640 single tiles, few of which wait, what is saved is little, and one long sequence's tiles, walked at the joined pace,
+    // are the launch's time: there only walks of up to 51 chunks share.  Shared / single, of equal lengths, lengths within a factor of
+    // two and of four: up to 640, 900 keys 0.858, 0.917, 0.974, 1500 keys 0.884, 0.941, 1.086, 2200 keys 0.892, 1.007, 1.140, 4096 keys
+    // 0.889, 1.020, 1.160 (up to 1.53); above 640, 900 keys 0.817, 0.841, 0.840, 2200 keys 0.841, 0.870, 0.959, 4096 keys 0.833, 0.903,
+    // 0.957 (185 launches to 640, 160 of two tiles above).
+    // One sequence's tiles differ in length and queue well by themselves (300 rows on 512 26.7 / 29.9): only where eight waves over four
+    // tiles leave no queue do they gain, and from 960 on, where single tiles fill two rounds, enough to be told from a change of box (512
+    // rows on 512 45.5 / 42.3, on 1500 66.5 / 60.9, on 6000 165 / 138, 40 heads, 384 rows on 512 40.7 / 36.3; but 32 heads, 384 rows, 768 tiles,
+    // 36.4 / 35.6 and 56.4 / 54.3).
     a.share = 1;
     a.launched_workgroups = a.workgroups;
     if (a.tiles == 1 && a.waves == 4 && hd == 128 && p.splits == 1 && !one_row) {
@@ -840,7 +847,7 @@ AttnTiles attn_tiles(int batch, int rows, int Hq, int Hkv, int hd, const AttnPla
         auto rounds_of = [](int64_t wgs) { return (double)((wgs + 511) / 512); };
         if (batch == 1) {
             if (a.workgroups >= 960 && shared(4) <= 256) a.share = 4;
-        } else if (a.workgroups > 512) {
+        } else if (a.workgroups > (walk <= 51 ? 512 : 640)) {
             double best = 0.97 * 0.5 * ((double)a.workgroups / 512.0 + rounds_of(a.workgroups));
             for (int t : {2, 4}) {
                 const double c = (t == 2 ? 1.5 : 2.55) * rounds_of(shared(t));

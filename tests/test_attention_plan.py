@@ -69,6 +69,9 @@ def _launch(*a, **k):
     (3, 100, 32, 32, 128, 900, 0, 2, 4, 384), (2, 256, 32, 32, 128, 1000, 0, 2, 4, 512), (8, 25, 40, 40, 128, 1000, 0, 2, 4, 320),
     (8, 68, 32, 32, 128, 900, 0, 4, 4, 512), (8, 68, 32, 32, 128, 100, 16, 4, 4, 512),
     (6, 68, 32, 32, 128, 900, 0, 1, 4, 960), (5, 100, 32, 32, 128, 2200, 0, 1, 4, 1120),
+    # up to 640 single tiles only on walks of up to 51 chunks
+    (4, 68, 32, 32, 128, 1456, 0, 2, 4, 384), (4, 68, 32, 32, 128, 1457, 0, 1, 4, 640), (3, 96, 32, 32, 128, 3000, 0, 1, 4, 576),
+    (3, 68, 40, 40, 128, 2200, 0, 1, 4, 600), (4, 68, 40, 40, 128, 4096, 0, 2, 4, 480),
     # up to 512 single tiles do not queue, eight waves, pairs of heads, 64-wide heads and key splits never share
     (3, 68, 32, 32, 128, 900, 0, 1, 4, 480), (4, 68, 32, 32, 128, 1500, 64, 1, 8, 640), (8, 68, 64, 8, 128, 2000, 0, 1, 4, 1088),
     (32, 68, 4, 4, 64, 1000, 0, 1, 4, 640), (1, 1, 32, 32, 128, 4096, 0, 1, 8, 256),
