@@ -123,7 +123,8 @@ struct GemmCfg {
 // 48 rows 196.5 / 197.0, 68 rows 204.8 / 204.0, four sequences of 68 431.4 / 430.2; 13B, 25 rows 213.8 / 214.8).
 // ROPE: a direct launch that rotates and stores the QKV columns (instantiations of their own: as one more case of the direct
 // ones its code cost gate/up and the LM head of a 64-node step 0.5 %).
-template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool DIRECT, bool PACK, bool THROUGH, bool ROPE>
+// TURNS: the two k groups take turns (below) instead of both at once; gemm_turns and launch_gemm_t say where.
+template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool DIRECT, bool PACK, bool THROUGH, bool ROPE, bool TURNS>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // The first 14 dwords of the argument block arrive in scalar registers with the wave
     // (kernel-argument preload); everything the first loads depend on is among them, the grid's
@@ -134,11 +135,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     float *__restrict__ out, int64_t ldo, GemmOutput direct) {
     using C = GemmCfg<MT, NW, SPLIT, KC, D, WAVES, KG, PACK, ROPE>;
     constexpr int WN = C::WN;
-    // Which loop: the two k groups in turns (below), or both at once.  Turns from 6 m-tiles on, and with passes of 5 on the
-    // forms that many rows take (14 and 16 waves) or with one plane; the packed 5 of a 64-node tree and the forms that 73 to 80
-    // rows of two planes take gain nothing by it (68 rows, both at once / turns: 12288 x 4096 30.4 / 30.9 us, 32000 x 4096 54.2 /
-    // 54.5, 57344 x 8192 154 / 153; 80 rows: 32000 x 4096 56.0 / 56.6, 8192 x 8192 37.5 / 38.2).
-    constexpr bool TURNS = KG == 2 && KC == 1 && (MT > 5 || (MT == 5 && !PACK && (WAVES >= 14 || !SPLIT)));
+    static_assert(!TURNS || (KG == 2 && KC == 1 && !PACK), "two k groups, whole fragments");
     constexpr int SUB = MT > 5 ? 2 : 1;                        // reads and multiplies of a k-step: all at once, or plane by plane
     extern __shared__ __attribute__((aligned(16))) uint4 smem_u4[];   // [KG][D][NFRAG][64] + dump slot
 
@@ -1034,18 +1031,36 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
     return p;
 }
 
-template <int MT, int NW, bool SPLIT, int WAVES, int D, int KG, bool DIRECT, bool PACK = false, bool THROUGH = DIRECT, bool ROPE = false>
+// Which loop: the two k groups in turns, or both at once.
+// Turns always: two planes from 6 m-tiles on; one plane in passes of 5 on fewer than 14 waves (20 to 80 rows of wide matrices 5 to 9 %
+// faster, narrow ones the same: 99 launches of 4 to 32 k-steps a group 0.998 of the time).
+// Never: the packed 5 of a 64-node tree and the forms that 73 to 80 rows of two planes take (68 rows, both at once / turns: 12288 x
+// 4096 30.4 / 30.9 us, 32000 x 4096 54.2 / 54.5, 57344 x 8192 154 / 153; 80 rows: 32000 x 4096 56.0 / 56.6, 8192 x 8192 37.5 / 38.2); one
+// plane on 14 and 16 waves (40 launches 1.000, five rows of the long ones 1.02).
+// Passes of 5 with two planes on 14 and 16 waves: where a split has 40 k-steps and the workgroups are more than half of the CUs (39
+// launches 0.980 of the time, 0.93 to 1.02: 8192 x 28672, 300 rows 270 -> 251 us, 4096 x 11008, 272 rows 67 -> 63, 12288 x 4096, 300 rows 76.8 ->
+// 73.5; the other 139 1.000, 0.96 to 1.07: 12432 x 1040, 166 rows 25.5 -> 27.1, 4096 x 4096, 170 rows 28.1 -> 28.8).
+constexpr bool gemm_turns(int MT, bool SPLIT, int WAVES, int KG) { return KG == 2 && (MT > 5 || (MT == 5 && !SPLIT && WAVES < 14)); }
+template <int MT, int NW, bool SPLIT, int WAVES, int D, int KG, bool DIRECT, bool PACK = false, bool THROUGH = DIRECT, bool ROPE = false,
+          bool TURNS = gemm_turns(MT, SPLIT, WAVES, KG)>
 static void launch_gemm_t(const void *a_frag, int M, int64_t K, const void *w, int64_t N, float *out, int64_t ldo,
                           const GemmPlan &p, hipStream_t s, const GemmOutput &direct) {
+    if constexpr (MT == 5 && SPLIT && !PACK && WAVES >= 14 && !TURNS) {
+        const int64_t blocks = (N / 16 + GemmCfg<MT, NW, SPLIT, 1, D, WAVES, KG>::WN * NW - 1) / (GemmCfg<MT, NW, SPLIT, 1, D, WAVES, KG>::WN * NW);
+        if (M > 80 && p.ksteps_per_split >= 40 && blocks * p.splits * ((M + 79) / 80) > 128) {
+            launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, THROUGH, ROPE, true>(a_frag, M, K, w, N, out, ldo, p, s, direct);
+            return;
+        }
+    }
     if constexpr (DIRECT && SPLIT && KG == 2 && !ROPE && (NW > 2 || WAVES == 8 || WAVES == 16) && D == 3) {
         if (direct.kind == GEMM_OUT_ROPE) {                    // (the forms that gemm_direct_output_possible says)
-            launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, THROUGH, true>(a_frag, M, K, w, N, out, ldo, p, s, direct);
+            launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, THROUGH, true, TURNS>(a_frag, M, K, w, N, out, ldo, p, s, direct);
             return;
         }
     }
     if constexpr (MT > 1 && SPLIT && KG > 1 && !THROUGH) {
         if (p.splits > 1 && (int64_t)p.splits * M * ldo * 4 >= (8 << 20) && ldo <= GEMM_THROUGH_MAX_LD) {
-            launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, true>(a_frag, M, K, w, N, out, ldo, p, s, direct);
+            launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, true, ROPE, TURNS>(a_frag, M, K, w, N, out, ldo, p, s, direct);
             return;
         }
     }
@@ -1053,13 +1068,13 @@ static void launch_gemm_t(const void *a_frag, int M, int64_t K, const void *w, i
     using C = GemmCfg<MT, NW, SPLIT, KC, D, WAVES, KG, PACK, ROPE>;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH, ROPE>,
+        (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH, ROPE, TURNS>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
         attr_set = true;
     }
     const int NT = (int)(N / 16), KS = (int)((K + 31) / 32), m_tiles = (M + 15) / 16;
     dim3 grid((NT + C::WN * NW - 1) / (C::WN * NW), p.splits, (m_tiles + MT - 1) / MT);
-    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH, ROPE>), grid, dim3(WAVES * 64), C::SMEM, s,
+    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, SPLIT, KC, D, WAVES, KG, DIRECT, PACK, THROUGH, ROPE, TURNS>), grid, dim3(WAVES * 64), C::SMEM, s,
                        (const uint4 *)a_frag, (const uint4 *)w, KS * m_tiles, M, m_tiles, NT, KS, p.ksteps_per_split,
                        (int)grid.x, (int)grid.y, (int)grid.z, ROPE ? direct.rope.hd / 16 : 0, out, ldo, direct);
 }

@@ -35,6 +35,25 @@ def test_gemm_rows_of_twelve_tiles(M, N, K, tiles, mt_pass, splits):
     assert float((out - ref).abs().max()) <= 2e-5 * scale + 1e-6         # fp32 accumulation, as everywhere
 
 
+@pytest.mark.parametrize("M,N,K,variant,splits", [
+    (300, 12288, 1280, 9, 1), (300, 12288, 1288, 9, 1), (300, 12288, 1320, 9, 1), (300, 12288, 1376, 9, 1), (300, 12288, 1400, 9, 1), (300, 12288, 1440, 9, 1),
+    (222, 35072, 1280, 11, 1), (222, 35072, 1304, 11, 1), (236, 9600, 4096, 9, 2), (236, 9600, 4136, 9, 2), (488, 4096, 4104, 9, 2),   # (the last writes its sums through)
+    (300, 12288, 1248, 9, 1), (300, 4096, 4096, 9, 4), (302, 272, 20512, 9, 8)])                     # too few k-steps, too few workgroups: both at once
+def test_passes_of_five_in_turns_and_both_at_once(M, N, K, variant, splits):
+    import paper_2401_12522_amd as bita
+    plan = bita.binding.gemm_plan_info(M, N, K)
+    assert (plan["variant"], plan["mt_pass"], plan["splits"]) == (variant, 0, splits), plan
+    g = torch.Generator().manual_seed(N + K)
+    a32 = torch.randn(M, K, generator=g)
+    hi = a32.to(torch.bfloat16)
+    lo = (a32 - hi.float()).to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=g) * 0.05).to(torch.bfloat16)
+    out = bita.gemm(hi.cuda(), bita.pack_weight(w.cuda()), N, a_lo=lo.cuda())
+    ref = (hi.cuda().float().double() + lo.cuda().double()) @ w.cuda().double().T
+    assert torch.isfinite(out).all()
+    assert float((out.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max()) + 1e-6         # fp32 accumulation, as everywhere
+
+
 @pytest.mark.parametrize("M,N,planes", [(272, 22016, 2), (112, 57344, 2), (150, 4096, 2), (300, 12288, 2), (20, 22016, 1), (300, 12288, 1)])
 @pytest.mark.parametrize("K", [32, 64, 96, 160, 224, 232])
 def test_k_groups_in_turns_at_short_k(M, N, planes, K):
