@@ -123,7 +123,7 @@ struct GemmCfg {
 // 48 rows 196.5 / 197.0, 68 rows 204.8 / 204.0, four sequences of 68 431.4 / 430.2; 13B, 25 rows 213.8 / 214.8).
 // ROPE: a direct launch that rotates and stores the QKV columns (instantiations of their own: as one more case of the direct
 // ones its code cost gate/up and the LM head of a 64-node step 0.5 %).
-// TURNS: the two k groups take turns (below) instead of both at once; gemm_turns and launch_gemm_t say where.
+// TURNS: the two k groups take turns (below) instead of both at once; launch_gemm_t says where.
 template <int MT, int NW, bool SPLIT, int KC, int D, int WAVES, int KG, bool DIRECT, bool PACK, bool THROUGH, bool ROPE, bool TURNS>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // The first 14 dwords of the argument block arrive in scalar registers with the wave
@@ -268,23 +268,27 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
             // a k group whose share of the range is shorter than the others' skips the k-steps
             // past its end (wave-uniform)
             if (ks_begin + stage * KC + s >= ks_end) continue;
-            // all LDS reads of the k-step are issued before its first MFMA; fragment f is
-            // waited for with the NF-1-f later reads still in flight
-            constexpr int NF = C::PL * MT - (PACK ? 1 : 0);
-            static_assert(NF <= 16, "lgkmcnt range");
-            bf16x8 a[NF];
-            static_for<0, NF>([&](auto f_c) {
-                constexpr int F = decltype(f_c)::value;
-                a[F] = lds_read_frag<((SLOT * C::NFRAG + F * KC) * 64) * 16>(lds_lane_base + s * 1024);
-            });
-            static_for<0, NF>([&](auto f_c) {
-                constexpr int F = decltype(f_c)::value, i = F % MT;
-                lds_wait_frag<NF - 1 - F>(a[F]);
+            // the LDS reads of a batch are issued before its first MFMA; fragment f is waited for with the
+            // batch's later reads still in flight.  Up to 5 m-tiles a k-step is one batch, above 4 fragments, so that the
+            // accumulators (MT x NW tiles) leave room for them.
+            constexpr int NF = C::PL * MT - (PACK ? 1 : 0), AB = MT > 5 ? 4 : NF, NB = (NF + AB - 1) / AB;
+            static_assert(AB <= 16, "lgkmcnt range");
+            static_for<0, NB>([&](auto b_c) {
+                constexpr int B0 = decltype(b_c)::value * AB, BN = (NF - B0) < AB ? (NF - B0) : AB;
+                bf16x8 a[BN];
+                static_for<0, BN>([&](auto f_c) {
+                    constexpr int F = B0 + decltype(f_c)::value;
+                    a[F - B0] = lds_read_frag<((SLOT * C::NFRAG + F * KC) * 64) * 16>(lds_lane_base + s * 1024);
+                });
+                static_for<0, BN>([&](auto f_c) {
+                    constexpr int F = B0 + decltype(f_c)::value, i = F % MT;
+                    lds_wait_frag<BN - 1 - (F - B0)>(a[F - B0]);
 #pragma unroll
-                for (int j = 0; j < NW; j++)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        a[F], __builtin_bit_cast(bf16x8, w[SLOT][j][s]), acc[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);          // keeps the next fragment's wait behind these MFMAs
+                    for (int j = 0; j < NW; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            a[F - B0], __builtin_bit_cast(bf16x8, w[SLOT][j][s]), acc[i][j], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);      // keeps the next fragment's wait behind these MFMAs
+                });
             });
         }
     };
@@ -1032,22 +1036,39 @@ GemmPlan gemm_plan(int m_rows, int64_t n_rows, int64_t k, int planes) {
 }
 
 // Which loop: the two k groups in turns, or both at once.
-// Turns always: two planes from 6 m-tiles on; one plane in passes of 5 on fewer than 14 waves (20 to 80 rows of wide matrices 5 to 9 %
-// faster, narrow ones the same: 99 launches of 4 to 32 k-steps a group 0.998 of the time).
+// Turns always: two planes and complete sums from 6 m-tiles on (38 products of 81 to 512 rows 0.85 to 1.01 of the time), passes of 10 and 11; one
+// plane in passes of 5 on fewer than 14 waves (20 to 80 rows of wide matrices 5 to 9 % faster, narrow ones the same: 99 launches of 4 to 32
+// k-steps a group 0.998 of the time).
 // Never: the packed 5 of a 64-node tree and the forms that 73 to 80 rows of two planes take (68 rows, both at once / turns: 12288 x
 // 4096 30.4 / 30.9 us, 32000 x 4096 54.2 / 54.5, 57344 x 8192 154 / 153; 80 rows: 32000 x 4096 56.0 / 56.6, 8192 x 8192 37.5 / 38.2); one
 // plane on 14 and 16 waves (40 launches 1.000, five rows of the long ones 1.02).
-// Passes of 5 with two planes on 14 and 16 waves: where a split has 40 k-steps and the workgroups are more than half of the CUs (39
-// launches 0.980 of the time, 0.93 to 1.02: 8192 x 28672, 300 rows 270 -> 251 us, 4096 x 11008, 272 rows 67 -> 63, 12288 x 4096, 300 rows 76.8 ->
-// 73.5; the other 139 1.000, 0.96 to 1.07: 12432 x 1040, 166 rows 25.5 -> 27.1, 4096 x 4096, 170 rows 28.1 -> 28.8).
-constexpr bool gemm_turns(int MT, bool SPLIT, int WAVES, int KG) { return KG == 2 && (MT > 5 || (MT == 5 && !SPLIT && WAVES < 14)); }
+// The rest by gemm_turns_pay.  Passes of 5 with complete sums need 40 k-steps and more workgroups than half of the CUs (31 products 0.975 of
+// the time, 8192 x 28672, 300 rows 270 -> 251 us, 12288 x 4096, 300 rows 76.8 -> 73.5; the other 147 1.000, 12432 x 1040, 166 rows 25.5 -> 27.1).
+// Split sums gain by turns as products alone; inside a layer, between kernels that leave the clock high, only where the m-tiles times a
+// split's k-steps are more than 150 times the splits.  What turns cost a layer's time (two layers of 7B and 13B widths, one of 70B, each product
+// by itself, us): below the line 81 to 128 rows QKV of 26 k-steps in 5 splits +2 to +8, of 40 in 4 +10, down of 43 in 8 (161 to 256 rows) +13, of 72 in
+// 6 +2, of 112 in 8 (105 to 128 rows) +7, O of 54 in 3 +10, of 64 in 4 +4; above it QKV of 64 and 80 in 2 (161 to 272 rows) -2 to -9, of 86 in 3
+// -5, down of 108 in 4 (400 rows) -12, of 224 in 4 -4 to -15, of 448 in 2 -25.  One pass of 6 m-tiles is below it at any length (gate/up at 81
+// and 96 rows, 64 and 80 in 2, 0 to +6).  Cards differ below the line: of five, three lose 1 to 5 % of a layer by turns there, two gain up to 2.
+// With this rule 43 row counts of the three widths take 0.86 to 1.003 of what they took with both groups at once everywhere.
+static bool gemm_turns_pay(int mt, int passes, int64_t workgroups, const GemmPlan &p) {
+    if (p.splits == 1) return mt > 5 || (p.ksteps_per_split >= 40 && workgroups > 128);
+    return mt * p.ksteps_per_split > 150 * p.splits && workgroups > 128 && (mt > 6 || passes > 1);
+}
+constexpr bool gemm_either_loop(int MT, bool SPLIT, int WAVES, int KG, bool DIRECT, bool PACK) {
+    return KG == 2 && SPLIT && !PACK && ((MT == 5 && WAVES >= 14) || (MT > 5 && MT < 10 && !DIRECT));
+}
+constexpr bool gemm_turns(int MT, bool SPLIT, int WAVES, int KG, bool DIRECT, bool PACK) {
+    return KG == 2 && !gemm_either_loop(MT, SPLIT, WAVES, KG, DIRECT, PACK) && (MT > 5 || (MT == 5 && !SPLIT && WAVES < 14));
+}
 template <int MT, int NW, bool SPLIT, int WAVES, int D, int KG, bool DIRECT, bool PACK = false, bool THROUGH = DIRECT, bool ROPE = false,
-          bool TURNS = gemm_turns(MT, SPLIT, WAVES, KG)>
+          bool TURNS = gemm_turns(MT, SPLIT, WAVES, KG, DIRECT, PACK)>
 static void launch_gemm_t(const void *a_frag, int M, int64_t K, const void *w, int64_t N, float *out, int64_t ldo,
                           const GemmPlan &p, hipStream_t s, const GemmOutput &direct) {
-    if constexpr (MT == 5 && SPLIT && !PACK && WAVES >= 14 && !TURNS) {
-        const int64_t blocks = (N / 16 + GemmCfg<MT, NW, SPLIT, 1, D, WAVES, KG>::WN * NW - 1) / (GemmCfg<MT, NW, SPLIT, 1, D, WAVES, KG>::WN * NW);
-        if (M > 80 && p.ksteps_per_split >= 40 && blocks * p.splits * ((M + 79) / 80) > 128) {
+    if constexpr (gemm_either_loop(MT, SPLIT, WAVES, KG, DIRECT, PACK) && !TURNS) {
+        constexpr int TILES = GemmCfg<MT, NW, SPLIT, 1, D, WAVES, KG>::WN * NW;
+        const int passes = (M + 16 * MT - 1) / (16 * MT);
+        if (M > 80 && gemm_turns_pay(MT, passes, (N / 16 + TILES - 1) / TILES * p.splits * passes, p)) {
             launch_gemm_t<MT, NW, SPLIT, WAVES, D, KG, DIRECT, PACK, THROUGH, ROPE, true>(a_frag, M, K, w, N, out, ldo, p, s, direct);
             return;
         }

@@ -35,10 +35,29 @@ def test_gemm_rows_of_twelve_tiles(M, N, K, tiles, mt_pass, splits):
     assert float((out - ref).abs().max()) <= 2e-5 * scale + 1e-6         # fp32 accumulation, as everywhere
 
 
+@pytest.mark.parametrize("M,N,K,tiles,mt_pass,splits", [
+    # both k groups at once: few k-steps a split, or one pass of 6
+    (188, 4720, 11528, 12, 6, 5), (81, 22016, 4096, 12, 6, 2), (161, 4096, 11000, 16, 6, 8), (107, 12288, 4096, 16, 7, 5), (330, 4720, 3336, 16, 7, 4),
+    (113, 12288, 4088, 16, 8, 5), (113, 15360, 5120, 16, 8, 4), (256, 4096, 11008, 16, 8, 8), (140, 12288, 4096, 12, 9, 4), (257, 10240, 4096, 16, 9, 3),
+    # in turns
+    (161, 10240, 8184, 16, 6, 3), (105, 22016, 4088, 12, 7, 2), (120, 22016, 4096, 12, 8, 2), (265, 12288, 4096, 12, 9, 2), (340, 8192, 28672, 16, 6, 2)])
+def test_split_tall_launches_in_turns_and_both_at_once(M, N, K, tiles, mt_pass, splits):
+    import paper_2401_12522_amd as bita
+    plan = bita.binding.gemm_plan_info(M, N, K)
+    assert (plan["tall_tiles"], plan["mt_pass"], plan["splits"]) == (tiles, mt_pass, splits), plan
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    a32, w = torch.randn(M, K, generator=g, device="cuda"), (torch.randn(N, K, generator=g, device="cuda") * 0.05).to(torch.bfloat16)
+    hi = a32.to(torch.bfloat16)
+    lo = (a32 - hi.float()).to(torch.bfloat16)
+    out, ref = bita.gemm(hi, bita.pack_weight(w), N, a_lo=lo).double(), (hi.double() + lo.double()) @ w.double().T
+    assert torch.isfinite(out).all()
+    assert float((out - ref).abs().max()) <= 2e-5 * float(ref.abs().max()) + 1e-6         # fp32 accumulation, as everywhere
+
+
 @pytest.mark.parametrize("M,N,K,variant,splits", [
     (300, 12288, 1280, 9, 1), (300, 12288, 1288, 9, 1), (300, 12288, 1320, 9, 1), (300, 12288, 1376, 9, 1), (300, 12288, 1400, 9, 1), (300, 12288, 1440, 9, 1),
     (222, 35072, 1280, 11, 1), (222, 35072, 1304, 11, 1), (236, 9600, 4096, 9, 2), (236, 9600, 4136, 9, 2), (488, 4096, 4104, 9, 2),   # (the last writes its sums through)
-    (300, 12288, 1248, 9, 1), (300, 4096, 4096, 9, 4), (302, 272, 20512, 9, 8)])                     # too few k-steps, too few workgroups: both at once
+    (300, 12288, 1248, 9, 1), (300, 4096, 4096, 9, 4), (128, 4096, 11008, 9, 8), (302, 272, 20512, 9, 8)])     # too few k-steps, too few workgroups: both at once
 def test_passes_of_five_in_turns_and_both_at_once(M, N, K, variant, splits):
     import paper_2401_12522_amd as bita
     plan = bita.binding.gemm_plan_info(M, N, K)
