@@ -1178,8 +1178,8 @@ void launch_gemm(const void *a_frag, bool two_planes, int M, int64_t K, const vo
     // Row counts other than the 65..80 of the 64-node tree (Sec. 4.3.4, Table 4: 16 or 21 tree rows for
     // the efficient tree, 105 rows with a mask group behind each of its nodes): one pass over
     // the weights with 2, 3 or 7 m-tiles, for the planner's two variants.  Beyond 7 m-tiles
-    // the weight stream no longer bounds the kernel, and passes of 5 m-tiles (grid z)
-    // measured as fast as fewer passes of 7 or 10.
+    // the weight stream no longer bounds the kernel: tall passes (above), or passes of 5 m-tiles (grid z) where the
+    // planner finds those as fast.
     const bool planner_variant = p.variant == 6 || p.variant == 8;
     if (two_planes && planner_variant && (m_tiles <= 3 || (m_tiles >= 6 && m_tiles <= 7 && p.variant == 8))) {
         if (m_tiles == 2) launch_gemm_k<2>(a_frag, M, K, w, N, out, ldo, p, s, direct);
